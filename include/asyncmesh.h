@@ -234,8 +234,8 @@ am_status am_subset_indices(am_state *st, uint64_t t, uint64_t *dev_out, uint64_
 
 /* am_subset_indices for callers that cannot allocate: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same arguments, same result bit for bit, but the
- * per-tile offsets the three kernels share live in a static device array of the library
- * (2 MiB + 4.25 KiB, held by every GPU the library runs on until the process ends; its device
+ * counts its workgroups tell each other live in a static device array of the library
+ * (64 KiB, held by every GPU the library runs on until the process ends; its device
  * address is looked up once per device at am_init_state / am_resume_state) instead of the
  * caller's workspace, and the call allocates nothing, on the device or on the host.
  * Limit: n <= 2^27 = 134,217,728 coordinates; a larger stage is refused with AM_EINVAL (use

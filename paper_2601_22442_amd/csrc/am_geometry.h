@@ -4,6 +4,8 @@
 //   tile       = 64 groups = 256 consecutive coordinates = what one wavefront handles at a time
 //   superblock = 512 tiles; subset counts are scanned inside a superblock by one workgroup and
 //                across superblocks by a second tiny kernel
+//   strip      = 64 lanes x 32 consecutive coordinates = 8 tiles: what one wavefront hashes at a time
+//                where only the subset matters (one 32-bit mask per lane, in coordinate order)
 //   line       = 128 bytes = 32 floats, the unit in which memory is written
 //   block      = up to 8 replicas whose sparse values sit side by side in memory
 #pragma once
@@ -13,6 +15,8 @@ namespace am {
 
 constexpr uint32_t kTileCoords = 256;
 constexpr uint32_t kTilesPerSuperblock = 512;
+constexpr uint32_t kStripCoords = 2048;
+constexpr uint32_t kStripsPerSuperblock = kTileCoords * kTilesPerSuperblock / kStripCoords;
 constexpr uint32_t kLineFloats = 32;
 constexpr uint32_t kMaxReplicas = 32;
 constexpr uint32_t kMaxBlockReplicas = 8;

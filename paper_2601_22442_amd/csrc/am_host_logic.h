@@ -109,6 +109,24 @@ inline Layout make_layout(const am_config &c)
     return L;
 }
 
+// How a subset's index list is cut: a part = one workgroup of four waves with `strips` strips each.  Few
+// enough parts for every wave to be resident at once (32 waves per compute unit), so that each part finds the
+// counts of all before it after one round of hashing; at most 32 strips (32 KB of masks in LDS), from
+// where on the parts grow in number.
+struct ListShape {
+    uint32_t nstrips, strips, parts;
+};
+
+inline ListShape list_shape(uint64_t n, uint32_t compute_units)
+{
+    ListShape s;
+    s.nstrips = (uint32_t)((n + am::kStripCoords - 1) / am::kStripCoords);
+    const uint32_t waves = 32u * std::max(compute_units, 1u);
+    s.strips = std::min((s.nstrips + waves - 1u) / waves, 32u);
+    s.parts = (s.nstrips + 4u * s.strips - 1u) / (4u * s.strips);
+    return s;
+}
+
 // Floats of one array of the EMA vectors and how many arrays there are, per layout.
 inline void d_layout_shape(const am_config &c, uint32_t *rb, uint32_t *arrays, uint64_t *floats)
 {

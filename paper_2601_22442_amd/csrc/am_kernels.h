@@ -8,62 +8,75 @@ namespace am {
 // =============================================================================================
 // Subset offsets:   k_subset_count (or k_subset_offsets)  ->  k_subset_scan
 // =============================================================================================
-// cnt[512] (LDS) holds the sizes of the tiles of superblock blockIdx.x: write their exclusive
-// prefix to local_off and their total to sb_sum.  pack: a tile's word also carries its own size in
-// the high 8 bits (ring slots, where a tile owns at most 64 lines and a superblock at most 2^15).
-// Called by all 256 threads after a barrier.
-__device__ __forceinline__ void scan_superblock(const uint32_t *cnt, uint32_t *wave_tot, uint32_t ntiles, bool pack,
+// cnt[512] (LDS) holds the lines of the tiles of superblock blockIdx.x: write their exclusive
+// prefix, with the tile's own lines in the high 8 bits (a tile owns at most 64 lines and a superblock
+// at most 2^15), to local_off and their total to sb_sum.
+// Called by all threads of the workgroup (256 or more) after a barrier.
+__device__ __forceinline__ void scan_superblock(const uint32_t *cnt, uint32_t *wave_tot, uint32_t ntiles,
                                                 uint32_t *__restrict__ local_off, uint32_t *__restrict__ sb_sum)
 {
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const uint32_t tile0 = blockIdx.x * kTilesPerSuperblock;
-    // thread j owns entries 2j, 2j+1
-    const uint32_t a = cnt[2 * threadIdx.x], b = cnt[2 * threadIdx.x + 1];
-    uint32_t incl = a + b;                       // inclusive scan across the wave, by shuffles
+    uint32_t a = 0, b = 0, incl = 0;
+    if (wave < 4u) {                             // thread j owns entries 2j, 2j+1
+        a = cnt[2 * threadIdx.x]; b = cnt[2 * threadIdx.x + 1];
+        incl = a + b;                            // inclusive scan across the wave, by shuffles
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t up = __shfl_up(incl, off);
-        if ((int)lane >= off) incl += up;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t up = __shfl_up(incl, off);
+            if ((int)lane >= off) incl += up;
+        }
+        if (lane == 63) wave_tot[wave] = incl;
     }
-    if (lane == 63) wave_tot[wave] = incl;
     __syncthreads();
+    if (wave >= 4u) return;
     uint32_t base = 0;
     for (uint32_t w = 0; w < wave; ++w) base += wave_tot[w];
     const uint32_t excl = base + incl - (a + b);
     const uint32_t t_a = tile0 + 2 * threadIdx.x;
-    if (t_a < ntiles) local_off[t_a] = pack ? (excl | (a << 24)) : excl;
-    if (t_a + 1 < ntiles) local_off[t_a + 1] = pack ? ((excl + a) | (b << 24)) : excl + a;
+    if (t_a < ntiles) local_off[t_a] = excl | (a << 24);
+    if (t_a + 1 < ntiles) local_off[t_a + 1] = (excl + a) | (b << 24);
     if (threadIdx.x == 255) sb_sum[blockIdx.x] = base + incl;
 }
 
-// One workgroup (4 waves) per superblock of 512 tiles.  Pure integer hashing, no array reads.
-// A tile's size is ceil(count * mul / unit), count its number of selected coordinates:
-// mul = unit = 1 for packed index lists; mul = replicas per block, unit = 32 for ring slots, where a
-// tile owns whole 128-byte lines of [coordinate][replica] values.  Writes, per tile, the summed size
+// Which of the 32 consecutive coordinates of a lane (2048 strip + 32 lane + bit) are in the subset.
+__device__ __forceinline__ uint32_t strip_mask(const SubsetKey &key, uint64_t n, uint32_t strip, uint32_t lane)
+{
+    const uint64_t mu0 = (uint64_t)strip * kStripCoords + lane * 32u;
+    const bool whole = (uint64_t)(strip + 1u) * kStripCoords <= n;             // same for the whole wave
+    uint32_t m = 0;
+#pragma unroll 2
+    for (uint32_t q = 0; q < 8u; ++q) {
+        const uint64_t mu = mu0 + 4u * q;
+        const int nvalid = whole ? 4 : (mu >= n ? 0 : (n - mu >= 4u ? 4 : (int)(n - mu)));
+        m |= member_mask(key, mu >> 2, nvalid) << (4u * q);
+    }
+    return m;
+}
+
+// One workgroup (16 waves) per superblock of 512 tiles.  Pure integer hashing, no array reads.
+// A tile owns ceil(count * mul / 32) whole 128-byte lines of [coordinate][replica] values in a ring slot,
+// count its number of selected coordinates and mul the replicas per block.  Writes, per tile, the lines
 // of the tiles of the same superblock before it (local_off) and, per superblock, its total (sb_sum).
-__global__ void __launch_bounds__(256)
-k_subset_count(SubsetKey key, uint64_t n, uint32_t ntiles, uint32_t mul, uint32_t unit, uint32_t pack,
+// A small stage has few superblocks, so the time is what one workgroup needs for its 64 strips: sixteen
+// waves of four strips each.
+__global__ void __launch_bounds__(1024)
+k_subset_count(SubsetKey key, uint64_t n, uint32_t ntiles, uint32_t mul,
                uint32_t *__restrict__ local_off, uint32_t *__restrict__ sb_sum)
 {
     __shared__ uint32_t cnt[kTilesPerSuperblock];
     __shared__ uint32_t wave_tot[4];
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const uint32_t tile0 = blockIdx.x * kTilesPerSuperblock;
-
-    // wave w counts tiles tile0 + w, w+4, ... (adjacent waves hash adjacent tiles)
-    for (uint32_t k = wave; k < kTilesPerSuperblock; k += 4) {
-        const uint32_t tile = tile0 + k;
-        uint32_t total = 0;
-        if (tile < ntiles) {
-            const uint64_t group = (uint64_t)tile * 64u + lane;
-            const uint64_t mu = group * 4u;
-            const int nvalid = mu >= n ? 0 : (n - mu >= 4u ? 4 : (int)(n - mu));
-            (void)wave_prefix_mask4(member_mask(key, group, nvalid), total);
-        }
-        if (lane == 0) cnt[k] = (total * mul + unit - 1u) / unit;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    for (uint32_t k = wave; k < kStripsPerSuperblock; k += 16u) {
+        const uint32_t strip = blockIdx.x * kStripsPerSuperblock + k;
+        uint32_t count = (uint64_t)strip * kStripCoords < n ? (uint32_t)__popc(strip_mask(key, n, strip, lane)) : 0u;
+#pragma unroll
+        for (int off = 1; off < 8; off <<= 1) count += __shfl_xor(count, off);       // the eight lanes of a tile
+        if ((lane & 7u) == 0u) cnt[k * 8u + (lane >> 3)] = (count * mul + kLineFloats - 1u) / kLineFloats;
     }
     __syncthreads();
-    scan_superblock(cnt, wave_tot, ntiles, pack != 0u, local_off, sb_sum);
+    scan_superblock(cnt, wave_tot, ntiles, local_off, sb_sum);
 }
 
 // Same, from tile sizes that are already in memory (the fused step kernel leaves the line counts
@@ -78,14 +91,13 @@ k_subset_offsets(const uint32_t *__restrict__ tile_size, uint32_t ntiles,
     for (uint32_t k = threadIdx.x; k < kTilesPerSuperblock; k += 256u)
         cnt[k] = tile0 + k < ntiles ? tile_size[tile0 + k] : 0u;
     __syncthreads();
-    scan_superblock(cnt, wave_tot, ntiles, true, local_off, sb_sum);
+    scan_superblock(cnt, wave_tot, ntiles, local_off, sb_sum);
 }
 
 // Single workgroup: exclusive scan of the superblock totals, in place (sb[i] <- sum of sb[<i]),
 // grand total to sb[nsb]; raises flag bit 0 when the total exceeds the ring slot capacity.
 __global__ void __launch_bounds__(256)
-k_subset_scan(uint32_t *__restrict__ sb, uint32_t nsb, uint32_t capacity, uint32_t *__restrict__ flags,
-              uint64_t *__restrict__ count_out)
+k_subset_scan(uint32_t *__restrict__ sb, uint32_t nsb, uint32_t capacity, uint32_t *__restrict__ flags)
 {
     __shared__ uint64_t part[256];
     const uint32_t per = (nsb + 255u) / 256u;
@@ -99,34 +111,104 @@ k_subset_scan(uint32_t *__restrict__ sb, uint32_t nsb, uint32_t capacity, uint32
         uint64_t run = 0;
         for (int i = 0; i < 256; ++i) { const uint64_t x = part[i]; part[i] = run; run += x; }
         sb[nsb] = run > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)run;
-        if (run > capacity && flags) atomicOr(flags, 1u);
-        if (count_out) *count_out = run;
+        if (run > capacity) atomicOr(flags, 1u);
     }
     __syncthreads();
     uint64_t run = part[threadIdx.x];
     for (uint32_t i = lo; i < hi; ++i) { const uint32_t x = sb[i]; sb[i] = (uint32_t)run; run += x; }
 }
 
-// Ascending index list of a subset (for am_subset_indices).
+// =============================================================================================
+// Ascending index list of a subset (am_subset_indices):   k_list_clear  ->  k_subset_list
+// =============================================================================================
+// The cost is the generator (50 us for the words of 125.8M coordinates; the list itself is 50 MB at
+// p = 5 %), so every coordinate is hashed once: a workgroup (four waves of `strips` strips each) keeps its
+// masks in LDS, publishes how many coordinates it holds, adds up what all the workgroups before it
+// hold and writes its indices there.  A lane holds 32 consecutive coordinates, so a strip of 2048 needs one
+// scan over the lanes, and as many stores as the fullest lane has members.
+// No workgroup waits before it has published, and none for good: one that has not seen a count after
+// kListPatience looks (well over 10 ms; all workgroups of a call are normally running within microseconds of
+// each other) counts the members before its own part itself, so the kernel ends whatever else
+// happens to the scratch.
+// Measured, p = 5 %: 125.8M coordinates 85 us, 1M 9.7 us, 131,072 8.6 us (one workgroup per superblock
+// counting, a scan, and a second hashing pass that writes: 229, 55 and 54 us).
+// part_count: word p = the count of part p, bit 31 set once it is known; k_list_clear zeroes them first.
+constexpr uint32_t kListPatience = 1u << 15;
+
 __global__ void __launch_bounds__(256)
-k_subset_write(SubsetKey key, uint64_t n, uint32_t ntiles, const uint32_t *__restrict__ local_off,
-               const uint32_t *__restrict__ sb_base, uint64_t *__restrict__ out, uint64_t capacity)
+k_list_clear(uint32_t *__restrict__ part_count, uint32_t parts)
 {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i < parts) part_count[i] = 0u;
+}
+
+__global__ void __launch_bounds__(256)
+k_subset_list(SubsetKey key, uint64_t n, uint32_t nstrips, uint32_t strips, uint32_t patience, uint32_t *part_count,
+              uint64_t *__restrict__ out, uint64_t capacity, uint64_t *__restrict__ count_out)
+{
+    extern __shared__ uint32_t masks[];                       // [strips][256]
+    __shared__ uint32_t wave_count[4];
+    __shared__ uint64_t before[4];
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t nwaves = gridDim.x * 4u;
-    for (uint32_t tile = blockIdx.x * 4u + (threadIdx.x >> 6); tile < ntiles; tile += nwaves) {
-        const uint64_t group = (uint64_t)tile * 64u + lane;
-        const uint64_t mu = group * 4u;
-        const int nvalid = mu >= n ? 0 : (n - mu >= 4u ? 4 : (int)(n - mu));
-        const uint32_t mask = member_mask(key, group, nvalid);
-        uint32_t total;
-        uint64_t pos = (uint64_t)sb_base[tile / kTilesPerSuperblock] + local_off[tile] + wave_prefix_mask4(mask, total);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t part = blockIdx.x;
+    const uint32_t strip0 = (part * 4u + wave) * strips;
+
+    uint32_t mine = 0;                                        // members among the lane's coordinates of all its strips
+    for (uint32_t k = 0; k < strips; ++k) {
+        const uint32_t mask = strip0 + k < nstrips ? strip_mask(key, n, strip0 + k, lane) : 0u;
+        masks[k * 256u + threadIdx.x] = mask;
+        mine += (uint32_t)__popc(mask);
+    }
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if ((mask >> j) & 1u) {
-                if (pos < capacity) out[pos] = mu + j;
-                ++pos;
-            }
+    for (int off = 1; off < 64; off <<= 1) mine += __shfl_xor(mine, off);
+    if (lane == 0) wave_count[wave] = mine;
+    __syncthreads();
+    const uint32_t total = wave_count[0] + wave_count[1] + wave_count[2] + wave_count[3];
+    if (threadIdx.x == 0)
+        __hip_atomic_store(&part_count[part], total | 0x80000000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
+    uint64_t sum = 0;                                         // members of the parts before mine
+    uint32_t looks = 0;
+    for (uint32_t p = threadIdx.x; p < part; p += 256u) {
+        uint32_t x;
+        while (!((x = __hip_atomic_load(&part_count[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) & 0x80000000u) && looks < patience) {
+            ++looks;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        sum += x & 0x7FFFFFFFu;
+        if (looks >= patience) break;
+    }
+    if (__syncthreads_or(looks >= patience)) {
+        sum = 0;
+        for (uint32_t k = wave; k < part * 4u * strips; k += 4u) sum += (uint32_t)__popc(strip_mask(key, n, k, lane));
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) sum += __shfl_xor(sum, off);
+    if (lane == 0) before[wave] = sum;
+    __syncthreads();
+    uint64_t pos = before[0] + before[1] + before[2] + before[3];
+    if (part == gridDim.x - 1u && threadIdx.x == 0) *count_out = pos + total;
+    if (capacity == 0u) return;
+    for (uint32_t w = 0; w < wave; ++w) pos += wave_count[w];
+
+    for (uint32_t k = 0; k < strips; ++k) {
+        uint32_t mask = masks[k * 256u + threadIdx.x];
+        const uint32_t members = (uint32_t)__popc(mask);
+        uint32_t incl = members;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t up = __shfl_up(incl, off);
+            if ((int)lane >= off) incl += up;
+        }
+        uint64_t at = pos + (incl - members);
+        const uint64_t mu0 = (uint64_t)(strip0 + k) * kStripCoords + lane * 32u;
+        while (mask) {
+            if (at < capacity) out[at] = mu0 + (uint32_t)__builtin_ctz(mask);
+            ++at;
+            mask &= mask - 1u;
+        }
+        pos += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
     }
 }
 

@@ -20,16 +20,15 @@
 #define AM_SOURCE_HASH "unknown"
 #endif
 
-// Scratch of am_subset_indices_static: per-tile offsets and per-superblock bases of one subset,
-// for stages of up to kStaticMaxN coordinates.  Every GPU the library runs on holds its own copy of
+// Scratch of am_subset_indices_static: how many members each part of one subset has, for stages of up
+// to kStaticMaxN coordinates.  Every GPU the library runs on holds its own copy of
 // this array for the life of the process.  The name is a host-side stand-in: host code reaches the
 // memory only through the address hipGetSymbolAddress returns for the current device.
 namespace {
 constexpr uint64_t kStaticMaxN = 1ull << 27;
-constexpr uint32_t kStaticMaxTiles = (uint32_t)(kStaticMaxN / am::kTileCoords);
-constexpr uint32_t kStaticMaxSb = kStaticMaxTiles / am::kTilesPerSuperblock;
+constexpr uint32_t kStaticMaxParts = (uint32_t)(kStaticMaxN / (4u * am::kStripCoords));      // a part is four strips or more
 }
-static __device__ __align__(256) uint32_t scratch[kStaticMaxTiles + kStaticMaxSb + 64];
+static __device__ __align__(256) uint32_t scratch[kStaticMaxParts];
 
 namespace {
 
@@ -113,7 +112,7 @@ struct am_state {
     Layout lay;
     hipStream_t stream;
     int device;
-    uint32_t grid_sparse;
+    uint32_t compute_units;
     float *w[AM_MAX_REPLICAS], *m[AM_MAX_REPLICAS], *v[AM_MAX_REPLICAS];
     float *d[AM_MAX_REPLICAS];   // per replica, or (interleaved layout) per block
     uint32_t d_arrays, d_rb;     // how many entries of d are in use; replicas per array (1 = per replica)
@@ -168,12 +167,12 @@ am_status launch_ring_offsets(am_state *st, uint64_t step, uint32_t slot)
         // the previous fused step already sized this subset's tiles
         am::k_subset_offsets<<<L.nsb, 256, 0, st->stream>>>(st->next_lines(), L.ntiles, st->meta_local(slot), st->meta_sb(slot));
     } else {
-        am::k_subset_count<<<L.nsb, 256, 0, st->stream>>>(make_key(st, step), st->cfg.n, L.ntiles, L.blocks.rb, am::kLineFloats, 1u,
-                                                          st->meta_local(slot), st->meta_sb(slot));
+        am::k_subset_count<<<L.nsb, 1024, 0, st->stream>>>(make_key(st, step), st->cfg.n, L.ntiles, L.blocks.rb,
+                                                           st->meta_local(slot), st->meta_sb(slot));
     }
     AM_HIP(hipGetLastError());
     const uint32_t cap = L.cap_lines > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)L.cap_lines;
-    am::k_subset_scan<<<1, 256, 0, st->stream>>>(st->meta_sb(slot), L.nsb, cap, st->flags(), nullptr);
+    am::k_subset_scan<<<1, 256, 0, st->stream>>>(st->meta_sb(slot), L.nsb, cap, st->flags());
     AM_HIP(hipGetLastError());
     return AM_OK;
 }
@@ -187,21 +186,16 @@ am_status check_index_list_args(const am_state *st, const uint64_t *dev_out, uin
     return AM_OK;
 }
 
-// S^t as an ascending index list: sizes of the tiles (in coordinates) -> offsets -> indices.  local_off
-// (ntiles words) and sb_base (nsb + 1 words) are the scratch the three kernels share; every word of
-// them that is read is written first, so the scratch needs no clearing.
-am_status launch_index_list(am_state *st, uint64_t t, uint32_t *local_off, uint32_t *sb_base,
-                            uint64_t *dev_out, uint64_t capacity, uint64_t *dev_count)
+// S^t as an ascending index list.  part_count: one word per part (at most one for every 32 tiles), which
+// the first kernel clears, so it needs no clearing of its own.
+am_status launch_index_list(am_state *st, uint64_t t, uint32_t *part_count, uint64_t *dev_out, uint64_t capacity, uint64_t *dev_count)
 {
-    const Layout &L = st->lay;
-    am::k_subset_count<<<L.nsb, 256, 0, st->stream>>>(make_key(st, t), st->cfg.n, L.ntiles, 1u, 1u, 0u, local_off, sb_base);
+    const am_host::ListShape s = am_host::list_shape(st->cfg.n, st->compute_units);
+    am::k_list_clear<<<(s.parts + 255u) / 256u, 256, 0, st->stream>>>(part_count, s.parts);
     AM_HIP(hipGetLastError());
-    am::k_subset_scan<<<1, 256, 0, st->stream>>>(sb_base, L.nsb, 0u, nullptr, dev_count);
+    am::k_subset_list<<<s.parts, 256, s.strips * 256u * sizeof(uint32_t), st->stream>>>(
+        make_key(st, t), st->cfg.n, s.nstrips, s.strips, am::kListPatience, part_count, dev_out, capacity, dev_count);
     AM_HIP(hipGetLastError());
-    if (capacity) {
-        am::k_subset_write<<<st->grid_sparse, 256, 0, st->stream>>>(make_key(st, t), st->cfg.n, L.ntiles, local_off, sb_base, dev_out, capacity);
-        AM_HIP(hipGetLastError());
-    }
     return AM_OK;
 }
 
@@ -410,10 +404,7 @@ am_status create_state(const am_config *cfg, const am_buffers *buf, void *hip_st
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, st->device);
     if (e != hipSuccess) { delete st; return fail(AM_EHIP, "device query: %s", hipGetErrorString(e)); }
     if (am_status s = resolve_static_scratch(st->device, &st->static_scratch)) { delete st; return s; }
-    // the stand-alone kernels stride over the tiles with a fixed number of workgroups per compute unit
-    const uint32_t tile_groups = (lay.ntiles + 3) / 4;
-    const uint32_t want = (uint32_t)cus * 8u;
-    st->grid_sparse = tile_groups < want ? tile_groups : want;
+    st->compute_units = (uint32_t)cus;
     *out = st;
     return AM_OK;
 }
@@ -690,7 +681,7 @@ am_status am_subset_indices(am_state *st, uint64_t t, uint64_t *dev_out, uint64_
 {
     if (am_status s = check_index_list_args(st, dev_out, capacity, dev_count)) return s;
     const uint32_t meta_slot = st->lay.slots;        // the metadata block after the ring slots' own
-    return launch_index_list(st, t, st->meta_local(meta_slot), st->meta_sb(meta_slot), dev_out, capacity, dev_count);
+    return launch_index_list(st, t, st->meta_local(meta_slot), dev_out, capacity, dev_count);
 }
 
 am_status am_subset_indices_static(am_state *st, uint64_t t, uint64_t *dev_out, uint64_t capacity, uint64_t *dev_count)
@@ -702,8 +693,8 @@ am_status am_subset_indices_static(am_state *st, uint64_t t, uint64_t *dev_out, 
     int device = -1;
     AM_HIP(hipGetDevice(&device));
     if (device != st->device) return fail(AM_EINVAL, "device %d is current, the state lives on device %d", device, st->device);
-    uint32_t *base = st->static_scratch;             // looked up at am_init_state / am_resume_state
-    return launch_index_list(st, t, base, base + kStaticMaxTiles, dev_out, capacity, dev_count);
+    // the scratch was looked up at am_init_state / am_resume_state
+    return launch_index_list(st, t, st->static_scratch, dev_out, capacity, dev_count);
 }
 
 am_status am_set_delay(am_state *st, uint32_t tau)

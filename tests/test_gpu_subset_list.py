@@ -1,0 +1,52 @@
+"""The index list of a subset (am_subset_indices) where its cut into parts can go wrong: the ends of a
+lane's 32 coordinates, of a strip, of a part, one strip a wave and several, all three sampling rules, and
+capacities around the count.  Whole numbers: equal to the oracle's list."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+def _stage(am, n, p, seed, **kw):
+    return am.init_state(am.make_config(n, 1, fraction=p, seed=seed, optimizer=am.OPT_SGD, beta1=0.0,
+                                        correction=am.CORR_NONE, **kw), torch.zeros(n))
+
+
+@pytest.mark.parametrize("n,p", [
+    (31, 1.0), (32, 1.0), (33, 0.5), (2047, 0.3), (2048, 1.0), (2049, 1.0), (8191, 0.05), (8192, 1.0), (8193, 0.9),
+    (8192 * 64 + 2047, 0.02),
+    (1 << 24, 0.01), ((1 << 24) + 1, 0.01),           # one strip a wave, two strips a wave on 256 compute units
+    ((1 << 25) + 8193, 0.003),                        # three strips a wave, the last part cut
+])
+def test_parts_of_the_list(amlib, n, p):
+    st = _stage(amlib, n, p, 17)
+    for t in (1, (1 << 32) + 9):
+        idx, k = st.subset_indices(t)
+        want = O.subset(17, t, n, p)
+        assert k == want.size and np.array_equal(idx.cpu().numpy().astype(np.uint64), want), (n, p, t)
+
+
+@pytest.mark.parametrize("kw,okw", [(dict(subset_granule=32), dict(granule=32)),
+                                    (dict(subset_kind=1), dict(stratified=True))])
+@pytest.mark.parametrize("n", [2049, 100_003])
+def test_other_sampling_rules(amlib, kw, okw, n):
+    st = _stage(amlib, n, 0.07, 3, **kw)
+    idx, k = st.subset_indices(5)
+    want = O.subset(3, 5, n, 0.07, **okw)
+    assert k == want.size and np.array_equal(idx.cpu().numpy().astype(np.uint64), want)
+
+
+def test_capacity_around_the_count(amlib):
+    st = _stage(amlib, 70_001, 0.1, 4)
+    want = O.subset(4, 2, 70_001, 0.1).astype(np.int64)
+    for cap in (0, 1, want.size - 1, want.size, want.size + 1):
+        out = torch.full((max(cap, 1) + 8,), -1, dtype=torch.int64, device="cuda")
+        count = torch.full((1,), -1, dtype=torch.int64, device="cuda")
+        st.subset_indices_static(2, out[:cap], count)
+        assert int(count.item()) == want.size
+        got = out.cpu().numpy()
+        kept = min(cap, want.size)
+        assert np.array_equal(got[:kept], want[:kept]) and (got[kept:] == -1).all()
