@@ -1084,85 +1084,155 @@ struct DiagArgs {
     uint32_t d_stride;                 // 1 (one array per replica) or the replicas per block (interleaved)
 };
 
-// The EMA entries of coordinates mu .. mu + 3 of every replica from the interleaved layout: per block
-// the 4 RB values are contiguous (the arrays are padded to whole tiles, so all four coordinates exist).
-template <int RMAX, int RB>
-__device__ __forceinline__ void diag_load_interleaved(const DiagArgs &a, uint64_t mu, F4 (&x)[RMAX])
+// Squared distance of the replicas' values x[0 .. R) of one coordinate from their mean, in fp64: the sum over
+// the coordinates and the largest one.
+struct Spread {
+    double sum = 0., max = 0.;
+    __device__ __forceinline__ void add(double e) { sum += e; max = e > max ? e : max; }
+};
+
+// One array per replica.  A thread takes groups of 4 coordinates and holds a group's values of all
+// replicas in registers (RMAX >= replicas of them).  A wave's U groups of 64 follow each other in
+// memory, and all their loads are requested before the first is used (few replicas: U > 1, so that as many
+// bytes are in flight as with many).
+template <int RMAX, int U>
+__device__ __forceinline__ void diag_flat(const float *const *arrays, uint32_t R, uint64_t n, Spread &out)
 {
+    const uint64_t ngroups = (n + 3u) / 4u;
+    const double inv_r = 1.0 / (double)R;
+    for (uint64_t g0 = ((uint64_t)blockIdx.x * 256u + (threadIdx.x & 192u)) * U + (threadIdx.x & 63u); g0 < ngroups;
+         g0 += (uint64_t)gridDim.x * (256u * U)) {
+        F4 x[U][RMAX];
 #pragma unroll
-    for (int b = 0; b < RMAX / RB; ++b) {
-        if ((uint32_t)(b * RB) >= a.replicas) continue;
-        const v4f *p = reinterpret_cast<const v4f *>(a.d[b] + mu * RB);
-        float t[4 * RB];
+        for (int u = 0; u < U; ++u) {
+            const uint64_t mu = (g0 + 64u * u) * 4u;
+            const int nvalid = mu >= n ? 0 : n - mu >= 4u ? 4 : (int)(n - mu);
 #pragma unroll
-        for (int q = 0; q < RB; ++q) {
-            const v4f u = __builtin_nontemporal_load(p + q);
-            t[4 * q] = u.x; t[4 * q + 1] = u.y; t[4 * q + 2] = u.z; t[4 * q + 3] = u.w;
+            for (int i = 0; i < RMAX; ++i)
+                if ((uint32_t)i < R) x[u][i] = load_f32x4(arrays[i], mu, nvalid);
         }
 #pragma unroll
-        for (int k = 0; k < RB; ++k)
+        for (int u = 0; u < U; ++u) {
+            const uint64_t mu = (g0 + 64u * u) * 4u;
+            const int nvalid = mu >= n ? 0 : n - mu >= 4u ? 4 : (int)(n - mu);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) x[b * RB + k].v[j] = t[j * RB + k];
+            for (int j = 0; j < 4; ++j) {
+                if (j >= nvalid) continue;
+                double mean = 0., e = 0.;
+#pragma unroll
+                for (int i = 0; i < RMAX; ++i) if ((uint32_t)i < R) mean += (double)x[u][i].v[j];
+                mean *= inv_r;
+#pragma unroll
+                for (int i = 0; i < RMAX; ++i) if ((uint32_t)i < R) { const double y = (double)x[u][i].v[j] - mean; e += y * y; }
+                out.add(e);
+            }
+        }
     }
 }
 
-// Every thread takes groups of 4 coordinates (group = thread index, + threads of the grid, ...), holds
-// the group's values of all replicas in registers (RMAX >= replicas of them, all requested before the
-// first is used) and accumulates its three partial results; a fixed grid and a fixed order make the
-// result reproducible.
+// One array [coordinate][RB] per block of RB replicas (NB blocks at most).  A thread takes 16-byte chunks, so
+// that a wave reads whole lines with every load: a chunk is four replicas of a coordinate (RB = 8: the
+// lane beside it has the other four) or (RB = 2) two coordinates.  A thread that took whole coordinates would
+// read every line eight times over, 16 bytes of each at a time.  A wave's U runs of 64 chunks follow
+// each other in memory.
+// Measured (8 x 31.5M, weights and interleaved EMA vectors, whole call): 338 us = 6.0 TB/s, 570 us with a thread
+// per four coordinates, 369 us with a wave's runs a grid apart.
+template <int RB, int NB, int U>
+__device__ __forceinline__ void diag_interleaved(const float *const *arrays, uint32_t R, uint64_t n, Spread &out)
+{
+    const uint64_t nchunks = (n * RB + 3u) / 4u;
+    const double inv_r = 1.0 / (double)R;
+    for (uint64_t g0 = ((uint64_t)blockIdx.x * 256u + (threadIdx.x & 192u)) * U + (threadIdx.x & 63u); g0 < nchunks; g0 += (uint64_t)gridDim.x * (256u * U)) {
+        v4f x[U][NB];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const uint64_t g = g0 + 64u * u;
+                x[u][b] = v4f{0.f, 0.f, 0.f, 0.f};
+                if (g < nchunks && (uint32_t)(b * RB) < R) x[u][b] = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(arrays[b]) + g);
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint64_t g = g0 + 64u * u;
+            if (g >= nchunks) continue;                        // (RB = 8: the same for both lanes of a coordinate)
+            if constexpr (RB == 2) {                           // chunk = coordinates 2 g, 2 g + 1
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    if (2u * g + c >= n) continue;
+                    const double p = (double)x[u][0][2 * c], q = R > 1u ? (double)x[u][0][2 * c + 1] : 0.;
+                    const double mean = (p + q) * inv_r, a = p - mean, b = R > 1u ? q - mean : 0.;
+                    out.add(a * a + b * b);
+                }
+            } else {
+                const uint32_t first = RB == 8 ? 4u * (threadIdx.x & 1u) : 0u;        // replica of the chunk's first value
+                double mean = 0., e = 0.;
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (b * RB + first + j < R) mean += (double)x[u][b][j];
+                if (RB == 8) mean += __shfl_xor(mean, 1);
+                mean *= inv_r;
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (b * RB + first + j < R) { const double y = (double)x[u][b][j] - mean; e += y * y; }
+                if (RB == 8) e += __shfl_xor(e, 1);
+                if (RB == 4 || (threadIdx.x & 1u) == 0u) out.add(e);
+            }
+        }
+    }
+}
+
+// grid = (blocks, 2): row 0 the weights, row 1 the EMA vectors (1 row without them); partial[row][block] = (sum, largest).
+// A fixed grid and a fixed order make the result reproducible.
 template <int RMAX>
 __global__ void __launch_bounds__(256)
 k_diag_partial(const DiagArgs a, double *__restrict__ partial)
 {
-    __shared__ double red[3][256];
-    double cons = 0., var_sum = 0., var_max = 0.;
+    __shared__ double red[2][256];
+    Spread s;
     const uint32_t R = a.replicas;
-    const uint64_t stride = (uint64_t)gridDim.x * 256u, ngroups = (a.n + 3u) / 4u;
-    const double inv_r = 1.0 / (double)R;
-    for (uint64_t g = (uint64_t)blockIdx.x * 256u + threadIdx.x; g < ngroups; g += stride) {
-        const uint64_t mu = g * 4u;
-        const int nvalid = a.n - mu >= 4u ? 4 : (int)(a.n - mu);
-        F4 x[RMAX];
-#pragma unroll
-        for (int i = 0; i < RMAX; ++i)
-            if ((uint32_t)i < R) x[i] = load_f32x4(a.w[i], mu, nvalid);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (j >= nvalid) continue;
-            double mean = 0.;
-#pragma unroll
-            for (int i = 0; i < RMAX; ++i) if ((uint32_t)i < R) mean += (double)x[i].v[j];
-            mean *= inv_r;
-#pragma unroll
-            for (int i = 0; i < RMAX; ++i) if ((uint32_t)i < R) { const double e = (double)x[i].v[j] - mean; cons += e * e; }
+    constexpr int NB = RMAX >= 8 ? RMAX / 8 : 1, U = RMAX == 2 ? 4 : RMAX == 4 ? 2 : 1;
+    if (blockIdx.y == 0u) diag_flat<RMAX, U>(a.w, R, a.n, s);
+    else if (a.d_stride == 1u) diag_flat<RMAX, U>(a.d, R, a.n, s);
+    else if constexpr (RMAX == 2) diag_interleaved<2, 1, 4>(a.d, R, a.n, s);
+    else if constexpr (RMAX == 4) diag_interleaved<4, 1, 4>(a.d, R, a.n, s);
+    else diag_interleaved<8, NB, NB == 1 ? 4 : NB == 2 ? 2 : 1>(a.d, R, a.n, s);
+    red[0][threadIdx.x] = s.sum; red[1][threadIdx.x] = s.max;
+    __syncthreads();
+    for (uint32_t off = 128; off > 0; off >>= 1) {
+        if (threadIdx.x < off) {
+            red[0][threadIdx.x] += red[0][threadIdx.x + off];
+            const double o = red[1][threadIdx.x + off];
+            if (o > red[1][threadIdx.x]) red[1][threadIdx.x] = o;
         }
-        if (a.has_d) {
-#pragma unroll
-            for (int i = 0; i < RMAX; ++i) {
-                if ((uint32_t)i >= R) continue;
-                if (a.d_stride == 1u) x[i] = load_f32x4(a.d[i], mu, nvalid);
-            }
-            if (a.d_stride == 8u) diag_load_interleaved<RMAX, 8>(a, mu, x);
-            else if (a.d_stride == 4u) diag_load_interleaved<RMAX, 4>(a, mu, x);
-            else if (a.d_stride == 2u) diag_load_interleaved<RMAX, 2>(a, mu, x);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (j >= nvalid) continue;
-                double dm = 0., v = 0.;
-#pragma unroll
-                for (int i = 0; i < RMAX; ++i) if ((uint32_t)i < R) dm += (double)x[i].v[j];
-                dm *= inv_r;
-#pragma unroll
-                for (int i = 0; i < RMAX; ++i) if ((uint32_t)i < R) { const double e = (double)x[i].v[j] - dm; v += e * e; }
-                v *= inv_r;
-                var_sum += v;
-                var_max = v > var_max ? v : var_max;
-            }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        double *p = partial + 2u * (blockIdx.y * gridDim.x + blockIdx.x);
+        p[0] = red[0][0]; p[1] = red[1][0];
+    }
+}
+
+__global__ void __launch_bounds__(1024)
+k_diag_final(const double *__restrict__ partial, uint32_t nblocks, uint32_t rows, uint32_t replicas, uint64_t n, double *__restrict__ out3)
+{
+    __shared__ double red[3][1024];
+    double cons = 0., var_sum = 0., var_max = 0.;
+    for (uint32_t b = threadIdx.x; b < nblocks; b += 1024u) {
+        cons += partial[2u * b];
+        if (rows == 2u) {
+            var_sum += partial[2u * (nblocks + b)];
+            const double o = partial[2u * (nblocks + b) + 1u];
+            var_max = o > var_max ? o : var_max;
         }
     }
     red[0][threadIdx.x] = cons; red[1][threadIdx.x] = var_sum; red[2][threadIdx.x] = var_max;
     __syncthreads();
-    for (uint32_t off = 128; off > 0; off >>= 1) {
+    for (uint32_t off = 512; off > 0; off >>= 1) {
         if (threadIdx.x < off) {
             red[0][threadIdx.x] += red[0][threadIdx.x + off];
             red[1][threadIdx.x] += red[1][threadIdx.x + off];
@@ -1172,34 +1242,9 @@ k_diag_partial(const DiagArgs a, double *__restrict__ partial)
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        partial[3 * blockIdx.x + 0] = red[0][0];
-        partial[3 * blockIdx.x + 1] = red[1][0];
-        partial[3 * blockIdx.x + 2] = red[2][0];
+        const double inv_r = 1.0 / (double)replicas;
+        out3[0] = red[0][0]; out3[1] = red[1][0] * inv_r / (double)n; out3[2] = red[2][0] * inv_r;
     }
-}
-
-__global__ void __launch_bounds__(256)
-k_diag_final(const double *__restrict__ partial, uint32_t nblocks, uint64_t n, double *__restrict__ out3)
-{
-    __shared__ double red[3][256];
-    double cons = 0., var_sum = 0., var_max = 0.;
-    for (uint32_t b = threadIdx.x; b < nblocks; b += 256u) {
-        cons += partial[3 * b]; var_sum += partial[3 * b + 1];
-        const double o = partial[3 * b + 2];
-        var_max = o > var_max ? o : var_max;
-    }
-    red[0][threadIdx.x] = cons; red[1][threadIdx.x] = var_sum; red[2][threadIdx.x] = var_max;
-    __syncthreads();
-    for (uint32_t off = 128; off > 0; off >>= 1) {
-        if (threadIdx.x < off) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + off];
-            red[1][threadIdx.x] += red[1][threadIdx.x + off];
-            const double o = red[2][threadIdx.x + off];
-            if (o > red[2][threadIdx.x]) red[2][threadIdx.x] = o;
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) { out3[0] = red[0][0]; out3[1] = red[1][0] / (double)n; out3[2] = red[2][0]; }
 }
 
 // =============================================================================================

@@ -717,12 +717,17 @@ am_status am_diagnostics(am_state *st, double *dev_out3)
     for (uint32_t k = 0; k < st->d_arrays; ++k) a.d[k] = st->d[k];          // per replica, or (interleaved) per block
     a.n = st->cfg.n; a.replicas = st->cfg.replicas;
     const uint64_t want = ((st->cfg.n + 3) / 4 + 255) / 256;               // a thread takes groups of 4 coordinates
-    const uint32_t blocks = (uint32_t)(want < 4096 ? want : 4096);          // 3 doubles each in the partials area (32 x 1024 doubles)
-    if (a.replicas <= 8) am::k_diag_partial<8><<<blocks, 256, 0, st->stream>>>(a, st->reduce_partials());
-    else if (a.replicas <= 16) am::k_diag_partial<16><<<blocks, 256, 0, st->stream>>>(a, st->reduce_partials());
-    else am::k_diag_partial<32><<<blocks, 256, 0, st->stream>>>(a, st->reduce_partials());
+    const uint32_t blocks = (uint32_t)(want < 2048 ? want : 2048);          // 2 x 2 doubles each in the partials area (32 x 1024 doubles)
+    const uint32_t rows = a.has_d ? 2u : 1u;
+    const dim3 grid(blocks, rows);
+    // the smallest instantiation that holds the replicas (interleaved arrays have as many per block: 2, 4 or 8)
+    if (a.replicas <= 2) am::k_diag_partial<2><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
+    else if (a.replicas <= 4) am::k_diag_partial<4><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
+    else if (a.replicas <= 8) am::k_diag_partial<8><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
+    else if (a.replicas <= 16) am::k_diag_partial<16><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
+    else am::k_diag_partial<32><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
     AM_HIP(hipGetLastError());
-    am::k_diag_final<<<1, 256, 0, st->stream>>>(st->reduce_partials(), blocks, st->cfg.n, dev_out3);
+    am::k_diag_final<<<1, 1024, 0, st->stream>>>(st->reduce_partials(), blocks, rows, a.replicas, st->cfg.n, dev_out3);
     AM_HIP(hipGetLastError());
     return AM_OK;
 }

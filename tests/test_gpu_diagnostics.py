@@ -1,0 +1,34 @@
+"""Consensus error and EMA variance where the reduction's cut can go wrong: around one pass of the grid
+(2048 workgroups of 256 threads with U groups of four coordinates each, U = 4, 2, 1 by the number of
+replicas) and at ragged ends, for both layouts.  Reference: the same sums in fp64.  Sums of fewer than
+2^26 non-negative fp64 terms differ by at most 2^26 * 2^-53 < 1e-8 between two orders; block-wise sums by far less."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+PASS = 2048 * 256 * 4
+
+
+@pytest.mark.parametrize("n,R", [(4 * PASS + 3, 1), (4 * PASS - 1, 2), (4 * PASS + 257, 2), (2 * PASS + 1, 3), (2 * PASS + 2049, 4),
+                                 (PASS + 1, 8), (PASS // 2 + 63, 5), (PASS // 4 + 5, 12), (1025, 32), (2, 7)])
+@pytest.mark.parametrize("interleaved", [False, True])
+def test_diagnostics_over_grid_edges(amlib, n, R, interleaved):
+    am = amlib
+    st = am.init_state(am.make_config(n, R, delay=0, fraction=0.5, seed=1, optimizer=am.OPT_SGD, beta1=0.0,
+                                      d_layout=am.D_INTERLEAVED if interleaved else am.D_PER_REPLICA))
+    g = torch.Generator(device="cuda").manual_seed(n + R)
+    for i in range(R):
+        st.w[i].copy_(torch.randn(n, generator=g, device="cuda"))
+        st.d[i].copy_(torch.randn(n, generator=g, device="cuda"))
+
+    def squares(xs):
+        mean = sum(x.double() for x in xs) / R
+        return sum((x.double() - mean) ** 2 for x in xs)
+
+    cons, vmean, vmax = st.diagnostics()
+    want_c, want_v = squares(st.w), squares(st.d) / R
+    for got, want in ((cons, want_c.sum()), (vmean, want_v.mean()), (vmax, want_v.max())):
+        want = float(want)
+        assert abs(got - want) <= 1e-10 * want, (got, want)
+    assert st.diagnostics() == (cons, vmean, vmax)
