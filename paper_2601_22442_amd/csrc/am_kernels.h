@@ -787,9 +787,18 @@ k_step(const StepArgs a)
 // of replicas) and keeps the block's RB replicas side by side in registers: lane l holds the four
 // coordinates of its group for every replica of the block.  The RB values of a coordinate are one
 // aligned stretch of 4 RB bytes in the ring slot and in the interleaved EMA vector ([coordinate][RB]),
-// so the lane reads and writes them with one or two 128-bit accesses: no LDS, no barrier, two dozen
+// so the lane reads and writes them with one or two 128-bit accesses: no barrier, two dozen
 // tiles per compute unit in flight.  (Several lanes write parts of one line within a few
 // instructions of each other; these are ordinary cached stores, which the L2 merges.)
+// What bounds it is the chain of waits a wave goes through, so everything a tile reads is requested at
+// once: the first kilobyte of its ring lines (256 / RB received coordinates: nearly always all of them)
+// and their EMA entries go straight into the wave's own stretch of LDS beside the loads of the weights
+// (read where they are used, they are up to eight waits in a row); more coordinates come a kilobyte at a
+// time.  In the per-replica layout the EMA entries are dense loads anyway, so there the staging pays while a
+// tile's subset fits (the host's rule).  31.5M coordinates, us a call before / after: interleaved, R = 8, p = 1 % 264 /
+// 210, 5 % 465 / 421, 20 % 717 / 712, 100 % (7.9M) 508 / 431; R = 12, 5 % 848 / 692; no correction 408 / 331; per
+// replica, 1 %: R = 8 345 / 283, R = 4 175 / 151; 5 %: R = 8 684 / 690, R = 4 344 / 327, R = 2 179 / 154; 125.8M, R = 8, 5 %:
+// 1797 / 1716 (8.56 GB in whole lines: 5.0 TB/s).
 // Arithmetic and its order are those of the fused kernel: mean in fp64 in replica order, rounded to
 // fp32; d <- coef_d d + coef_s (w^ - sent) and w = mean + d in fp64, rounded once each.
 // =============================================================================================
@@ -852,15 +861,15 @@ __device__ __forceinline__ void average_send_block(float *slot, const F4 (&w)[RB
 
 // Coordinate j of the group receives the old average abar: EMA of the staleness of each replica of the
 // block (own[k] = what replica k itself sent), corrected weight.  dp: the coordinate's RB entries of the
-// interleaved EMA vector (DIL), else the entries are in dv.
+// interleaved EMA vector (DIL; d_old: the same or their copy in LDS), else the entries are in dv.
 template <bool DIL, int RB>
-__device__ __forceinline__ void average_receive(const StepArgs &a, int j, float abar, const float (&own)[RB], float *dp,
+__device__ __forceinline__ void average_receive(const StepArgs &a, int j, float abar, const float (&own)[RB], const float *d_old, float *dp,
                                                 F4 (&w)[RB], F4 (&dv)[RB])
 {
     if (a.ema) {
         float d_new[RB];
         if (DIL) {
-            load_block_values<RB>(dp, d_new);
+            load_block_values<RB>(d_old, d_new);
         } else {
 #pragma unroll
             for (int k = 0; k < RB; ++k) d_new[k] = dv[k].v[j];
@@ -878,14 +887,28 @@ __device__ __forceinline__ void average_receive(const StepArgs &a, int j, float 
     }
 }
 
+// Bytes of dynamic LDS of a workgroup: per wave a kilobyte of ring values per block, one of EMA entries
+// (interleaved), and the list of received coordinates.  Blocks of fewer than four replicas have
+// entries shorter than a direct-to-LDS load and read them from memory.
+constexpr uint32_t kStageFloats = 256;
+template <bool DIL, int RB>
+constexpr bool kStageD = DIL && RB >= 4;
+template <bool DIL, int RB>
+__host__ __device__ constexpr uint32_t average_wave_bytes(uint32_t nblocks)
+{
+    return (nblocks * kStageFloats + (kStageD<DIL, RB> ? kStageFloats + 64u : 0u)) * (uint32_t)sizeof(float);
+}
+
 // grid = (ceil(tiles / 4), blocks) (TAU0: (ceil(tiles / 4), 1)); blockDim = 256: four waves, each with
-// a tile of its own (no LDS).
+// a tile and (STAGED) average_wave_bytes() of LDS of its own.
 // DIL: the EMA vectors are interleaved ([coordinate][RB] per block); else one flat array per replica.
 // TAU0: the average is of this very call's values (tau = 0): the wave walks all blocks of its tile,
 // once for the sums and the send, once more for the update (another wave must not rewrite a block's
 // weights while this one still needs them for the mean).
-template <bool DIL, int RB, bool TAU0>
-__global__ void __launch_bounds__(256, (DIL && !TAU0) ? 6 : 4)     // at most 80 (else 128) registers: 24 (16) tiles per compute unit in flight
+// STAGED: a kilobyte at a time through LDS; else (per-replica layout with subsets of several kilobytes a tile)
+// the ring is read where its values are used.
+template <bool DIL, int RB, bool TAU0, bool STAGED>
+__global__ void __launch_bounds__(256, 4)     // at most 128 registers: 16 tiles or more per compute unit in flight (kept to 80, the interleaved form spills)
 k_average(const StepArgs a)
 {
     constexpr uint32_t kPerLine = kLineFloats / RB;                        // coordinates a ring line holds
@@ -900,6 +923,11 @@ k_average(const StepArgs a)
     const uint64_t tbase = (uint64_t)tile * kTileCoords;
     const uint32_t loff = lane * 4u;
     const uint64_t block_floats = (uint64_t)a.cap_lines * kLineFloats;     // one block's part of a ring slot
+
+    // ---- where the tile's lines sit in the two slots (scalar loads, on their way while the subsets are hashed)
+    uint32_t word_s = 0, base_s = 0, word_r = 0, base_r = 0;
+    if (a.do_send) { word_s = uniform_load(a.send_meta, tile); base_s = uniform_load(a.send_sb_base, tile / kTilesPerSuperblock); }
+    if (a.do_recv && !TAU0) { word_r = uniform_load(a.recv_meta, tile); base_r = uniform_load(a.recv_sb_base, tile / kTilesPerSuperblock); }
 
     // ---- the subsets: bit j of a lane's mask = coordinate 4 group + j is received / sent now
     uint32_t mask_recv = 0, mask_send = 0;
@@ -919,11 +947,7 @@ k_average(const StepArgs a)
         if (lane == 0) a.next_lines[tile] = (count * RB + kLineFloats - 1u) / kLineFloats;
     }
 
-    // ---- where the tile's lines sit in the two slots; a tile whose lines would pass the slot
-    //      capacity is left out, at send and at receive alike
-    uint32_t word_s = 0, base_s = 0, word_r = 0, base_r = 0;
-    if (a.do_send) { word_s = uniform_load(a.send_meta, tile); base_s = uniform_load(a.send_sb_base, tile / kTilesPerSuperblock); }
-    if (a.do_recv && !TAU0) { word_r = uniform_load(a.recv_meta, tile); base_r = uniform_load(a.recv_sb_base, tile / kTilesPerSuperblock); }
+    // a tile whose lines would pass the slot capacity is left out, at send and at receive alike
     const uint32_t first_s = base_s + (word_s & 0xFFFFFFu), first_r = base_r + (word_r & 0xFFFFFFu);
     uint32_t lines_s = word_s >> 24, lines_r = word_r >> 24;
     if ((uint64_t)first_s + lines_s > a.cap_lines) { lines_s = 0; mask_send = 0u; }
@@ -970,22 +994,53 @@ k_average(const StepArgs a)
     };
 
     if constexpr (!TAU0) {
+        constexpr uint32_t kStaged = kStageFloats / RB;                    // received coordinates whose values are staged
+        extern __shared__ __attribute__((aligned(16))) float lds[];
+        float *const ring_lds = lds + wave * (average_wave_bytes<DIL, RB>(a.nblocks) / sizeof(float));
+        float *const d_lds = ring_lds + a.nblocks * kStageFloats;
+        // requests what the received coordinates of rank c0 .. c0 + kStaged - 1 need
+        auto stage = [&](const uint32_t c0) {
+            const uint32_t at = c0 * RB + lane * 4u;                       // a lane takes 16 bytes
+            if (at < lines_r * kLineFloats) {
+                const float *src = a.ring_recv + (uint64_t)first_r * kLineFloats + at;
+                for (uint32_t b = 0; b < a.nblocks; ++b) lds_dma_16(src + b * block_floats, ring_lds + b * kStageFloats);
+            }
+            if (kStageD<DIL, RB> && a.ema) {
+                uint8_t *const list = reinterpret_cast<uint8_t *>(d_lds + kStageFloats);
+                uint32_t c = rank_recv - c0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if ((mask_recv >> j) & 1u) {
+                        if (c < kStaged) list[c] = (uint8_t)(loff + (uint32_t)j);
+                        ++c;
+                    }
+                wave_lds_sync();
+                const uint32_t rank = lane * 4u / RB;                      // all or half of a coordinate's entries
+                if (c0 + rank < count_recv) lds_dma_16(a.d[b0] + (tbase + list[rank]) * RB + (lane * 4u) % RB, d_lds);
+            }
+        };
+        if (STAGED && count_recv != 0u) stage(0u);
         load_block(b0, true, true);
+        if (STAGED) {
+            lds_dma_wait();
+            wave_lds_sync();
+        }
         if (a.do_send && lines_s != 0u)
             average_send_block<RB>(a.ring_send + b0 * block_floats + (uint64_t)first_s * kLineFloats, w, mask_send, rank_send,
                                    count_send, lines_s * kPerLine, lane);
         // ---- receive: old average of what every replica sent (+ EMA of staleness)
-        if (count_recv != 0u) {                                            // same for the whole wave
-            const float *slot = a.ring_recv + (uint64_t)first_r * kLineFloats;
-            uint32_t c = rank_recv;
+        // the received coordinates of rank c0 .. c0 + most - 1; values(b, c, x): what block b's replicas sent for rank c0 + c
+        auto receive = [&](const uint32_t c0, const uint32_t most, auto values) {
+            uint32_t c = rank_recv - c0;                                   // (wraps below c0: not this turn's)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (((mask_recv >> j) & 1u) && c < lines_r * kPerLine) {   // (as at the send)
+                if (!((mask_recv >> j) & 1u)) continue;
+                if (c < most && c0 + c < lines_r * kPerLine) {             // (as at the send)
                     double sum = 0.;
                     float own[RB];
                     for (uint32_t b = 0; b < a.nblocks; ++b) {
                         float x[RB];
-                        load_block_values<RB>(slot + b * block_floats + (uint64_t)c * RB, x);
+                        values(b, c, x);
                         const uint32_t nrep = R - b * RB;                  // replicas present in this block (>= RB: all)
 #pragma unroll
                         for (int k = 0; k < RB; ++k) {
@@ -994,10 +1049,27 @@ k_average(const StepArgs a)
                             if ((uint32_t)k < nrep) sum += (double)q;
                         }
                     }
-                    average_receive<DIL, RB>(a, j, (float)(sum * inv_replicas), own,
-                                             DIL ? a.d[b0] + (tbase + loff + (uint32_t)j) * RB : nullptr, w, dv);
-                    ++c;
+                    float *const dp = DIL ? a.d[b0] + (tbase + loff + (uint32_t)j) * RB : nullptr;
+                    average_receive<DIL, RB>(a, j, (float)(sum * inv_replicas), own, kStageD<DIL, RB> ? d_lds + c * RB : dp, dp, w, dv);
                 }
+                ++c;
+            }
+        };
+        if constexpr (!STAGED) {
+            receive(0u, kTileCoords, [&](const uint32_t b, const uint32_t c, float (&x)[RB]) {
+                load_block_values<RB>(a.ring_recv + (uint64_t)first_r * kLineFloats + b * block_floats + (uint64_t)c * RB, x);
+            });
+        } else {
+            for (uint32_t c0 = 0; c0 < count_recv; c0 += kStaged) {        // nearly always one turn
+                if (c0 != 0u) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup"); // what the last turn read from LDS has been read
+                    stage(c0);
+                    lds_dma_wait();
+                    wave_lds_sync();
+                }
+                receive(c0, kStaged, [&](const uint32_t b, const uint32_t c, float (&x)[RB]) {
+                    load_block_values<RB>(ring_lds + b * kStageFloats + c * RB, x);
+                });
             }
         }
         store_block(b0);
@@ -1032,8 +1104,8 @@ k_average(const StepArgs a)
                         float own[RB];
 #pragma unroll
                         for (int k = 0; k < RB; ++k) own[k] = w[k].v[j];   // no delay: what was sent is this very value
-                        average_receive<DIL, RB>(a, j, (float)(sum[j] * inv_replicas), own,
-                                                 DIL ? a.d[b] + (tbase + loff + (uint32_t)j) * RB : nullptr, w, dv);
+                        float *const dp = DIL ? a.d[b] + (tbase + loff + (uint32_t)j) * RB : nullptr;
+                        average_receive<DIL, RB>(a, j, (float)(sum[j] * inv_replicas), own, dp, dp, w, dv);
                         ++c;
                     }
                 }

@@ -243,19 +243,37 @@ am_status launch_step_grad(am_state *st, const am::StepArgs &a)
 
 // The averaging-only kernel: one wave per (tile, block of replicas); with tau = 0 (the average is of this
 // call's own values) one wave per tile, which walks the blocks.
-template <bool DIL, bool TAU0>
-am_status launch_average(am_state *st, const am::StepArgs &a)
+template <bool DIL, int RB, bool TAU0, bool STAGED>
+am_status launch_average_kernel(am_state *st, const am::StepArgs &a)
 {
-    const am_host::Blocks &B = st->lay.blocks;
-    const dim3 grid((st->lay.ntiles + 3u) / 4u, TAU0 ? 1u : B.nblocks), block(256);
-    switch (B.rb) {
-    case 8: am::k_average<DIL, 8, TAU0><<<grid, block, 0, st->stream>>>(a); break;
-    case 4: am::k_average<DIL, 4, TAU0><<<grid, block, 0, st->stream>>>(a); break;
-    case 2: am::k_average<DIL, 2, TAU0><<<grid, block, 0, st->stream>>>(a); break;
-    default: am::k_average<DIL, 1, TAU0><<<grid, block, 0, st->stream>>>(a); break;
-    }
+    const uint32_t nblocks = st->lay.blocks.nblocks;
+    const dim3 grid((st->lay.ntiles + 3u) / 4u, TAU0 ? 1u : nblocks), block(256);
+    am::k_average<DIL, RB, TAU0, STAGED><<<grid, block, STAGED ? 4u * am::average_wave_bytes<DIL, RB>(nblocks) : 0u, st->stream>>>(a);
     AM_HIP(hipGetLastError());
     return AM_OK;
+}
+
+template <bool DIL, int RB>
+am_status launch_average_block(am_state *st, const am::StepArgs &a)
+{
+    if (a.do_recv && a.same_slot) return launch_average_kernel<DIL, RB, true, false>(st, a);
+    // Interleaved EMA vectors: always through LDS.  Per-replica ones: when a tile's ring values are expected to
+    // fill at most half of the staged kilobyte, so that one turn nearly always does (R = 8: p <= 6.25 %; measured
+    // there at 31.5M: 1 % 283 us against 345, 5 % 690 against 684, and with every coordinate selected 375 against 340).
+    if constexpr (!DIL)
+        if (st->cfg.fraction * am::kTileCoords * RB > am::kStageFloats / 2) return launch_average_kernel<DIL, RB, false, false>(st, a);
+    return launch_average_kernel<DIL, RB, false, true>(st, a);
+}
+
+template <bool DIL>
+am_status launch_average(am_state *st, const am::StepArgs &a)
+{
+    switch (st->lay.blocks.rb) {
+    case 8: return launch_average_block<DIL, 8>(st, a);
+    case 4: return launch_average_block<DIL, 4>(st, a);
+    case 2: return launch_average_block<DIL, 2>(st, a);
+    default: return launch_average_block<DIL, 1>(st, a);
+    }
 }
 
 // The averaging part of the kernel arguments for step t; launches the offsets pass when t sends.
@@ -649,9 +667,7 @@ am_status am_sparse_average(am_state *st, uint64_t t, float lambda_t)
             a.next_lines = st->next_lines();
         }
         const bool dil = st->cfg.d_layout == AM_D_INTERLEAVED && a.ema;
-        const bool tau0 = r.recv && r.same_slot;           // the average is of this call's own values
-        if (am_status s = dil ? (tau0 ? launch_average<true, true>(st, a) : launch_average<true, false>(st, a))
-                              : (tau0 ? launch_average<false, true>(st, a) : launch_average<false, false>(st, a))) return s;
+        if (am_status s = dil ? launch_average<true>(st, a) : launch_average<false>(st, a)) return s;
         if (do_next) st->next_lines_step = t + 1;
     }
     st->last_t = t;
