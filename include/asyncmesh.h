@@ -282,7 +282,7 @@ typedef struct {
     uint64_t last_t;            /* the last step made                                           */
     uint64_t next_lines_step;   /* the step whose send subset is already sized in the workspace */
     uint32_t delay_now;         /* the delay in force (am_set_delay)                            */
-    uint32_t reserved;
+    uint32_t reserved;          /* bit 0: which of the workspace's two size tables holds that subset's sizes */
     uint64_t opt_steps[AM_MAX_REPLICAS];   /* optimizer steps each replica has made             */
     double   mu_product[AM_MAX_REPLICAS];  /* NADAMW: running product of the momentum schedule  */
 } am_snapshot;

@@ -156,6 +156,7 @@ struct F4 { float v[4]; };
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 // The arrays of this update are streamed: every element is read once and written once per step,
 // so the dense accesses carry the non-temporal hint.

@@ -77,7 +77,7 @@ inline uint64_t slot_capacity_lines(uint64_t ntiles, double p, uint32_t rb, bool
 }
 
 // workspace = [flags 256 B][reduction partials 32 x 1024 doubles][next_lines u32[ntiles]][meta x (slots + 1)][ring values x slots]
-//   meta = tile words u32[ntiles] | sb_base u32[nsb + 1]      (the extra block serves am_subset_indices)
+//   meta = tile words u32[ntiles] | sb_base u32[nsb + 1]      (tile words of the extra block: the second table of next_lines; its sb_base is unused)
 //   ring slot = nblocks * cap_lines * 32 fp32: [block][line][32], a line = [coordinate][replica in block]
 struct Layout {
     uint32_t ntiles, nsb, slots;

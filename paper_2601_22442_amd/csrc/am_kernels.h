@@ -10,10 +10,10 @@ namespace am {
 // =============================================================================================
 // cnt[512] (LDS) holds the lines of the tiles of superblock blockIdx.x: write their exclusive
 // prefix, with the tile's own lines in the high 8 bits (a tile owns at most 64 lines and a superblock
-// at most 2^15), to local_off and their total to sb_sum.
+// at most 2^15), to local_off and their sum to *total.
 // Called by all threads of the workgroup (256 or more) after a barrier.
 __device__ __forceinline__ void scan_superblock(const uint32_t *cnt, uint32_t *wave_tot, uint32_t ntiles,
-                                                uint32_t *__restrict__ local_off, uint32_t *__restrict__ sb_sum)
+                                                uint32_t *__restrict__ local_off, uint32_t *__restrict__ total)
 {
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const uint32_t tile0 = blockIdx.x * kTilesPerSuperblock;
@@ -36,7 +36,7 @@ __device__ __forceinline__ void scan_superblock(const uint32_t *cnt, uint32_t *w
     const uint32_t t_a = tile0 + 2 * threadIdx.x;
     if (t_a < ntiles) local_off[t_a] = excl | (a << 24);
     if (t_a + 1 < ntiles) local_off[t_a + 1] = (excl + a) | (b << 24);
-    if (threadIdx.x == 255) sb_sum[blockIdx.x] = base + incl;
+    if (threadIdx.x == 255) *total = base + incl;
 }
 
 // Which of the 32 consecutive coordinates of a lane (2048 strip + 32 lane + bit) are in the subset.
@@ -76,7 +76,7 @@ k_subset_count(SubsetKey key, uint64_t n, uint32_t ntiles, uint32_t mul,
         if ((lane & 7u) == 0u) cnt[k * 8u + (lane >> 3)] = (count * mul + kLineFloats - 1u) / kLineFloats;
     }
     __syncthreads();
-    scan_superblock(cnt, wave_tot, ntiles, local_off, sb_sum);
+    scan_superblock(cnt, wave_tot, ntiles, local_off, sb_sum + blockIdx.x);
 }
 
 // Same, from tile sizes that are already in memory (the fused step kernel leaves the line counts
@@ -91,7 +91,67 @@ k_subset_offsets(const uint32_t *__restrict__ tile_size, uint32_t ntiles,
     for (uint32_t k = threadIdx.x; k < kTilesPerSuperblock; k += 256u)
         cnt[k] = tile0 + k < ntiles ? tile_size[tile0 + k] : 0u;
     __syncthreads();
-    scan_superblock(cnt, wave_tot, ntiles, local_off, sb_sum);
+    scan_superblock(cnt, wave_tot, ntiles, local_off, sb_sum + blockIdx.x);
+}
+
+// The same with the superblocks' bases, in one launch instead of k_subset_offsets and k_subset_scan (9 to 10 us
+// with the gap between them): every workgroup adds up all tiles before its own.  5.8 us for 54 superblocks,
+// 12 us for 240, so it serves stages of at most kOffsetsAtOnce superblocks (16.8M coordinates).
+constexpr uint32_t kOffsetsAtOnce = 128;
+__global__ void __launch_bounds__(1024)
+k_subset_offsets_at_once(const uint32_t *__restrict__ tile_size, uint32_t ntiles, uint32_t nsb, uint32_t capacity,
+                         uint32_t *__restrict__ local_off, uint32_t *__restrict__ sb_base, uint32_t *__restrict__ flags)
+{
+    __shared__ uint32_t cnt[kTilesPerSuperblock];
+    __shared__ uint32_t wave_tot[4], before[16], total;
+    const uint32_t tile0 = blockIdx.x * kTilesPerSuperblock;
+    if (threadIdx.x < kTilesPerSuperblock) cnt[threadIdx.x] = tile0 + threadIdx.x < ntiles ? tile_size[tile0 + threadIdx.x] : 0u;
+    uint32_t sum = 0;
+    for (uint32_t q = threadIdx.x; q < tile0 / 4u; q += 1024u) {
+        const v4u x = reinterpret_cast<const v4u *>(tile_size)[q];
+        sum += x.x + x.y + x.z + x.w;
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) sum += __shfl_xor(sum, off);
+    if ((threadIdx.x & 63u) == 0u) before[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    scan_superblock(cnt, wave_tot, ntiles, local_off, &total);
+    if (threadIdx.x == 255u) {                       // the thread that wrote the superblock's total
+        uint32_t base = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) base += before[w];
+        sb_base[blockIdx.x] = base;
+        if (blockIdx.x == nsb - 1u) {
+            sb_base[nsb] = base + total;
+            if (base + total > capacity) atomicOr(flags, 1u);
+        }
+    }
+}
+
+// Lines of the tiles before `tile`, this wave's share: of `waves` waves, wave w adds up words 256 w .. 256 w + 255,
+// then the stretch 256 waves further on, and so on for kSumLoads loads.  The shares of all waves add up to all of
+// them when tile <= kSumWords * waves.  lines: padded to whole 256 bytes.
+constexpr uint32_t kSumLoads = 4, kSumWords = 256 * kSumLoads;
+// The fused step adds up its tiles' places itself for at most this many tiles (524,288 coordinates), and no launch
+// precedes it: 500,000 coordinates, R = 4 18.9 us a step against 19.9 with k_subset_offsets_at_once (scaled from
+// 550,000), 262,144, R = 1 7.8 against 9.3; at 1M, R = 4 both take 35.1 us, at 2M, R = 8 it is 94.8 against 93.9.
+// The averaging-only kernel (four waves, and little else to read) does so for as many as four waves can add up
+// (4096 tiles: 1M, R = 4, p = 1 % 11.4 us a call, 17.4 with two offset launches).
+constexpr uint32_t kSumTilesStep = 2048;
+__device__ __forceinline__ uint32_t lines_before(const uint32_t *__restrict__ lines, uint32_t tile, uint32_t wave, uint32_t waves, uint32_t lane)
+{
+    uint32_t sum = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < kSumLoads; ++q) {
+        const uint32_t at = (wave + q * waves) * 256u + lane * 4u;
+        if (at < tile) {
+            const v4u x = *reinterpret_cast<const v4u *>(lines + at);
+            sum += x.x + (at + 1u < tile ? x.y : 0u) + (at + 2u < tile ? x.z : 0u) + (at + 3u < tile ? x.w : 0u);
+        }
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) sum += __shfl_xor(sum, off);
+    return sum;
 }
 
 // Single workgroup: exclusive scan of the superblock totals, in place (sb[i] <- sum of sb[<i]),
@@ -245,8 +305,12 @@ struct StepArgs {
     uint32_t do_send, do_recv, ema, same_slot;     // ema: a correction vector d is kept; same_slot: tau = 0,
                                                    // the average is of this step's w^
     uint32_t do_next;                              // also count the lines each tile will send next step
+    uint32_t sum_lines;                            // small stage: the kernel itself adds up where the tile's lines start in the
+                                                   // send slot (from send_lines) and writes the tile's word for the receive
     uint32_t msg_dtype;                            // precision of the exchanged values: 0 fp32, 1 bf16, 2 E4M3
     uint32_t cap_lines;                            // lines (of 32 floats) per block in a ring slot
+    const uint32_t *send_lines;                    // [ntiles] lines each tile sends now (sum_lines)
+    uint32_t *send_meta_out, *send_sb_out, *flags; // where its words go (sum_lines)
     const uint32_t *send_meta, *send_sb_base;      // tile's word: lines << 24 | offset in its superblock; first line = sb_base[tile >> 9] + offset
     const uint32_t *recv_meta, *recv_sb_base;
     float *ring_send;                              // slot written now: [block][line][32], a line = [coordinate][rb]
@@ -298,6 +362,17 @@ struct GroupIn {
     F4 w, g, m, v;          // weights, gradients (widened), moments
     F4 d;                   // EMA entries of the group (per-replica layout: loaded when its line receives)
 };
+
+// A small stage's tile word and superblock base as the offsets pass would leave them for the receive; the
+// word holds the first line in the slot itself, so every base is zero.  Called by one lane of one
+// workgroup per tile; first + lines is the slot's total for the last tile.
+__device__ __forceinline__ void write_send_word(const StepArgs &a, uint32_t tile, uint32_t first, uint32_t lines)
+{
+    a.send_meta_out[tile] = first | (lines << 24);
+    if (tile % kTilesPerSuperblock == 0u) a.send_sb_out[tile / kTilesPerSuperblock] = 0u;
+    if (first + lines > a.cap_lines) atomicOr(a.flags, 1u);
+    if (tile + 1u == a.ntiles) a.send_sb_out[tile / kTilesPerSuperblock + 1u] = first + lines;
+}
 
 // Local optimizer step on one group, from loaded operands.
 template <int OPT>
@@ -357,6 +432,7 @@ struct TileLds {
     float *send;        // [256 coordinates in rank order][rb]
     uint32_t *list;     // [64] tile-local index of the q-th touched line of d
     uint8_t *masks;     // [0..63] the lanes' masks of the sent subset, [64..127] of the received one
+    uint32_t *part;     // [8] the waves' shares of the lines before the tile (sum_lines)
     float *abar;        // [256] mean over the replicas of what they sent, per received coordinate in rank order
 };
 
@@ -384,27 +460,15 @@ __device__ __forceinline__ void load_group_sparse(const StepArgs &a, uint32_t i,
     if (!DIL && a.ema && s.line_recv) in.d = load_f32x4(a.d[i] + tbase, loff, nvalid);
 }
 
-// Replica i (slot `slot` of its block) of one group, from loaded operands to stored results.
-// recv_block: what the replicas of i's block sent tau rounds ago, [rank][rb].
-template <int OPT, int FWD, bool DIL, bool TAU0>
-__device__ __forceinline__ void step_replica(const StepArgs &a, const ReplicaArgs &r, uint32_t i, uint32_t slot, uint64_t tbase, uint32_t loff, int nvalid,
-                                             const GroupSubsets &s, const bool tile_receives, const float (&abar)[4], GroupIn &in,
-                                             F4 &w_hat, F4 &m_new, F4 &v_new, const float *recv_block, const TileLds &L)
+// Replica i (slot `slot` of its block) of one group, from its stepped weights to stored results: the
+// receive, the new weights and the forward copy.
+// recv_block: what the replicas of i's block sent tau rounds ago, [rank][rb] (TAU0: unused, the sent value is w^ itself).
+template <int FWD, bool DIL, bool TAU0>
+__device__ __forceinline__ void finish_replica(const StepArgs &a, const ReplicaArgs &r, uint32_t i, uint32_t slot, uint64_t tbase, uint32_t loff, int nvalid,
+                                               const GroupSubsets &s, const bool tile_receives, const float (&abar)[4], GroupIn &in,
+                                               const F4 &w_hat, const float *recv_block, const TileLds &L)
 {
     const uint32_t rb = a.rb;
-    if (TAU0 || !DIL) local_step<OPT>(a, r, i, in, w_hat, m_new, v_new);      // (else: done by the caller while it waited)
-    if (TAU0 || !DIL) {                                    // the moments are final: out they go, before the averaging needs registers
-        if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_f32x4(r.m + tbase, loff, nvalid, m_new);
-        if (OPT == kOptAdam) store_f32x4(r.v + tbase, loff, nvalid, v_new);
-    }
-
-    if (s.mask_send) {                                     // send: into the staging lines, [rank][rb]
-        uint32_t c = s.rank_send;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if ((s.mask_send >> j) & 1u) L.send[(c++) * rb + slot] = w_hat.v[j];
-    }
-
     F4 w_new;
 #pragma unroll
     for (int j = 0; j < 4; ++j) w_new.v[j] = w_hat.v[j];
@@ -458,6 +522,29 @@ __device__ __forceinline__ void step_replica(const StepArgs &a, const ReplicaArg
             store_bf16x4_from_f64(static_cast<uint16_t *>(r.fwd) + tbase, loff, nvalid, f);
         }
     }
+}
+
+// The same from loaded operands: local step (unless the caller has done it while it waited), send, receive.
+template <int OPT, int FWD, bool DIL, bool TAU0>
+__device__ __forceinline__ void step_replica(const StepArgs &a, const ReplicaArgs &r, uint32_t i, uint32_t slot, uint64_t tbase, uint32_t loff, int nvalid,
+                                             const GroupSubsets &s, const bool tile_receives, const float (&abar)[4], GroupIn &in,
+                                             F4 &w_hat, F4 &m_new, F4 &v_new, const float *recv_block, const TileLds &L)
+{
+    const uint32_t rb = a.rb;
+    if (TAU0 || !DIL) {
+        local_step<OPT>(a, r, i, in, w_hat, m_new, v_new);
+        // the moments are final: out they go, before the averaging needs registers
+        if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_f32x4(r.m + tbase, loff, nvalid, m_new);
+        if (OPT == kOptAdam) store_f32x4(r.v + tbase, loff, nvalid, v_new);
+    }
+
+    if (s.mask_send) {                                     // send: into the staging lines, [rank][rb]
+        uint32_t c = s.rank_send;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if ((s.mask_send >> j) & 1u) L.send[(c++) * rb + slot] = w_hat.v[j];
+    }
+    finish_replica<FWD, DIL, TAU0>(a, r, i, slot, tbase, loff, nvalid, s, tile_receives, abar, in, w_hat, recv_block, L);
 }
 
 // Mean over the replicas, in replica order and in fp64, of what they sent for the coordinate of
@@ -610,15 +697,28 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     }
     // ---- the tile's words in the offset tables of the two slots (scalar loads)
     uint32_t word_s = 0, base_s = 0, word_r = 0, base_r = 0;
-    if (a.do_send) { word_s = uniform_load(a.send_meta, tile); base_s = uniform_load(a.send_sb_base, tile / kTilesPerSuperblock); }
+    if (a.sum_lines) word_s = uniform_load(a.send_lines, tile) << 24;
+    else if (a.do_send) { word_s = uniform_load(a.send_meta, tile); base_s = uniform_load(a.send_sb_base, tile / kTilesPerSuperblock); }
     if (a.do_recv && !TAU0) { word_r = uniform_load(a.recv_meta, tile); base_r = uniform_load(a.recv_sb_base, tile / kTilesPerSuperblock); }
 
     // ---- where the tile's lines sit in the two slots.  A tile whose lines would pass the slot
-    //      capacity is left out, at send and at receive alike.
+    //      capacity is left out, at send and at receive alike.  (sum_lines: where it sends to is known after
+    //      the barrier.)
     uint32_t first_s = base_s + (word_s & 0xFFFFFFu), lines_s = word_s >> 24;
     uint32_t first_r = base_r + (word_r & 0xFFFFFFu), lines_r = word_r >> 24;
     bool keep_s = a.do_send != 0u, keep_r = a.do_recv != 0u;
-    if ((uint64_t)first_s + lines_s > a.cap_lines) { keep_s = false; lines_s = 0; }
+    auto find_send = [&]() {                                // every wave's share is in LDS
+        first_s = 0;
+        for (uint32_t w = 0; w < rb; ++w) first_s += L.part[w];
+        first_s = (uint32_t)__builtin_amdgcn_readfirstlane((int)first_s);
+        if (b0 == 0u && flat == 0u) write_send_word(a, tile, first_s, lines_s);
+        if (first_s + lines_s > a.cap_lines) { keep_s = false; lines_s = 0; s.mask_send = 0u; }
+    };
+    if (a.sum_lines) {
+        const uint32_t share = lines_before(a.send_lines, tile, wave, rb, lane);
+        if (lane == 0) L.part[wave] = share;
+        if (TAU0) { __syncthreads(); find_send(); }
+    } else if ((uint64_t)first_s + lines_s > a.cap_lines) { keep_s = false; lines_s = 0; }
     if (recv_is_send) { first_r = first_s; lines_r = lines_s; keep_r = keep_s; }
     else if ((uint64_t)first_r + lines_r > a.cap_lines) { keep_r = false; lines_r = 0; }
 
@@ -696,6 +796,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
         if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_f32x4(rep.m + tbase, loff, nvalid, m_new);
         if (OPT == kOptAdam) store_f32x4(rep.v + tbase, loff, nvalid, v_new);
     }
+    if (!TAU0 && a.sum_lines) find_send();
     if (!recv_is_send) finish_subsets();
 
     // ---- old average of the coordinates received now: thread c forms the mean of the coordinate of
@@ -750,7 +851,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
 // Floats of dynamic LDS a workgroup needs.
 __host__ __device__ inline uint32_t step_lds_floats(uint32_t rb, uint32_t nblocks, bool d_interleaved)
 {
-    return nblocks * kTileCoords * rb + (d_interleaved ? kTileCoords * rb : 0u) + kTileCoords * rb + 64u + 32u + kTileCoords;
+    return nblocks * kTileCoords * rb + (d_interleaved ? kTileCoords * rb : 0u) + kTileCoords * rb + 64u + 32u + 8u + kTileCoords;
 }
 
 // grid = (tiles, blocks) (tau = 0: (tiles, 1)); blockDim = 64 rb; dynamic LDS = step_lds_floats() floats
@@ -770,7 +871,8 @@ k_step(const StepArgs a)
     L.send = L.d + (DIL ? tile_floats : 0u);
     L.list = reinterpret_cast<uint32_t *>(L.send + tile_floats);
     L.masks = reinterpret_cast<uint8_t *>(L.list + 64);
-    L.abar = reinterpret_cast<float *>(L.list + 96);
+    L.part = L.list + 96;
+    L.abar = reinterpret_cast<float *>(L.list + 104);
     if ((uint64_t)(tile + 1u) * kTileCoords <= a.n)
         step_tile<OPT, GRAD_BF16, FWD, DIL, TAU0, true>(a, tile, b0, wave, lane, L);
     else
@@ -915,7 +1017,22 @@ k_average(const StepArgs a)
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t tile = blockIdx.x * 4u + wave, b0 = TAU0 ? 0u : blockIdx.y;
+    // small stage: the lines before the workgroup's first tile, a share a wave, and those of its own tiles before mine
+    uint32_t first_sum = 0, lines_sum = 0;
+    if (a.sum_lines) {
+        __shared__ uint32_t part[4];
+        const uint32_t share = lines_before(a.send_lines, blockIdx.x * 4u, wave, 4u, lane);
+        if (lane == 0) part[wave] = share;
+        __syncthreads();
+        first_sum = part[0] + part[1] + part[2] + part[3];
+        for (uint32_t w = 0; w < wave; ++w) first_sum += tile < a.ntiles ? uniform_load(a.send_lines, blockIdx.x * 4u + w) : 0u;
+        first_sum = (uint32_t)__builtin_amdgcn_readfirstlane((int)first_sum);
+    }
     if (tile >= a.ntiles) return;
+    if (a.sum_lines) {
+        lines_sum = uniform_load(a.send_lines, tile);
+        if (b0 == 0u && lane == 0) write_send_word(a, tile, first_sum, lines_sum);
+    }
     const uint32_t R = a.replicas;
     const uint64_t group = (uint64_t)tile * 64u + lane;
     const uint64_t mu = group * 4u;
@@ -926,7 +1043,8 @@ k_average(const StepArgs a)
 
     // ---- where the tile's lines sit in the two slots (scalar loads, on their way while the subsets are hashed)
     uint32_t word_s = 0, base_s = 0, word_r = 0, base_r = 0;
-    if (a.do_send) { word_s = uniform_load(a.send_meta, tile); base_s = uniform_load(a.send_sb_base, tile / kTilesPerSuperblock); }
+    if (a.sum_lines) { word_s = lines_sum << 24; base_s = first_sum; }
+    else if (a.do_send) { word_s = uniform_load(a.send_meta, tile); base_s = uniform_load(a.send_sb_base, tile / kTilesPerSuperblock); }
     if (a.do_recv && !TAU0) { word_r = uniform_load(a.recv_meta, tile); base_r = uniform_load(a.recv_sb_base, tile / kTilesPerSuperblock); }
 
     // ---- the subsets: bit j of a lane's mask = coordinate 4 group + j is received / sent now

@@ -121,7 +121,8 @@ struct am_state {
     bool has_fwd;
     char *ws;
     uint64_t last_t;
-    uint64_t next_lines_step;    // the step whose send subset next_lines() was sized for (0 = none)
+    uint64_t next_lines_step;    // the step whose send subset next_lines(next_buf) was sized for (0 = none)
+    uint32_t next_buf;           // which of the two size tables that is; a step reads one and fills the other
     uint32_t delay_now;          // the delay in force (<= cfg.delay, which sizes the ring)
     bool overflow_seen;          // am_read_flags has reported a subset that did not fit its ring slot
     // per replica, because replicas of unequal speed make unequal numbers of local steps:
@@ -136,7 +137,8 @@ struct am_state {
 
     uint32_t *flags() const { return reinterpret_cast<uint32_t *>(ws + lay.off_flags); }
     double *reduce_partials() const { return reinterpret_cast<double *>(ws + lay.off_reduce); }
-    uint32_t *next_lines() const { return reinterpret_cast<uint32_t *>(ws + lay.off_next); }
+    // sizes of the tiles of the next subset to be sent: the table of its own, or the offset block after the ring slots' own
+    uint32_t *next_lines(uint32_t buf) const { return buf ? meta_local(lay.slots) : reinterpret_cast<uint32_t *>(ws + lay.off_next); }
     uint32_t *meta_local(uint32_t slot) const { return reinterpret_cast<uint32_t *>(ws + lay.off_meta + lay.meta_stride * slot); }
     uint32_t *meta_sb(uint32_t slot) const { return reinterpret_cast<uint32_t *>(ws + lay.off_meta + lay.meta_stride * slot + lay.meta_sb_off); }
     float *ring(uint32_t slot) const { return reinterpret_cast<float *>(ws + lay.off_ring + lay.ring_stride * slot); }
@@ -163,15 +165,21 @@ am::SubsetKey make_key(const am_state *st, uint64_t step)
 am_status launch_ring_offsets(am_state *st, uint64_t step, uint32_t slot)
 {
     const Layout &L = st->lay;
+    const uint32_t cap = L.cap_lines > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)L.cap_lines;
     if (st->next_lines_step == step && step != 0) {
-        // the previous fused step already sized this subset's tiles
-        am::k_subset_offsets<<<L.nsb, 256, 0, st->stream>>>(st->next_lines(), L.ntiles, st->meta_local(slot), st->meta_sb(slot));
+        // the previous step already sized this subset's tiles
+        const uint32_t *sizes = st->next_lines(st->next_buf);
+        if (L.nsb <= am::kOffsetsAtOnce) {
+            am::k_subset_offsets_at_once<<<L.nsb, 1024, 0, st->stream>>>(sizes, L.ntiles, L.nsb, cap, st->meta_local(slot), st->meta_sb(slot), st->flags());
+            AM_HIP(hipGetLastError());
+            return AM_OK;
+        }
+        am::k_subset_offsets<<<L.nsb, 256, 0, st->stream>>>(sizes, L.ntiles, st->meta_local(slot), st->meta_sb(slot));
     } else {
         am::k_subset_count<<<L.nsb, 1024, 0, st->stream>>>(make_key(st, step), st->cfg.n, L.ntiles, L.blocks.rb,
                                                            st->meta_local(slot), st->meta_sb(slot));
     }
     AM_HIP(hipGetLastError());
-    const uint32_t cap = L.cap_lines > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)L.cap_lines;
     am::k_subset_scan<<<1, 256, 0, st->stream>>>(st->meta_sb(slot), L.nsb, cap, st->flags());
     AM_HIP(hipGetLastError());
     return AM_OK;
@@ -276,8 +284,9 @@ am_status launch_average(am_state *st, const am::StepArgs &a)
     }
 }
 
-// The averaging part of the kernel arguments for step t; launches the offsets pass when t sends.
-am_status fill_averaging(am_state *st, uint64_t t, float lambda_t, const Round &r, am::StepArgs &a)
+// The averaging part of the kernel arguments for step t; launches the offsets pass when t sends, unless the
+// stage has at most sum_tiles tiles: then the kernel's workgroups add up the sizes before their tile themselves.
+am_status fill_averaging(am_state *st, uint64_t t, float lambda_t, const Round &r, uint32_t sum_tiles, am::StepArgs &a)
 {
     const am_config &c = st->cfg;
     const am_host::Blocks &B = st->lay.blocks;
@@ -293,7 +302,15 @@ am_status fill_averaging(am_state *st, uint64_t t, float lambda_t, const Round &
     a.key = make_key(st, 0);
     for (uint32_t k = 0; k < st->d_arrays; ++k) a.d[k] = st->d[k];
     if (r.send) {
-        if (am_status s = launch_ring_offsets(st, t, r.slot_send)) return s;
+        a.sum_lines = st->next_lines_step == t && st->lay.ntiles <= sum_tiles;
+        if (a.sum_lines) {
+            a.send_lines = st->next_lines(st->next_buf);
+            a.send_meta_out = st->meta_local(r.slot_send);
+            a.send_sb_out = st->meta_sb(r.slot_send);
+            a.flags = st->flags();
+        } else if (am_status s = launch_ring_offsets(st, t, r.slot_send)) {
+            return s;
+        }
         a.step_lo[1] = (uint32_t)t; a.step_hi[1] = (uint32_t)(t >> 32);
         a.ring_send = st->ring(r.slot_send);
         a.send_meta = st->meta_local(r.slot_send);
@@ -402,6 +419,7 @@ am_status create_state(const am_config *cfg, const am_buffers *buf, void *hip_st
     st->ws = static_cast<char *>(buf->workspace);
     st->last_t = 0;
     st->next_lines_step = 0;
+    st->next_buf = 0;
     st->delay_now = cfg->delay;
     st->overflow_seen = false;
     for (uint32_t i = 0; i < AM_MAX_REPLICAS; ++i) { st->opt_steps[i] = 0; st->mu_product[i] = 1.0; }
@@ -463,7 +481,7 @@ am_status am_export_state(const am_state *st, am_snapshot *out)
     out->next_lines_step = st->next_lines_step;
     for (uint32_t i = 0; i < AM_MAX_REPLICAS; ++i) { out->opt_steps[i] = st->opt_steps[i]; out->mu_product[i] = st->mu_product[i]; }
     out->delay_now = st->delay_now;
-    out->reserved = 0;
+    out->reserved = st->next_buf;
     return AM_OK;
 }
 
@@ -481,6 +499,7 @@ am_status am_resume_state(const am_config *cfg, const am_buffers *buf, void *hip
     if (am_status s = create_state(cfg, buf, hip_stream, &st)) return s;
     st->last_t = snapshot->last_t;
     st->next_lines_step = snapshot->next_lines_step;
+    st->next_buf = snapshot->reserved & 1u;
     for (uint32_t i = 0; i < AM_MAX_REPLICAS; ++i) { st->opt_steps[i] = snapshot->opt_steps[i]; st->mu_product[i] = snapshot->mu_product[i]; }
     st->delay_now = snapshot->delay_now;
     *out = st;
@@ -608,13 +627,13 @@ am_status step_impl(am_state *st, uint64_t t, const void *const *grads, float lr
             if (b * B.rb + k >= c.replicas) a.rep[8u * b + k] = a.rep[8u * b];
 
     const Round r = plan_round(st, t);
-    if (am_status s = fill_averaging(st, t, lambda_t, r, a)) return s;
+    if (am_status s = fill_averaging(st, t, lambda_t, r, std::min(am::kSumWords * B.rb, am::kSumTilesStep), a)) return s;
 
     const bool do_next = (t + 1) % c.avg_interval == 0;      // the next step sends: size its tiles on the way
     a.do_next = do_next;
     if (do_next) {
         a.step_lo[2] = (uint32_t)(t + 1); a.step_hi[2] = (uint32_t)((t + 1) >> 32);
-        a.next_lines = st->next_lines();
+        a.next_lines = st->next_lines(st->next_buf ^ 1u);
     }
 
     if (timed) AM_HIP(hipEventRecord(ev0, st->stream));
@@ -627,7 +646,7 @@ am_status step_impl(am_state *st, uint64_t t, const void *const *grads, float lr
         st->ev_used += 2;
     }
     st->last_t = t;
-    if (do_next) st->next_lines_step = t + 1;
+    if (do_next) { st->next_lines_step = t + 1; st->next_buf ^= 1u; }
     for (uint32_t i = 0; i < c.replicas; ++i) { st->opt_steps[i] = steps_next[i]; st->mu_product[i] = mu_prod_next[i]; }
     return AM_OK;
 }
@@ -660,15 +679,15 @@ am_status am_sparse_average(am_state *st, uint64_t t, float lambda_t)
         am::StepArgs a;
         std::memset(&a, 0, sizeof a);
         for (uint32_t i = 0; i < st->cfg.replicas; ++i) a.rep[8u * (i / st->lay.blocks.rb) + i % st->lay.blocks.rb].w = st->w[i];
-        if (am_status s = fill_averaging(st, t, lambda_t, r, a)) return s;
+        if (am_status s = fill_averaging(st, t, lambda_t, r, am::kSumWords * 4u, a)) return s;
         a.do_next = do_next;
         if (do_next) {
             a.step_lo[2] = (uint32_t)(t + 1); a.step_hi[2] = (uint32_t)((t + 1) >> 32);
-            a.next_lines = st->next_lines();
+            a.next_lines = st->next_lines(st->next_buf ^ 1u);
         }
         const bool dil = st->cfg.d_layout == AM_D_INTERLEAVED && a.ema;
         if (am_status s = dil ? launch_average<true>(st, a) : launch_average<false>(st, a)) return s;
-        if (do_next) st->next_lines_step = t + 1;
+        if (do_next) { st->next_lines_step = t + 1; st->next_buf ^= 1u; }
     }
     st->last_t = t;
     return AM_OK;
@@ -696,8 +715,8 @@ am_status am_lookahead(void *out, uint32_t out_dtype, const float *w, const floa
 am_status am_subset_indices(am_state *st, uint64_t t, uint64_t *dev_out, uint64_t capacity, uint64_t *dev_count)
 {
     if (am_status s = check_index_list_args(st, dev_out, capacity, dev_count)) return s;
-    const uint32_t meta_slot = st->lay.slots;        // the metadata block after the ring slots' own
-    return launch_index_list(st, t, st->meta_local(meta_slot), dev_out, capacity, dev_count);
+    // the reductions' partials are free between calls on the stream; 2^32 coordinates have 16,384 parts of 32 strips a wave
+    return launch_index_list(st, t, reinterpret_cast<uint32_t *>(st->reduce_partials()), dev_out, capacity, dev_count);
 }
 
 am_status am_subset_indices_static(am_state *st, uint64_t t, uint64_t *dev_out, uint64_t capacity, uint64_t *dev_count)
