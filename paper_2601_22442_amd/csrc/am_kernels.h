@@ -879,6 +879,168 @@ k_step(const StepArgs a)
         step_tile<OPT, GRAD_BF16, FWD, DIL, TAU0, false>(a, tile, b0, wave, lane, L);
 }
 
+// tau = 0 with at most kSyncWaves replicas: the average is of this step's values, so a tile needs all its
+// replicas at once.  One workgroup per tile, one wave per replica whatever its block: every operand is read once
+// and every local step made once, the stepped weights of the sampled coordinates meet in LDS (they are also
+// the lines that are sent), and from there on it is the delayed kernel.  (A workgroup of one block's waves
+// walking the blocks reads the operands of all blocks but its first twice and steps every replica twice.
+// Measured, us a step before / after: R = 12, 7.1M, AdamW, no correction 529 / 417 (5.7 TB/s), R = 16, 10M, bf16 1149 /
+// 796, R = 8, 10M, EMA 500 / 460 (interleaved) and 531 / 488 (per replica), R = 3 213 / 193.)
+constexpr uint32_t kSyncWaves = 16;
+
+template <int OPT, bool GRAD_BF16, int FWD, bool DIL, bool FULL>
+__device__ __forceinline__ void step_tile_sync(const StepArgs &a, const uint32_t tile, const uint32_t wave, const uint32_t lane, const TileLds &L)
+{
+    const uint32_t R = a.replicas, rb = a.rb, sh = a.rb_shift;
+    const uint32_t b = wave >> sh, slot = wave & (rb - 1u), flat = wave * 64u + lane, threads = R * 64u;
+    const uint64_t group = (uint64_t)tile * 64u + lane;
+    const uint64_t mu = group * 4u;
+    const int nvalid = FULL ? 4 : (mu >= a.n ? 0 : (a.n - mu >= 4u ? 4 : (int)(a.n - mu)));
+    const uint64_t tbase = (uint64_t)tile * kTileCoords;
+    const uint32_t loff = lane * 4u, tile_floats = kTileCoords * rb;
+    const uint64_t block_floats = (uint64_t)a.cap_lines * kLineFloats;
+
+    const ReplicaArgs rep = a.rep[8u * b + slot];
+    GroupIn in;
+    load_group<OPT, GRAD_BF16>(rep, tbase, loff, nvalid, in);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- the subset: hashed by the first wave of every block (which requests its block's lines of an
+    //      interleaved d), and by every wave where it steers the loads of a per-replica d
+    GroupSubsets s;
+    s.mask_send = s.mask_recv = s.rank_send = s.rank_recv = s.d_slot = 0;
+    s.line_recv = false;
+    const uint32_t lpl = 8u >> sh, leader = lane & ~(lpl - 1u);            // lanes (groups) per 128-byte line of an interleaved d
+    auto leaders_of = [&](const uint32_t mask) {                           // bit = first lane of a touched line of d
+        const uint64_t any = __ballot(mask != 0u);
+        return (uint64_t)__ballot(((any >> leader) & ((1ull << lpl) - 1ull)) != 0ull && lane == leader);
+    };
+    SubsetKey key = a.key;
+    if (slot == 0u || (!DIL && a.ema)) {
+        key.step_lo = a.step_lo[1]; key.step_hi = a.step_hi[1];
+        const uint32_t mask = member_mask(key, group, nvalid);
+        if (wave == 0u) L.masks[lane] = (uint8_t)mask;
+        if (DIL && a.ema) {
+            const uint64_t leaders = leaders_of(mask);
+            const uint32_t nlines = (uint32_t)__popcll(leaders);
+            if ((leaders >> lane) & 1ull) L.list[__popcll(leaders & ((1ull << lane) - 1ull))] = lane >> (3u - sh);    // (the same from every block)
+            wave_lds_sync();
+            const float *src = a.d[b] + (uint64_t)tile * tile_floats + (lane & 7u) * 4u;
+            for (uint32_t q0 = 0; q0 < nlines; q0 += 8u) {
+                const uint32_t q = q0 + (lane >> 3);
+                if (q < nlines) lds_dma_16(src + L.list[q] * kLineFloats, L.d + b * tile_floats + q0 * kLineFloats);
+            }
+        }
+        if (!DIL && a.ema) {
+            const uint64_t any = __ballot(mask != 0u);
+            s.line_recv = ((any >> (lane & ~7u)) & 0xFFull) != 0ull;
+            load_group_sparse<DIL>(a, wave, tbase, loff, nvalid, s, in);
+        }
+    }
+    if (a.do_next && wave == (R > 1u ? 1u : 0u)) {
+        key.step_lo = a.step_lo[2]; key.step_hi = a.step_hi[2];
+        uint32_t count;
+        (void)wave_prefix_mask4(member_mask(key, group, nvalid), count);
+        if (lane == 0) a.next_lines[tile] = (count * rb + kLineFloats - 1u) / kLineFloats;
+    }
+
+    // ---- where the tile's lines sit in the slot
+    uint32_t first = 0, lines;
+    if (a.sum_lines) {
+        lines = uniform_load(a.send_lines, tile);
+        const uint32_t share = lines_before(a.send_lines, tile, wave, R, lane);
+        if (lane == 0) L.part[wave] = share;
+    } else {
+        const uint32_t word = uniform_load(a.send_meta, tile);
+        first = uniform_load(a.send_sb_base, tile / kTilesPerSuperblock) + (word & 0xFFFFFFu);
+        lines = word >> 24;
+    }
+    for (uint32_t q = 0; q < a.nblocks; ++q)               // line tails and the slots of absent replicas are zero
+        for (uint32_t f = flat; f < lines * 8u; f += threads)
+            *reinterpret_cast<v4f *>(L.recv + q * tile_floats + f * 4u) = v4f{0.f, 0.f, 0.f, 0.f};
+
+    F4 w_hat, m_new, v_new;
+    local_step<OPT>(a, rep, wave, in, w_hat, m_new, v_new);
+    lds_dma_wait();
+    __syncthreads();
+    if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_f32x4(rep.m + tbase, loff, nvalid, m_new);
+    if (OPT == kOptAdam) store_f32x4(rep.v + tbase, loff, nvalid, v_new);
+
+    if (a.sum_lines) {
+        for (uint32_t w = 0; w < R; ++w) first += L.part[w];
+        first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
+        if (flat == 0u) write_send_word(a, tile, first, lines);
+    }
+    if ((uint64_t)first + lines > a.cap_lines) lines = 0;  // a tile whose lines would pass the slot capacity is left out
+    s.mask_send = s.mask_recv = lines ? (uint32_t)L.masks[lane] : 0u;
+    uint32_t count, d_lines = 0;
+    s.rank_send = s.rank_recv = wave_prefix_mask4(s.mask_recv, count);
+    const uint64_t any = __ballot(s.mask_recv != 0u);
+    s.line_recv = ((any >> (lane & ~7u)) & 0xFFull) != 0ull;
+    if (DIL && a.ema) {
+        const uint64_t leaders = leaders_of(s.mask_recv);
+        d_lines = (uint32_t)__popcll(leaders);
+        s.d_slot = (uint32_t)__popcll(leaders & ((1ull << leader) - 1ull)) * kLineFloats + (lane & (lpl - 1u)) * 4u * rb;
+    }
+
+    float abar[4] = {0.f, 0.f, 0.f, 0.f};
+    if (count) {                                           // same for the whole workgroup
+        uint32_t c = s.rank_send;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if ((s.mask_send >> j) & 1u) L.recv[b * tile_floats + (c++) * rb + slot] = w_hat.v[j];
+        __syncthreads();
+        for (uint32_t q = 0; q < a.nblocks; ++q)           // whole lines leave with 16 bytes per thread
+            for (uint32_t f = flat; f < lines * 8u; f += threads) {
+                float *dst = a.ring_send + q * block_floats + (uint64_t)first * kLineFloats + f * 4u;
+                __builtin_nontemporal_store(*reinterpret_cast<const v4f *>(L.recv + q * tile_floats + f * 4u), reinterpret_cast<v4f *>(dst));
+            }
+        for (c = flat; c < count; c += threads)
+            L.abar[c] = rb == 8u ? replica_mean<8>(a, L.recv, c) : rb == 4u ? replica_mean<4>(a, L.recv, c)
+                      : rb == 2u ? replica_mean<2>(a, L.recv, c) : replica_mean<1>(a, L.recv, c);
+        __syncthreads();
+        c = s.rank_recv;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { const uint32_t bit = (s.mask_recv >> j) & 1u; abar[j] = L.abar[bit ? c : 0u]; c += bit; }
+    }
+    TileLds mine = L;
+    if (DIL) mine.d = L.d + b * tile_floats;
+    finish_replica<FWD, DIL, true>(a, rep, wave, slot, tbase, loff, nvalid, s, count != 0u, abar, in, w_hat, nullptr, mine);
+    if (DIL && a.ema && d_lines) {
+        __syncthreads();
+        for (uint32_t q = 0; q < a.nblocks; ++q)
+            for (uint32_t f = flat; f < d_lines * 8u; f += threads) {
+                float *dst = a.d[q] + (uint64_t)tile * tile_floats + L.list[f >> 3] * kLineFloats + (f & 7u) * 4u;
+                __builtin_nontemporal_store(*reinterpret_cast<const v4f *>(L.d + q * tile_floats + f * 4u), reinterpret_cast<v4f *>(dst));
+            }
+    }
+}
+
+__host__ __device__ inline uint32_t step_sync_lds_floats(uint32_t rb, uint32_t nblocks, bool d_interleaved)
+{
+    return nblocks * kTileCoords * rb * (d_interleaved ? 2u : 1u) + 64u + 32u + kSyncWaves + kTileCoords;
+}
+
+// grid = tiles; blockDim = 64 replicas; dynamic LDS = step_sync_lds_floats() floats
+template <int OPT, bool GRAD_BF16, int FWD, bool DIL>
+__global__ void __launch_bounds__(64 * kSyncWaves, 6)
+k_step_sync(const StepArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t tile = blockIdx.x, all_floats = a.nblocks * kTileCoords * a.rb;
+    TileLds L;
+    L.recv = L.send = lds;
+    L.d = L.recv + all_floats;
+    L.list = reinterpret_cast<uint32_t *>(L.d + (DIL ? all_floats : 0u));
+    L.masks = reinterpret_cast<uint8_t *>(L.list + 64);
+    L.part = L.list + 96;
+    L.abar = reinterpret_cast<float *>(L.list + 96 + kSyncWaves);
+    if ((uint64_t)(tile + 1u) * kTileCoords <= a.n) step_tile_sync<OPT, GRAD_BF16, FWD, DIL, true>(a, tile, wave, lane, L);
+    else step_tile_sync<OPT, GRAD_BF16, FWD, DIL, false>(a, tile, wave, lane, L);
+}
+
 // =============================================================================================
 // Averaging alone (am_sparse_average): subset, send, replica mean, EMA correction and scatter
 // (asynchronous sparse averaging equations) on weights the caller has already stepped.

@@ -212,14 +212,20 @@ Round plan_round(const am_state *st, uint64_t t)
     return am_host::plan_round(st->cfg.avg_interval, (uint64_t)st->cfg.delay + 1, st->delay_now, t);
 }
 
-// One workgroup per (tile, block of replicas), one wave per replica of the block; when the average
-// is of this very step's values (tau = 0) a workgroup walks all the blocks of its tile, because it
-// needs every replica's new weights.
+// One workgroup per (tile, block of replicas), one wave per replica of the block.  When the average is
+// of this very step's values (tau = 0) a workgroup needs every replica's new weights: up to 16 replicas
+// (1024 threads) it has a wave for each, beyond that it walks the blocks of its tile.
 template <int OPT, bool GBF, int FWD, bool DIL>
 am_status launch_step_tau(am_state *st, const am::StepArgs &a)
 {
     const am_host::Blocks &B = st->lay.blocks;
     const bool tau0 = a.do_recv && a.same_slot;
+    if (tau0 && a.replicas <= am::kSyncWaves) {
+        const size_t lds = (size_t)am::step_sync_lds_floats(B.rb, B.nblocks, DIL) * sizeof(float);
+        am::k_step_sync<OPT, GBF, FWD, DIL><<<st->lay.ntiles, 64u * a.replicas, lds, st->stream>>>(a);
+        AM_HIP(hipGetLastError());
+        return AM_OK;
+    }
     const dim3 grid(st->lay.ntiles, tau0 ? 1u : B.nblocks), block(64u * B.rb);
     const size_t lds = (size_t)am::step_lds_floats(B.rb, B.nblocks, DIL) * sizeof(float);
     if (tau0) am::k_step<OPT, GBF, FWD, DIL, true><<<grid, block, lds, st->stream>>>(a);

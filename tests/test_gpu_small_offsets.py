@@ -66,7 +66,7 @@ def test_resumed_record_names_its_size_table(amlib, steps, n):
         g, gd = grads_for(n, R, t, 8, False)
         st.step(t, gd, 1e-3, 0.5); orc.step(t, g, 1e-3, 0.5)
     torch.cuda.synchronize()
-    st2 = am.Stage.resume(st.cfg, st.export_state(), *[[x.clone() for x in getattr(st, k)] for k in ("w", "m", "v", "d")], None, st.workspace.clone())
+    st2 = am.Stage.resume(st.cfg, st.export_state(), *[[x.clone() for x in getattr(st, k)] for k in ("w", "m", "v", "d_storage")], None, st.workspace.clone())
     for t in range(steps + 1, steps + 4):
         g, gd = grads_for(n, R, t, 8, False)
         for s in (st, st2):
