@@ -608,10 +608,12 @@ __device__ __forceinline__ float replica_mean(const StepArgs &a, const float *re
 //
 // FULL = every coordinate of the tile exists (all but possibly the last tile of the stage): all
 // dense accesses are unconditional 128-bit ones.
+// SUM = small stage: the workgroup adds up where its tile's lines start in the send slot itself (as a run-time
+// switch it costs every stage 0.5 %: 5990 against 5962 us on the headline one).
 // TAU0 = the average is of this very step's values (tau = 0): the workgroup walks all the blocks
 // of its tile, because it needs every replica's new weights (a rarely used mode, kept out of the
 // code of the common one).
-template <int OPT, bool GRAD_BF16, int FWD, bool DIL, bool TAU0, bool FULL>
+template <int OPT, bool GRAD_BF16, int FWD, bool DIL, bool TAU0, bool SUM, bool FULL>
 __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile, const uint32_t b0, const uint32_t wave,
                                           const uint32_t lane, const TileLds &L)
 {
@@ -619,6 +621,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     // loads of per-replica arrays that should leave before the barrier (per-replica layout of d).
     const bool kShareRecv = DIL || !a.ema;
     constexpr bool kShareSend = true;
+    const bool sum_lines = TAU0 ? a.sum_lines != 0u : SUM;
     const uint32_t R = a.replicas, rb = a.rb, sh = a.rb_shift;
     const uint32_t flat = wave * 64u + lane;                               // 64 rb threads; thread f owns 16-byte chunk f
     const uint64_t group = (uint64_t)tile * 64u + lane;
@@ -696,7 +699,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     }
     // ---- the tile's words in the offset tables of the two slots (scalar loads)
     uint32_t word_s = 0, base_s = 0, word_r = 0, base_r = 0;
-    if (a.sum_lines) word_s = uniform_load(a.send_lines, tile) << 24;
+    if (sum_lines) word_s = uniform_load(a.send_lines, tile) << 24;
     else if (a.do_send) { word_s = uniform_load(a.send_meta, tile); base_s = uniform_load(a.send_sb_base, tile / kTilesPerSuperblock); }
     if (a.do_recv && !TAU0) { word_r = uniform_load(a.recv_meta, tile); base_r = uniform_load(a.recv_sb_base, tile / kTilesPerSuperblock); }
 
@@ -713,7 +716,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
         if (b0 == 0u && flat == 0u) write_send_word(a, tile, first_s, lines_s);
         if (first_s + lines_s > a.cap_lines) { keep_s = false; lines_s = 0; s.mask_send = 0u; }
     };
-    if (a.sum_lines) {
+    if (sum_lines) {
         const uint32_t share = lines_before(a.send_lines, tile, wave, rb, lane);
         if (lane == 0) L.part[wave] = share;
         if (TAU0) { __syncthreads(); find_send(); }
@@ -799,7 +802,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
         if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_f32x4(rep.m + tbase, loff, nvalid, m_new);
         if (OPT == kOptAdam) store_f32x4(rep.v + tbase, loff, nvalid, v_new);
     }
-    if (!TAU0 && a.sum_lines) find_send();
+    if (!TAU0 && sum_lines) find_send();
     if (!recv_is_send) finish_subsets();
 
     // ---- old average of the coordinates received now: thread c forms the mean of the coordinate of
@@ -859,7 +862,7 @@ __host__ __device__ inline uint32_t step_lds_floats(uint32_t rb, uint32_t nblock
 
 // grid = (tiles, blocks) (tau = 0: (tiles, 1)); blockDim = 64 rb; dynamic LDS = step_lds_floats() floats
 // (at most 80 registers, so that three workgroups of eight waves fit a compute unit)
-template <int OPT, bool GRAD_BF16, int FWD, bool DIL, bool TAU0>
+template <int OPT, bool GRAD_BF16, int FWD, bool DIL, bool TAU0, bool SUM>
 __global__ void __launch_bounds__(512, 6)
 k_step(const StepArgs a)
 {
@@ -877,9 +880,9 @@ k_step(const StepArgs a)
     L.part = L.list + 96;
     L.abar = reinterpret_cast<float *>(L.list + 104);
     if ((uint64_t)(tile + 1u) * kTileCoords <= a.n)
-        step_tile<OPT, GRAD_BF16, FWD, DIL, TAU0, true>(a, tile, b0, wave, lane, L);
+        step_tile<OPT, GRAD_BF16, FWD, DIL, TAU0, SUM, true>(a, tile, b0, wave, lane, L);
     else
-        step_tile<OPT, GRAD_BF16, FWD, DIL, TAU0, false>(a, tile, b0, wave, lane, L);
+        step_tile<OPT, GRAD_BF16, FWD, DIL, TAU0, SUM, false>(a, tile, b0, wave, lane, L);
 }
 
 // tau = 0 with at most kSyncWaves replicas: the average is of this step's values, so a tile needs all its

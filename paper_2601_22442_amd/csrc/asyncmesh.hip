@@ -228,8 +228,9 @@ am_status launch_step_tau(am_state *st, const am::StepArgs &a)
     }
     const dim3 grid(st->lay.ntiles, tau0 ? 1u : B.nblocks), block(64u * B.rb);
     const size_t lds = (size_t)am::step_lds_floats(B.rb, B.nblocks, DIL) * sizeof(float);
-    if (tau0) am::k_step<OPT, GBF, FWD, DIL, true><<<grid, block, lds, st->stream>>>(a);
-    else am::k_step<OPT, GBF, FWD, DIL, false><<<grid, block, lds, st->stream>>>(a);
+    if (tau0) am::k_step<OPT, GBF, FWD, DIL, true, false><<<grid, block, lds, st->stream>>>(a);
+    else if (a.sum_lines) am::k_step<OPT, GBF, FWD, DIL, false, true><<<grid, block, lds, st->stream>>>(a);
+    else am::k_step<OPT, GBF, FWD, DIL, false, false><<<grid, block, lds, st->stream>>>(a);
     AM_HIP(hipGetLastError());
     return AM_OK;
 }
