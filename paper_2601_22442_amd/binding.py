@@ -6,6 +6,7 @@ module without the built library raises.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes as C
 from pathlib import Path
 
@@ -162,6 +163,14 @@ def _stream_handle(device) -> int:
     return int(torch.cuda.current_stream(device).cuda_stream)
 
 
+_NO_SWITCH = contextlib.nullcontext()
+
+
+def _on(device):
+    """Context in which `device` is current; entering torch's is 1.3 us a call, so only when it is not already."""
+    return _NO_SWITCH if device.index == torch.cuda.current_device() else torch.cuda.device(device)
+
+
 class Stage:
     """State of one pipeline stage replicated R times on one GPU (am_state plus the device
     tensors it is bound to).  Methods carry the names of the C entry points."""
@@ -250,7 +259,7 @@ class Stage:
                 setattr(bufs, name, C.cast(self._tables[name], C.POINTER(C.c_void_p)))
         bufs.workspace = self.workspace.data_ptr()
         bufs.workspace_bytes = self.workspace.numel()
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             if snapshot is None:
                 _check(lib.am_init_state(C.byref(self.cfg), C.byref(bufs), _stream_handle(self.device), C.byref(self._handle)))
             else:
@@ -282,7 +291,7 @@ class Stage:
     def step(self, t: int, grads, lr: float, lambda_t: float = 0.5, grad_scale: float = 1.0):
         self._check_grads(grads)
         table = _ptr_table(grads)
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             _check(lib.am_step(self._handle, t, table, lr, lambda_t, grad_scale))
 
     def step_scaled(self, t: int, grads, lr: float, lambda_t: float, grad_scale: float, replica_scale: torch.Tensor):
@@ -291,7 +300,7 @@ class Stage:
         assert replica_scale.is_cuda and replica_scale.dtype == torch.float32
         assert replica_scale.numel() == self.R and replica_scale.is_contiguous()
         table = _ptr_table(grads)
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             _check(lib.am_step_scaled(self._handle, t, table, lr, lambda_t, grad_scale, replica_scale.data_ptr()))
 
     def step_masked(self, t: int, grads, lr: float, lambda_t: float, active_mask: int, grad_scale: float = 1.0,
@@ -300,7 +309,7 @@ class Stage:
         grads[i] of an idle replica may be None."""
         self._check_grads([g if (active_mask >> i) & 1 else None for i, g in enumerate(grads)], allow_none=True)
         table = (C.c_void_p * self.R)(*[None if g is None else g.data_ptr() for g in grads])
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             _check(lib.am_step_masked(self._handle, t, table, lr, lambda_t, grad_scale,
                                       None if replica_scale is None else replica_scale.data_ptr(), active_mask))
 
@@ -309,19 +318,19 @@ class Stage:
         self._check_grads(grads)
         out = torch.empty(self.R, dtype=torch.float64, device=self.device)
         table = _ptr_table(grads)
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             _check(lib.am_grad_sqnorm(self._handle, table, out.data_ptr()))
         return out
 
     def sparse_average(self, t: int, lambda_t: float = 0.5):
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             _check(lib.am_sparse_average(self._handle, t, lambda_t))
 
     def subset_indices(self, t: int, capacity: int | None = None) -> torch.Tensor:
         cap = self.n if capacity is None else capacity
         out = torch.empty(max(cap, 1), dtype=torch.int64, device=self.device)
-        count = torch.zeros(1, dtype=torch.int64, device=self.device)
-        with torch.cuda.device(self.device):
+        count = torch.empty(1, dtype=torch.int64, device=self.device)
+        with _on(self.device):
             _check(lib.am_subset_indices(self._handle, t, out.data_ptr(), cap, count.data_ptr()))
         k = int(count.item())
         return out[:min(k, cap)], k
@@ -332,7 +341,7 @@ class Stage:
         read back."""
         assert out.is_cuda and out.dtype == torch.int64 and out.is_contiguous()
         assert count.is_cuda and count.dtype == torch.int64 and count.numel() == 1
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             _check(lib.am_subset_indices_static(self._handle, t, out.data_ptr(), out.numel(), count.data_ptr()))
 
     def set_delay(self, tau: int):
@@ -340,8 +349,8 @@ class Stage:
 
     def diagnostics(self):
         """(consensus error, mean EMA variance, max EMA variance) as Python floats (synchronises)."""
-        out = torch.zeros(3, dtype=torch.float64, device=self.device)
-        with torch.cuda.device(self.device):
+        out = torch.empty(3, dtype=torch.float64, device=self.device)      # the library writes all three
+        with _on(self.device):
             _check(lib.am_diagnostics(self._handle, out.data_ptr()))
         return tuple(float(x) for x in out.cpu())
 
@@ -391,7 +400,7 @@ def lookahead(w: torch.Tensor, w_prev: torch.Tensor, gamma: float, out_dtype=F32
     assert w.is_cuda and w_prev.is_cuda and w.dtype == torch.float32 and w_prev.dtype == torch.float32
     assert w.is_contiguous() and w_prev.is_contiguous() and w.numel() == w_prev.numel()
     out = torch.empty(w.numel(), dtype=torch.bfloat16 if out_dtype == BF16 else torch.float32, device=w.device)
-    with torch.cuda.device(w.device):
+    with _on(w.device):
         _check(lib.am_lookahead(out.data_ptr(), out_dtype, w.data_ptr(), w_prev.data_ptr(), w.numel(), gamma,
                                 _stream_handle(w.device)))
     return out
