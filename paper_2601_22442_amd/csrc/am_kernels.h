@@ -602,17 +602,17 @@ __device__ __forceinline__ float replica_mean(const StepArgs &a, const float *re
 // Hashing a subset costs ten rounds of two 32 x 32 -> 64 multiplies per lane; the subsets are the
 // same for every wave of the workgroup, so (fused step) one wave hashes the received subset, one
 // the sent one, one the next step's, and the others read the 4-bit masks from LDS after the barrier
-// they have to pass anyway.  (Where the masks steer loads of per-replica arrays -- the per-replica
-// layout of d -- every wave still hashes the received subset itself, so that those loads go out
+// they have to pass anyway.  (Where the masks steer loads of per-replica arrays -- a correction vector in
+// the per-replica layout -- every wave still hashes the received subset itself, so that those loads go out
 // before the barrier.)
 //
 // FULL = every coordinate of the tile exists (all but possibly the last tile of the stage): all
 // dense accesses are unconditional 128-bit ones.
 // SUM = small stage: the workgroup adds up where its tile's lines start in the send slot itself (as a run-time
 // switch it costs every stage 0.5 %: 5990 against 5962 us on the headline one).
-// TAU0 = the average is of this very step's values (tau = 0): the workgroup walks all the blocks
-// of its tile, because it needs every replica's new weights (a rarely used mode, kept out of the
-// code of the common one).
+// TAU0 = the average is of this very step's values (tau = 0) and there are more than kSyncWaves replicas: the
+// workgroup walks all the blocks of its tile, because it needs every replica's new weights (fewer
+// replicas: step_tile_sync).
 template <int OPT, bool GRAD_BF16, int FWD, bool DIL, bool TAU0, bool SUM, bool FULL>
 __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile, const uint32_t b0, const uint32_t wave,
                                           const uint32_t lane, const TileLds &L)
