@@ -185,7 +185,11 @@ k_subset_scan(uint32_t *__restrict__ sb, uint32_t nsb, uint32_t capacity, uint32
 // p = 5 %), so every coordinate is hashed once: a workgroup (four waves of `strips` strips each) keeps its
 // masks in LDS, publishes how many coordinates it holds, adds up what all the workgroups before it
 // hold and writes its indices there.  A lane holds 32 consecutive coordinates, so a strip of 2048 needs one
-// scan over the lanes, and as many stores as the fullest lane has members.
+// scan over the lanes, and as many stores as the fullest lane has members.  Those stores scatter over as many lines as
+// there are lanes, so a strip with kListDense members or more is written row by row instead: 64 consecutive
+// coordinates, one a lane, whose members go next to each other, 32 stores a strip.  Both ways over the fraction, us:
+// 130M 15 % 106 / 143, 20 % 132 / 144, 25 % 167 / 147, 50 % 313 / 155, 100 % 589 / 219; 4M 15 % 12.6 / 13.6,
+// 20 % 13.9 / 13.8, 25 % 15.4 / 14.1, 100 % 70 / 15.5: they cross between 20 and 25 % of the 2048.
 // No workgroup waits before it has published, and none for good: one that has not seen a count after
 // kListPatience looks (well over 10 ms; all workgroups of a call are normally running within microseconds of
 // each other) counts the members before its own part itself, so the kernel ends whatever else
@@ -194,6 +198,7 @@ k_subset_scan(uint32_t *__restrict__ sb, uint32_t nsb, uint32_t capacity, uint32
 // counting, a scan, and a second hashing pass that writes: 229, 55 and 54 us).
 // part_count: word p = the count of part p, bit 31 set once it is known; k_list_clear zeroes them first.
 constexpr uint32_t kListPatience = 1u << 15;
+constexpr uint32_t kListDense = 448;
 
 __global__ void __launch_bounds__(256)
 k_list_clear(uint32_t *__restrict__ part_count, uint32_t parts)
@@ -261,14 +266,27 @@ k_subset_list(SubsetKey key, uint64_t n, uint32_t nstrips, uint32_t strips, uint
             const uint32_t up = __shfl_up(incl, off);
             if ((int)lane >= off) incl += up;
         }
-        uint64_t at = pos + (incl - members);
-        const uint64_t mu0 = (uint64_t)(strip0 + k) * kStripCoords + lane * 32u;
-        while (mask) {
-            if (at < capacity) out[at] = mu0 + (uint32_t)__builtin_ctz(mask);
-            ++at;
-            mask &= mask - 1u;
+        const uint32_t strip_members = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        const uint64_t strip_mu = (uint64_t)(strip0 + k) * kStripCoords;
+        uint64_t at = pos;
+        if (strip_members < kListDense) {
+            const uint64_t mu0 = strip_mu + lane * 32u;
+            at += incl - members;
+            while (mask) {
+                if (at < capacity) out[at] = mu0 + (uint32_t)__builtin_ctz(mask);
+                ++at;
+                mask &= mask - 1u;
+            }
+        } else {
+            for (uint32_t q = 0; q < 32u; ++q) {              // coordinates 64 q .. 64 q + 63 of the strip, one a lane
+                const uint64_t row = (uint32_t)__builtin_amdgcn_readlane((int)mask, (int)(2u * q))
+                                     | (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mask, (int)(2u * q + 1u)) << 32;
+                const uint64_t mine = at + lanes_below(row);
+                if (((row >> lane) & 1ull) && mine < capacity) out[mine] = strip_mu + q * 64u + lane;
+                at += (uint32_t)__popcll(row);
+            }
         }
-        pos += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        pos += strip_members;
     }
 }
 

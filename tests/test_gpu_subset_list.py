@@ -50,3 +50,20 @@ def test_capacity_around_the_count(amlib):
         got = out.cpu().numpy()
         kept = min(cap, want.size)
         assert np.array_equal(got[:kept], want[:kept]) and (got[kept:] == -1).all()
+
+
+@pytest.mark.parametrize("n", [2049, 100_003, (1 << 24) + 4097])
+@pytest.mark.parametrize("p,kw,okw", [(0.2, {}, {}), (0.219, {}, {}), (0.25, {}, {}), (0.97, {}, {}), (0.22, dict(subset_granule=32), dict(granule=32)),
+                                      (0.25, dict(subset_kind=1), dict(stratified=True))])
+def test_strips_on_both_sides_of_the_dense_line(amlib, n, p, kw, okw):
+    """A strip of 2048 coordinates with 448 members or more is written row by row: fractions below, at (strips of both
+    kinds beside each other) and above 448 / 2048, and capacities that cut a list of either kind short."""
+    st = _stage(amlib, n, p, 23, **kw)
+    want = O.subset(23, 3, n, p, **okw).astype(np.int64)
+    for cap in (want.size // 2, want.size - 1, want.size + 1):
+        out = torch.full((cap + 8,), -1, dtype=torch.int64, device="cuda")
+        count = torch.full((1,), -1, dtype=torch.int64, device="cuda")
+        st.subset_indices_static(3, out[:cap], count)
+        got, kept = out.cpu().numpy(), min(cap, want.size)
+        assert int(count.item()) == want.size
+        assert np.array_equal(got[:kept], want[:kept]) and (got[kept:] == -1).all()
