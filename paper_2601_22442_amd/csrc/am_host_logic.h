@@ -164,4 +164,11 @@ inline Round plan_round(uint64_t K, uint64_t depth, uint64_t tau, uint64_t t)
     return r;
 }
 
+// What a checkpoint record says about subsets that are already sized, and what a record is taken to say.
+// The record has always named the table at off_next.  Sizes pending in the second table, and records
+// whose reserved field is not zero (some named the table in its bit 0), therefore count as not sized: the step
+// after the resume hashes its subset once more and finds the same sizes.
+inline uint64_t record_sized_step(uint64_t next_lines_step, uint32_t next_buf) { return next_buf ? 0 : next_lines_step; }
+inline uint64_t resumed_sized_step(const am_snapshot &s) { return s.reserved ? 0 : s.next_lines_step; }
+
 }  // namespace am_host

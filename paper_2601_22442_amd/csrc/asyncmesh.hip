@@ -485,10 +485,10 @@ am_status am_export_state(const am_state *st, am_snapshot *out)
     out->magic = kSnapshotMagic;
     out->config_digest = config_digest(st->cfg);
     out->last_t = st->last_t;
-    out->next_lines_step = st->next_lines_step;
+    out->next_lines_step = am_host::record_sized_step(st->next_lines_step, st->next_buf);
     for (uint32_t i = 0; i < AM_MAX_REPLICAS; ++i) { out->opt_steps[i] = st->opt_steps[i]; out->mu_product[i] = st->mu_product[i]; }
     out->delay_now = st->delay_now;
-    out->reserved = st->next_buf;
+    out->reserved = 0;
     return AM_OK;
 }
 
@@ -505,8 +505,7 @@ am_status am_resume_state(const am_config *cfg, const am_buffers *buf, void *hip
     am_state *st = nullptr;
     if (am_status s = create_state(cfg, buf, hip_stream, &st)) return s;
     st->last_t = snapshot->last_t;
-    st->next_lines_step = snapshot->next_lines_step;
-    st->next_buf = snapshot->reserved & 1u;
+    st->next_lines_step = am_host::resumed_sized_step(*snapshot);
     for (uint32_t i = 0; i < AM_MAX_REPLICAS; ++i) { st->opt_steps[i] = snapshot->opt_steps[i]; st->mu_product[i] = snapshot->mu_product[i]; }
     st->delay_now = snapshot->delay_now;
     *out = st;

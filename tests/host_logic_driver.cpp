@@ -44,4 +44,14 @@ void hl_list_shape(uint64_t n, uint32_t compute_units, uint32_t *out)
 
 void hl_d_shape(const am_config *c, uint32_t *rb, uint32_t *arrays, uint64_t *floats) { am_host::d_layout_shape(*c, rb, arrays, floats); }
 
+uint64_t hl_record_sized_step(uint64_t next_lines_step, uint32_t next_buf) { return am_host::record_sized_step(next_lines_step, next_buf); }
+
+uint64_t hl_resumed_sized_step(uint64_t next_lines_step, uint32_t reserved)
+{
+    am_snapshot s = {};
+    s.next_lines_step = next_lines_step;
+    s.reserved = reserved;
+    return am_host::resumed_sized_step(s);
+}
+
 }  // extern "C"

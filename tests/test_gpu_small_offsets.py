@@ -58,7 +58,7 @@ def test_mixed_calls_share_the_size_tables(amlib, n):
 
 @pytest.mark.parametrize("steps", [3, 4])                   # either size table holds the pending sizes
 @pytest.mark.parametrize("n", [70_001, 700_001])
-def test_resumed_record_names_its_size_table(amlib, steps, n):
+def test_resumed_record_from_either_size_table(amlib, steps, n):
     am = amlib
     R, kw = 2, dict(delay=1, fraction=0.1, seed=8)
     st, orc = make_pair(am, n, R, **kw)
@@ -73,6 +73,30 @@ def test_resumed_record_names_its_size_table(amlib, steps, n):
             s.step(t, gd, 1e-3, 0.5)
         orc.step(t, g, 1e-3, 0.5)
     compare(st2, orc, "resumed")
+    for k in ("w", "m", "v", "d"):
+        assert all(torch.equal(x, y) for x, y in zip(getattr(st, k), getattr(st2, k)))
+
+
+@pytest.mark.parametrize("reserved", [0, 1, 1 << 31])
+@pytest.mark.parametrize("steps", [3, 4])
+@pytest.mark.parametrize("n", [70_001, 700_001])
+def test_record_of_any_build(amlib, n, steps, reserved):
+    """A record leaves `reserved` at zero and names sizes only where every build looks for them; records that
+    hold something else there (bit 0 has named the second table) resume as well."""
+    am = amlib
+    R = 2
+    st, _ = make_pair(am, n, R, delay=1, fraction=0.1, seed=8)
+    for t in range(1, steps + 1):
+        st.step(t, grads_for(n, R, t, 8, False)[1], 1e-3, 0.5)
+    torch.cuda.synchronize()
+    snap = st.export_state()
+    assert snap.reserved == 0
+    if reserved:
+        snap.reserved, snap.next_lines_step = reserved, steps + 1
+    st2 = am.Stage.resume(st.cfg, snap, *[[x.clone() for x in getattr(st, k)] for k in ("w", "m", "v", "d_storage")], None, st.workspace.clone())
+    for t in range(steps + 1, steps + 4):
+        for s in (st, st2):
+            s.step(t, grads_for(n, R, t, 8, False)[1], 1e-3, 0.5)
     for k in ("w", "m", "v", "d"):
         assert all(torch.equal(x, y) for x, y in zip(getattr(st, k), getattr(st2, k)))
 

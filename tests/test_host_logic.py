@@ -159,3 +159,13 @@ def test_list_parts_cover_the_stage_and_fit_their_scratch(hl, compute_units):
         assert parts * 4 <= -(-ntiles * 4 // 256) * 256
         if n <= 1 << 27:
             assert parts <= (1 << 27) // 8192
+
+
+def test_a_record_names_sizes_that_every_build_finds(hl):
+    """Sizes are named only where they lie in the first table, which is the one every build reads; a record whose
+    reserved field is not zero may mean another table, so nothing in it counts as sized."""
+    for f in (hl.hl_record_sized_step, hl.hl_resumed_sized_step):
+        f.argtypes, f.restype = [C.c_uint64, C.c_uint32], C.c_uint64
+    assert hl.hl_record_sized_step(9, 0) == 9 and hl.hl_record_sized_step(9, 1) == 0 and hl.hl_record_sized_step(0, 0) == 0
+    assert hl.hl_resumed_sized_step(9, 0) == 9
+    assert all(hl.hl_resumed_sized_step(9, r) == 0 for r in (1, 2, 3, 1 << 31))
