@@ -79,6 +79,7 @@ inline uint64_t slot_capacity_lines(uint64_t ntiles, double p, uint32_t rb, bool
 // workspace = [flags 256 B][reduction partials 32 x 1024 doubles][next_lines u32[ntiles]][meta x (slots + 1)][ring values x slots]
 //   meta = tile words u32[ntiles] | sb_base u32[nsb + 1]      (tile words of the extra block: the second table of next_lines; its sb_base is unused)
 //   ring slot = nblocks * cap_lines * 32 fp32: [block][line][32], a line = [coordinate][replica in block]
+constexpr uint64_t kReduceBytes = (uint64_t)AM_MAX_REPLICAS * 1024 * 8;
 struct Layout {
     uint32_t ntiles, nsb, slots;
     Blocks blocks;
@@ -99,7 +100,7 @@ inline Layout make_layout(const am_config &c)
                                                          c.subset_kind == AM_SUBSET_STRATIFIED ? stratified_block(c.fraction) : 0);
     L.off_flags = 0;
     L.off_reduce = 256;
-    L.off_next = L.off_reduce + (uint64_t)AM_MAX_REPLICAS * 1024 * 8;
+    L.off_next = L.off_reduce + kReduceBytes;
     L.off_meta = L.off_next + round_up((uint64_t)L.ntiles * 4, 256);
     L.meta_sb_off = round_up((uint64_t)L.ntiles * 4, 256);
     L.meta_stride = L.meta_sb_off + round_up(((uint64_t)L.nsb + 1) * 4, 256);

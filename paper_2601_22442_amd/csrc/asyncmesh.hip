@@ -194,11 +194,12 @@ am_status check_index_list_args(const am_state *st, const uint64_t *dev_out, uin
     return AM_OK;
 }
 
-// S^t as an ascending index list.  part_count: one word per part (at most one for every 32 tiles), which
-// the first kernel clears, so it needs no clearing of its own.
-am_status launch_index_list(am_state *st, uint64_t t, uint32_t *part_count, uint64_t *dev_out, uint64_t capacity, uint64_t *dev_count)
+// S^t as an ascending index list.  part_count: room for `words` words, one per part; the first kernel clears
+// them, so they need no clearing of their own.
+am_status launch_index_list(am_state *st, uint64_t t, uint32_t *part_count, uint64_t words, uint64_t *dev_out, uint64_t capacity, uint64_t *dev_count)
 {
     const am_host::ListShape s = am_host::list_shape(st->cfg.n, st->compute_units);
+    if (s.parts > words) return fail(AM_EINVAL, "%u parts of the index list in a scratch of %llu words", s.parts, (unsigned long long)words);
     am::k_list_clear<<<(s.parts + 255u) / 256u, 256, 0, st->stream>>>(part_count, s.parts);
     AM_HIP(hipGetLastError());
     am::k_subset_list<<<s.parts, 256, s.strips * 256u * sizeof(uint32_t), st->stream>>>(
@@ -721,8 +722,8 @@ am_status am_lookahead(void *out, uint32_t out_dtype, const float *w, const floa
 am_status am_subset_indices(am_state *st, uint64_t t, uint64_t *dev_out, uint64_t capacity, uint64_t *dev_count)
 {
     if (am_status s = check_index_list_args(st, dev_out, capacity, dev_count)) return s;
-    // the reductions' partials are free between calls on the stream; 2^32 coordinates have 16,384 parts of 32 strips a wave
-    return launch_index_list(st, t, reinterpret_cast<uint32_t *>(st->reduce_partials()), dev_out, capacity, dev_count);
+    // the reductions' partials are free between calls on the stream
+    return launch_index_list(st, t, reinterpret_cast<uint32_t *>(st->reduce_partials()), am_host::kReduceBytes / sizeof(uint32_t), dev_out, capacity, dev_count);
 }
 
 am_status am_subset_indices_static(am_state *st, uint64_t t, uint64_t *dev_out, uint64_t capacity, uint64_t *dev_count)
@@ -735,7 +736,7 @@ am_status am_subset_indices_static(am_state *st, uint64_t t, uint64_t *dev_out, 
     AM_HIP(hipGetDevice(&device));
     if (device != st->device) return fail(AM_EINVAL, "device %d is current, the state lives on device %d", device, st->device);
     // the scratch was looked up at am_init_state / am_resume_state
-    return launch_index_list(st, t, st->static_scratch, dev_out, capacity, dev_count);
+    return launch_index_list(st, t, st->static_scratch, kStaticMaxParts, dev_out, capacity, dev_count);
 }
 
 am_status am_set_delay(am_state *st, uint32_t tau)
