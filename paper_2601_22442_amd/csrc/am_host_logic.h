@@ -128,6 +128,39 @@ inline ListShape list_shape(uint64_t n, uint32_t compute_units)
     return s;
 }
 
+// Whether the averaging-only call (with a delay) takes its ring values and interleaved EMA entries through LDS,
+// am::kStageFloats of a block at a time (a turn), or reads them where they are used.  Staging hides the
+// latency of scattered reads, but every turn after a tile's first repeats the arithmetic of the receive with
+// fewer lanes busy.  So it serves tiles that nearly always take one turn, and more turns where the weights
+// come from memory and not from the caches.  Figures: time staged / time direct, on the same arrays.
+inline bool average_staged(const am_config &c, uint32_t ntiles, const Blocks &b, bool interleaved_d)
+{
+    const bool by_line = c.subset_granule == 32, e4m3 = c.msg_dtype == AM_MSG_E4M3;
+    const double drawn = c.fraction * am::kTileCoords, turn = (double)am::kStageFloats / b.rb;     // members of a tile, and those a turn holds
+    // Per-replica EMA vectors are dense reads in both forms.  R = 8: 20M 1 % 0.84, 5 % 0.98, 6.25 % 0.985, 20 % 1.00,
+    // 100 % 1.11; 2M 1 % 0.94, 5 % 0.97, 6.25 % 0.98, 10 % 1.01, 50 % 1.10.
+    if (!interleaved_d) return drawn <= 0.5 * turn;
+    const double members = by_line ? std::max(drawn, (double)am::kLineFloats) : drawn;             // of a tile that receives
+    // Members in whole lines bring whole lines of EMA entries, and E4M3 rounding is most of the arithmetic: with both,
+    // R = 8 5 % 500k 1.48, 8M 1.19; R = 4 20 % 500k 1.47, 8M 1.10, but 100 % 2M 0.77, 8M 0.70.
+    if (by_line && e4m3 && b.rb >= 4u && c.fraction < 0.75) return false;
+    // One turn at most: R = 8 5 % 262k 0.92, 1M 0.92, 8M 0.82, 20M 0.80; R = 4 16 % 500k 0.90.  Several blocks take a
+    // second turn now and then more lightly than every block's reads in place (12 %, R = 12: 2M 1.0, 8M 0.86),
+    // unless it is E4M3 on a small stage (10 %, R = 12: 1.3M 1.12, 4M 0.90).
+    const bool tight = b.nblocks == 1u || by_line || (e4m3 && ntiles <= 6144u);
+    if (members + (tight ? 1.5 * std::sqrt(members * (1.0 - c.fraction)) : 0.0) <= turn) return true;
+    // More turns.  E4M3, R = 12: 8M 14 % 1.06, 30 % 1.17, 100 % 1.08 (2M 1.23, 1.54, 1.26).
+    if (e4m3 && b.nblocks > 1u) return false;
+    // R = 8: 20 % 20M 0.97, 8M 0.89, 4M 1.00, 2M 1.07, 1M 1.20, 262k 1.28; 40 % 20M 0.95, 2M 1.04, 1M 1.23; R = 20 20 %
+    // 2M 0.99, 1.3M 1.08.  Eight replicas a block in E4M3, 20 %: 8M 0.91, 4M 1.14; members in whole lines, 10 %: 8M 0.98, 4M 1.09.
+    const bool wide = b.rb == 8u && (by_line || e4m3);
+    const uint64_t weights = c.n * c.replicas;
+    if (ntiles > (wide ? 24576u : 12288u) || weights > (wide ? 1ull << 26 : 1ull << 25)) return true;
+    // Nearly whole tiles, where the EMA entries are the most of what moves: 100 %, R = 8 2M 0.84, 900k 0.93, 500k 1.31; R = 12
+    // 500k 0.81, 262k 1.65; 60 %, R = 8 2M 0.99, 1M 1.11; bf16 messages 50 % 2M 1.06; E4M3 100 % R = 4 2M 0.77, R = 8 1.14.
+    return c.fraction > (c.msg_dtype != AM_MSG_F32 ? 0.75 : 0.5) && (ntiles > 3072u || weights >= 6000000u) && !(e4m3 && b.rb == 8u);
+}
+
 // Floats of one array of the EMA vectors and how many arrays there are, per layout.
 inline void d_layout_shape(const am_config &c, uint32_t *rb, uint32_t *arrays, uint64_t *floats)
 {

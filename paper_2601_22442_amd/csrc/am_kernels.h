@@ -1082,10 +1082,10 @@ k_step_sync(const StepArgs a)
 // once: the first kilobyte of its ring lines (256 / RB received coordinates: nearly always all of them)
 // and their EMA entries go straight into the wave's own stretch of LDS beside the loads of the weights
 // (read where they are used, they are up to eight waits in a row); more coordinates come a kilobyte at a
-// time.  In the per-replica layout the EMA entries are dense loads anyway, so there the staging pays while a
-// tile's subset fits (the host's rule).  31.5M coordinates, us a call before / after: interleaved, R = 8, p = 1 % 264 /
-// 210, 5 % 465 / 421, 20 % 717 / 712, 100 % (7.9M) 508 / 431; R = 12, 5 % 848 / 692; no correction 408 / 331; per
-// replica, 1 %: R = 8 345 / 283, R = 4 175 / 151; 5 %: R = 8 684 / 690, R = 4 344 / 327, R = 2 179 / 154; 125.8M, R = 8, 5 %:
+// time.  The staging does not pay everywhere (am_host::average_staged); where it does not, the ring and the EMA
+// entries are read in place.  31.5M coordinates, us a call in place / staged: interleaved, R = 8, p = 1 % 264 / 210, 5 % 465 /
+// 421, 20 % 717 / 712, 100 % (7.9M) 508 / 431; R = 12, 5 % 848 / 692; no correction 408 / 331; per replica, 20M, 1 %: R = 8
+// 234 / 196, R = 4 122 / 113; 5 %: R = 8 416 / 407, R = 4 220 / 211, R = 2 122 / 105; 125.8M, R = 8, 5 %:
 // 1797 / 1716 (8.56 GB in whole lines: 5.0 TB/s).
 // Arithmetic and its order are those of the fused kernel: mean in fp64 in replica order, rounded to
 // fp32; d <- coef_d d + coef_s (w^ - sent) and w = mean + d in fp64, rounded once each.
@@ -1178,13 +1178,12 @@ __device__ __forceinline__ void average_receive(const StepArgs &a, int j, float 
 // Bytes of dynamic LDS of a workgroup: per wave a kilobyte of ring values per block, one of EMA entries
 // (interleaved), and the list of received coordinates.  Blocks of fewer than four replicas have
 // entries shorter than a direct-to-LDS load and read them from memory.
-constexpr uint32_t kStageFloats = 256;
-template <bool DIL, int RB>
-constexpr bool kStageD = DIL && RB >= 4;
+template <bool DIL, int RB, bool STAGED>
+constexpr bool kStageD = STAGED && DIL && RB >= 4;
 template <bool DIL, int RB>
 __host__ __device__ constexpr uint32_t average_wave_bytes(uint32_t nblocks)
 {
-    return (nblocks * kStageFloats + (kStageD<DIL, RB> ? kStageFloats + 64u : 0u)) * (uint32_t)sizeof(float);
+    return (nblocks * kStageFloats + (kStageD<DIL, RB, true> ? kStageFloats + 64u : 0u)) * (uint32_t)sizeof(float);
 }
 
 // grid = (ceil(tiles / 4), blocks) (TAU0: (ceil(tiles / 4), 1)); blockDim = 256: four waves, each with
@@ -1193,8 +1192,8 @@ __host__ __device__ constexpr uint32_t average_wave_bytes(uint32_t nblocks)
 // TAU0: the average is of this very call's values (tau = 0): the wave walks all blocks of its tile,
 // once for the sums and the send, once more for the update (another wave must not rewrite a block's
 // weights while this one still needs them for the mean).
-// STAGED: a kilobyte at a time through LDS; else (per-replica layout with subsets of several kilobytes a tile)
-// the ring is read where its values are used.
+// STAGED: a kilobyte at a time through LDS; else (where am_host::average_staged says so) the ring and the
+// interleaved EMA entries are read where their values are used.
 template <bool DIL, int RB, bool TAU0, bool STAGED>
 __global__ void __launch_bounds__(256, 4)     // at most 128 registers: 16 tiles or more per compute unit in flight (kept to 80, the interleaved form spills)
 k_average(const StepArgs a)
@@ -1309,7 +1308,7 @@ k_average(const StepArgs a)
                 const float *src = a.ring_recv + (uint64_t)first_r * kLineFloats + at;
                 for (uint32_t b = 0; b < a.nblocks; ++b) lds_dma_16(src + b * block_floats, ring_lds + b * kStageFloats);
             }
-            if (kStageD<DIL, RB> && a.ema) {
+            if (kStageD<DIL, RB, STAGED> && a.ema) {
                 uint8_t *const list = reinterpret_cast<uint8_t *>(d_lds + kStageFloats);
                 uint32_t c = rank_recv - c0;
 #pragma unroll
@@ -1354,7 +1353,7 @@ k_average(const StepArgs a)
                         }
                     }
                     float *const dp = DIL ? a.d[b0] + (tbase + loff + (uint32_t)j) * RB : nullptr;
-                    average_receive<DIL, RB>(a, j, (float)(sum * inv_replicas), own, kStageD<DIL, RB> ? d_lds + c * RB : dp, dp, w, dv);
+                    average_receive<DIL, RB>(a, j, (float)(sum * inv_replicas), own, kStageD<DIL, RB, STAGED> ? d_lds + c * RB : dp, dp, w, dv);
                 }
                 ++c;
             }

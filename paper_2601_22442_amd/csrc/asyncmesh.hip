@@ -273,11 +273,7 @@ template <bool DIL, int RB>
 am_status launch_average_block(am_state *st, const am::StepArgs &a)
 {
     if (a.do_recv && a.same_slot) return launch_average_kernel<DIL, RB, true, false>(st, a);
-    // Interleaved EMA vectors: always through LDS.  Per-replica ones: when a tile's ring values are expected to
-    // fill at most half of the staged kilobyte, so that one turn nearly always does (R = 8: p <= 6.25 %; measured
-    // there at 31.5M: 1 % 283 us against 345, 5 % 690 against 684, and with every coordinate selected 375 against 340).
-    if constexpr (!DIL)
-        if (st->cfg.fraction * am::kTileCoords * RB > am::kStageFloats / 2) return launch_average_kernel<DIL, RB, false, false>(st, a);
+    if (!am_host::average_staged(st->cfg, st->lay.ntiles, st->lay.blocks, DIL)) return launch_average_kernel<DIL, RB, false, false>(st, a);
     return launch_average_kernel<DIL, RB, false, true>(st, a);
 }
 

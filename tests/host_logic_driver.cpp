@@ -44,6 +44,12 @@ void hl_list_shape(uint64_t n, uint32_t compute_units, uint32_t *out)
 
 void hl_d_shape(const am_config *c, uint32_t *rb, uint32_t *arrays, uint64_t *floats) { am_host::d_layout_shape(*c, rb, arrays, floats); }
 
+int hl_average_staged(const am_config *c, int interleaved_d)
+{
+    const am_host::Layout L = am_host::make_layout(*c);
+    return am_host::average_staged(*c, L.ntiles, L.blocks, interleaved_d != 0);
+}
+
 uint64_t hl_record_sized_step(uint64_t next_lines_step, uint32_t next_buf) { return am_host::record_sized_step(next_lines_step, next_buf); }
 
 uint64_t hl_resumed_sized_step(uint64_t next_lines_step, uint32_t reserved)

@@ -1,6 +1,6 @@
 """The averaging-only kernel where what a tile receives fills the kilobyte it stages: just below and above,
-several turns of it, tiles whose members come in whole lines, both sides of the rule that picks the
-unstaged form for per-replica EMA vectors, and more than one block of replicas.  Against the oracle, fp32 bar."""
+several turns of it (large stages only: smaller ones read in place), tiles whose members come in whole lines, both
+sides of the rule that picks the unstaged form, and more than one block of replicas.  Against the oracle, fp32 bar."""
 import pytest
 from test_gpu_parity import both_layouts, run_average
 
@@ -19,3 +19,16 @@ def test_staged_kilobyte(amlib, R, p, d_layout):
 def test_members_in_whole_lines(amlib, R, d_layout):
     """Blocks of 32 coordinates drawn as a whole: most tiles receive nothing, some several turns' worth."""
     run_average(amlib, 40_003, R, 6, delay=1, fraction=0.06, subset_granule=32, d_layout=d_layout)
+
+
+@pytest.mark.parametrize("n,R,kw", [(3_200_003, 8, dict(fraction=0.3)), (3_100_000, 8, dict(fraction=0.3)),       # several turns / read in place
+                                    (800_001, 5, dict(fraction=1.0)), (500_001, 12, dict(fraction=1.0)),           # eight turns
+                                    (3_200_003, 4, dict(fraction=0.7)), (3_200_003, 2, dict(fraction=0.6)), (3_200_003, 1, dict(fraction=1.0))])
+def test_turns_on_both_sides_of_the_line(amlib, n, R, kw):
+    run_average(amlib, n, R, 4, delay=1, d_layout=amlib.D_INTERLEAVED, **kw)
+
+
+@pytest.mark.parametrize("n,R,p,granule", [(1_600_003, 11, 0.12, 1), (1_600_003, 11, 0.2, 1), (30_003, 8, 0.3, 1), (30_003, 4, 0.2, 32),
+                                           (30_003, 4, 0.8, 32), (30_003, 12, 0.05, 32)])
+def test_quantised_messages_in_both_forms(amlib, n, R, p, granule):
+    run_average(amlib, n, R, 4, delay=1, fraction=p, subset_granule=granule, msg_dtype=amlib.MSG_E4M3, d_layout=amlib.D_INTERLEAVED)

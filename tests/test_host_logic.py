@@ -171,3 +171,26 @@ def test_a_record_names_sizes_that_every_build_finds(hl):
     assert hl.hl_record_sized_step(9, 0) == 9 and hl.hl_record_sized_step(9, 1) == 0 and hl.hl_record_sized_step(0, 0) == 0
     assert hl.hl_resumed_sized_step(9, 0) == 9
     assert all(hl.hl_resumed_sized_step(9, r) == 0 for r in (1, 2, 3, 1 << 31))
+
+
+@pytest.mark.parametrize("n,R,kw,staged", [
+    # per-replica EMA vectors: up to half a turn of 256 ring values
+    (20_000_000, 8, dict(fraction=0.0625, d_layout=0), True), (20_000_000, 8, dict(fraction=0.0626, d_layout=0), False),
+    # interleaved: one turn, or weights that come from memory
+    (100_000, 8, dict(fraction=0.09), True), (100_000, 8, dict(fraction=0.1), False), (2_000_000, 8, dict(fraction=0.2), False),
+    (4_000_000, 8, dict(fraction=0.2), True), (2_000_000, 20, dict(fraction=0.2), True), (500_000, 2, dict(fraction=0.4), True),
+    (500_000, 12, dict(fraction=0.12), True), (500_000, 12, dict(fraction=0.13), False),
+    # nearly whole tiles
+    (1_000_000, 8, dict(fraction=1.0), True), (500_000, 8, dict(fraction=1.0), False), (500_000, 12, dict(fraction=1.0), True), (1_300_000, 8, dict(fraction=0.6), True),
+    (1_300_000, 8, dict(fraction=0.6, msg_dtype=1), False),
+    # E4M3 and members in whole lines
+    (8_000_000, 12, dict(fraction=0.12, msg_dtype=2), True), (8_000_000, 12, dict(fraction=0.2, msg_dtype=2), False),
+    (4_000_000, 8, dict(fraction=0.2, msg_dtype=2), False), (8_000_000, 8, dict(fraction=0.2, msg_dtype=2), True),
+    (4_000_000, 8, dict(fraction=0.05, subset_granule=32), False), (20_000_000, 8, dict(fraction=0.05, subset_granule=32), True),
+    (20_000_000, 8, dict(fraction=0.05, subset_granule=32, msg_dtype=2), False),
+    # the measured cases
+    (125_829_120, 8, dict(fraction=0.05), True), (1_048_576, 4, dict(fraction=0.01, d_layout=0), True),
+])
+def test_averaging_stages_where_that_is_the_faster_form(hl, n, R, kw, staged):
+    kw = dict(dict(d_layout=1), **kw)
+    assert bool(hl.hl_average_staged(C.byref(_config(n=n, replicas=R, delay=1, **kw)), kw["d_layout"])) == staged
