@@ -114,8 +114,12 @@ inline Layout make_layout(const am_config &c)
 // enough parts for every wave to be resident at once (32 waves per compute unit), so that each part finds the
 // counts of all before it after one round of hashing; at most 32 strips (32 KB of masks in LDS), from
 // where on the parts grow in number.
+// dense: the members from which a strip of 2048 is written row by row.  Lane by lane / row by row, us: 130M 15 % 106 / 143,
+// 20 % 132 / 144, 25 % 167 / 147, 50 % 313 / 155, 100 % 589 / 219; 17M 20 % 28.6 / 30.4, 25 % 33.6 / 31.0; 4M 20 %
+// 13.9 / 13.8, 100 % 70 / 15.5; up to 2M, where little is written and the slowest strip counts, 1M 30 % 11.2 / 11.8, 50 %
+// 13.0 / 11.9, 100,003 40 % 9.4 / 9.8, 50 % 9.9 / 9.8.
 struct ListShape {
-    uint32_t nstrips, strips, parts;
+    uint32_t nstrips, strips, parts, dense;
 };
 
 inline ListShape list_shape(uint64_t n, uint32_t compute_units)
@@ -125,6 +129,7 @@ inline ListShape list_shape(uint64_t n, uint32_t compute_units)
     const uint32_t waves = 32u * std::max(compute_units, 1u);
     s.strips = std::min((s.nstrips + waves - 1u) / waves, 32u);
     s.parts = (s.nstrips + 4u * s.strips - 1u) / (4u * s.strips);
+    s.dense = s.nstrips <= 1024u ? 960u : 480u;
     return s;
 }
 

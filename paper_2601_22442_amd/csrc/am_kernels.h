@@ -186,10 +186,8 @@ k_subset_scan(uint32_t *__restrict__ sb, uint32_t nsb, uint32_t capacity, uint32
 // masks in LDS, publishes how many coordinates it holds, adds up what all the workgroups before it
 // hold and writes its indices there.  A lane holds 32 consecutive coordinates, so a strip of 2048 needs one
 // scan over the lanes, and as many stores as the fullest lane has members.  Those stores scatter over as many lines as
-// there are lanes, so a strip with kListDense members or more is written row by row instead: 64 consecutive
-// coordinates, one a lane, whose members go next to each other, 32 stores a strip.  Both ways over the fraction, us:
-// 130M 15 % 106 / 143, 20 % 132 / 144, 25 % 167 / 147, 50 % 313 / 155, 100 % 589 / 219; 4M 15 % 12.6 / 13.6,
-// 20 % 13.9 / 13.8, 25 % 15.4 / 14.1, 100 % 70 / 15.5: they cross between 20 and 25 % of the 2048.
+// there are lanes, so a strip with `dense` members or more is written row by row instead: 64 consecutive
+// coordinates, one a lane, whose members go next to each other, 32 stores a strip (am_host::list_shape has the line).
 // No workgroup waits before it has published, and none for good: one that has not seen a count after
 // kListPatience looks (well over 10 ms; all workgroups of a call are normally running within microseconds of
 // each other) counts the members before its own part itself, so the kernel ends whatever else
@@ -198,7 +196,6 @@ k_subset_scan(uint32_t *__restrict__ sb, uint32_t nsb, uint32_t capacity, uint32
 // counting, a scan, and a second hashing pass that writes: 229, 55 and 54 us).
 // part_count: word p = the count of part p, bit 31 set once it is known; k_list_clear zeroes them first.
 constexpr uint32_t kListPatience = 1u << 15;
-constexpr uint32_t kListDense = 448;
 
 __global__ void __launch_bounds__(256)
 k_list_clear(uint32_t *__restrict__ part_count, uint32_t parts)
@@ -208,7 +205,7 @@ k_list_clear(uint32_t *__restrict__ part_count, uint32_t parts)
 }
 
 __global__ void __launch_bounds__(256)
-k_subset_list(SubsetKey key, uint64_t n, uint32_t nstrips, uint32_t strips, uint32_t patience, uint32_t *part_count,
+k_subset_list(SubsetKey key, uint64_t n, uint32_t nstrips, uint32_t strips, uint32_t dense, uint32_t patience, uint32_t *part_count,
               uint64_t *__restrict__ out, uint64_t capacity, uint64_t *__restrict__ count_out)
 {
     extern __shared__ uint32_t masks[];                       // [strips][256]
@@ -269,7 +266,7 @@ k_subset_list(SubsetKey key, uint64_t n, uint32_t nstrips, uint32_t strips, uint
         const uint32_t strip_members = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
         const uint64_t strip_mu = (uint64_t)(strip0 + k) * kStripCoords;
         uint64_t at = pos;
-        if (strip_members < kListDense) {
+        if (__builtin_expect(strip_members < dense, 1)) {
             const uint64_t mu0 = strip_mu + lane * 32u;
             at += incl - members;
             while (mask) {
@@ -278,6 +275,7 @@ k_subset_list(SubsetKey key, uint64_t n, uint32_t nstrips, uint32_t strips, uint
                 mask &= mask - 1u;
             }
         } else {
+#pragma unroll 4
             for (uint32_t q = 0; q < 32u; ++q) {              // coordinates 64 q .. 64 q + 63 of the strip, one a lane
                 const uint64_t row = (uint32_t)__builtin_amdgcn_readlane((int)mask, (int)(2u * q))
                                      | (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mask, (int)(2u * q + 1u)) << 32;

@@ -203,7 +203,7 @@ am_status launch_index_list(am_state *st, uint64_t t, uint32_t *part_count, uint
     am::k_list_clear<<<(s.parts + 255u) / 256u, 256, 0, st->stream>>>(part_count, s.parts);
     AM_HIP(hipGetLastError());
     am::k_subset_list<<<s.parts, 256, s.strips * 256u * sizeof(uint32_t), st->stream>>>(
-        make_key(st, t), st->cfg.n, s.nstrips, s.strips, am::kListPatience, part_count, dev_out, capacity, dev_count);
+        make_key(st, t), st->cfg.n, s.nstrips, s.strips, s.dense, am::kListPatience, part_count, dev_out, capacity, dev_count);
     AM_HIP(hipGetLastError());
     return AM_OK;
 }

@@ -52,12 +52,14 @@ def test_capacity_around_the_count(amlib):
         assert np.array_equal(got[:kept], want[:kept]) and (got[kept:] == -1).all()
 
 
-@pytest.mark.parametrize("n", [2049, 100_003, (1 << 24) + 4097])
-@pytest.mark.parametrize("p,kw,okw", [(0.2, {}, {}), (0.219, {}, {}), (0.25, {}, {}), (0.97, {}, {}), (0.22, dict(subset_granule=32), dict(granule=32)),
-                                      (0.25, dict(subset_kind=1), dict(stratified=True))])
+@pytest.mark.parametrize("n", [2049, 100_003, 1024 * 2048, 1024 * 2048 + 1, (1 << 24) + 4097])
+@pytest.mark.parametrize("p,kw,okw", [(0.2, {}, {}), (0.234, {}, {}), (0.25, {}, {}), (0.469, {}, {}), (0.97, {}, {}),
+                                      (0.23, dict(subset_granule=32), dict(granule=32)), (0.25, dict(subset_kind=1), dict(stratified=True)),
+                                      (0.5, dict(subset_kind=1), dict(stratified=True))])
 def test_strips_on_both_sides_of_the_dense_line(amlib, n, p, kw, okw):
-    """A strip of 2048 coordinates with 448 members or more is written row by row: fractions below, at (strips of both
-    kinds beside each other) and above 448 / 2048, and capacities that cut a list of either kind short."""
+    """A strip of 2048 coordinates with 480 members or more (960 on stages of up to 1024 strips) is written row by row:
+    fractions below, at (strips of both kinds beside each other) and above that, and capacities that cut a list of either
+    kind short."""
     st = _stage(amlib, n, p, 23, **kw)
     want = O.subset(23, 3, n, p, **okw).astype(np.int64)
     for cap in (want.size // 2, want.size - 1, want.size + 1):
