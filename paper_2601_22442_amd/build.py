@@ -15,6 +15,8 @@ SRC = PKG / "csrc" / "asyncmesh.hip"
 DEPS = [SRC, PKG / "csrc" / "am_kernels.h", PKG / "csrc" / "am_device.h", PKG / "csrc" / "am_geometry.h",
         PKG / "csrc" / "am_host_logic.h", PKG.parent / "include" / "asyncmesh.h"]
 LIB = PKG / "libasyncmesh.so"
+TEST_SRC = PKG.parent / "tests" / "list_kernel_driver.hip"      # kernels under launch parameters that only a test uses
+TEST_LIB = PKG.parent / "tests" / "liblist_kernel.so"
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -45,6 +47,11 @@ def build_library(force: bool = True, verbose: bool = False) -> Path:
             cmd.insert(1, "-Rpass-analysis=kernel-resource-usage")
         subprocess.run(cmd, check=True)
     return LIB
+
+
+def build_test_kernels() -> Path:
+    subprocess.run(["hipcc", *HIPCC_FLAGS, "-Wno-unused-function", f'-DAM_SOURCE_HASH="{source_hash()}"', "-o", str(TEST_LIB), str(TEST_SRC)], check=True)
+    return TEST_LIB
 
 
 def check_library_is_current(version: str) -> str:

@@ -1,6 +1,8 @@
 """The index list of a subset (am_subset_indices) where its cut into parts can go wrong: the ends of a
 lane's 32 coordinates, of a strip, of a part, one strip a wave and several, all three sampling rules, and
 capacities around the count.  Whole numbers: equal to the oracle's list."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -69,3 +71,33 @@ def test_strips_on_both_sides_of_the_dense_line(amlib, n, p, kw, okw):
         got, kept = out.cpu().numpy(), min(cap, want.size)
         assert int(count.item()) == want.size
         assert np.array_equal(got[:kept], want[:kept]) and (got[kept:] == -1).all()
+
+
+@pytest.fixture(scope="module")
+def list_kernel():
+    """The kernels under a patience and a cut that the entry points never use (tests/list_kernel_driver.hip)."""
+    from paper_2601_22442_amd.build import TEST_LIB, build_test_kernels, source_hash
+    if not TEST_LIB.exists():
+        build_test_kernels()
+    lib = C.CDLL(str(TEST_LIB))
+    lib.tk_source_hash.restype = C.c_char_p
+    assert lib.tk_source_hash().decode() == source_hash(), "tests/liblist_kernel.so is stale: build again"
+    lib.tk_subset_list.argtypes = [C.c_uint64] * 4 + [C.c_uint32] * 3 + [C.c_void_p, C.c_uint32, C.c_void_p, C.c_uint64, C.c_void_p, C.c_void_p]
+    return lib.tk_subset_list
+
+
+@pytest.mark.parametrize("patience", [0, 1])              # every workgroup counts what is before it itself; only those that had to wait
+@pytest.mark.parametrize("n,p,strips", [(2049, 0.5, 1), (100_003, 0.05, 1), (100_003, 1.0, 3), (700_001, 0.3, 2), (1_500_001, 0.02, 5)])
+def test_a_wait_that_gives_up(list_kernel, n, p, strips, patience):
+    """A workgroup that has not seen the counts before it after `patience` looks hashes those coordinates itself: the
+    same list and count, for one and several strips a wave and a cut last part."""
+    want = O.subset(29, 6, n, p).astype(np.int64)
+    words = -(-n // (8192 * strips))
+    parts = torch.zeros(words, dtype=torch.int32, device="cuda")
+    out = torch.full((want.size + 8,), -1, dtype=torch.int64, device="cuda")
+    count = torch.full((1,), -1, dtype=torch.int64, device="cuda")
+    assert list_kernel(n, 29, 6, int(p * 2**32), strips, 480, patience, parts.data_ptr(), words, out.data_ptr(), want.size, count.data_ptr(),
+                       torch.cuda.current_stream().cuda_stream) == 0
+    got = out.cpu().numpy()
+    assert int(count.item()) == want.size
+    assert np.array_equal(got[:want.size], want) and (got[want.size:] == -1).all()
