@@ -1,9 +1,8 @@
 // Device-side building blocks of the AsyncMesh stage update for gfx950 (wave64).
 //
 // Geometry (group, tile, superblock, line, block): am_geometry.h.
-// A tile's first entry in a packed list (of selected coordinates, or of the whole lines a tile
-// owns in a ring slot) is  sb_base[tile >> 9] + local_off[tile]  (ring slots: the low 24 bits of
-// the tile's word; the high 8 bits hold the number of lines the tile owns).
+// A tile's first line in a ring slot is  sb_base[tile >> 9] + the low 24 bits of the tile's word; the
+// high 8 bits of the word hold the number of lines the tile owns.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

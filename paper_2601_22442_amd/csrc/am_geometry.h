@@ -2,8 +2,8 @@
 // that the host logic also compiles with a plain C++ compiler).
 //   group      = 4 consecutive coordinates (one 128-bit access, one Philox4x32 block)
 //   tile       = 64 groups = 256 consecutive coordinates = what one wavefront handles at a time
-//   superblock = 512 tiles; subset counts are scanned inside a superblock by one workgroup and
-//                across superblocks by a second tiny kernel
+//   superblock = 512 tiles: one workgroup of the passes that find where the tiles' lines start in a ring slot; a
+//                tile's word is its offset inside the superblock, and each superblock has a base
 //   strip      = 64 lanes x 32 consecutive coordinates = 8 tiles: what one wavefront hashes at a time
 //                where only the subset matters (one 32-bit mask per lane, in coordinate order)
 //   line       = 128 bytes = 32 floats, the unit in which memory is written

@@ -110,10 +110,10 @@ inline Layout make_layout(const am_config &c)
     return L;
 }
 
-// How a subset's index list is cut: a part = one workgroup of four waves with `strips` strips each.  Few
-// enough parts for every wave to be resident at once (32 waves per compute unit), so that each part finds the
-// counts of all before it after one round of hashing; at most 32 strips (32 KB of masks in LDS), from
-// where on the parts grow in number.
+// How a subset's index list is cut: a part = one workgroup of four waves with `strips` strips each.  32 waves a
+// compute unit, which is more than the kernel's registers (20 waves) and, from 20 strips on, its masks in LDS (a
+// kilobyte a strip) keep resident at once: the parts run in up to two rounds, in order, and a part waits only for
+// earlier ones.  At most 32 strips, from where on the parts grow in number.
 // dense: the members from which a strip of 2048 is written row by row.  Lane by lane / row by row, us: 130M 15 % 106 / 143,
 // 20 % 132 / 144, 25 % 167 / 147, 50 % 313 / 155, 100 % 589 / 219; 17M 20 % 28.6 / 30.4, 25 % 33.6 / 31.0; 4M 20 %
 // 13.9 / 13.8, 100 % 70 / 15.5; up to 2M, where little is written and the slowest strip counts, 1M 30 % 11.2 / 11.8, 50 %

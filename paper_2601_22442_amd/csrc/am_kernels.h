@@ -6,7 +6,8 @@
 namespace am {
 
 // =============================================================================================
-// Subset offsets:   k_subset_count (or k_subset_offsets)  ->  k_subset_scan
+// Where the tiles' lines start in a ring slot:  k_subset_count (sizes not known yet)  ->  k_subset_scan, or from
+// known sizes  k_subset_offsets_at_once,  or  k_subset_offsets  ->  k_subset_scan,  or lines_before in the kernel itself
 // =============================================================================================
 // cnt[512] (LDS) holds the lines of the tiles of superblock blockIdx.x: write their exclusive
 // prefix, with the tile's own lines in the high 8 bits (a tile owns at most 64 lines and a superblock
@@ -129,11 +130,12 @@ k_subset_offsets_at_once(const uint32_t *__restrict__ tile_size, uint32_t ntiles
 }
 
 // Lines of the tiles before `tile`, this wave's share: of `waves` waves, wave w adds up words 256 w .. 256 w + 255,
-// then the stretch 256 waves further on, and so on for kSumLoads loads.  The shares of all waves add up to all of
-// them when tile <= kSumWords * waves.  lines: padded to whole 256 bytes.
+// then the stretch 256 waves further on, and so on for kSumLoads loads (each in a branch of its own, which the compiler
+// ends with a wait: they follow one another, as many as the tile's place needs).  The shares of all waves add up to all
+// of them when tile <= kSumWords * waves.  lines: padded to whole 256 bytes.
 constexpr uint32_t kSumLoads = 4, kSumWords = 256 * kSumLoads;
-// The fused step adds up its tiles' places itself for at most this many tiles (524,288 coordinates), and no launch
-// precedes it: 500,000 coordinates, R = 4 18.9 us a step against 19.9 with k_subset_offsets_at_once (scaled from
+// The fused step adds up its tiles' places itself for at most this many tiles (524,288 coordinates; with one replica the
+// 1024 tiles of its one wave), and no launch precedes it: 500,000 coordinates, R = 4 18.9 us a step against 19.9 with k_subset_offsets_at_once (scaled from
 // 550,000), 262,144, R = 1 7.8 against 9.3; at 1M, R = 4 both take 35.1 us, at 2M, R = 8 it is 94.8 against 93.9.
 // The averaging-only kernel (four waves, and little else to read) does so for as many as four waves can add up
 // (4096 tiles: 1M, R = 4, p = 1 % 11.4 us a call, 17.4 with two offset launches).
@@ -188,10 +190,10 @@ k_subset_scan(uint32_t *__restrict__ sb, uint32_t nsb, uint32_t capacity, uint32
 // scan over the lanes, and as many stores as the fullest lane has members.  Those stores scatter over as many lines as
 // there are lanes, so a strip with `dense` members or more is written row by row instead: 64 consecutive
 // coordinates, one a lane, whose members go next to each other, 32 stores a strip (am_host::list_shape has the line).
-// No workgroup waits before it has published, and none for good: one that has not seen a count after
-// kListPatience looks (well over 10 ms; all workgroups of a call are normally running within microseconds of
-// each other) counts the members before its own part itself, so the kernel ends whatever else
-// happens to the scratch.
+// No workgroup waits before it has published, and each only for lower-numbered ones, which start before it; so
+// every wait ends without all of them being resident (at 86 registers 20 waves a compute unit are: 125.8M
+// coordinates take one and a half rounds).  None waits for good: one that has not seen a count after kListPatience looks
+// (well over 10 ms) counts the members before its own part itself, so the kernel ends whatever else happens to the scratch.
 // Measured, p = 5 %: 125.8M coordinates 85 us, 1M 9.7 us, 131,072 8.6 us (one workgroup per superblock
 // counting, a scan, and a second hashing pass that writes: 229, 55 and 54 us).
 // part_count: word p = the count of part p, bit 31 set once it is known; k_list_clear zeroes them first.
@@ -315,7 +317,7 @@ struct StepArgs {
     // blocks: replicas b rb .. b rb + rb - 1 form block b; one wave of a workgroup per replica of a block
     uint32_t rb, rb_shift;                         // replicas per block (1, 2, 4 or 8) and its log2
     uint32_t nblocks;                              // ceil(replicas / rb)
-    uint32_t blocks_per_wg;                        // 1 (grid = tiles x blocks), or nblocks when tau = 0 (grid = tiles)
+    uint32_t blocks_per_wg;                        // k_step: 1 (grid = tiles x blocks), or nblocks when tau = 0 (grid = tiles)
     uint32_t lookahead;
     // averaging
     uint32_t do_send, do_recv, ema, same_slot;     // ema: a correction vector d is kept; same_slot: tau = 0,
@@ -636,7 +638,6 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     // One wave hashes the sent subset for all; so it is with the received subset, unless its masks steer
     // loads of per-replica arrays that should leave before the barrier (per-replica layout of d).
     const bool kShareRecv = DIL || !a.ema;
-    constexpr bool kShareSend = true;
     const bool sum_lines = TAU0 ? a.sum_lines != 0u : SUM;
     const uint32_t R = a.replicas, rb = a.rb, sh = a.rb_shift;
     const uint32_t flat = wave * 64u + lane;                               // 64 rb threads; thread f owns 16-byte chunk f
@@ -691,7 +692,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     };
 #pragma unroll
     for (uint32_t job = 0; job < 3u; ++job) {
-        const bool shared = job == 0u ? kShareRecv : job == 1u ? kShareSend : true;
+        const bool shared = job == 0u ? kShareRecv : true;
         if (shared && wave != (job & (rb - 1u))) continue;
         if (job == 0u && !a.do_recv) continue;
         if (job == 1u && (!a.do_send || recv_is_send)) continue;
@@ -706,7 +707,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
             if (DIL && a.ema && wave == 0u) request_d_lines(lines_of(mask));
         } else if (job == 1u) {
             s.mask_send = mask;
-            if (kShareSend) L.masks[lane] = (uint8_t)mask;
+            L.masks[lane] = (uint8_t)mask;
         } else {
             uint32_t count;
             (void)wave_prefix_mask4(mask, count);
@@ -755,7 +756,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     uint32_t count_recv = 0, d_lines = 0;
     auto finish_subsets = [&]() {
         if (kShareRecv) s.mask_recv = keep_r ? (uint32_t)L.masks[64u + lane] : 0u;
-        if (kShareSend) s.mask_send = recv_is_send ? s.mask_recv : (keep_s ? (uint32_t)L.masks[lane] : 0u);
+        s.mask_send = recv_is_send ? s.mask_recv : (keep_s ? (uint32_t)L.masks[lane] : 0u);
         uint32_t count_send;
         s.rank_send = wave_prefix_mask4(s.mask_send, count_send);
         if (recv_is_send) { s.rank_recv = s.rank_send; count_recv = count_send; }
@@ -807,14 +808,13 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     // for LDS and the other waves' operands are still on their way.  The branch (the same for the whole wave)
     // keeps absent replicas' waves idle and the conversions of the operands behind the hashing: 56 to 58
     // registers instead of 66 to 72.  Measured with that, in us a step, before / after: no correction, bf16, R = 16, 125.8M
-    // 10107 / 9924, R = 8, 31.5M 1195 / 1162; per-replica d, 31.5M, R = 8 1940 / 1916, R = 2 369 / 363; absent replicas: R = 12,
-    // 10M, bf16 772 / 751 (per replica), 713 / 692 (interleaved), R = 6 386 / 364; the headline step 5933 / 5921.
+    // 10107 / 9924, R = 8, 31.5M 1195 / 1162; per-replica d, 31.5M, R = 2 369 / 363; absent replicas: R = 12, 10M, bf16 772 /
+    // 751 (per replica), 713 / 692 (interleaved), R = 6 386 / 364; no change beyond noise on the headline step.
     F4 w_hat, m_new, v_new;
     if (!TAU0 && i < R) local_step<OPT>(a, rep, i, in, w_hat, m_new, v_new);
     lds_dma_wait();
     __syncthreads();
-    constexpr bool kEarlyLocal = !TAU0;
-    if (kEarlyLocal && i < R) {                            // the moments are final: out they go at once
+    if (!TAU0 && i < R) {                                  // the moments are final: out they go at once
         if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_f32x4(rep.m + tbase, loff, nvalid, m_new);
         if (OPT == kOptAdam) store_f32x4(rep.v + tbase, loff, nvalid, v_new);
     }
@@ -1453,7 +1453,6 @@ struct DiagArgs {
                                        // [coordinate][d_stride] (padded to whole tiles); all NULL when there is no correction vector
     uint64_t n;
     uint32_t replicas;
-    uint32_t has_d;
     uint32_t d_stride;                 // 1 (one array per replica) or the replicas per block (interleaved)
 };
 

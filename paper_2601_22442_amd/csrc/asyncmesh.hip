@@ -749,14 +749,13 @@ am_status am_diagnostics(am_state *st, double *dev_out3)
     if (!aligned(dev_out3, 8)) return fail(AM_EALIGN, "dev_out3 is not 8-byte aligned");
     am::DiagArgs a;
     std::memset(&a, 0, sizeof a);
-    a.has_d = st->d_arrays != 0;
     a.d_stride = st->d_rb;
     for (uint32_t i = 0; i < st->cfg.replicas; ++i) a.w[i] = st->w[i];
     for (uint32_t k = 0; k < st->d_arrays; ++k) a.d[k] = st->d[k];          // per replica, or (interleaved) per block
     a.n = st->cfg.n; a.replicas = st->cfg.replicas;
     const uint64_t want = ((st->cfg.n + 3) / 4 + 255) / 256;               // a thread takes groups of 4 coordinates
     const uint32_t blocks = (uint32_t)(want < 2048 ? want : 2048);          // 2 x 2 doubles each in the partials area (32 x 1024 doubles)
-    const uint32_t rows = a.has_d ? 2u : 1u;
+    const uint32_t rows = st->d_arrays != 0 ? 2u : 1u;
     const dim3 grid(blocks, rows);
     // the smallest instantiation that holds the replicas (interleaved arrays have as many per block: 2, 4 or 8)
     if (a.replicas <= 2) am::k_diag_partial<2><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
