@@ -114,22 +114,22 @@ inline Layout make_layout(const am_config &c)
 // compute unit, which is more than the kernel's registers (20 waves) and, from 20 strips on, its masks in LDS (a
 // kilobyte a strip) keep resident at once: the parts run in up to two rounds, in order, and a part waits only for
 // earlier ones.  At most 32 strips, from where on the parts grow in number.
-// dense: the members from which a strip of 2048 is written row by row.  Lane by lane / row by row, us: 130M 15 % 106 / 143,
-// 20 % 132 / 144, 25 % 167 / 147, 50 % 313 / 155, 100 % 589 / 219; 17M 20 % 28.6 / 30.4, 25 % 33.6 / 31.0; 4M 20 %
-// 13.9 / 13.8, 100 % 70 / 15.5; up to 2M, where little is written and the slowest strip counts, 1M 30 % 11.2 / 11.8, 50 %
-// 13.0 / 11.9, 100,003 40 % 9.4 / 9.8, 50 % 9.9 / 9.8.
+// rows: a strip is written row by row.  Lane by lane / row by row, us: 130M 15 % 106 / 143, 20 % 132 / 144, 25 % 167 / 147,
+// 50 % 313 / 155, 100 % 589 / 219; 17M 20 % 28.6 / 30.4, 25 % 33.6 / 31.0; 4M 20 % 13.9 / 13.8, 100 % 70 / 15.5; up to 2M,
+// where little is written, 1M 30 % 11.2 / 11.8, 50 % 13.0 / 11.9, 100,003 40 % 9.4 / 9.8, 50 % 9.9 / 9.8.
 struct ListShape {
-    uint32_t nstrips, strips, parts, dense;
+    uint32_t nstrips, strips, parts;
+    bool rows;
 };
 
-inline ListShape list_shape(uint64_t n, uint32_t compute_units)
+inline ListShape list_shape(uint64_t n, double fraction, uint32_t compute_units)
 {
     ListShape s;
     s.nstrips = (uint32_t)((n + am::kStripCoords - 1) / am::kStripCoords);
     const uint32_t waves = 32u * std::max(compute_units, 1u);
     s.strips = std::min((s.nstrips + waves - 1u) / waves, 32u);
     s.parts = (s.nstrips + 4u * s.strips - 1u) / (4u * s.strips);
-    s.dense = s.nstrips <= 1024u ? 960u : 480u;
+    s.rows = fraction >= (s.nstrips <= 1024u ? 0.45 : 0.22);
     return s;
 }
 

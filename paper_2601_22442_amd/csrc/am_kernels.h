@@ -188,8 +188,8 @@ k_subset_scan(uint32_t *__restrict__ sb, uint32_t nsb, uint32_t capacity, uint32
 // masks in LDS, publishes how many coordinates it holds, adds up what all the workgroups before it
 // hold and writes its indices there.  A lane holds 32 consecutive coordinates, so a strip of 2048 needs one
 // scan over the lanes, and as many stores as the fullest lane has members.  Those stores scatter over as many lines as
-// there are lanes, so a strip with `dense` members or more is written row by row instead: 64 consecutive
-// coordinates, one a lane, whose members go next to each other, 32 stores a strip (am_host::list_shape has the line).
+// there are lanes, so where many coordinates are members (am_host::list_shape) a strip is written row by row instead
+// (ROWS): 64 consecutive coordinates, one a lane, whose members go next to each other, 32 stores a strip.
 // No workgroup waits before it has published, and each only for lower-numbered ones, which start before it; so
 // every wait ends without all of them being resident (at 86 registers 20 waves a compute unit are: 125.8M
 // coordinates take one and a half rounds).  None waits for good: one that has not seen a count after kListPatience looks
@@ -206,8 +206,9 @@ k_list_clear(uint32_t *__restrict__ part_count, uint32_t parts)
     if (i < parts) part_count[i] = 0u;
 }
 
+template <bool ROWS>
 __global__ void __launch_bounds__(256)
-k_subset_list(SubsetKey key, uint64_t n, uint32_t nstrips, uint32_t strips, uint32_t dense, uint32_t patience, uint32_t *part_count,
+k_subset_list(SubsetKey key, uint64_t n, uint32_t nstrips, uint32_t strips, uint32_t patience, uint32_t *part_count,
               uint64_t *__restrict__ out, uint64_t capacity, uint64_t *__restrict__ count_out)
 {
     extern __shared__ uint32_t masks[];                       // [strips][256]
@@ -258,35 +259,33 @@ k_subset_list(SubsetKey key, uint64_t n, uint32_t nstrips, uint32_t strips, uint
 
     for (uint32_t k = 0; k < strips; ++k) {
         uint32_t mask = masks[k * 256u + threadIdx.x];
-        const uint32_t members = (uint32_t)__popc(mask);
-        uint32_t incl = members;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t up = __shfl_up(incl, off);
-            if ((int)lane >= off) incl += up;
-        }
-        const uint32_t strip_members = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
         const uint64_t strip_mu = (uint64_t)(strip0 + k) * kStripCoords;
-        uint64_t at = pos;
-        if (__builtin_expect(strip_members < dense, 1)) {
+        if constexpr (ROWS) {
+#pragma unroll 4
+            for (uint32_t q = 0; q < 32u; ++q) {              // coordinates 64 q .. 64 q + 63 of the strip, one a lane
+                const uint64_t row = (uint32_t)__builtin_amdgcn_readlane((int)mask, (int)(2u * q))
+                                     | (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mask, (int)(2u * q + 1u)) << 32;
+                const uint64_t at = pos + lanes_below(row);
+                if (((row >> lane) & 1ull) && at < capacity) out[at] = strip_mu + q * 64u + lane;
+                pos += (uint32_t)__popcll(row);
+            }
+        } else {
+            const uint32_t members = (uint32_t)__popc(mask);
+            uint32_t incl = members;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t up = __shfl_up(incl, off);
+                if ((int)lane >= off) incl += up;
+            }
+            uint64_t at = pos + (incl - members);
             const uint64_t mu0 = strip_mu + lane * 32u;
-            at += incl - members;
             while (mask) {
                 if (at < capacity) out[at] = mu0 + (uint32_t)__builtin_ctz(mask);
                 ++at;
                 mask &= mask - 1u;
             }
-        } else {
-#pragma unroll 4
-            for (uint32_t q = 0; q < 32u; ++q) {              // coordinates 64 q .. 64 q + 63 of the strip, one a lane
-                const uint64_t row = (uint32_t)__builtin_amdgcn_readlane((int)mask, (int)(2u * q))
-                                     | (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mask, (int)(2u * q + 1u)) << 32;
-                const uint64_t mine = at + lanes_below(row);
-                if (((row >> lane) & 1ull) && mine < capacity) out[mine] = strip_mu + q * 64u + lane;
-                at += (uint32_t)__popcll(row);
-            }
+            pos += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
         }
-        pos += strip_members;
     }
 }
 

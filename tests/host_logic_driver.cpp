@@ -35,11 +35,11 @@ void hl_plan_round(uint64_t K, uint64_t depth, uint64_t tau, uint64_t t, uint64_
     out[0] = r.send; out[1] = r.recv; out[2] = r.same_slot; out[3] = r.slot_send; out[4] = r.slot_recv; out[5] = r.step_recv;
 }
 
-// out: nstrips, strips, parts
-void hl_list_shape(uint64_t n, uint32_t compute_units, uint32_t *out)
+// out: nstrips, strips, parts, rows
+void hl_list_shape(uint64_t n, double fraction, uint32_t compute_units, uint32_t *out)
 {
-    const am_host::ListShape s = am_host::list_shape(n, compute_units);
-    out[0] = s.nstrips; out[1] = s.strips; out[2] = s.parts;
+    const am_host::ListShape s = am_host::list_shape(n, fraction, compute_units);
+    out[0] = s.nstrips; out[1] = s.strips; out[2] = s.parts; out[3] = s.rows;
 }
 
 void hl_d_shape(const am_config *c, uint32_t *rb, uint32_t *arrays, uint64_t *floats) { am_host::d_layout_shape(*c, rb, arrays, floats); }

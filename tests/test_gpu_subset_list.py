@@ -55,13 +55,11 @@ def test_capacity_around_the_count(amlib):
 
 
 @pytest.mark.parametrize("n", [2049, 100_003, 1024 * 2048, 1024 * 2048 + 1, (1 << 24) + 4097])
-@pytest.mark.parametrize("p,kw,okw", [(0.2, {}, {}), (0.234, {}, {}), (0.25, {}, {}), (0.469, {}, {}), (0.97, {}, {}),
-                                      (0.23, dict(subset_granule=32), dict(granule=32)), (0.25, dict(subset_kind=1), dict(stratified=True)),
-                                      (0.5, dict(subset_kind=1), dict(stratified=True))])
-def test_strips_on_both_sides_of_the_dense_line(amlib, n, p, kw, okw):
-    """A strip of 2048 coordinates with 480 members or more (960 on stages of up to 1024 strips) is written row by row:
-    fractions below, at (strips of both kinds beside each other) and above that, and capacities that cut a list of either
-    kind short."""
+@pytest.mark.parametrize("p,kw,okw", [(0.219, {}, {}), (0.22, {}, {}), (0.449, {}, {}), (0.45, {}, {}), (0.97, {}, {}),
+                                      (0.45, dict(subset_granule=32), dict(granule=32)), (0.5, dict(subset_kind=1), dict(stratified=True))])
+def test_both_sides_of_the_line_to_rows(amlib, n, p, kw, okw):
+    """From p = 0.22 (0.45 on stages of up to 1024 strips) a strip is written row by row: below, at and above that, for
+    all three sampling rules, with capacities that cut the list short."""
     st = _stage(amlib, n, p, 23, **kw)
     want = O.subset(23, 3, n, p, **okw).astype(np.int64)
     for cap in (want.size // 2, want.size - 1, want.size + 1):
@@ -82,21 +80,22 @@ def list_kernel():
     lib = C.CDLL(str(TEST_LIB))
     lib.tk_source_hash.restype = C.c_char_p
     assert lib.tk_source_hash().decode() == source_hash(), "tests/liblist_kernel.so is stale: build again"
-    lib.tk_subset_list.argtypes = [C.c_uint64] * 4 + [C.c_uint32] * 3 + [C.c_void_p, C.c_uint32, C.c_void_p, C.c_uint64, C.c_void_p, C.c_void_p]
+    lib.tk_subset_list.argtypes = [C.c_uint64] * 4 + [C.c_uint32, C.c_int, C.c_uint32] + [C.c_void_p, C.c_uint32, C.c_void_p, C.c_uint64, C.c_void_p, C.c_void_p]
     return lib.tk_subset_list
 
 
 @pytest.mark.parametrize("patience", [0, 1])              # every workgroup counts what is before it itself; only those that had to wait
+@pytest.mark.parametrize("rows", [0, 1])
 @pytest.mark.parametrize("n,p,strips", [(2049, 0.5, 1), (100_003, 0.05, 1), (100_003, 1.0, 3), (700_001, 0.3, 2), (1_500_001, 0.02, 5)])
-def test_a_wait_that_gives_up(list_kernel, n, p, strips, patience):
+def test_a_wait_that_gives_up(list_kernel, n, p, strips, rows, patience):
     """A workgroup that has not seen the counts before it after `patience` looks hashes those coordinates itself: the
-    same list and count, for one and several strips a wave and a cut last part."""
+    same list and count, for one and several strips a wave, a cut last part and either way of writing."""
     want = O.subset(29, 6, n, p).astype(np.int64)
     words = -(-n // (8192 * strips))
     parts = torch.zeros(words, dtype=torch.int32, device="cuda")
     out = torch.full((want.size + 8,), -1, dtype=torch.int64, device="cuda")
     count = torch.full((1,), -1, dtype=torch.int64, device="cuda")
-    assert list_kernel(n, 29, 6, int(p * 2**32), strips, 480, patience, parts.data_ptr(), words, out.data_ptr(), want.size, count.data_ptr(),
+    assert list_kernel(n, 29, 6, int(p * 2**32), strips, rows, patience, parts.data_ptr(), words, out.data_ptr(), want.size, count.data_ptr(),
                        torch.cuda.current_stream().cuda_stream) == 0
     got = out.cpu().numpy()
     assert int(count.item()) == want.size

@@ -149,13 +149,13 @@ def test_static_scratch_limit_is_stated_consistently():
 def test_list_parts_cover_the_stage_and_fit_their_scratch(hl, compute_units):
     """Every strip belongs to exactly one part; the parts' counts fit the reductions' partials, whose size does not
     grow with the stage, and, up to 2^27 coordinates, the static scratch (a word per four strips)."""
-    layout, out = (C.c_uint64 * 13)(), (C.c_uint32 * 3)()
+    layout, out = (C.c_uint64 * 13)(), (C.c_uint32 * 4)()
     for n in (1, 255, 2048, 2049, 8192, 8193, 1 << 24, (1 << 24) + 1, 125_829_120, 1 << 27, 1 << 30, (1 << 32) - (1 << 20) - 1):
         hl.hl_layout(C.byref(_config(n=n, replicas=1)), layout)
         partials_words = (layout[6] - layout[5]) // 4
         assert partials_words == 32 * 1024 * 2
-        hl.hl_list_shape(C.c_uint64(n), compute_units, out)
-        nstrips, strips, parts = list(out)
+        hl.hl_list_shape(C.c_uint64(n), C.c_double(0.05), compute_units, out)
+        nstrips, strips, parts = list(out)[:3]
         assert nstrips == -(-n // 2048) and 1 <= strips <= 32
         assert (parts - 1) * 4 * strips < nstrips <= parts * 4 * strips
         assert parts <= partials_words
