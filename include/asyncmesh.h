@@ -30,8 +30,8 @@
  *     are found before anything is enqueued (a step whose kernel launch itself fails may already
  *     have enqueued its subset-offsets pass, which a repeated call simply redoes).
  *     am_last_error() gives a message for the calling thread.
- *   - Calls on one state come from one thread at a time: they share its host record and the scratch in
- *     its workspace.
+ *   - Calls that change a state's host record (steps, averaging, delay, flags, profiling) come from one thread at a
+ *     time.  am_grad_sqnorm, am_diagnostics and am_subset_indices may come from other threads beside them.
  *   - No exception crosses this boundary.
  */
 #ifndef ASYNCMESH_H

@@ -129,6 +129,8 @@ struct am_state {
     uint64_t opt_steps[AM_MAX_REPLICAS];     // optimizer steps made so far (the t of the bias corrections)
     double mu_product[AM_MAX_REPLICAS];      // NAdam: running product of the momentum schedule
     uint64_t threshold;
+    std::mutex scratch;          // the norms, the diagnostics and the index list hand results from kernel to kernel through
+                                 // reduce_partials(): each enqueues its kernels with nothing of another thread's between them
     uint32_t *static_scratch;    // this device's copy of the static scratch array (am_subset_indices_static)
     // profiling of the fused kernel: a fixed pool of event pairs, created on first use
     bool profiling;
@@ -531,6 +533,7 @@ am_status am_grad_sqnorm(am_state *st, const void *const *grads, double *dev_out
     a.n = c.n; a.replicas = c.replicas; a.is_bf16 = c.grad_dtype == AM_BF16;
     const uint64_t want = ((c.n + 3) / 4 + 255) / 256;
     const uint32_t blocks = (uint32_t)(want < 1024 ? want : 1024);
+    std::lock_guard<std::mutex> lock(st->scratch);
     am::k_sqnorm_partial<<<dim3(blocks, c.replicas), 256, 0, st->stream>>>(a, st->reduce_partials());
     AM_HIP(hipGetLastError());
     am::k_sqnorm_final<<<c.replicas, 256, 0, st->stream>>>(st->reduce_partials(), blocks, dev_out);
@@ -719,7 +722,7 @@ am_status am_lookahead(void *out, uint32_t out_dtype, const float *w, const floa
 am_status am_subset_indices(am_state *st, uint64_t t, uint64_t *dev_out, uint64_t capacity, uint64_t *dev_count)
 {
     if (am_status s = check_index_list_args(st, dev_out, capacity, dev_count)) return s;
-    // the reductions' partials are free between calls on the stream
+    std::lock_guard<std::mutex> lock(st->scratch);
     return launch_index_list(st, t, reinterpret_cast<uint32_t *>(st->reduce_partials()), am_host::kReduceBytes / sizeof(uint32_t), dev_out, capacity, dev_count);
 }
 
@@ -758,6 +761,7 @@ am_status am_diagnostics(am_state *st, double *dev_out3)
     const uint32_t blocks = (uint32_t)(want < 2048 ? want : 2048);          // 2 x 2 doubles each in the partials area (32 x 1024 doubles)
     const uint32_t rows = st->d_arrays != 0 ? 2u : 1u;
     const dim3 grid(blocks, rows);
+    std::lock_guard<std::mutex> lock(st->scratch);
     // the smallest instantiation that holds the replicas (interleaved arrays have as many per block: 2, 4 or 8)
     if (a.replicas <= 2) am::k_diag_partial<2><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
     else if (a.replicas <= 4) am::k_diag_partial<4><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
