@@ -1146,8 +1146,9 @@ __device__ __forceinline__ void average_send_block(float *slot, const F4 (&w)[RB
 
 // Coordinate j of the group receives the old average abar: EMA of the staleness of each replica of the
 // block (own[k] = what replica k itself sent), corrected weight.  dp: the coordinate's RB entries of the
-// interleaved EMA vector (DIL; d_old: the same or their copy in LDS), else the entries are in dv.
-template <bool DIL, int RB>
+// interleaved EMA vector (DIL; d_old: the same or their copy in LDS), else the entries are in dv.  HALVES: the
+// replicas' fp64 values are formed four at a time, not eight (76 registers instead of 84).
+template <bool DIL, int RB, bool HALVES>
 __device__ __forceinline__ void average_receive(const StepArgs &a, int j, float abar, const float (&own)[RB], const float *d_old, float *dp,
                                                 F4 (&w)[RB], F4 (&dv)[RB])
 {
@@ -1161,6 +1162,7 @@ __device__ __forceinline__ void average_receive(const StepArgs &a, int j, float 
         }
 #pragma unroll
         for (int k = 0; k < RB; ++k) {
+            if (HALVES && k == 4) __builtin_amdgcn_sched_barrier(0);
             d_new[k] = (float)fma(a.coef_d, (double)d_new[k], a.coef_s * ((double)w[k].v[j] - (double)own[k]));
             w[k].v[j] = (float)((double)abar + (double)d_new[k]);
             if (!DIL) dv[k].v[j] = d_new[k];
@@ -1191,8 +1193,11 @@ __host__ __device__ constexpr uint32_t average_wave_bytes(uint32_t nblocks)
 // weights while this one still needs them for the mean).
 // STAGED: a kilobyte at a time through LDS; else (where am_host::average_staged says so) the ring and the
 // interleaved EMA entries are read where their values are used.
+// At most 128 registers: 16 tiles or more per compute unit in flight (kept to 80, the staged form spills); in place with
+// interleaved EMA entries, where latency is the cost, at most 80 and 24 tiles: 20 replicas, us a call relative to
+// the form before the staging, 500k p = 0.2 0.85, p = 0.3 0.89, 900k p = 0.2 0.94 (slower than that form at 84 registers).
 template <bool DIL, int RB, bool TAU0, bool STAGED>
-__global__ void __launch_bounds__(256, 4)     // at most 128 registers: 16 tiles or more per compute unit in flight (kept to 80, the interleaved form spills)
+__global__ void __launch_bounds__(256, (DIL && !TAU0 && !STAGED) ? 6 : 4)
 k_average(const StepArgs a)
 {
     constexpr uint32_t kPerLine = kLineFloats / RB;                        // coordinates a ring line holds
@@ -1350,7 +1355,7 @@ k_average(const StepArgs a)
                         }
                     }
                     float *const dp = DIL ? a.d[b0] + (tbase + loff + (uint32_t)j) * RB : nullptr;
-                    average_receive<DIL, RB>(a, j, (float)(sum * inv_replicas), own, kStageD<DIL, RB, STAGED> ? d_lds + c * RB : dp, dp, w, dv);
+                    average_receive<DIL, RB, DIL && !STAGED>(a, j, (float)(sum * inv_replicas), own, kStageD<DIL, RB, STAGED> ? d_lds + c * RB : dp, dp, w, dv);
                 }
                 ++c;
             }
@@ -1405,7 +1410,7 @@ k_average(const StepArgs a)
 #pragma unroll
                         for (int k = 0; k < RB; ++k) own[k] = w[k].v[j];   // no delay: what was sent is this very value
                         float *const dp = DIL ? a.d[b] + (tbase + loff + (uint32_t)j) * RB : nullptr;
-                        average_receive<DIL, RB>(a, j, (float)(sum[j] * inv_replicas), own, dp, dp, w, dv);
+                        average_receive<DIL, RB, false>(a, j, (float)(sum[j] * inv_replicas), own, dp, dp, w, dv);
                         ++c;
                     }
                 }
