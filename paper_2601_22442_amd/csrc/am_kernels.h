@@ -1043,8 +1043,11 @@ __host__ __device__ inline uint32_t step_sync_lds_floats(uint32_t rb, uint32_t n
 }
 
 // grid = tiles; blockDim = 64 replicas; dynamic LDS = step_sync_lds_floats() floats
+// At most 80 scalar registers: with the trap handler's reserve more leave seven waves a SIMD, and two workgroups of 13
+// to 16 waves a compute unit need eight on one of them.  With interleaved EMA vectors AdamW had 83: us a step relative to
+// the walking form at p = 50 %, 13 replicas of 1.5M 1.15, 16 of 1.5M 1.08; with 80, 13 of 1M 0.95, 16 of 1M 0.77.
 template <int OPT, bool GRAD_BF16, int FWD, bool DIL>
-__global__ void __launch_bounds__(64 * kSyncWaves, 6)
+__global__ void __launch_bounds__(64 * kSyncWaves, 6) __attribute__((amdgpu_num_sgpr(80)))
 k_step_sync(const StepArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
