@@ -143,21 +143,31 @@ inline bool average_staged(const am_config &c, uint32_t ntiles, const Blocks &b,
     const bool by_line = c.subset_granule == 32, e4m3 = c.msg_dtype == AM_MSG_E4M3;
     const double drawn = c.fraction * am::kTileCoords, turn = (double)am::kStageFloats / b.rb;     // members of a tile, and those a turn holds
     // Per-replica EMA vectors are dense reads in both forms.  R = 8: 20M 1 % 0.84, 5 % 0.98, 6.25 % 0.985, 20 % 1.00,
-    // 100 % 1.11; 2M 1 % 0.94, 5 % 0.97, 6.25 % 0.98, 10 % 1.01, 50 % 1.10.
-    if (!interleaved_d) return drawn <= 0.5 * turn;
+    // 100 % 1.11; 2M 1 % 0.94, 5 % 0.97, 6.25 % 0.98, 10 % 1.01, 50 % 1.10.  Up to four replicas on stages whose weights
+    // come from memory gain at every fraction: 11M R = 1 to 4 25 % 0.86 to 0.95, 100 % 0.80 to 0.91 (1M, R = 4 25 % 1.07, 100 % 1.15).
+    // Members in whole lines fill a turn of eight replicas each; rounded messages of several blocks, 5 %: R = 12 600k 1.4
+    // to 1.6, 3.6M 1.08 to 1.18, 2 % 1.03 to 1.25 (fp32 3.6M 5 % 0.99, 600k 1.22 but 0.98 of the form before the staging).
+    if (!interleaved_d) {
+        if (by_line && c.msg_dtype != AM_MSG_F32 && b.nblocks > 1u) return false;
+        return drawn <= 0.5 * turn || (b.rb <= 4u && !by_line && c.msg_dtype == AM_MSG_F32 && ntiles > 24576u);
+    }
     const double members = by_line ? std::max(drawn, (double)am::kLineFloats) : drawn;             // of a tile that receives
     // Members in whole lines bring whole lines of EMA entries, and E4M3 rounding is most of the arithmetic: with both,
     // R = 8 5 % 500k 1.48, 8M 1.19; R = 4 20 % 500k 1.47, 8M 1.10, but 100 % 2M 0.77, 8M 0.70.
     if (by_line && e4m3 && b.rb >= 4u && c.fraction < 0.75) return false;
+    // Eight replicas a block: 8M 5 % R = 8 1.04, R = 5 1.07, 10 % 1.05 and 1.09, 25 % 0.98 and 1.01, 50 % 0.90; 19M 5 % 0.99 and
+    // 1.03; bf16 8M 10 % 1.13, 25 % 1.08, 50 % 0.94.
+    if (by_line && b.rb == 8u && c.fraction < (c.msg_dtype == AM_MSG_F32 ? 0.25 : 0.5)) return false;
     // One turn at most: R = 8 5 % 262k 0.92, 1M 0.92, 8M 0.82, 20M 0.80; R = 4 16 % 500k 0.90.  Several blocks take a
     // second turn now and then more lightly than every block's reads in place (12 %, R = 12: 2M 1.0, 8M 0.86),
-    // unless it is E4M3 on a small stage (10 %, R = 12: 1.3M 1.12, 4M 0.90).
-    const bool tight = b.nblocks == 1u || by_line || (e4m3 && ntiles <= 6144u);
+    // unless the stage is small (12 %: 500k R = 12 1.18, R = 20 1.40, 900k R = 20 1.14, 2M 0.97) or, with rounded messages, not
+    // large (12 %, bf16 2M R = 12 1.08, 4M 0.89; E4M3 10 %, R = 12 1.3M 1.12, 4M 0.90).
+    const bool tight = b.nblocks == 1u || by_line || ntiles <= 4096u || (c.msg_dtype != AM_MSG_F32 && ntiles <= 8192u);
     if (members + (tight ? 1.5 * std::sqrt(members * (1.0 - c.fraction)) : 0.0) <= turn) return true;
     // More turns.  E4M3, R = 12: 8M 14 % 1.06, 30 % 1.17, 100 % 1.08 (2M 1.23, 1.54, 1.26).
     if (e4m3 && b.nblocks > 1u) return false;
     // R = 8: 20 % 20M 0.97, 8M 0.89, 4M 1.00, 2M 1.07, 1M 1.20, 262k 1.28; 40 % 20M 0.95, 2M 1.04, 1M 1.23; R = 20 20 %
-    // 2M 0.99, 1.3M 1.08.  Eight replicas a block in E4M3, 20 %: 8M 0.91, 4M 1.14; members in whole lines, 10 %: 8M 0.98, 4M 1.09.
+    // 2M 0.99, 1.3M 1.08.  Eight replicas a block in E4M3, 20 %: 8M 0.91, 4M 1.14; members in whole lines, 25 %, R = 5: 8M 1.01, 4M 1.11.
     const bool wide = b.rb == 8u && (by_line || e4m3);
     const uint64_t weights = c.n * c.replicas;
     if (ntiles > (wide ? 24576u : 12288u) || weights > (wide ? 1ull << 26 : 1ull << 25)) return true;

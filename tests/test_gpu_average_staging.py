@@ -32,3 +32,16 @@ def test_turns_on_both_sides_of_the_line(amlib, n, R, kw):
                                            (30_003, 4, 0.8, 32), (30_003, 12, 0.05, 32)])
 def test_quantised_messages_in_both_forms(amlib, n, R, p, granule):
     run_average(amlib, n, R, 4, delay=1, fraction=p, subset_granule=granule, msg_dtype=amlib.MSG_E4M3, d_layout=amlib.D_INTERLEAVED)
+
+
+@pytest.mark.parametrize("n", [24576 * 256, 24576 * 256 + 1])
+@pytest.mark.parametrize("R,kw", [(3, dict(fraction=1.0)), (4, dict(fraction=0.5, correction=0)), (1, dict(fraction=0.7))])
+def test_per_replica_turns_of_a_large_stage(amlib, n, R, kw):
+    """Up to four replicas take several turns beyond 24576 tiles and read in place up to there."""
+    run_average(amlib, n, R, 3, delay=1, d_layout=amlib.D_PER_REPLICA, **kw)
+
+
+@pytest.mark.parametrize("n,R,p", [(30_003, 12, 0.1), (30_003, 12, 0.14), (30_003, 20, 0.12)])
+def test_several_blocks_of_a_small_stage(amlib, n, R, p):
+    for msg in (amlib.MSG_F32, amlib.MSG_BF16):
+        run_average(amlib, n, R, 4, delay=1, fraction=p, msg_dtype=msg, d_layout=amlib.D_INTERLEAVED)

@@ -176,17 +176,25 @@ def test_a_record_names_sizes_that_every_build_finds(hl):
 @pytest.mark.parametrize("n,R,kw,staged", [
     # per-replica EMA vectors: up to half a turn of 256 ring values
     (20_000_000, 8, dict(fraction=0.0625, d_layout=0), True), (20_000_000, 8, dict(fraction=0.0626, d_layout=0), False),
+    # ... more with up to four replicas of a large stage; none where rounded messages of several blocks come in whole lines
+    (6_300_000, 4, dict(fraction=1.0, d_layout=0), True), (6_200_000, 4, dict(fraction=1.0, d_layout=0), False),
+    (20_000_000, 3, dict(fraction=0.5, d_layout=0, correction=0), True), (20_000_000, 3, dict(fraction=0.5, d_layout=0, msg_dtype=1), False),
+    (600_000, 12, dict(fraction=0.05, d_layout=0, subset_granule=32), True), (600_000, 12, dict(fraction=0.05, d_layout=0, subset_granule=32, msg_dtype=1), False),
+    (600_000, 8, dict(fraction=0.05, d_layout=0, subset_granule=32, msg_dtype=1), True),
     # interleaved: one turn, or weights that come from memory
     (100_000, 8, dict(fraction=0.09), True), (100_000, 8, dict(fraction=0.1), False), (2_000_000, 8, dict(fraction=0.2), False),
     (4_000_000, 8, dict(fraction=0.2), True), (2_000_000, 20, dict(fraction=0.2), True), (500_000, 2, dict(fraction=0.4), True),
-    (500_000, 12, dict(fraction=0.12), True), (500_000, 12, dict(fraction=0.13), False),
+    (500_000, 12, dict(fraction=0.08), True), (500_000, 12, dict(fraction=0.12), False),
+    (2_000_000, 12, dict(fraction=0.12), True), (2_000_000, 12, dict(fraction=0.12, msg_dtype=1), False), (4_000_000, 12, dict(fraction=0.12, msg_dtype=1), True),
     # nearly whole tiles
     (1_000_000, 8, dict(fraction=1.0), True), (500_000, 8, dict(fraction=1.0), False), (500_000, 12, dict(fraction=1.0), True), (1_300_000, 8, dict(fraction=0.6), True),
     (1_300_000, 8, dict(fraction=0.6, msg_dtype=1), False),
     # E4M3 and members in whole lines
     (8_000_000, 12, dict(fraction=0.12, msg_dtype=2), True), (8_000_000, 12, dict(fraction=0.2, msg_dtype=2), False),
     (4_000_000, 8, dict(fraction=0.2, msg_dtype=2), False), (8_000_000, 8, dict(fraction=0.2, msg_dtype=2), True),
-    (4_000_000, 8, dict(fraction=0.05, subset_granule=32), False), (20_000_000, 8, dict(fraction=0.05, subset_granule=32), True),
+    (4_000_000, 8, dict(fraction=0.05, subset_granule=32), False), (20_000_000, 8, dict(fraction=0.24, subset_granule=32), False),
+    (20_000_000, 8, dict(fraction=0.25, subset_granule=32), True), (20_000_000, 8, dict(fraction=0.25, subset_granule=32, msg_dtype=1), False),
+    (20_000_000, 8, dict(fraction=0.5, subset_granule=32, msg_dtype=1), True),
     (20_000_000, 8, dict(fraction=0.05, subset_granule=32, msg_dtype=2), False),
     # the measured cases
     (125_829_120, 8, dict(fraction=0.05), True), (1_048_576, 4, dict(fraction=0.01, d_layout=0), True),
