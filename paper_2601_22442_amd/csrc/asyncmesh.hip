@@ -762,14 +762,18 @@ am_status am_diagnostics(am_state *st, double *dev_out3)
     const uint32_t rows = st->d_arrays != 0 ? 2u : 1u;
     const dim3 grid(blocks, rows);
     std::lock_guard<std::mutex> lock(st->scratch);
+    // Whole-wave loads while every workgroup is resident (up to 16 replicas: three a compute unit) or has one to itself.  Without d,
+    // us a call, branches / whole: 255k R = 16 11.3 / 8.5, R = 32 22.5 / 13.2; 400k R = 16 10.2 / 10.1, R = 32 17.0 / 21.2.
+    const bool whole = blocks * rows <= st->compute_units * (a.replicas <= 16 ? 3u : 1u);
     // the smallest instantiation that holds the replicas (interleaved arrays have as many per block: 2, 4 or 8)
-    if (a.replicas <= 2) am::k_diag_partial<2><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
-    else if (a.replicas <= 4) am::k_diag_partial<4><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
-    else if (a.replicas <= 8) am::k_diag_partial<8><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
-    else if (a.replicas <= 16) am::k_diag_partial<16><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
-    else am::k_diag_partial<32><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
+    if (a.replicas <= 2) am::k_diag_partial<2, false><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
+    else if (a.replicas <= 4) am::k_diag_partial<4, false><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
+    else if (a.replicas <= 8) am::k_diag_partial<8, false><<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
+    else if (a.replicas <= 16) (whole ? am::k_diag_partial<16, true> : am::k_diag_partial<16, false>)<<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
+    else (whole ? am::k_diag_partial<32, true> : am::k_diag_partial<32, false>)<<<grid, 256, 0, st->stream>>>(a, st->reduce_partials());
     AM_HIP(hipGetLastError());
-    am::k_diag_final<<<1, 1024, 0, st->stream>>>(st->reduce_partials(), blocks, rows, a.replicas, st->cfg.n, dev_out3);
+    if (blocks <= 256u) am::k_diag_final<256><<<1, 256, 0, st->stream>>>(st->reduce_partials(), blocks, rows, a.replicas, st->cfg.n, dev_out3);
+    else am::k_diag_final<1024><<<1, 1024, 0, st->stream>>>(st->reduce_partials(), blocks, rows, a.replicas, st->cfg.n, dev_out3);
     AM_HIP(hipGetLastError());
     return AM_OK;
 }

@@ -11,7 +11,10 @@ PASS = 2048 * 256 * 4
 
 
 @pytest.mark.parametrize("n,R", [(4 * PASS + 3, 1), (4 * PASS - 1, 2), (4 * PASS + 257, 2), (2 * PASS + 1, 3), (2 * PASS + 2049, 4),
-                                 (PASS + 1, 8), (PASS // 2 + 63, 5), (PASS // 4 + 5, 12), (1025, 32), (2, 7)])
+                                 (PASS + 1, 8), (PASS // 2 + 63, 5), (PASS // 4 + 5, 12), (1025, 32), (2, 7),
+                                 # ends of a grid that loads whole waves (768 workgroups up to 16 replicas, 256 beyond) and of 256 partials
+                                 (768 * 1024, 9), (768 * 1024 + 1, 16), (384 * 1024, 16), (384 * 1024 + 1, 12), (256 * 1024, 17), (256 * 1024 + 1, 32),
+                                 (128 * 1024, 32), (128 * 1024 + 3, 20), (256 * 1024, 2), (256 * 1024 + 1, 2), (131, 16)])
 @pytest.mark.parametrize("interleaved", [False, True])
 def test_diagnostics_over_grid_edges(amlib, n, R, interleaved):
     am = amlib
