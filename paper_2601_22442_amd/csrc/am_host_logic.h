@@ -110,10 +110,11 @@ inline Layout make_layout(const am_config &c)
     return L;
 }
 
-// How a subset's index list is cut: a part = one workgroup of four waves with `strips` strips each.  32 waves a
-// compute unit, which is more than the kernel's registers (20 waves) and, from 20 strips on, its masks in LDS (a
-// kilobyte a strip) keep resident at once: the parts run in up to two rounds, in order, and a part waits only for
-// earlier ones.  At most 32 strips, from where on the parts grow in number.
+// How a subset's index list is cut: a part = one workgroup of four waves with `strips` strips each.  The kernel's registers
+// keep 20 waves a compute unit resident.  Up to eight strips a wave one round of them is the fastest cut (20 / 40 waves a compute unit,
+// p = 5 %: 16M 14.2 / 17.1 us, 31.5M, p = 10 % 24.5 / 25.3, 60M 35.3 / 35.6); beyond, two rounds let the second's hashing run beside the
+// first's stores (125.8M 62.7 / 60.5).  A part waits only for earlier ones.  At most 32 strips (a kilobyte of masks in LDS each),
+// from where on the parts grow in number.
 // rows: a strip is written row by row.  Lane by lane / row by row, us: 130M 15 % 106 / 143, 20 % 132 / 144, 25 % 167 / 147,
 // 50 % 313 / 155, 100 % 589 / 219; 17M 20 % 28.6 / 30.4, 25 % 33.6 / 31.0; 4M 20 % 13.9 / 13.8, 100 % 70 / 15.5; up to 2M,
 // where little is written, 1M 30 % 11.2 / 11.8, 50 % 13.0 / 11.9, 100,003 40 % 9.4 / 9.8, 50 % 9.9 / 9.8.
@@ -126,7 +127,7 @@ inline ListShape list_shape(uint64_t n, double fraction, uint32_t compute_units)
 {
     ListShape s;
     s.nstrips = (uint32_t)((n + am::kStripCoords - 1) / am::kStripCoords);
-    const uint32_t waves = 32u * std::max(compute_units, 1u);
+    const uint32_t resident = 20u * std::max(compute_units, 1u), waves = s.nstrips > 8u * resident ? 2u * resident : resident;
     s.strips = std::min((s.nstrips + waves - 1u) / waves, 32u);
     s.parts = (s.nstrips + 4u * s.strips - 1u) / (4u * s.strips);
     s.rows = fraction >= (s.nstrips <= 1024u ? 0.45 : 0.22);

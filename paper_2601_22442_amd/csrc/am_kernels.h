@@ -46,6 +46,16 @@ __device__ __forceinline__ uint32_t strip_mask(const SubsetKey &key, uint64_t n,
     const uint64_t mu0 = (uint64_t)strip * kStripCoords + lane * 32u;
     const bool whole = (uint64_t)(strip + 1u) * kStripCoords <= n;             // same for the whole wave
     uint32_t m = 0;
+    if (whole && key.mode == kDrawCoordinate && key.threshold != 0u) {
+        const uint32_t group = strip * (kStripCoords / 4u) + lane * 8u, last = (uint32_t)(key.threshold - 1u);
+#pragma unroll
+        for (uint32_t q = 0; q < 8u; ++q) {
+            const U4 x = philox4x32_10_group(group + q, key.step_lo, key.step_hi, key.seed_lo, key.seed_hi);
+            m |= (x.x0 <= last ? 1u : 0u) << (4u * q) | (x.x1 <= last ? 2u : 0u) << (4u * q)
+               | (x.x2 <= last ? 4u : 0u) << (4u * q) | (x.x3 <= last ? 8u : 0u) << (4u * q);
+        }
+        return m;
+    }
 #pragma unroll 2
     for (uint32_t q = 0; q < 8u; ++q) {
         const uint64_t mu = mu0 + 4u * q;
@@ -183,7 +193,7 @@ k_subset_scan(uint32_t *__restrict__ sb, uint32_t nsb, uint32_t capacity, uint32
 // =============================================================================================
 // Ascending index list of a subset (am_subset_indices):   k_list_clear  ->  k_subset_list
 // =============================================================================================
-// The cost is the generator (50 us for the words of 125.8M coordinates; the list itself is 50 MB at
+// The cost is the generator (40 us for the words of 125.8M coordinates; the list itself is 50 MB at
 // p = 5 %), so every coordinate is hashed once: a workgroup (four waves of `strips` strips each) keeps its
 // masks in LDS, publishes how many coordinates it holds, adds up what all the workgroups before it
 // hold and writes its indices there.  A lane holds 32 consecutive coordinates, so a strip of 2048 needs one
@@ -191,11 +201,11 @@ k_subset_scan(uint32_t *__restrict__ sb, uint32_t nsb, uint32_t capacity, uint32
 // there are lanes, so where many coordinates are members (am_host::list_shape) a strip is written row by row instead
 // (ROWS): 64 consecutive coordinates, one a lane, whose members go next to each other, 32 stores a strip.
 // No workgroup waits before it has published, and each only for lower-numbered ones, which start before it; so
-// every wait ends without all of them being resident (at 86 registers 20 waves a compute unit are: 125.8M
-// coordinates take one and a half rounds).  None waits for good: one that has not seen a count after kListPatience looks
+// every wait ends without all of them being resident (at 82 registers 20 waves a compute unit are).  None waits for good: one that has not seen a count after kListPatience looks
 // (well over 10 ms) counts the members before its own part itself, so the kernel ends whatever else happens to the scratch.
-// Measured, p = 5 %: 125.8M coordinates 85 us, 1M 9.7 us, 131,072 8.6 us (one workgroup per superblock
-// counting, a scan, and a second hashing pass that writes: 229, 55 and 54 us).
+// A thread looks at one count at a time: the counts sit in few lines, and eight looks in flight a thread make them the
+// bottleneck (16M 14.2 -> 18.7 us, 31.5M 24.5 -> 29.0).
+// Measured, p = 5 %: 125.8M coordinates 60.5 us (85.4 with the general form of the generator), 16M 14.2 (19.4), 1M 8.4 (9.9).
 // part_count: word p = the count of part p, bit 31 set once it is known; k_list_clear zeroes them first.
 constexpr uint32_t kListPatience = 1u << 15;
 
