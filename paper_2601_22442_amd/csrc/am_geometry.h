@@ -19,6 +19,7 @@ constexpr uint32_t kStripCoords = 2048;
 constexpr uint32_t kStripsPerSuperblock = kTileCoords * kTilesPerSuperblock / kStripCoords;
 constexpr uint32_t kLineFloats = 32;
 constexpr uint32_t kStageFloats = 256;      // ring values of a block (and EMA entries) the averaging-only kernel stages at a time
+constexpr uint32_t kLdsBytes = 160 * 1024, kLdsGranule = 1280;      // of a compute unit
 constexpr uint32_t kMaxReplicas = 32;
 constexpr uint32_t kMaxBlockReplicas = 8;
 

@@ -177,6 +177,34 @@ inline bool average_staged(const am_config &c, uint32_t ntiles, const Blocks &b,
     return c.fraction > (c.msg_dtype != AM_MSG_F32 ? 0.75 : 0.5) && (ntiles > 3072u || weights >= 6000000u) && !(e4m3 && b.rb == 8u);
 }
 
+// Workgroups (of four tiles, a wave each) of the staged averaging-only call that a compute unit may hold at a time; 0: as many as
+// fit.  Where the weights come from memory (more than the 256 MB cache holds) it is fastest with some 114 KB of lines a compute
+// unit on their way; with more the streams get in each other's way, as in the fused step, with fewer latency shows.  So the number
+// follows from the lines that a wave reads.  us a call by workgroups a compute unit, * the one chosen: interleaved, R = 8, 125.8M 5 %
+// 2: 1711, 3: 1574*, 4: 1631, 8: 1675; 1 % 3: 1030, 5: 717, 6: 655, as many as fit 636*; 31.5M 2 % 3: 291, 4: 257*, 8: 271; 10 % 2: 533*, 3: 559, 8: 568; 40 % 2: 936*,
+// 8: 957; R = 4 5 % 4: 231, 5: 228*, 8: 239; R = 12 2: 790, 3: 664*, 8: 727; per replica, 125.8M 5 % 2: 2358*, 3: 2468, 8: 2500; no
+// correction, 31.5M 5 % 3: 318, 4: 310*, 8: 310.  Weights that the cache holds: R = 8, 7M 3: 90.8, 4: 86.1, 8: 83.4.
+inline uint32_t average_workgroups(const am_config &c, const Blocks &b, bool interleaved_d)
+{
+    if (c.n * c.replicas <= 1ull << 26) return 0;
+    const bool by_line = c.subset_granule == 32;
+    auto touched = [&](double coordinates) { return 1.0 - std::pow(1.0 - c.fraction, by_line ? std::ceil(coordinates / am::kLineFloats) : coordinates); };
+    double kb = touched(2.0 * am::kLineFloats) + c.fraction * b.nblocks;           // of each replica: weights sent or received, ring values
+    if (c.correction != AM_CORR_NONE) kb += touched(interleaved_d ? (double)am::kLineFloats / b.rb : am::kLineFloats);
+    const double workgroups = std::floor(114.0 / 4.0 / (kb * b.rb) + 0.5);
+    return workgroups >= 7.0 ? 0u : std::max(2u, (uint32_t)workgroups);
+}
+
+// Dynamic LDS of a workgroup that needs `need` bytes, with which a compute unit holds at most `workgroups` of them (0: no limit).
+constexpr uint32_t lds_for_residency(uint32_t need, uint32_t workgroups)
+{
+    if (workgroups == 0u) return need;
+    const uint32_t share = am::kLdsBytes / workgroups / am::kLdsGranule * am::kLdsGranule - am::kLdsGranule;
+    return need > share ? need : share;
+}
+static_assert(lds_for_residency(1, 2) * 3 > am::kLdsBytes && lds_for_residency(1, 3) * 4 > am::kLdsBytes && lds_for_residency(1, 4) * 5 > am::kLdsBytes
+              && lds_for_residency(1, 5) * 6 > am::kLdsBytes && lds_for_residency(1, 6) * 7 > am::kLdsBytes, "one workgroup more does not fit");
+
 // Floats of one array of the EMA vectors and how many arrays there are, per layout.
 inline void d_layout_shape(const am_config &c, uint32_t *rb, uint32_t *arrays, uint64_t *floats)
 {

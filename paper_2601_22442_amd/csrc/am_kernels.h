@@ -1093,10 +1093,16 @@ k_step_sync(const StepArgs a)
 // and their EMA entries go straight into the wave's own stretch of LDS beside the loads of the weights
 // (read where they are used, they are up to eight waits in a row); more coordinates come a kilobyte at a
 // time.  The staging does not pay everywhere (am_host::average_staged); where it does not, the ring and the EMA
-// entries are read in place.  31.5M coordinates, us a call in place / staged: interleaved, R = 8, p = 1 % 264 / 210, 5 % 465 /
-// 421, 20 % 717 / 712, 100 % (7.9M) 508 / 431; R = 12, 5 % 848 / 692; no correction 408 / 331; per replica, 20M, 1 %: R = 8
-// 234 / 196, R = 4 122 / 113; 5 %: R = 8 416 / 407, R = 4 220 / 211, R = 2 122 / 105; 125.8M, R = 8, 5 %:
-// 1797 / 1716 (8.56 GB in whole lines: 5.0 TB/s).
+// entries are read in place.
+// Few of a lane's coordinates are members (one in twenty at p = 5 %), so with blocks of four and eight replicas the lanes do not
+// work on their own coordinates one bit position after the other, with a few lanes busy each time: the members' values change
+// hands through LDS and a lane takes four replicas of one member, for the send as for the receive (937 -> about 500
+// vector instructions a tile; the sent lines leave with 16 bytes a lane side by side).  And memory writes whole 64-byte halves of a line at
+// half a line's cost (reads move the line whatever part of it is asked for), so only halves that hold a received
+// coordinate are written: 56 % at p = 5 %, 81 % of the lines.  How many workgroups are resident: am_host::average_workgroups.
+// us a call before / after the three: interleaved, R = 8, 125.8M 5 % 1693 / 1567 (7.7 GB: 4.9 TB/s), 1 % 804 / 640, 31.5M 0.5 % 184 / 148,
+// 2 % 262 / 257, 10 % 550 / 519, 40 % 972 / 937, 7M 5 % 94 / 83.5, 2M 37.3 / 31.6, 500k 13.0 / 11.3; R = 12, 31.5M 5 % 688 / 659;
+// R = 4 240 / 228; no correction 325 / 304; per replica, 125.8M 5 % 2681 / 2413, 31.5M 1 % 287 / 266.
 // Arithmetic and its order are those of the fused kernel: mean in fp64 in replica order, rounded to
 // fp32; d <- coef_d d + coef_s (w^ - sent) and w = mean + d in fp64, rounded once each.
 // =============================================================================================
@@ -1162,13 +1168,12 @@ __device__ __forceinline__ void average_send_block(float *slot, const F4 (&w)[RB
 // interleaved EMA vector (DIL; d_old: the same or their copy in LDS), else the entries are in dv.  HALVES: the
 // replicas' fp64 values are formed four at a time, not eight (76 registers instead of 84).
 template <bool DIL, int RB, bool HALVES>
-__device__ __forceinline__ void average_receive(const StepArgs &a, int j, float abar, const float (&own)[RB], const float *d_old, float *dp,
-                                                F4 (&w)[RB], F4 (&dv)[RB])
+__device__ __forceinline__ void average_receive(const StepArgs &a, int j, float abar, const float (&own)[RB], float *dp, F4 (&w)[RB], F4 (&dv)[RB])
 {
     if (a.ema) {
         float d_new[RB];
         if (DIL) {
-            load_block_values<RB>(d_old, d_new);
+            load_block_values<RB>(dp, d_new);
         } else {
 #pragma unroll
             for (int k = 0; k < RB; ++k) d_new[k] = dv[k].v[j];
@@ -1187,26 +1192,27 @@ __device__ __forceinline__ void average_receive(const StepArgs &a, int j, float 
     }
 }
 
-// Bytes of dynamic LDS of a workgroup: per wave a kilobyte of ring values per block, one of EMA entries
-// (interleaved), and the list of received coordinates.  Blocks of fewer than four replicas have
-// entries shorter than a direct-to-LDS load and read them from memory.
-template <bool DIL, int RB, bool STAGED>
-constexpr bool kStageD = STAGED && DIL && RB >= 4;
+// Blocks of four and eight replicas: a coordinate's values change hands through LDS, and lanes work on four of them each
+// (blocks of fewer have stretches shorter than 16 bytes).
+template <int RB, bool STAGED>
+constexpr bool kAverageItems = STAGED && RB >= 4;
+// Bytes of dynamic LDS of a workgroup: per wave a kilobyte of ring values per block, and (items) one of weights, one of EMA
+// entries and the list of received coordinates.
 template <bool DIL, int RB>
 __host__ __device__ constexpr uint32_t average_wave_bytes(uint32_t nblocks)
 {
-    return (nblocks * kStageFloats + (kStageD<DIL, RB, true> ? kStageFloats + 64u : 0u)) * (uint32_t)sizeof(float);
+    return (nblocks * kStageFloats + (kAverageItems<RB, true> ? 2u * kStageFloats + (DIL ? 64u : 0u) : 0u)) * (uint32_t)sizeof(float);
 }
 
 // grid = (ceil(tiles / 4), blocks) (TAU0: (ceil(tiles / 4), 1)); blockDim = 256: four waves, each with
-// a tile and (STAGED) average_wave_bytes() of LDS of its own.
+// a tile and (STAGED) average_wave_bytes() of LDS of its own, or more where fewer are to be resident.
 // DIL: the EMA vectors are interleaved ([coordinate][RB] per block); else one flat array per replica.
 // TAU0: the average is of this very call's values (tau = 0): the wave walks all blocks of its tile,
 // once for the sums and the send, once more for the update (another wave must not rewrite a block's
 // weights while this one still needs them for the mean).
 // STAGED: a kilobyte at a time through LDS; else (where am_host::average_staged says so) the ring and the
 // interleaved EMA entries are read where their values are used.
-// At most 128 registers: 16 tiles or more per compute unit in flight (kept to 80, the staged form spills); in place with
+// At most 128 registers (the staged form with interleaved EMA entries and items takes 72); in place with
 // interleaved EMA entries, where latency is the cost, at most 80 and 24 tiles: 20 replicas, us a call relative to
 // the form before the staging, 500k p = 0.2 0.85, p = 0.3 0.89, 900k p = 0.2 0.94 (slower than that form at 84 registers).
 template <bool DIL, int RB, bool TAU0, bool STAGED>
@@ -1277,8 +1283,8 @@ k_average(const StepArgs a)
     const uint32_t rank_recv = TAU0 ? rank_send : wave_prefix_mask4(mask_recv, count_recv);
     if (TAU0) count_recv = count_send;
     const uint64_t any_recv = __ballot(mask_recv != 0u);
-    const bool line_recv = ((any_recv >> (lane & ~7u)) & 0xFFull) != 0ull;    // my 128-byte line of a per-replica array receives
-    const bool need_w = mask_send != 0u || line_recv;
+    const bool half_recv = ((any_recv >> (lane & ~3u)) & 0xFull) != 0ull;     // my 64 bytes of a per-replica array receive
+    const bool need_w = mask_send != 0u || half_recv;
     const double inv_replicas = 1.0 / (double)R;
 
     F4 w[RB], dv[RB];
@@ -1295,13 +1301,13 @@ k_average(const StepArgs a)
             if (with_d) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) dv[k].v[j] = 0.f;
-                if (!DIL && a.ema && i < R && line_recv) dv[k] = load_f32x4(a.d[i] + tbase, loff, nvalid);
+                if (!DIL && a.ema && i < R && half_recv) dv[k] = load_f32x4(a.d[i] + tbase, loff, nvalid);
             }
         }
     };
-    // only lines that received are rewritten
+    // only half lines that received are rewritten
     auto store_block = [&](const uint32_t b) {
-        if (!line_recv) return;
+        if (!half_recv) return;
 #pragma unroll
         for (int k = 0; k < RB; ++k) {
             const uint32_t i = b * RB + k;
@@ -1313,9 +1319,22 @@ k_average(const StepArgs a)
 
     if constexpr (!TAU0) {
         constexpr uint32_t kStaged = kStageFloats / RB;                    // received coordinates whose values are staged
+        constexpr bool kItems = kAverageItems<RB, STAGED>;
         extern __shared__ __attribute__((aligned(16))) float lds[];
         float *const ring_lds = lds + wave * (average_wave_bytes<DIL, RB>(a.nblocks) / sizeof(float));
-        float *const d_lds = ring_lds + a.nblocks * kStageFloats;
+        float *const x_lds = ring_lds + a.nblocks * kStageFloats;          // [RB][kStaged] weights of the received coordinates
+        float *const d_lds = x_lds + kStageFloats;                         // their EMA entries: interleaved [kStaged][RB], else [RB][kStaged]
+        uint8_t *const list = reinterpret_cast<uint8_t *>(d_lds + kStageFloats);
+        // the rank in this turn of the lane's coordinates that are in `mask`, one after the other; `rank`: of the first
+        auto each = [&](const uint32_t mask, const uint32_t rank, auto use) {
+            uint32_t c = rank;                                             // (wraps below the turn's first: not this turn's)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if ((mask >> j) & 1u) {
+                    if (c < kStaged) use(j, c);
+                    ++c;
+                }
+        };
         // requests what the received coordinates of rank c0 .. c0 + kStaged - 1 need
         auto stage = [&](const uint32_t c0) {
             const uint32_t at = c0 * RB + lane * 4u;                       // a lane takes 16 bytes
@@ -1323,15 +1342,8 @@ k_average(const StepArgs a)
                 const float *src = a.ring_recv + (uint64_t)first_r * kLineFloats + at;
                 for (uint32_t b = 0; b < a.nblocks; ++b) lds_dma_16(src + b * block_floats, ring_lds + b * kStageFloats);
             }
-            if (kStageD<DIL, RB, STAGED> && a.ema) {
-                uint8_t *const list = reinterpret_cast<uint8_t *>(d_lds + kStageFloats);
-                uint32_t c = rank_recv - c0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if ((mask_recv >> j) & 1u) {
-                        if (c < kStaged) list[c] = (uint8_t)(loff + (uint32_t)j);
-                        ++c;
-                    }
+            if (kItems && DIL && a.ema) {
+                each(mask_recv, rank_recv - c0, [&](int j, uint32_t c) { list[c] = (uint8_t)(loff + (uint32_t)j); });
                 wave_lds_sync();
                 const uint32_t rank = lane * 4u / RB;                      // all or half of a coordinate's entries
                 if (c0 + rank < count_recv) lds_dma_16(a.d[b0] + (tbase + list[rank]) * RB + (lane * 4u) % RB, d_lds);
@@ -1339,55 +1351,134 @@ k_average(const StepArgs a)
         };
         if (STAGED && count_recv != 0u) stage(0u);
         load_block(b0, true, true);
-        if (STAGED) {
+        if (STAGED) {                                                      // (before the first store: the wait counts stores, too)
             lds_dma_wait();
             wave_lds_sync();
         }
-        if (a.do_send && lines_s != 0u)
-            average_send_block<RB>(a.ring_send + b0 * block_floats + (uint64_t)first_s * kLineFloats, w, mask_send, rank_send,
-                                   count_send, lines_s * kPerLine, lane);
-        // ---- receive: old average of what every replica sent (+ EMA of staleness)
-        // the received coordinates of rank c0 .. c0 + most - 1; values(b, c, x): what block b's replicas sent for rank c0 + c
-        auto receive = [&](const uint32_t c0, const uint32_t most, auto values) {
-            uint32_t c = rank_recv - c0;                                   // (wraps below c0: not this turn's)
+        if constexpr (kItems) {
+            // A coordinate's values change hands through LDS: the lane that holds its group puts them there, and lane l takes
+            // item l, replicas 4 l mod RB .. + 3 of the coordinate of rank 4 l / RB: sixteen bytes of [coordinate][RB].
+            const uint32_t ci = lane * 4u / RB, k0 = (lane * 4u) % RB;
+            if (a.do_send) {
+                for (uint32_t c0 = 0; c0 * RB < lines_s * kLineFloats; c0 += kStaged) {
+                    each(mask_send, rank_send - c0, [&](int j, uint32_t c) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (!((mask_recv >> j) & 1u)) continue;
-                if (c < most && c0 + c < lines_r * kPerLine) {             // (as at the send)
-                    double sum = 0.;
-                    float own[RB];
-                    for (uint32_t b = 0; b < a.nblocks; ++b) {
-                        float x[RB];
-                        values(b, c, x);
-                        const uint32_t nrep = R - b * RB;                  // replicas present in this block (>= RB: all)
-#pragma unroll
-                        for (int k = 0; k < RB; ++k) {
-                            if (b == b0) own[k] = x[k];                    // my own staleness term takes the exact value
-                            const float q = a.msg_dtype != 0u ? quantize_message(x[k], a.msg_dtype) : x[k];
-                            if ((uint32_t)k < nrep) sum += (double)q;
-                        }
+                        for (int k = 0; k < RB; ++k) x_lds[k * kStaged + c] = w[k].v[j];
+                    });
+                    wave_lds_sync();
+                    const uint32_t at = c0 * RB + lane * 4u;
+                    v4f x = {0.f, 0.f, 0.f, 0.f};                          // the rest of the tile's last line is zero
+                    if (c0 + ci < count_send) {
+                        const float *p = x_lds + k0 * kStaged + ci;
+                        x = v4f{p[0], p[kStaged], p[2 * kStaged], p[3 * kStaged]};
                     }
-                    float *const dp = DIL ? a.d[b0] + (tbase + loff + (uint32_t)j) * RB : nullptr;
-                    average_receive<DIL, RB, DIL && !STAGED>(a, j, (float)(sum * inv_replicas), own, kStageD<DIL, RB, STAGED> ? d_lds + c * RB : dp, dp, w, dv);
+                    if (at < lines_s * kLineFloats)
+                        *reinterpret_cast<v4f *>(a.ring_send + b0 * block_floats + (uint64_t)first_s * kLineFloats + at) = x;
+                    wave_lds_sync();
                 }
-                ++c;
             }
-        };
-        if constexpr (!STAGED) {
-            receive(0u, kTileCoords, [&](const uint32_t b, const uint32_t c, float (&x)[RB]) {
-                load_block_values<RB>(a.ring_recv + (uint64_t)first_r * kLineFloats + b * block_floats + (uint64_t)c * RB, x);
-            });
-        } else {
             for (uint32_t c0 = 0; c0 < count_recv; c0 += kStaged) {        // nearly always one turn
                 if (c0 != 0u) {
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup"); // what the last turn read from LDS has been read
                     stage(c0);
                     lds_dma_wait();
-                    wave_lds_sync();
                 }
-                receive(c0, kStaged, [&](const uint32_t b, const uint32_t c, float (&x)[RB]) {
-                    load_block_values<RB>(ring_lds + b * kStageFloats + c * RB, x);
+                each(mask_recv, rank_recv - c0, [&](int j, uint32_t c) {
+#pragma unroll
+                    for (int k = 0; k < RB; ++k) {
+                        x_lds[k * kStaged + c] = w[k].v[j];
+                        if (!DIL) d_lds[k * kStaged + c] = dv[k].v[j];
+                    }
                 });
+                wave_lds_sync();
+                if (c0 + ci < count_recv && c0 + ci < lines_r * kPerLine) {        // (the rank is below that by construction of the table)
+                    double sum = 0.;
+                    for (uint32_t b = 0; b < a.nblocks; ++b) {
+                        float x[RB];
+                        load_block_values<RB>(ring_lds + b * kStageFloats + ci * RB, x);
+                        if (a.msg_dtype != 0u) {
+#pragma unroll
+                            for (int k = 0; k < RB; ++k) x[k] = quantize_message(x[k], a.msg_dtype);
+                        }
+                        const uint32_t nrep = R - b * RB;                  // replicas present in this block (>= RB: all)
+#pragma unroll
+                        for (int k = 0; k < RB; ++k)
+                            if ((uint32_t)k < nrep) sum += (double)x[k];
+                    }
+                    const float abar = (float)(sum * inv_replicas);
+                    float *const xp = x_lds + k0 * kStaged + ci, *const dp = DIL ? d_lds + lane * 4u : d_lds + k0 * kStaged + ci;
+                    constexpr uint32_t ds = DIL ? 1u : kStaged;
+                    if (a.ema) {
+                        const v4f own = *reinterpret_cast<const v4f *>(ring_lds + b0 * kStageFloats + lane * 4u);     // my own staleness term takes the exact value
+                        v4f d_new;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            d_new[q] = (float)fma(a.coef_d, (double)dp[q * ds], a.coef_s * ((double)xp[q * kStaged] - (double)own[q]));
+                            xp[q * kStaged] = (float)((double)abar + (double)d_new[q]);
+                            if (!DIL) dp[q * ds] = d_new[q];
+                        }
+                        if (DIL) *reinterpret_cast<v4f *>(a.d[b0] + (tbase + list[ci]) * RB + k0) = d_new;
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) xp[q * kStaged] = abar;
+                    }
+                }
+                wave_lds_sync();
+                each(mask_recv, rank_recv - c0, [&](int j, uint32_t c) {
+#pragma unroll
+                    for (int k = 0; k < RB; ++k) {
+                        w[k].v[j] = x_lds[k * kStaged + c];
+                        if (!DIL) dv[k].v[j] = d_lds[k * kStaged + c];
+                    }
+                });
+            }
+        } else {
+            if (a.do_send && lines_s != 0u)
+                average_send_block<RB>(a.ring_send + b0 * block_floats + (uint64_t)first_s * kLineFloats, w, mask_send, rank_send,
+                                       count_send, lines_s * kPerLine, lane);
+            // ---- receive: old average of what every replica sent (+ EMA of staleness)
+            // the received coordinates of rank c0 .. c0 + most - 1; values(b, c, x): what block b's replicas sent for rank c0 + c
+            auto receive = [&](const uint32_t c0, const uint32_t most, auto values) {
+                uint32_t c = rank_recv - c0;                                   // (wraps below c0: not this turn's)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (!((mask_recv >> j) & 1u)) continue;
+                    if (c < most && c0 + c < lines_r * kPerLine) {             // (as at the send)
+                        double sum = 0.;
+                        float own[RB];
+                        for (uint32_t b = 0; b < a.nblocks; ++b) {
+                            float x[RB];
+                            values(b, c, x);
+                            const uint32_t nrep = R - b * RB;                  // replicas present in this block (>= RB: all)
+#pragma unroll
+                            for (int k = 0; k < RB; ++k) {
+                                if (b == b0) own[k] = x[k];                    // my own staleness term takes the exact value
+                                const float q = a.msg_dtype != 0u ? quantize_message(x[k], a.msg_dtype) : x[k];
+                                if ((uint32_t)k < nrep) sum += (double)q;
+                            }
+                        }
+                        float *const dp = DIL ? a.d[b0] + (tbase + loff + (uint32_t)j) * RB : nullptr;
+                        average_receive<DIL, RB, DIL && !STAGED>(a, j, (float)(sum * inv_replicas), own, dp, w, dv);
+                    }
+                    ++c;
+                }
+            };
+            if constexpr (!STAGED) {
+                receive(0u, kTileCoords, [&](const uint32_t b, const uint32_t c, float (&x)[RB]) {
+                    load_block_values<RB>(a.ring_recv + (uint64_t)first_r * kLineFloats + b * block_floats + (uint64_t)c * RB, x);
+                });
+            } else {
+                for (uint32_t c0 = 0; c0 < count_recv; c0 += kStaged) {        // nearly always one turn
+                    if (c0 != 0u) {
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup"); // what the last turn read from LDS has been read
+                        stage(c0);
+                        lds_dma_wait();
+                        wave_lds_sync();
+                    }
+                    receive(c0, kStaged, [&](const uint32_t b, const uint32_t c, float (&x)[RB]) {
+                        load_block_values<RB>(ring_lds + b * kStageFloats + c * RB, x);
+                    });
+                }
             }
         }
         store_block(b0);
@@ -1423,7 +1514,7 @@ k_average(const StepArgs a)
 #pragma unroll
                         for (int k = 0; k < RB; ++k) own[k] = w[k].v[j];   // no delay: what was sent is this very value
                         float *const dp = DIL ? a.d[b] + (tbase + loff + (uint32_t)j) * RB : nullptr;
-                        average_receive<DIL, RB, false>(a, j, (float)(sum[j] * inv_replicas), own, dp, dp, w, dv);
+                        average_receive<DIL, RB, false>(a, j, (float)(sum[j] * inv_replicas), own, dp, w, dv);
                         ++c;
                     }
                 }

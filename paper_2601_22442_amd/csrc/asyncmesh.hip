@@ -267,7 +267,8 @@ am_status launch_average_kernel(am_state *st, const am::StepArgs &a)
 {
     const uint32_t nblocks = st->lay.blocks.nblocks;
     const dim3 grid((st->lay.ntiles + 3u) / 4u, TAU0 ? 1u : nblocks), block(256);
-    am::k_average<DIL, RB, TAU0, STAGED><<<grid, block, STAGED ? 4u * am::average_wave_bytes<DIL, RB>(nblocks) : 0u, st->stream>>>(a);
+    const uint32_t lds = STAGED ? am_host::lds_for_residency(4u * am::average_wave_bytes<DIL, RB>(nblocks), am_host::average_workgroups(st->cfg, st->lay.blocks, DIL)) : 0u;
+    am::k_average<DIL, RB, TAU0, STAGED><<<grid, block, lds, st->stream>>>(a);
     AM_HIP(hipGetLastError());
     return AM_OK;
 }
