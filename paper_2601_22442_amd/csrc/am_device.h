@@ -208,6 +208,25 @@ __device__ __forceinline__ void store_f32x4(float *__restrict__ p, uint64_t mu, 
     }
 }
 
+// A store that goes through to memory (system scope) besides the non-temporal hint, of 16 or 8 bytes at float / element `mu` of
+// p, the same for the whole wave.  The stream mix of the fused step on 125.8M x 8 without its arithmetic: 5.66 ms, 5.82 with the
+// hint alone; but a working set that the caches hold from call to call loses by it (500k x 4 +4 %).
+template <typename T>
+__device__ __forceinline__ void store_through(void *p, uint32_t byte, const T &x)
+{
+    constexpr int kNt = 2, kSystem = 16;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(p, 0, kTileCoords * 4u, 0x00020000);      // one tile's kilobyte: nothing is written past it
+    if constexpr (sizeof(T) == 16) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, x), r, (int)byte, 0, kNt | kSystem);
+    else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, x), r, (int)byte, 0, kNt | kSystem);
+}
+
+// store_f32x4 at float `at` of a tile's part of an array; through: see store_through
+__device__ __forceinline__ void store_tile_f32x4(float *__restrict__ p, uint32_t at, int nvalid, const F4 &x, bool through)
+{
+    if (through && nvalid == 4) store_through(p, at * 4u, v4f{x.v[0], x.v[1], x.v[2], x.v[3]});
+    else store_f32x4(p, at, nvalid, x);
+}
+
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 // round-to-nearest-even fp32 -> bfloat16 (the compiler selects the gfx950 conversion instruction)
@@ -267,13 +286,14 @@ __device__ __forceinline__ uint16_t f64_to_bf16_bits(double x)
     return f32_to_bf16_bits(f);
 }
 
-__device__ __forceinline__ void store_bf16x4_from_f64(uint16_t *__restrict__ p, uint64_t mu, int nvalid, const double (&x)[4])
+__device__ __forceinline__ void store_bf16x4_from_f64(uint16_t *__restrict__ p, uint64_t mu, int nvalid, const double (&x)[4], bool through = false)
 {
     if (nvalid == 4) {
         v2u t;
         t.x = (uint32_t)f64_to_bf16_bits(x[0]) | ((uint32_t)f64_to_bf16_bits(x[1]) << 16);
         t.y = (uint32_t)f64_to_bf16_bits(x[2]) | ((uint32_t)f64_to_bf16_bits(x[3]) << 16);
-        __builtin_nontemporal_store(t, reinterpret_cast<v2u *>(p + mu));
+        if (through) store_through(p, (uint32_t)mu * 2u, t);
+        else __builtin_nontemporal_store(t, reinterpret_cast<v2u *>(p + mu));
     } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j)

@@ -177,6 +177,22 @@ inline bool average_staged(const am_config &c, uint32_t ntiles, const Blocks &b,
     return c.fraction > (c.msg_dtype != AM_MSG_F32 ? 0.75 : 0.5) && (ntiles > 3072u || weights >= 6000000u) && !(e4m3 && b.rb == 8u);
 }
 
+// Whether a step's arrays come from memory each time (20 to 36 bytes a parameter and replica; half of the 256 MB that the caches hold
+// survives to the next call).  Stores through to memory / with the non-temporal hint alone, us a step: R = 8 125.8M 5834 / 5882, 31.5M 1799 / 1816,
+// R = 4 7.1M 171.7 / 174.5, R = 2 30M SGD 287.7 / 295.4, 3M SGD 23.2 / 23.9; R = 4 1M 31.7 / 31.4, 500k 17.8 / 17.0.
+inline bool beyond_caches(const am_config &c) { return c.n * c.replicas > 5ull << 20; }
+
+// Workgroups (a wave per replica of a block) of the fused step that a compute unit may hold at a time; 0: as many as fit (three of
+// eight waves).  The stream mix moves fastest with few requests on their way (without arithmetic, 125.8M x 8: 16 waves a compute unit 6.05 to 6.3
+// TB/s, 24 5.5 to 6.1); fewer waves than these leave the step's chain of waits visible.  us a step, as many as fit / these / the next
+// fewer: R = 4 31.5M 742 / 717 / 714, per replica 839 / 808 / 799, without forward copy 648 / 639 / 651, 7.1M 177 / 172 / 174; R = 2 31.5M 360 / 352
+// / 358; R = 1 191 / 190 / 195.  Eight replicas: 1480 / 1504 with two.
+inline uint32_t step_workgroups(const am_config &c, const Blocks &b)
+{
+    if (!beyond_caches(c)) return 0;
+    return b.rb == 4u ? 5u : b.rb == 2u ? 12u : b.rb == 1u ? 28u : 0u;
+}
+
 // Workgroups (of four tiles, a wave each) of the staged averaging-only call that a compute unit may hold at a time; 0: as many as
 // fit.  Where the weights come from memory (more than the 256 MB cache holds) it is fastest with some 114 KB of lines a compute
 // unit on their way; with more the streams get in each other's way, as in the fused step, with fewer latency shows.  So the number

@@ -331,6 +331,7 @@ struct StepArgs {
     // averaging
     uint32_t do_send, do_recv, ema, same_slot;     // ema: a correction vector d is kept; same_slot: tau = 0,
                                                    // the average is of this step's w^
+    uint32_t through;                              // more than the caches hold: stores go through to memory
     uint32_t do_next;                              // also count the lines each tile will send next step
     uint32_t sum_lines;                            // small stage: the kernel itself adds up where the tile's lines start in the
                                                    // send slot (from send_lines) and writes the tile's word for the receive
@@ -353,7 +354,7 @@ struct StepArgs {
     //   w^ = w - (c_wd w + (c_g g + c_m m') / (c_v sqrt(v') + eps))           (Adam family)
     //   w^ = w - (c_wd w + c_m m')     resp.     w - (c_wd w + c_g g)          (SGD with / without momentum)
     double a_m, b_m, a_v, b_v, c_wd, eps;
-    double gamma;
+    double gamma, inv_replicas;
     float *d[kMaxReplicas];          // one array per replica, or (interleaved) one per block: [tiles * 256][rb]
     ReplicaArgs rep[kMaxReplicas];
 };
@@ -362,26 +363,25 @@ struct StepArgs {
 // (moments, weight update, EMA, look-ahead) are evaluated in fp64 from the stored fp32 values
 // and rounded once on store, so that rounding noise does not random-walk over hundreds of steps;
 // on this chip an fp64 FMA issues at the rate of an unpacked fp32 FMA, and the kernel is bound by
-// memory.  The square root and the quotient start from the fp32 hardware approximations and take
-// one Newton step in fp64 each, which is far cheaper than fp64 sqrt / divide sequences.
+// memory.  The square root and the quotient start from the hardware's fp64 approximations of the reciprocal
+// root and the reciprocal (some 24 bits, at a quarter of the rate) and take one Newton step each: 7 and 4 instructions, where the correctly
+// rounded fp32 root with its scaling and an fp32 reciprocal with the conversions took 28 and 10 (a local step of four
+// coordinates 250 -> 125 vector instructions).
 
 // sqrt(x) of an fp32 value x >= 0, to (nearly) double accuracy
 __device__ __forceinline__ double sqrt_refined(float x)
 {
-    if (x == 0.0f) return 0.0;
-    const float s0 = sqrtf(x);
-    const double s0d = (double)s0;
-    const double residual = fma(-s0d, s0d, (double)x);                     // x - s0^2, exact to fp64
-    return s0d + (double)((float)residual * (0.5f * __builtin_amdgcn_rcpf(s0)));
+    const double xd = (double)x, y = __builtin_amdgcn_rsq(xd);
+    const double s = xd * y;
+    return x == 0.0f ? 0.0 : fma(fma(-s, s, xd), 0.5 * y, s);             // (the reciprocal root of zero is infinite)
 }
 
 // num / den for den > 0, to (nearly) double accuracy
 __device__ __forceinline__ double quotient_refined(double num, double den)
 {
-    const float rden = __builtin_amdgcn_rcpf((float)den);
-    const float q0 = (float)num * rden;
-    const double residual = fma(-(double)q0, den, num);                    // num - q0 den
-    return (double)q0 + (double)((float)residual * rden);
+    const double y = __builtin_amdgcn_rcp(den);
+    const double q = num * y;
+    return fma(fma(-q, den, num), y, q);
 }
 
 // What one replica's update of one group reads from memory.
@@ -406,32 +406,38 @@ template <int OPT>
 __device__ __forceinline__ void local_step(const StepArgs &a, const ReplicaArgs &r, uint32_t i, const GroupIn &in,
                                            F4 &w_hat, F4 &m_new, F4 &v_new)
 {
-    // A replica that is idle in this tick goes through the same arithmetic with the coefficients of
-    // the identity (m' = m, v' = v, w^ = w exactly); its gradient was not loaded.
-    const bool idle = r.g == nullptr;
-    const double rs = (a.replica_scale && !idle) ? (double)a.replica_scale[i] : 1.0;
-    const double a_m = idle ? 1.0 : a.a_m, b_m = idle ? 0.0 : a.b_m;
-    const double a_v = idle ? 1.0 : a.a_v, b_v = idle ? 0.0 : a.b_v;
-    const double c_wd = idle ? 0.0 : a.c_wd;
-    const double c_g = r.c_g, c_m = r.c_m, c_v = r.c_v;
+    // A replica that is idle in this tick keeps its weights and moments; its gradient was not loaded.
+    if (r.g == nullptr) {
+        w_hat = in.w;
+        if (OPT == kOptSgdMomentum || OPT == kOptAdam) m_new = in.m;
+        if (OPT == kOptAdam) v_new = in.v;
+        return;
+    }
+    double g[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) g[j] = (double)in.g.v[j];      // grad_scale is folded into b_m, b_v, c_g
+    if (a.replica_scale) {
+        const double rs = (double)a.replica_scale[i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) g[j] *= rs;
+    }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const double gj = idle ? 0.0 : rs * (double)in.g.v[j]; // grad_scale is folded into b_m, b_v, c_g; idle: what was loaded is not a gradient
         const double wo = (double)in.w.v[j];
         double step;                                           // what is subtracted besides the decay
         if (OPT == kOptSgdPlain) {
-            step = c_g * gj;
+            step = r.c_g * g[j];
         } else if (OPT == kOptSgdMomentum) {
-            m_new.v[j] = (float)fma(a_m, (double)in.m.v[j], b_m * gj);
-            step = c_m * (double)m_new.v[j];
+            m_new.v[j] = (float)fma(a.a_m, (double)in.m.v[j], a.b_m * g[j]);
+            step = r.c_m * (double)m_new.v[j];
         } else {
-            m_new.v[j] = (float)fma(a_m, (double)in.m.v[j], b_m * gj);
-            v_new.v[j] = (float)fma(a_v, (double)in.v.v[j], b_v * gj * gj);
-            const double den = fma(c_v, sqrt_refined(v_new.v[j]), a.eps);
-            const double num = fma(c_g, gj, c_m * (double)m_new.v[j]);
+            m_new.v[j] = (float)fma(a.a_m, (double)in.m.v[j], a.b_m * g[j]);
+            v_new.v[j] = (float)fma(a.a_v, (double)in.v.v[j], a.b_v * g[j] * g[j]);
+            const double den = fma(r.c_v, sqrt_refined(v_new.v[j]), a.eps);
+            const double num = fma(r.c_g, g[j], r.c_m * (double)m_new.v[j]);
             step = quotient_refined(num, den);
         }
-        w_hat.v[j] = (float)(wo - fma(c_wd, wo, idle ? 0.0 : step));
+        w_hat.v[j] = (float)(wo - fma(a.c_wd, wo, step));
     }
 }
 
@@ -443,11 +449,20 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Whether half `half` (64 bytes) of line `line` of the tile's interleaved EMA entries holds a received coordinate.
+// masks: the lanes' masks of the received subset; sh: log2 of the replicas per block.
+__device__ __forceinline__ bool half_received(const uint8_t *masks, uint32_t line, uint32_t half, uint32_t sh)
+{
+    if (sh == 3u) return ((masks[line] >> (2u * half)) & 3u) != 0u;                     // two coordinates of one group
+    const uint8_t *p = masks + (2u * line + half) * (4u >> sh);
+    return sh == 2u ? *p != 0u : sh == 1u ? *reinterpret_cast<const uint16_t *>(p) != 0u : *reinterpret_cast<const uint32_t *>(p) != 0u;
+}
+
 // Where the coordinates of one group (= one lane) sit in the subsets of this step.
 struct GroupSubsets {
     uint32_t mask_send, mask_recv;      // bit j: coordinate 4*group + j is sent / received now
     uint32_t rank_send, rank_recv;      // rank of the first such coordinate among those of the tile
-    bool line_recv;                     // the 128-byte line of a per-replica array (8 lanes) holding the group receives something
+    bool half_recv;                     // the 64 bytes of a per-replica array (4 lanes) holding the group receive something
     uint32_t d_slot;                    // interleaved d: float offset, in the LDS staging area, of the group's first entry
 };
 
@@ -484,7 +499,7 @@ template <bool DIL>
 __device__ __forceinline__ void load_group_sparse(const StepArgs &a, uint32_t i, uint64_t tbase, uint32_t loff, int nvalid,
                                                   const GroupSubsets &s, GroupIn &in)
 {
-    if (!DIL && a.ema && s.line_recv) in.d = load_f32x4(a.d[i] + tbase, loff, nvalid);
+    if (!DIL && a.ema && s.half_recv) in.d = load_f32x4(a.d[i] + tbase, loff, nvalid);
 }
 
 // Replica i (slot `slot` of its block) of one group, from its stepped weights to stored results: the
@@ -529,9 +544,9 @@ __device__ __forceinline__ void finish_replica(const StepArgs &a, const ReplicaA
                 if ((s.mask_recv >> j) & 1u) w_new.v[j] = abar[j];
         }
     }
-    if (!DIL && a.ema && s.line_recv) store_f32x4(a.d[i] + tbase, loff, nvalid, in.d);
+    if (!DIL && a.ema && s.half_recv) store_tile_f32x4(a.d[i] + tbase, loff, nvalid, in.d, a.through != 0u);
 
-    store_f32x4(r.w + tbase, loff, nvalid, w_new);
+    store_tile_f32x4(r.w + tbase, loff, nvalid, w_new, a.through != 0u);
     if (FWD != kFwdNone) {
         // fwd = w + gamma (w^ - w_before): product and sum rounded separately in fp64, then ONE
         // rounding to the stored type
@@ -544,9 +559,9 @@ __device__ __forceinline__ void finish_replica(const StepArgs &a, const ReplicaA
             F4 o;
 #pragma unroll
             for (int j = 0; j < 4; ++j) o.v[j] = (float)f[j];
-            store_f32x4(static_cast<float *>(r.fwd) + tbase, loff, nvalid, o);
+            store_tile_f32x4(static_cast<float *>(r.fwd) + tbase, loff, nvalid, o, a.through != 0u);
         } else {
-            store_bf16x4_from_f64(static_cast<uint16_t *>(r.fwd) + tbase, loff, nvalid, f);
+            store_bf16x4_from_f64(static_cast<uint16_t *>(r.fwd) + tbase, loff, nvalid, f, a.through != 0u);
         }
     }
 }
@@ -561,8 +576,8 @@ __device__ __forceinline__ void step_replica(const StepArgs &a, const ReplicaArg
     if (TAU0) {
         local_step<OPT>(a, r, i, in, w_hat, m_new, v_new);
         // the moments are final: out they go, before the averaging needs registers
-        if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_f32x4(r.m + tbase, loff, nvalid, m_new);
-        if (OPT == kOptAdam) store_f32x4(r.v + tbase, loff, nvalid, v_new);
+        if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_tile_f32x4(r.m + tbase, loff, nvalid, m_new, a.through != 0u);
+        if (OPT == kOptAdam) store_tile_f32x4(r.v + tbase, loff, nvalid, v_new, a.through != 0u);
     }
 
     if (s.mask_send) {                                     // send: into the staging lines, [rank][rb]
@@ -574,39 +589,54 @@ __device__ __forceinline__ void step_replica(const StepArgs &a, const ReplicaArg
     finish_replica<FWD, DIL, TAU0>(a, r, i, slot, tbase, loff, nvalid, s, tile_receives, abar, in, w_hat, recv_block, L);
 }
 
+template <int RB>
+__device__ __forceinline__ void load_block_values(const float *p, float (&x)[RB])
+{
+    if constexpr (RB == 8) {
+        const v4f lo = *reinterpret_cast<const v4f *>(p), hi = *reinterpret_cast<const v4f *>(p + 4);
+        x[0] = lo.x; x[1] = lo.y; x[2] = lo.z; x[3] = lo.w; x[4] = hi.x; x[5] = hi.y; x[6] = hi.z; x[7] = hi.w;
+    } else if constexpr (RB == 4) {
+        const v4f lo = *reinterpret_cast<const v4f *>(p);
+        x[0] = lo.x; x[1] = lo.y; x[2] = lo.z; x[3] = lo.w;
+    } else if constexpr (RB == 2) {
+        const v2f lo = *reinterpret_cast<const v2f *>(p);
+        x[0] = lo.x; x[1] = lo.y;
+    } else {
+        x[0] = p[0];
+    }
+}
+
 // Mean over the replicas, in replica order and in fp64, of what they sent for the coordinate of
 // rank c of the tile (recv: [block][rank][RB]): the RB values of a block come with one or two wide
-// LDS reads.
-template <int RB>
+// LDS reads.  ABSENT: the slots of absent replicas may hold anything; else they hold zeros, which add nothing.
+template <int RB, bool ABSENT>
 __device__ __forceinline__ float replica_mean(const StepArgs &a, const float *recv, uint32_t c)
 {
     double sum = 0.;
     for (uint32_t b = 0; b < a.nblocks; ++b) {
-        const uint32_t nrep = a.replicas - b * RB;         // replicas present in this block (>= RB: all)
         const float *p = recv + b * (kTileCoords * RB) + c * RB;
         float x[RB];
-        if (RB == 8) {
-            const v4f lo = *reinterpret_cast<const v4f *>(p), hi = *reinterpret_cast<const v4f *>(p + 4);
-            x[0] = lo.x; x[1 % RB] = lo.y; x[2 % RB] = lo.z; x[3 % RB] = lo.w;
-            x[4 % RB] = hi.x; x[5 % RB] = hi.y; x[6 % RB] = hi.z; x[7 % RB] = hi.w;
-        } else if (RB == 4) {
-            const v4f lo = *reinterpret_cast<const v4f *>(p);
-            x[0] = lo.x; x[1 % RB] = lo.y; x[2 % RB] = lo.z; x[3 % RB] = lo.w;
-        } else if (RB == 2) {
-            const v2f lo = *reinterpret_cast<const v2f *>(p);
-            x[0] = lo.x; x[1 % RB] = lo.y;
-        } else {
-            x[0] = p[0];
-        }
+        load_block_values<RB>(p, x);
         if (a.msg_dtype != 0u) {
 #pragma unroll
             for (int k = 0; k < RB; ++k) x[k] = quantize_message(x[k], a.msg_dtype);
         }
+        const uint32_t nrep = a.replicas - b * RB;         // replicas present in this block (>= RB: all)
 #pragma unroll
         for (int k = 0; k < RB; ++k)
-            if ((uint32_t)k < nrep) sum += (double)x[k];
+            if (!ABSENT || (uint32_t)k < nrep) sum += (double)x[k];
     }
-    return (float)(sum * (1.0 / (double)a.replicas));
+    return (float)(sum * a.inv_replicas);
+}
+
+// The means of the received coordinates of ranks first, first + stride, ... below count, into L.abar.
+template <bool ABSENT>
+__device__ __forceinline__ void tile_means(const StepArgs &a, const TileLds &L, uint32_t first, uint32_t stride, uint32_t count)
+{
+    if (a.rb == 8u) for (uint32_t c = first; c < count; c += stride) L.abar[c] = replica_mean<8, ABSENT>(a, L.recv, c);
+    else if (a.rb == 4u) for (uint32_t c = first; c < count; c += stride) L.abar[c] = replica_mean<4, ABSENT>(a, L.recv, c);
+    else if (a.rb == 2u) for (uint32_t c = first; c < count; c += stride) L.abar[c] = replica_mean<2, ABSENT>(a, L.recv, c);
+    else for (uint32_t c = first; c < count; c += stride) L.abar[c] = replica_mean<1, ABSENT>(a, L.recv, c);
 }
 
 // One workgroup per (tile of 256 coordinates, block of rb <= 8 replicas); its rb waves are the
@@ -632,6 +662,13 @@ __device__ __forceinline__ float replica_mean(const StepArgs &a, const float *re
 // they have to pass anyway.  (Where the masks steer loads of per-replica arrays -- a correction vector in
 // the per-replica layout -- every wave still hashes the received subset itself, so that those loads go out
 // before the barrier.)
+//
+// What the write-back of d costs is halved by halves: only the 64-byte halves of a line that hold a received coordinate are
+// written (interleaved, R = 8, p = 5 %: 9.8 % of them instead of 18.5 % of the lines; per replica 56 % instead of 81 %); with fewer vector instructions
+// in the local step and the mean, stores that go through to memory (store_through) and the residency of
+// am_host::step_workgroups, us a step before / after: R = 8 125.8M interleaved 5940 / 5834 (34.0 GB: 5.8 TB/s), 31.5M per replica 1840 / 1799,
+// R = 4 31.5M 757 / 722, 7.1M 178.5 / 171.7, R = 2 31.5M 373 / 363, R = 1 200 / 193, R = 16 125.8M bf16 9931 / 9845, R = 2 3M SGD with K = 5 24.5 / 23.2,
+// 1M R = 4 32.5 / 31.1 and 500k 17.7 / 17.0 (ordinary non-temporal stores).
 //
 // FULL = every coordinate of the tile exists (all but possibly the last tile of the stage): all
 // dense accesses are unconditional 128-bit ones.
@@ -675,7 +712,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     //      A shared job is done by wave (job mod rb), the others by every wave for itself.
     GroupSubsets s;
     s.mask_send = s.mask_recv = s.rank_send = s.rank_recv = s.d_slot = 0;
-    s.line_recv = false;
+    s.half_recv = false;
     const uint32_t lpl = 8u >> sh;                                         // lanes (groups) per 128-byte line of d
     const uint32_t leader = lane & ~(lpl - 1u);
     // interleaved d: the lines of the tile that hold a received coordinate go straight into LDS, requested
@@ -771,7 +808,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
         if (recv_is_send) { s.rank_recv = s.rank_send; count_recv = count_send; }
         else s.rank_recv = wave_prefix_mask4(s.mask_recv, count_recv);
         const uint64_t any_recv = __ballot(s.mask_recv != 0u);
-        s.line_recv = ((any_recv >> (lane & ~7u)) & 0xFFull) != 0ull;
+        s.half_recv = ((any_recv >> (lane & ~3u)) & 0xFull) != 0ull;
         if (DIL && a.ema) {
             const bool touched = ((any_recv >> leader) & ((1ull << lpl) - 1ull)) != 0ull;
             const uint64_t leaders = __ballot(touched && lane == leader);
@@ -782,7 +819,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
 
     if (!DIL && a.ema) {                                   // loads of per-replica arrays that the masks steer
         const uint64_t any_recv = __ballot(s.mask_recv != 0u);
-        s.line_recv = ((any_recv >> (lane & ~7u)) & 0xFFull) != 0ull;
+        s.half_recv = ((any_recv >> (lane & ~3u)) & 0xFull) != 0ull;
         if (i < R) load_group_sparse<DIL>(a, i, tbase, loff, nvalid, s, in);
     }
 
@@ -815,7 +852,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     }
     // the local optimizer step needs nothing but the wave's own operands: it runs while the lines
     // for LDS and the other waves' operands are still on their way.  The branch (the same for the whole wave)
-    // keeps absent replicas' waves idle and the conversions of the operands behind the hashing: 56 to 58
+    // keeps absent replicas' waves idle and the conversions of the operands behind the hashing: 54
     // registers instead of 66 to 72.  Measured with that, in us a step, before / after: no correction, bf16, R = 16, 125.8M
     // 10107 / 9924, R = 8, 31.5M 1195 / 1162; per-replica d, 31.5M, R = 2 369 / 363; absent replicas: R = 12, 10M, bf16 772 /
     // 751 (per replica), 713 / 692 (interleaved), R = 6 386 / 364; no change beyond noise on the headline step.
@@ -824,8 +861,8 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     lds_dma_wait();
     __syncthreads();
     if (!TAU0 && i < R) {                                  // the moments are final: out they go at once
-        if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_f32x4(rep.m + tbase, loff, nvalid, m_new);
-        if (OPT == kOptAdam) store_f32x4(rep.v + tbase, loff, nvalid, v_new);
+        if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_tile_f32x4(rep.m + tbase, loff, nvalid, m_new, a.through != 0u);
+        if (OPT == kOptAdam) store_tile_f32x4(rep.v + tbase, loff, nvalid, v_new, a.through != 0u);
     }
     if (!TAU0 && sum_lines) find_send();
     if (!recv_is_send) finish_subsets();
@@ -836,9 +873,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     //      drops it, so that the four reads are in flight together)
     float abar[4] = {0.f, 0.f, 0.f, 0.f};
     if (count_recv) {                                      // same for the whole workgroup
-        for (uint32_t c = flat; c < count_recv; c += 64u * rb)
-            L.abar[c] = rb == 8u ? replica_mean<8>(a, L.recv, c) : rb == 4u ? replica_mean<4>(a, L.recv, c)
-                      : rb == 2u ? replica_mean<2>(a, L.recv, c) : replica_mean<1>(a, L.recv, c);
+        tile_means<TAU0>(a, L, flat, 64u * rb, count_recv);
         __syncthreads();
         uint32_t c = s.rank_recv;
 #pragma unroll
@@ -847,6 +882,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
 
     // my chunk of the touched lines of d: float offset inside the tile's part of the array
     const uint32_t d_chunk_off = (DIL && flat < d_lines * 8u) ? L.list[flat >> 3] * kLineFloats + (flat & 7u) * 4u : 0u;
+    const bool d_chunk_changes = DIL && flat < d_lines * 8u && half_received(L.masks + 64u, L.list[flat >> 3], (flat >> 2) & 1u, sh);
 
     // ---- my replica of each block of this workgroup (one block, except when tau = 0 and R > 8)
     for (uint32_t bb = 0; bb < (TAU0 ? a.blocks_per_wg : 1u); ++bb) {
@@ -872,7 +908,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
             float *dst = a.ring_send + b * block_floats + (uint64_t)first_s * kLineFloats + flat * 4u;
             __builtin_nontemporal_store(*reinterpret_cast<const v4f *>(L.send + flat * 4u), reinterpret_cast<v4f *>(dst));
         }
-        if (DIL && flat < d_lines * 8u) {
+        if (d_chunk_changes) {
             float *dst = a.d[b] + (uint64_t)tile * tile_floats + d_chunk_off;
             __builtin_nontemporal_store(*reinterpret_cast<const v4f *>(L.d + flat * 4u), reinterpret_cast<v4f *>(dst));
         }
@@ -940,7 +976,7 @@ __device__ __forceinline__ void step_tile_sync(const StepArgs &a, const uint32_t
     //      interleaved d), and by every wave where it steers the loads of a per-replica d
     GroupSubsets s;
     s.mask_send = s.mask_recv = s.rank_send = s.rank_recv = s.d_slot = 0;
-    s.line_recv = false;
+    s.half_recv = false;
     const uint32_t lpl = 8u >> sh, leader = lane & ~(lpl - 1u);            // lanes (groups) per 128-byte line of an interleaved d
     auto leaders_of = [&](const uint32_t mask) {                           // bit = first lane of a touched line of d
         const uint64_t any = __ballot(mask != 0u);
@@ -964,7 +1000,7 @@ __device__ __forceinline__ void step_tile_sync(const StepArgs &a, const uint32_t
         }
         if (!DIL && a.ema) {
             const uint64_t any = __ballot(mask != 0u);
-            s.line_recv = ((any >> (lane & ~7u)) & 0xFFull) != 0ull;
+            s.half_recv = ((any >> (lane & ~3u)) & 0xFull) != 0ull;
             load_group_sparse<DIL>(a, wave, tbase, loff, nvalid, s, in);
         }
     }
@@ -994,8 +1030,8 @@ __device__ __forceinline__ void step_tile_sync(const StepArgs &a, const uint32_t
     local_step<OPT>(a, rep, wave, in, w_hat, m_new, v_new);
     lds_dma_wait();
     __syncthreads();
-    if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_f32x4(rep.m + tbase, loff, nvalid, m_new);
-    if (OPT == kOptAdam) store_f32x4(rep.v + tbase, loff, nvalid, v_new);
+    if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_tile_f32x4(rep.m + tbase, loff, nvalid, m_new, a.through != 0u);
+    if (OPT == kOptAdam) store_tile_f32x4(rep.v + tbase, loff, nvalid, v_new, a.through != 0u);
 
     if (a.sum_lines) {
         for (uint32_t w = 0; w < R; ++w) first += L.part[w];
@@ -1007,7 +1043,7 @@ __device__ __forceinline__ void step_tile_sync(const StepArgs &a, const uint32_t
     uint32_t count, d_lines = 0;
     s.rank_send = s.rank_recv = wave_prefix_mask4(s.mask_recv, count);
     const uint64_t any = __ballot(s.mask_recv != 0u);
-    s.line_recv = ((any >> (lane & ~7u)) & 0xFFull) != 0ull;
+    s.half_recv = ((any >> (lane & ~3u)) & 0xFull) != 0ull;
     if (DIL && a.ema) {
         const uint64_t leaders = leaders_of(s.mask_recv);
         d_lines = (uint32_t)__popcll(leaders);
@@ -1026,9 +1062,7 @@ __device__ __forceinline__ void step_tile_sync(const StepArgs &a, const uint32_t
                 float *dst = a.ring_send + q * block_floats + (uint64_t)first * kLineFloats + f * 4u;
                 __builtin_nontemporal_store(*reinterpret_cast<const v4f *>(L.recv + q * tile_floats + f * 4u), reinterpret_cast<v4f *>(dst));
             }
-        for (c = flat; c < count; c += threads)
-            L.abar[c] = rb == 8u ? replica_mean<8>(a, L.recv, c) : rb == 4u ? replica_mean<4>(a, L.recv, c)
-                      : rb == 2u ? replica_mean<2>(a, L.recv, c) : replica_mean<1>(a, L.recv, c);
+        tile_means<false>(a, L, flat, threads, count);
         __syncthreads();
         c = s.rank_recv;
 #pragma unroll
@@ -1041,6 +1075,7 @@ __device__ __forceinline__ void step_tile_sync(const StepArgs &a, const uint32_t
         __syncthreads();
         for (uint32_t q = 0; q < a.nblocks; ++q)
             for (uint32_t f = flat; f < d_lines * 8u; f += threads) {
+                if (!half_received(L.masks, L.list[f >> 3], (f >> 2) & 1u, sh)) continue;
                 float *dst = a.d[q] + (uint64_t)tile * tile_floats + L.list[f >> 3] * kLineFloats + (f & 7u) * 4u;
                 __builtin_nontemporal_store(*reinterpret_cast<const v4f *>(L.d + q * tile_floats + f * 4u), reinterpret_cast<v4f *>(dst));
             }
@@ -1106,23 +1141,6 @@ k_step_sync(const StepArgs a)
 // Arithmetic and its order are those of the fused kernel: mean in fp64 in replica order, rounded to
 // fp32; d <- coef_d d + coef_s (w^ - sent) and w = mean + d in fp64, rounded once each.
 // =============================================================================================
-template <int RB>
-__device__ __forceinline__ void load_block_values(const float *p, float (&x)[RB])
-{
-    if constexpr (RB == 8) {
-        const v4f lo = *reinterpret_cast<const v4f *>(p), hi = *reinterpret_cast<const v4f *>(p + 4);
-        x[0] = lo.x; x[1] = lo.y; x[2] = lo.z; x[3] = lo.w; x[4] = hi.x; x[5] = hi.y; x[6] = hi.z; x[7] = hi.w;
-    } else if constexpr (RB == 4) {
-        const v4f lo = *reinterpret_cast<const v4f *>(p);
-        x[0] = lo.x; x[1] = lo.y; x[2] = lo.z; x[3] = lo.w;
-    } else if constexpr (RB == 2) {
-        const v2f lo = *reinterpret_cast<const v2f *>(p);
-        x[0] = lo.x; x[1] = lo.y;
-    } else {
-        x[0] = p[0];
-    }
-}
-
 template <int RB>
 __device__ __forceinline__ void store_block_values(float *p, const float (&x)[RB])
 {
@@ -1285,7 +1303,7 @@ k_average(const StepArgs a)
     const uint64_t any_recv = __ballot(mask_recv != 0u);
     const bool half_recv = ((any_recv >> (lane & ~3u)) & 0xFull) != 0ull;     // my 64 bytes of a per-replica array receive
     const bool need_w = mask_send != 0u || half_recv;
-    const double inv_replicas = 1.0 / (double)R;
+    const double inv_replicas = a.inv_replicas;
 
     F4 w[RB], dv[RB];
     // the weights (and, per-replica layout, the EMA entries) of block b's replicas; an absent replica counts as zeros

@@ -231,7 +231,7 @@ am_status launch_step_tau(am_state *st, const am::StepArgs &a)
         return AM_OK;
     }
     const dim3 grid(st->lay.ntiles, tau0 ? 1u : B.nblocks), block(64u * B.rb);
-    const size_t lds = (size_t)am::step_lds_floats(B.rb, B.nblocks, DIL) * sizeof(float);
+    const uint32_t lds = am_host::lds_for_residency(am::step_lds_floats(B.rb, B.nblocks, DIL) * (uint32_t)sizeof(float), tau0 ? 0u : am_host::step_workgroups(st->cfg, B));
     if (tau0) am::k_step<OPT, GBF, FWD, DIL, true, false><<<grid, block, lds, st->stream>>>(a);
     else if (a.sum_lines) am::k_step<OPT, GBF, FWD, DIL, false, true><<<grid, block, lds, st->stream>>>(a);
     else am::k_step<OPT, GBF, FWD, DIL, false, false><<<grid, block, lds, st->stream>>>(a);
@@ -298,7 +298,7 @@ am_status fill_averaging(am_state *st, uint64_t t, float lambda_t, const Round &
 {
     const am_config &c = st->cfg;
     const am_host::Blocks &B = st->lay.blocks;
-    a.n = c.n; a.ntiles = st->lay.ntiles; a.replicas = c.replicas;
+    a.n = c.n; a.ntiles = st->lay.ntiles; a.replicas = c.replicas; a.inv_replicas = 1.0 / (double)c.replicas;
     a.rb = B.rb; a.rb_shift = B.rb_shift; a.nblocks = B.nblocks;
     a.blocks_per_wg = (r.recv && r.same_slot) ? B.nblocks : 1u;
     a.cap_lines = st->lay.cap_lines > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)st->lay.cap_lines;
@@ -592,6 +592,7 @@ am_status step_impl(am_state *st, uint64_t t, const void *const *grads, float lr
         r.g = ((mask >> i) & 1u) ? grads[i] : nullptr;                      // NULL = idle in this launch
     }
     a.lookahead = c.lookahead != 0; a.gamma = (double)c.gamma;
+    a.through = am_host::beyond_caches(c);
     a.replica_scale = dev_replica_scale;
     const double gs = (double)grad_scale;        // folded into the coefficients that multiply g
 
