@@ -76,8 +76,9 @@ inline uint64_t slot_capacity_lines(uint64_t ntiles, double p, uint32_t rb, bool
     return cap >= (double)all ? all : (uint64_t)cap;
 }
 
-// workspace = [flags 256 B][reduction partials 32 x 1024 doubles][next_lines u32[ntiles]][meta x (slots + 1)][ring values x slots]
-//   meta = tile words u32[ntiles] | sb_base u32[nsb + 1]      (tile words of the extra block: the second table of next_lines; its sb_base is unused)
+// workspace = [flags 256 B][reduction partials 32 x 1024 doubles][sizes of a record u32[ntiles]][meta x (slots + 1)][ring values x slots]
+//   meta = tile words u32[ntiles] | sb_base u32[nsb + 1]      (tile words of the extra block: two tables of the tiles' sizes, a byte each; its
+//   sb_base is unused).  The sizes of a record: words that builds before the byte tables left for a resumed step; only read.
 //   ring slot = nblocks * cap_lines * 32 fp32: [block][line][32], a line = [coordinate][replica in block]
 constexpr uint64_t kReduceBytes = (uint64_t)AM_MAX_REPLICAS * 1024 * 8;
 struct Layout {
@@ -259,9 +260,10 @@ inline Round plan_round(uint64_t K, uint64_t depth, uint64_t tau, uint64_t t)
 }
 
 // What a checkpoint record says about subsets that are already sized, and what a record is taken to say.
-// The record has always named the table at off_next.  Sizes pending in the second table, and records
-// whose reserved field is not zero (some named the table in its bit 0), therefore count as not sized: the step
-// after the resume hashes its subset once more and finds the same sizes.
+// A record names sizes only where every build has looked for them, in the words at off_next, which this one does not write: a
+// record says that nothing is sized (unless it was resumed from one that names words not yet used), and the step after the resume
+// hashes its subset once more and finds the same sizes.  Records whose reserved field is not zero (some named
+// another table in its bit 0) count as not sized, too.
 inline uint64_t record_sized_step(uint64_t next_lines_step, uint32_t next_buf) { return next_buf ? 0 : next_lines_step; }
 inline uint64_t resumed_sized_step(const am_snapshot &s) { return s.reserved ? 0 : s.next_lines_step; }
 

@@ -90,10 +90,12 @@ k_subset_count(SubsetKey key, uint64_t n, uint32_t ntiles, uint32_t mul,
     scan_superblock(cnt, wave_tot, ntiles, local_off, sb_sum + blockIdx.x);
 }
 
-// Same, from tile sizes that are already in memory (the fused step kernel leaves the line counts
-// of the next step's subset there, so that step needs no hashing pass of its own).
+// Same, from tile sizes that are already in memory (the step and averaging kernels leave the line counts of
+// the next step's subset there, a byte a tile, so that step needs no hashing pass of its own; T = uint32_t: the words of a
+// checkpoint record of builds that kept words).
+template <typename T>
 __global__ void __launch_bounds__(256)
-k_subset_offsets(const uint32_t *__restrict__ tile_size, uint32_t ntiles,
+k_subset_offsets(const T *__restrict__ tile_size, uint32_t ntiles,
                  uint32_t *__restrict__ local_off, uint32_t *__restrict__ sb_sum)
 {
     __shared__ uint32_t cnt[kTilesPerSuperblock];
@@ -105,12 +107,21 @@ k_subset_offsets(const uint32_t *__restrict__ tile_size, uint32_t ntiles,
     scan_superblock(cnt, wave_tot, ntiles, local_off, sb_sum + blockIdx.x);
 }
 
+// Sum of the sixteen bytes of x and acc.
+__device__ __forceinline__ uint32_t sum_bytes(const v4u &x, uint32_t acc)
+{
+    acc = __builtin_amdgcn_sad_u8(x.x, 0u, acc);
+    acc = __builtin_amdgcn_sad_u8(x.y, 0u, acc);
+    acc = __builtin_amdgcn_sad_u8(x.z, 0u, acc);
+    return __builtin_amdgcn_sad_u8(x.w, 0u, acc);
+}
+
 // The same with the superblocks' bases, in one launch instead of k_subset_offsets and k_subset_scan (9 to 10 us
-// with the gap between them): every workgroup adds up all tiles before its own.  5.8 us for 54 superblocks,
-// 12 us for 240, so it serves stages of at most kOffsetsAtOnce superblocks (16.8M coordinates).
-constexpr uint32_t kOffsetsAtOnce = 128;
+// with the gap between them): every workgroup adds up the sizes of all tiles before its own.  4.7 us for 123 superblocks, 5.1 for
+// 237, 7.7 for 504 (a word a tile: 12 us for 240), so it serves stages of at most kOffsetsAtOnce superblocks (67M coordinates).
+constexpr uint32_t kOffsetsAtOnce = 512;
 __global__ void __launch_bounds__(1024)
-k_subset_offsets_at_once(const uint32_t *__restrict__ tile_size, uint32_t ntiles, uint32_t nsb, uint32_t capacity,
+k_subset_offsets_at_once(const uint8_t *__restrict__ tile_size, uint32_t ntiles, uint32_t nsb, uint32_t capacity,
                          uint32_t *__restrict__ local_off, uint32_t *__restrict__ sb_base, uint32_t *__restrict__ flags)
 {
     __shared__ uint32_t cnt[kTilesPerSuperblock];
@@ -118,10 +129,7 @@ k_subset_offsets_at_once(const uint32_t *__restrict__ tile_size, uint32_t ntiles
     const uint32_t tile0 = blockIdx.x * kTilesPerSuperblock;
     if (threadIdx.x < kTilesPerSuperblock) cnt[threadIdx.x] = tile0 + threadIdx.x < ntiles ? tile_size[tile0 + threadIdx.x] : 0u;
     uint32_t sum = 0;
-    for (uint32_t q = threadIdx.x; q < tile0 / 4u; q += 1024u) {
-        const v4u x = reinterpret_cast<const v4u *>(tile_size)[q];
-        sum += x.x + x.y + x.z + x.w;
-    }
+    for (uint32_t q = threadIdx.x; q < tile0 / 16u; q += 1024u) sum = sum_bytes(reinterpret_cast<const v4u *>(tile_size)[q], sum);
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) sum += __shfl_xor(sum, off);
     if ((threadIdx.x & 63u) == 0u) before[threadIdx.x >> 6] = sum;
@@ -139,32 +147,47 @@ k_subset_offsets_at_once(const uint32_t *__restrict__ tile_size, uint32_t ntiles
     }
 }
 
-// Lines of the tiles before `tile`, this wave's share: of `waves` waves, wave w adds up words 256 w .. 256 w + 255,
-// then the stretch 256 waves further on, and so on for kSumLoads loads (each in a branch of its own, which the compiler
-// ends with a wait: they follow one another, as many as the tile's place needs).  The shares of all waves add up to all
-// of them when tile <= kSumWords * waves.  lines: padded to whole 256 bytes.
-constexpr uint32_t kSumLoads = 4, kSumWords = 256 * kSumLoads;
-// The fused step adds up its tiles' places itself for at most this many tiles (524,288 coordinates; with one replica the
-// 1024 tiles of its one wave), and no launch precedes it: 500,000 coordinates, R = 4 18.9 us a step against 19.9 with k_subset_offsets_at_once (scaled from
-// 550,000), 262,144, R = 1 7.8 against 9.3; at 1M, R = 4 both take 35.1 us, at 2M, R = 8 it is 94.8 against 93.9.
-// The averaging-only kernel (four waves, and little else to read) does so for as many as four waves can add up
-// (4096 tiles: 1M, R = 4, p = 1 % 11.4 us a call, 17.4 with two offset launches).
-constexpr uint32_t kSumTilesStep = 2048;
-__device__ __forceinline__ uint32_t lines_before(const uint32_t *__restrict__ lines, uint32_t tile, uint32_t wave, uint32_t waves, uint32_t lane)
+// Lines that tile `tile` sends (lines: a byte a tile), as a scalar.
+__device__ __forceinline__ uint32_t lines_of_tile(const uint8_t *lines, uint32_t tile)
 {
-    uint32_t sum = 0;
+    return (uniform_load(reinterpret_cast<const uint32_t *>(lines), tile / 4u) >> (8u * (tile % 4u))) & 0xFFu;
+}
+
+// Lines of the tiles before `tile`, this wave's share: of `waves` waves, wave w adds up the tiles 1024 w .. 1024 w + 1023, sixteen
+// a lane, then the stretch 1024 waves further on, and so on for kSumLoads loads.  The shares of all waves add up to
+// all of them when tile <= kSumTiles * waves.  All loads leave together: what lies past the tile's sixteen reads as zero, because the
+// buffer descriptor ends there; those sixteen are added by the last wave.  lines: padded to whole 128 bytes.
+constexpr uint32_t kSumLoads = 4, kSumTiles = 1024 * kSumLoads;
+__device__ __forceinline__ uint32_t lines_before(const uint8_t *lines, uint32_t tile, uint32_t wave, uint32_t waves, uint32_t lane)
+{
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(lines), 0, tile & ~15u, 0x00020000);
+    v4u x[kSumLoads];
 #pragma unroll
-    for (uint32_t q = 0; q < kSumLoads; ++q) {
-        const uint32_t at = (wave + q * waves) * 256u + lane * 4u;
-        if (at < tile) {
-            const v4u x = *reinterpret_cast<const v4u *>(lines + at);
-            sum += x.x + (at + 1u < tile ? x.y : 0u) + (at + 2u < tile ? x.z : 0u) + (at + 3u < tile ? x.w : 0u);
-        }
+    for (uint32_t q = 0; q < kSumLoads; ++q) x[q] = v4u{0u, 0u, 0u, 0u};
+    x[0] = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(wave * 1024u + lane * 16u), 0, 0);
+    if (tile > 1024u * waves) {
+#pragma unroll
+        for (uint32_t q = 1; q < kSumLoads; ++q)
+            x[q] = __builtin_amdgcn_raw_buffer_load_b128(r, (int)((wave + q * waves) * 1024u + lane * 16u), 0, 0);
     }
+    uint32_t sum = 0;
+    if (wave + 1u == waves && lane < 4u) {               // the tiles of the tile's own sixteen that come before it
+        const uint32_t first = (tile & ~15u) + 4u * lane, count = tile > first ? (tile - first < 4u ? tile - first : 4u) : 0u;
+        if (count) sum = __builtin_amdgcn_sad_u8(reinterpret_cast<const uint32_t *>(lines)[first / 4u] & (0xFFFFFFFFu >> (32u - 8u * count)), 0u, 0u);
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kSumLoads; ++q) sum = sum_bytes(x[q], sum);
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) sum += __shfl_xor(sum, off);
     return sum;
 }
+// The fused step adds up its tiles' places itself for at most this many tiles (2.1M coordinates, and what its waves can add up), and no launch
+// precedes it.  us a step, offsets launched / added up: R = 4 1M per replica 31.0 / 28.9, interleaved 29.0 / 27.9, 2M 53.4 / 52.9; R = 8 2M
+// 97.7 / 98.0, 4M 184.6 / 188.7; with twice the loads 7.1M R = 4 171.7 / 182.4.
+// The averaging-only kernel (four waves, and little else to read) does so for as many as four waves can add up, 16384
+// tiles (4.2M coordinates): R = 8 2M 31.8 / 29.8, 4.1M 53.5 / 51.4, R = 4 p = 2 % 34.6 / 32.3, R = 1 21.8 / 20.0; 1M R = 4 p = 1 %, whose four serial loads of
+// words became one of bytes, 10.9 / 10.4.
+constexpr uint32_t kSumTilesStep = 8192;
 
 // Single workgroup: exclusive scan of the superblock totals, in place (sb[i] <- sum of sb[<i]),
 // grand total to sb[nsb]; raises flag bit 0 when the total exceeds the ring slot capacity.
@@ -337,13 +360,13 @@ struct StepArgs {
                                                    // send slot (from send_lines) and writes the tile's word for the receive
     uint32_t msg_dtype;                            // precision of the exchanged values: 0 fp32, 1 bf16, 2 E4M3
     uint32_t cap_lines;                            // lines (of 32 floats) per block in a ring slot
-    const uint32_t *send_lines;                    // [ntiles] lines each tile sends now (sum_lines)
+    const uint8_t *send_lines;                     // [ntiles] lines each tile sends now (sum_lines)
     uint32_t *send_meta_out, *send_sb_out, *flags; // where its words go (sum_lines)
     const uint32_t *send_meta, *send_sb_base;      // tile's word: lines << 24 | offset in its superblock; first line = sb_base[tile >> 9] + offset
     const uint32_t *recv_meta, *recv_sb_base;
     float *ring_send;                              // slot written now: [block][line][32], a line = [coordinate][rb]
     const float *ring_recv;                        // slot sent tau rounds ago
-    uint32_t *next_lines;                          // [ntiles], written when do_next
+    uint8_t *next_lines;                           // [ntiles], written when do_next (a tile owns at most 64 lines)
     const float *replica_scale;                    // NULL, or one more gradient factor per replica (DEVICE)
     SubsetKey key;                                 // seed, threshold and sampling rule; the step words are filled per job
     uint32_t step_lo[3], step_hi[3];               // the steps whose subsets are hashed: [0] received now, [1] sent now, [2] sent next step
@@ -757,12 +780,12 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
         } else {
             uint32_t count;
             (void)wave_prefix_mask4(mask, count);
-            if (lane == 0) a.next_lines[tile] = (count * rb + kLineFloats - 1u) / kLineFloats;
+            if (lane == 0) a.next_lines[tile] = (uint8_t)((count * rb + kLineFloats - 1u) / kLineFloats);
         }
     }
     // ---- the tile's words in the offset tables of the two slots (scalar loads)
     uint32_t word_s = 0, base_s = 0, word_r = 0, base_r = 0;
-    if (sum_lines) word_s = uniform_load(a.send_lines, tile) << 24;
+    if (sum_lines) word_s = lines_of_tile(a.send_lines, tile) << 24;
     else if (a.do_send) { word_s = uniform_load(a.send_meta, tile); base_s = uniform_load(a.send_sb_base, tile / kTilesPerSuperblock); }
     if (a.do_recv && !TAU0) { word_r = uniform_load(a.recv_meta, tile); base_r = uniform_load(a.recv_sb_base, tile / kTilesPerSuperblock); }
 
@@ -1008,13 +1031,13 @@ __device__ __forceinline__ void step_tile_sync(const StepArgs &a, const uint32_t
         key.step_lo = a.step_lo[2]; key.step_hi = a.step_hi[2];
         uint32_t count;
         (void)wave_prefix_mask4(member_mask(key, group, nvalid), count);
-        if (lane == 0) a.next_lines[tile] = (count * rb + kLineFloats - 1u) / kLineFloats;
+        if (lane == 0) a.next_lines[tile] = (uint8_t)((count * rb + kLineFloats - 1u) / kLineFloats);
     }
 
     // ---- where the tile's lines sit in the slot
     uint32_t first = 0, lines;
     if (a.sum_lines) {
-        lines = uniform_load(a.send_lines, tile);
+        lines = lines_of_tile(a.send_lines, tile);
         const uint32_t share = lines_before(a.send_lines, tile, wave, R, lane);
         if (lane == 0) L.part[wave] = share;
     } else {
@@ -1249,12 +1272,12 @@ k_average(const StepArgs a)
         if (lane == 0) part[wave] = share;
         __syncthreads();
         first_sum = part[0] + part[1] + part[2] + part[3];
-        for (uint32_t w = 0; w < wave; ++w) first_sum += tile < a.ntiles ? uniform_load(a.send_lines, blockIdx.x * 4u + w) : 0u;
+        for (uint32_t w = 0; w < wave; ++w) first_sum += tile < a.ntiles ? lines_of_tile(a.send_lines, blockIdx.x * 4u + w) : 0u;
         first_sum = (uint32_t)__builtin_amdgcn_readfirstlane((int)first_sum);
     }
     if (tile >= a.ntiles) return;
     if (a.sum_lines) {
-        lines_sum = uniform_load(a.send_lines, tile);
+        lines_sum = lines_of_tile(a.send_lines, tile);
         if (b0 == 0u && lane == 0) write_send_word(a, tile, first_sum, lines_sum);
     }
     const uint32_t R = a.replicas;
@@ -1286,7 +1309,7 @@ k_average(const StepArgs a)
         key.step_lo = a.step_lo[2]; key.step_hi = a.step_hi[2];
         uint32_t count;
         (void)wave_prefix_mask4(member_mask(key, group, nvalid), count);
-        if (lane == 0) a.next_lines[tile] = (count * RB + kLineFloats - 1u) / kLineFloats;
+        if (lane == 0) a.next_lines[tile] = (uint8_t)((count * RB + kLineFloats - 1u) / kLineFloats);
     }
 
     // a tile whose lines would pass the slot capacity is left out, at send and at receive alike

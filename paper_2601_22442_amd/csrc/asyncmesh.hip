@@ -123,6 +123,7 @@ struct am_state {
     uint64_t last_t;
     uint64_t next_lines_step;    // the step whose send subset next_lines(next_buf) was sized for (0 = none)
     uint32_t next_buf;           // which of the two size tables that is; a step reads one and fills the other
+    uint64_t record_step;        // the step whose send subset record_lines() was sized for when the state was resumed (0 = none)
     uint32_t delay_now;          // the delay in force (<= cfg.delay, which sizes the ring)
     bool overflow_seen;          // am_read_flags has reported a subset that did not fit its ring slot
     // per replica, because replicas of unequal speed make unequal numbers of local steps:
@@ -139,8 +140,10 @@ struct am_state {
 
     uint32_t *flags() const { return reinterpret_cast<uint32_t *>(ws + lay.off_flags); }
     double *reduce_partials() const { return reinterpret_cast<double *>(ws + lay.off_reduce); }
-    // sizes of the tiles of the next subset to be sent: the table of its own, or the offset block after the ring slots' own
-    uint32_t *next_lines(uint32_t buf) const { return buf ? meta_local(lay.slots) : reinterpret_cast<uint32_t *>(ws + lay.off_next); }
+    // sizes of the tiles of the next subset to be sent, a byte each: two tables in the offset block after the ring slots' own
+    uint8_t *next_lines(uint32_t buf) const { return reinterpret_cast<uint8_t *>(meta_local(lay.slots)) + buf * (lay.meta_sb_off / 2); }
+    // and where the words are that a checkpoint record may name
+    const uint32_t *record_lines() const { return reinterpret_cast<const uint32_t *>(ws + lay.off_next); }
     uint32_t *meta_local(uint32_t slot) const { return reinterpret_cast<uint32_t *>(ws + lay.off_meta + lay.meta_stride * slot); }
     uint32_t *meta_sb(uint32_t slot) const { return reinterpret_cast<uint32_t *>(ws + lay.off_meta + lay.meta_stride * slot + lay.meta_sb_off); }
     float *ring(uint32_t slot) const { return reinterpret_cast<float *>(ws + lay.off_ring + lay.ring_stride * slot); }
@@ -170,13 +173,15 @@ am_status launch_ring_offsets(am_state *st, uint64_t step, uint32_t slot)
     const uint32_t cap = L.cap_lines > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)L.cap_lines;
     if (st->next_lines_step == step && step != 0) {
         // the previous step already sized this subset's tiles
-        const uint32_t *sizes = st->next_lines(st->next_buf);
+        const uint8_t *sizes = st->next_lines(st->next_buf);
         if (L.nsb <= am::kOffsetsAtOnce) {
             am::k_subset_offsets_at_once<<<L.nsb, 1024, 0, st->stream>>>(sizes, L.ntiles, L.nsb, cap, st->meta_local(slot), st->meta_sb(slot), st->flags());
             AM_HIP(hipGetLastError());
             return AM_OK;
         }
-        am::k_subset_offsets<<<L.nsb, 256, 0, st->stream>>>(sizes, L.ntiles, st->meta_local(slot), st->meta_sb(slot));
+        am::k_subset_offsets<uint8_t><<<L.nsb, 256, 0, st->stream>>>(sizes, L.ntiles, st->meta_local(slot), st->meta_sb(slot));
+    } else if (st->record_step == step && step != 0) {
+        am::k_subset_offsets<uint32_t><<<L.nsb, 256, 0, st->stream>>>(st->record_lines(), L.ntiles, st->meta_local(slot), st->meta_sb(slot));
     } else {
         am::k_subset_count<<<L.nsb, 1024, 0, st->stream>>>(make_key(st, step), st->cfg.n, L.ntiles, L.blocks.rb,
                                                            st->meta_local(slot), st->meta_sb(slot));
@@ -426,7 +431,7 @@ am_status create_state(const am_config *cfg, const am_buffers *buf, void *hip_st
     st->has_fwd = buf->fwd != nullptr;
     st->ws = static_cast<char *>(buf->workspace);
     st->last_t = 0;
-    st->next_lines_step = 0;
+    st->next_lines_step = st->record_step = 0;
     st->next_buf = 0;
     st->delay_now = cfg->delay;
     st->overflow_seen = false;
@@ -486,7 +491,7 @@ am_status am_export_state(const am_state *st, am_snapshot *out)
     out->magic = kSnapshotMagic;
     out->config_digest = config_digest(st->cfg);
     out->last_t = st->last_t;
-    out->next_lines_step = am_host::record_sized_step(st->next_lines_step, st->next_buf);
+    out->next_lines_step = am_host::record_sized_step(st->record_step > st->last_t ? st->record_step : 0, 0);
     for (uint32_t i = 0; i < AM_MAX_REPLICAS; ++i) { out->opt_steps[i] = st->opt_steps[i]; out->mu_product[i] = st->mu_product[i]; }
     out->delay_now = st->delay_now;
     out->reserved = 0;
@@ -506,7 +511,7 @@ am_status am_resume_state(const am_config *cfg, const am_buffers *buf, void *hip
     am_state *st = nullptr;
     if (am_status s = create_state(cfg, buf, hip_stream, &st)) return s;
     st->last_t = snapshot->last_t;
-    st->next_lines_step = am_host::resumed_sized_step(*snapshot);
+    st->record_step = am_host::resumed_sized_step(*snapshot);
     for (uint32_t i = 0; i < AM_MAX_REPLICAS; ++i) { st->opt_steps[i] = snapshot->opt_steps[i]; st->mu_product[i] = snapshot->mu_product[i]; }
     st->delay_now = snapshot->delay_now;
     *out = st;
@@ -636,7 +641,7 @@ am_status step_impl(am_state *st, uint64_t t, const void *const *grads, float lr
             if (b * B.rb + k >= c.replicas) a.rep[8u * b + k] = a.rep[8u * b];
 
     const Round r = plan_round(st, t);
-    if (am_status s = fill_averaging(st, t, lambda_t, r, std::min(am::kSumWords * B.rb, am::kSumTilesStep), a)) return s;
+    if (am_status s = fill_averaging(st, t, lambda_t, r, std::min(am::kSumTiles * B.rb, am::kSumTilesStep), a)) return s;
 
     const bool do_next = (t + 1) % c.avg_interval == 0;      // the next step sends: size its tiles on the way
     a.do_next = do_next;
@@ -688,7 +693,7 @@ am_status am_sparse_average(am_state *st, uint64_t t, float lambda_t)
         am::StepArgs a;
         std::memset(&a, 0, sizeof a);
         for (uint32_t i = 0; i < st->cfg.replicas; ++i) a.rep[8u * (i / st->lay.blocks.rb) + i % st->lay.blocks.rb].w = st->w[i];
-        if (am_status s = fill_averaging(st, t, lambda_t, r, am::kSumWords * 4u, a)) return s;
+        if (am_status s = fill_averaging(st, t, lambda_t, r, am::kSumTiles * 4u, a)) return s;
         a.do_next = do_next;
         if (do_next) {
             a.step_lo[2] = (uint32_t)(t + 1); a.step_hi[2] = (uint32_t)((t + 1) >> 32);
