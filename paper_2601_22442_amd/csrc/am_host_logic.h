@@ -194,6 +194,21 @@ inline uint32_t step_workgroups(const am_config &c, const Blocks &b)
     return b.rb == 4u ? 5u : b.rb == 2u ? 12u : b.rb == 1u ? 28u : 0u;
 }
 
+// Whether a step between two averaging rounds (which neither sends nor receives) goes through the kernel of its own.  It pays for blocks of
+// eight waves; the kernel change costs the round's step some microseconds of cold instructions.  us a step on average over rounds, by the
+// fused kernel / by its own: AdamW R = 8 K = 2 15M 575.7 / 571.7, 3M 150.1 / 145.3, 1.5M 81.0 / 78.0, K = 4 500k 25.1 / 24.2, 100,003 8.06 / 8.13; SGD R = 8 1M
+// K = 4 29.4 / 28.9; but AdamW R = 4 K = 4 6M 111.5 / 114.3, SGD R = 4 15M K = 2 203.0 / 205.7, R = 2 15M K = 4 100.2 / 102.7.
+inline bool local_step_alone(const am_config &c, const Blocks &b) { return b.rb == 8u && c.n * c.replicas > 1ull << 20; }
+
+// The workgroups (four tiles of one replica) of that kernel that a compute unit may hold at a time: some 60 KB of requested operands a compute
+// unit.  us a step by their number: AdamW 30M R = 8 as many as fit 1346, 3: 1285, 4: 1215, 5: 1260, 3M R = 8 135.8, 136.3, 126.8, 131.2; SGD with
+// momentum 30M R = 2 199.3, 211.5, 192.2, 190.7.  Plain SGD, which reads two streams: as many as fit.
+inline uint32_t local_step_workgroups(const am_config &c)
+{
+    if (!beyond_caches(c) || (c.optimizer == AM_OPT_SGD && c.beta1 == 0.f)) return 0;
+    return c.optimizer == AM_OPT_SGD ? 5u : 4u;
+}
+
 // Workgroups (of four tiles, a wave each) of the staged averaging-only call that a compute unit may hold at a time; 0: as many as
 // fit.  Where the weights come from memory (more than the 256 MB cache holds) it is fastest with some 114 KB of lines a compute
 // unit on their way; with more the streams get in each other's way, as in the fused step, with fewer latency shows.  So the number

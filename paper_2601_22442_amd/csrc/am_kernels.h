@@ -525,6 +525,31 @@ __device__ __forceinline__ void load_group_sparse(const StepArgs &a, uint32_t i,
     if (!DIL && a.ema && s.half_recv) in.d = load_f32x4(a.d[i] + tbase, loff, nvalid);
 }
 
+// The new weights of one group and their forward copy.
+template <int FWD>
+__device__ __forceinline__ void store_weights(const StepArgs &a, const ReplicaArgs &r, uint64_t tbase, uint32_t loff, int nvalid, const GroupIn &in,
+                                              const F4 &w_hat, const F4 &w_new)
+{
+    store_tile_f32x4(r.w + tbase, loff, nvalid, w_new, a.through != 0u);
+    if (FWD != kFwdNone) {
+        // fwd = w + gamma (w^ - w_before): product and sum rounded separately in fp64, then ONE
+        // rounding to the stored type
+        double f[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            f[j] = a.lookahead ? __dadd_rn((double)w_new.v[j], __dmul_rn(a.gamma, (double)w_hat.v[j] - (double)in.w.v[j]))
+                               : (double)w_new.v[j];
+        if (FWD == kFwdF32) {
+            F4 o;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o.v[j] = (float)f[j];
+            store_tile_f32x4(static_cast<float *>(r.fwd) + tbase, loff, nvalid, o, a.through != 0u);
+        } else {
+            store_bf16x4_from_f64(static_cast<uint16_t *>(r.fwd) + tbase, loff, nvalid, f, a.through != 0u);
+        }
+    }
+}
+
 // Replica i (slot `slot` of its block) of one group, from its stepped weights to stored results: the
 // receive, the new weights and the forward copy.
 // recv_block: what the replicas of i's block sent tau rounds ago, [rank][rb] (TAU0: unused, the sent value is w^ itself).
@@ -569,24 +594,7 @@ __device__ __forceinline__ void finish_replica(const StepArgs &a, const ReplicaA
     }
     if (!DIL && a.ema && s.half_recv) store_tile_f32x4(a.d[i] + tbase, loff, nvalid, in.d, a.through != 0u);
 
-    store_tile_f32x4(r.w + tbase, loff, nvalid, w_new, a.through != 0u);
-    if (FWD != kFwdNone) {
-        // fwd = w + gamma (w^ - w_before): product and sum rounded separately in fp64, then ONE
-        // rounding to the stored type
-        double f[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            f[j] = a.lookahead ? __dadd_rn((double)w_new.v[j], __dmul_rn(a.gamma, (double)w_hat.v[j] - (double)in.w.v[j]))
-                               : (double)w_new.v[j];
-        if (FWD == kFwdF32) {
-            F4 o;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) o.v[j] = (float)f[j];
-            store_tile_f32x4(static_cast<float *>(r.fwd) + tbase, loff, nvalid, o, a.through != 0u);
-        } else {
-            store_bf16x4_from_f64(static_cast<uint16_t *>(r.fwd) + tbase, loff, nvalid, f, a.through != 0u);
-        }
-    }
+    store_weights<FWD>(a, r, tbase, loff, nvalid, in, w_hat, w_new);
 }
 
 // The same from loaded operands: local step (unless the caller has done it while it waited), send, receive.
@@ -946,14 +954,10 @@ __host__ __device__ inline uint32_t step_lds_floats(uint32_t rb, uint32_t nblock
 
 // grid = (tiles, blocks) (tau = 0: (tiles, 1)); blockDim = 64 rb; dynamic LDS = step_lds_floats() floats
 // (at most 80 registers, so that three workgroups of eight waves fit a compute unit)
-template <int OPT, bool GRAD_BF16, int FWD, bool DIL, bool TAU0, bool SUM>
-__global__ void __launch_bounds__(512, 6)
-k_step(const StepArgs a)
+template <bool DIL>
+__device__ __forceinline__ TileLds step_lds(const StepArgs &a)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t tile = blockIdx.x, b0 = TAU0 ? 0u : blockIdx.y;
     const uint32_t tile_floats = kTileCoords * a.rb;
     TileLds L;
     L.recv = lds;
@@ -963,10 +967,69 @@ k_step(const StepArgs a)
     L.masks = reinterpret_cast<uint8_t *>(L.list + 64);
     L.part = L.list + 96;
     L.abar = reinterpret_cast<float *>(L.list + 104);
+    return L;
+}
+
+template <int OPT, bool GRAD_BF16, int FWD, bool DIL, bool TAU0>
+__global__ void __launch_bounds__(512, 6)
+k_step(const StepArgs a)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t tile = blockIdx.x, b0 = TAU0 ? 0u : blockIdx.y;
+    const TileLds L = step_lds<DIL>(a);
     if ((uint64_t)(tile + 1u) * kTileCoords <= a.n)
-        step_tile<OPT, GRAD_BF16, FWD, DIL, TAU0, SUM, true>(a, tile, b0, wave, lane, L);
+        step_tile<OPT, GRAD_BF16, FWD, DIL, TAU0, false, true>(a, tile, b0, wave, lane, L);
     else
-        step_tile<OPT, GRAD_BF16, FWD, DIL, TAU0, SUM, false>(a, tile, b0, wave, lane, L);
+        step_tile<OPT, GRAD_BF16, FWD, DIL, TAU0, false, false>(a, tile, b0, wave, lane, L);
+}
+
+// The same for small stages, which add up their tiles' places themselves (a delay).  Few tiles, whose chains of waits are the time: with at
+// most 80 scalar registers eight waves a SIMD are resident, not seven.  us a step, without / with that: R = 4 500k 16.5 / 15.2, 1M 29.0 / 28.6,
+// R = 8 2M 99.8 / 99.3.
+template <int OPT, bool GRAD_BF16, int FWD, bool DIL>
+__global__ void __launch_bounds__(512, 6) __attribute__((amdgpu_num_sgpr(80)))
+k_step_small(const StepArgs a)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t tile = blockIdx.x, b0 = blockIdx.y;
+    const TileLds L = step_lds<DIL>(a);
+    if ((uint64_t)(tile + 1u) * kTileCoords <= a.n)
+        step_tile<OPT, GRAD_BF16, FWD, DIL, false, true, true>(a, tile, b0, wave, lane, L);
+    else
+        step_tile<OPT, GRAD_BF16, FWD, DIL, false, true, false>(a, tile, b0, wave, lane, L);
+}
+
+// A step that neither sends nor receives (between two averaging rounds, interval > 1; am_host::local_step_alone): the local step alone,
+// a wave per tile of one replica, replica after replica, so that few streams are on their way at a time, without LDS and barriers.  us a
+// step, by k_step / by this: AdamW with look-ahead, R = 8 30M 1324 / 1215 (6.3 TB/s), 3M 136.2 / 126.8.
+// grid = (ceil(tiles / 4), replicas); blockDim = 256
+template <int OPT, bool GRAD_BF16, int FWD>
+__global__ void __launch_bounds__(256)
+k_step_local(const StepArgs a)
+{
+    const uint32_t lane = threadIdx.x & 63u, loff = lane * 4u;
+    const uint32_t tile = blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), i = blockIdx.y;
+    if (tile >= a.ntiles) return;
+    const uint64_t tbase = (uint64_t)tile * kTileCoords, mu = tbase + loff;
+    const int nvalid = tbase + kTileCoords <= a.n ? 4 : (mu >= a.n ? 0 : (a.n - mu >= 4u ? 4 : (int)(a.n - mu)));
+    const ReplicaArgs rep = a.rep[8u * (i >> a.rb_shift) + (i & (a.rb - 1u))];
+    GroupIn in;
+    load_group<OPT, GRAD_BF16>(rep, tbase, loff, nvalid, in);
+    __builtin_amdgcn_sched_barrier(0);
+    if (a.do_next && i == 0u) {                              // how many lines the tile sends next step
+        SubsetKey key = a.key;
+        key.step_lo = a.step_lo[2]; key.step_hi = a.step_hi[2];
+        uint32_t count;
+        (void)wave_prefix_mask4(member_mask(key, (uint64_t)tile * 64u + lane, nvalid), count);
+        if (lane == 0) a.next_lines[tile] = (uint8_t)((count * a.rb + kLineFloats - 1u) / kLineFloats);
+    }
+    F4 w_hat, m_new, v_new;
+    local_step<OPT>(a, rep, i, in, w_hat, m_new, v_new);
+    if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_tile_f32x4(rep.m + tbase, loff, nvalid, m_new, a.through != 0u);
+    if (OPT == kOptAdam) store_tile_f32x4(rep.v + tbase, loff, nvalid, v_new, a.through != 0u);
+    store_weights<FWD>(a, rep, tbase, loff, nvalid, in, w_hat, w_hat);
 }
 
 // tau = 0 with at most kSyncWaves replicas: the average is of this step's values, so a tile needs all its

@@ -237,9 +237,9 @@ am_status launch_step_tau(am_state *st, const am::StepArgs &a)
     }
     const dim3 grid(st->lay.ntiles, tau0 ? 1u : B.nblocks), block(64u * B.rb);
     const uint32_t lds = am_host::lds_for_residency(am::step_lds_floats(B.rb, B.nblocks, DIL) * (uint32_t)sizeof(float), tau0 ? 0u : am_host::step_workgroups(st->cfg, B));
-    if (tau0) am::k_step<OPT, GBF, FWD, DIL, true, false><<<grid, block, lds, st->stream>>>(a);
-    else if (a.sum_lines) am::k_step<OPT, GBF, FWD, DIL, false, true><<<grid, block, lds, st->stream>>>(a);
-    else am::k_step<OPT, GBF, FWD, DIL, false, false><<<grid, block, lds, st->stream>>>(a);
+    if (tau0) am::k_step<OPT, GBF, FWD, DIL, true><<<grid, block, lds, st->stream>>>(a);
+    else if (a.sum_lines) am::k_step_small<OPT, GBF, FWD, DIL><<<grid, block, lds, st->stream>>>(a);
+    else am::k_step<OPT, GBF, FWD, DIL, false><<<grid, block, lds, st->stream>>>(a);
     AM_HIP(hipGetLastError());
     return AM_OK;
 }
@@ -247,6 +247,12 @@ am_status launch_step_tau(am_state *st, const am::StepArgs &a)
 template <int OPT, bool GBF, int FWD>
 am_status launch_step_layout(am_state *st, const am::StepArgs &a)
 {
+    if (!a.do_send && am_host::local_step_alone(st->cfg, st->lay.blocks)) {
+        const uint32_t lds = am_host::lds_for_residency(0u, am_host::local_step_workgroups(st->cfg));
+        am::k_step_local<OPT, GBF, FWD><<<dim3((st->lay.ntiles + 3u) / 4u, a.replicas), 256, lds, st->stream>>>(a);
+        AM_HIP(hipGetLastError());
+        return AM_OK;
+    }
     if (st->cfg.d_layout == AM_D_INTERLEAVED && a.ema) return launch_step_tau<OPT, GBF, FWD, true>(st, a);
     return launch_step_tau<OPT, GBF, FWD, false>(st, a);
 }
