@@ -378,6 +378,8 @@ struct StepArgs {
     //   w^ = w - (c_wd w + c_m m')     resp.     w - (c_wd w + c_g g)          (SGD with / without momentum)
     double a_m, b_m, a_v, b_v, c_wd, eps;
     double gamma, inv_replicas;
+    float *w[kMaxReplicas];          // averaging alone: every replica's weights; a block's pointers share one line of the kernel's arguments (in the
+                                     // records they are eight lines, cold at every launch: 500k R = 8 11.4 / 10.4 us a call, 1M R = 4 10.6 / 10.5)
     float *d[kMaxReplicas];          // one array per replica, or (interleaved) one per block: [tiles * 256][rb]
     ReplicaArgs rep[kMaxReplicas];
 };
@@ -1400,7 +1402,7 @@ k_average(const StepArgs a)
             if (with_w) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) w[k].v[j] = 0.f;
-                if (i < R && need_w) w[k] = load_f32x4(a.rep[8u * b + k].w + tbase, loff, nvalid);
+                if (i < R && need_w) w[k] = load_f32x4(a.w[i] + tbase, loff, nvalid);
             }
             if (with_d) {
 #pragma unroll
@@ -1416,7 +1418,7 @@ k_average(const StepArgs a)
         for (int k = 0; k < RB; ++k) {
             const uint32_t i = b * RB + k;
             if (i >= R) continue;
-            store_f32x4(a.rep[8u * b + k].w + tbase, loff, nvalid, w[k]);
+            store_f32x4(a.w[i] + tbase, loff, nvalid, w[k]);
             if (!DIL && a.ema) store_f32x4(a.d[i] + tbase, loff, nvalid, dv[k]);
         }
     };

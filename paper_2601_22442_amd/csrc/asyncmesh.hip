@@ -698,7 +698,7 @@ am_status am_sparse_average(am_state *st, uint64_t t, float lambda_t)
     if (r.send) {
         am::StepArgs a;
         std::memset(&a, 0, sizeof a);
-        for (uint32_t i = 0; i < st->cfg.replicas; ++i) a.rep[8u * (i / st->lay.blocks.rb) + i % st->lay.blocks.rb].w = st->w[i];
+        for (uint32_t i = 0; i < st->cfg.replicas; ++i) a.w[i] = st->w[i];
         if (am_status s = fill_averaging(st, t, lambda_t, r, am::kSumTiles * 4u, a)) return s;
         a.do_next = do_next;
         if (do_next) {
