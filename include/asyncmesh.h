@@ -282,7 +282,7 @@ typedef struct {
     uint64_t magic;             /* layout version of this record                                */
     uint64_t config_digest;
     uint64_t last_t;            /* the last step made                                           */
-    uint64_t next_lines_step;   /* the step whose send subset is already sized in the workspace's first size table; 0: none */
+    uint64_t next_lines_step;   /* the step whose send subset an earlier build left sized, as words, in the workspace; 0: none */
     uint32_t delay_now;         /* the delay in force (am_set_delay)                            */
     uint32_t reserved;          /* written as 0; any other value: nothing counts as sized */
     uint64_t opt_steps[AM_MAX_REPLICAS];   /* optimizer steps each replica has made             */
