@@ -184,15 +184,40 @@ inline bool average_staged(const am_config &c, uint32_t ntiles, const Blocks &b,
 // R = 4 7.1M 171.7 / 174.5, R = 2 30M SGD 287.7 / 295.4, 3M SGD 23.2 / 23.9; R = 4 1M 31.7 / 31.4, 500k 17.8 / 17.0.
 inline bool beyond_caches(const am_config &c) { return c.n * c.replicas > 5ull << 20; }
 
-// Workgroups (a wave per replica of a block) of the fused step that a compute unit may hold at a time; 0: as many as fit (three of
-// eight waves).  The stream mix moves fastest with few requests on their way (without arithmetic, 125.8M x 8: 16 waves a compute unit 6.05 to 6.3
-// TB/s, 24 5.5 to 6.1); fewer waves than these leave the step's chain of waits visible.  us a step, as many as fit / these / the next
-// fewer: R = 4 31.5M 742 / 717 / 714, per replica 839 / 808 / 799, without forward copy 648 / 639 / 651, 7.1M 177 / 172 / 174; R = 2 31.5M 360 / 352
-// / 358; R = 1 191 / 190 / 195.  Eight replicas: 1480 / 1504 with two.
-inline uint32_t step_workgroups(const am_config &c, const Blocks &b)
+// Kilobytes that a step reads and writes of one replica's part of a tile: weights, gradient, moments, forward copy and, where it receives, the EMA
+// entries (whole lines are read, halves written) and the ring.
+inline double step_kilobytes(const am_config &c, const Blocks &b, bool forward_copy, bool receives)
+{
+    const double moments = c.optimizer != AM_OPT_SGD ? 2.0 : c.beta1 != 0.f ? 1.0 : 0.0;
+    double kb = 2.0 + (c.grad_dtype == AM_BF16 ? 0.5 : 1.0) + 2.0 * moments + (forward_copy ? (c.fwd_dtype == AM_BF16 ? 0.5 : 1.0) : 0.0);
+    if (!receives) return kb;
+    kb += 2.0 * c.fraction;
+    if (c.correction != AM_CORR_NONE) {
+        const double line = c.d_layout == AM_D_INTERLEAVED ? (double)am::kLineFloats / b.rb : am::kLineFloats;      // coordinates of one
+        kb += 2.0 - std::pow(1.0 - c.fraction, line) - std::pow(1.0 - c.fraction, line / 2.0);
+    }
+    return kb;
+}
+
+// Workgroups (a wave per replica of a block) of the fused step that a compute unit may hold at a time; 0: as many as fit.  The stream mix moves
+// fastest with few requests on their way (without arithmetic, 125.8M x 8: 16 waves a compute unit 6.05 to 6.3 TB/s, 24 5.5 to 6.1); fewer leave the
+// step's chain of waits visible, and a wave that moves less has less on its way.  So the limit follows what the step moves, and is there only for
+// whole blocks of two and four replicas.  Time with the limit / without, same arrays, 16M, 28M, 64M and 160M parameters x replicas, p = 5 %:
+//   R = 4, 5: per replica, AdamW with forward copy (9.5 KB) 0.96 0.96 0.98 1.02, without (8.5) 0.98 0.96 0.98 0.97, bf16 gradient (8.0) 0.98 0.97 0.98 0.98, SGD with
+//     momentum (6.5) 16M 0.98, 31M 0.98, 80M 0.98, without (4.5) 1.15, 1.18; interleaved, AdamW with forward copy (8.6) 0.99 0.99 1.00 1.02, without (7.6) 1.02 1.01
+//     1.02 0.99, there 6: 1.01 1.01 1.00 0.99, bf16 gradient (7.1) 6: 1.02 1.02 1.01 0.99, SGD 5: 1.03 to 1.17; no correction (8.1) 6: 0.99 0.99 0.99 1.00.
+//   R = 2, 11: per replica with forward copy 0.96 0.96 0.95 0.99, without 0.95 0.96 0.97 0.97, bf16 gradient 0.96 0.98 0.99 0.97; interleaved with forward copy 0.98
+//     0.99 1.00 0.97, without 1.02 1.02 1.05 0.98, bf16 gradient 1.00 1.02 1.03 0.97; no correction with 0.97 0.98 0.97 0.99, without 1.00 1.01 1.01 1.00.
+//   R = 3, 5: AdamW 16M 1.02 to 1.08, SGD 1.21; 6: 1.00 to 1.03, 1.09.  R = 1, 25 (one wave each): AdamW 0.97 to 1.03, SGD 1.05.  R = 8, 2: 1.02 to 1.15.
+// (Small stages that add up their offsets themselves take no limit: R = 4 6M, 5: AdamW 1.00 to 1.03, SGD 1.10 to 1.22.)
+inline uint32_t step_workgroups(const am_config &c, const Blocks &b, bool forward_copy, bool receives)
 {
     if (!beyond_caches(c)) return 0;
-    return b.rb == 4u ? 5u : b.rb == 2u ? 12u : b.rb == 1u ? 28u : 0u;
+    const double kb = step_kilobytes(c, b, forward_copy, receives);
+    const bool dense_d = receives && c.correction != AM_CORR_NONE && c.d_layout != AM_D_INTERLEAVED;
+    if (c.replicas == 4u) return kb >= (dense_d ? 6.4 : 8.2) ? 5u : kb >= 7.2 ? 6u : 0u;
+    if (c.replicas == 2u) return (dense_d ? kb >= 7.4 : forward_copy && c.grad_dtype != AM_BF16 && kb >= 8.0) ? 11u : 0u;
+    return 0;
 }
 
 // Whether a step between two averaging rounds (which neither sends nor receives) goes through the kernel of its own.  It pays for blocks of
@@ -228,15 +253,22 @@ inline uint32_t average_workgroups(const am_config &c, const Blocks &b, bool int
     return workgroups >= 7.0 ? 0u : std::max(2u, (uint32_t)workgroups);
 }
 
-// Dynamic LDS of a workgroup that needs `need` bytes, with which a compute unit holds at most `workgroups` of them (0: no limit).
-constexpr uint32_t lds_for_residency(uint32_t need, uint32_t workgroups)
+// Dynamic LDS of a workgroup that needs `need` bytes besides `fixed` bytes of static LDS, with which a compute unit holds at most `workgroups` of them (0: no limit):
+// the smallest allocation of which one more does not fit.
+constexpr uint32_t kLdsGranules = am::kLdsBytes / am::kLdsGranule;
+constexpr uint32_t lds_for_residency(uint32_t need, uint32_t workgroups, uint32_t fixed = 0)
 {
     if (workgroups == 0u) return need;
-    const uint32_t share = am::kLdsBytes / workgroups / am::kLdsGranule * am::kLdsGranule - am::kLdsGranule;
+    const uint32_t share = (kLdsGranules / (workgroups + 1u) + 1u) * am::kLdsGranule - fixed;
     return need > share ? need : share;
 }
-static_assert(lds_for_residency(1, 2) * 3 > am::kLdsBytes && lds_for_residency(1, 3) * 4 > am::kLdsBytes && lds_for_residency(1, 4) * 5 > am::kLdsBytes
-              && lds_for_residency(1, 5) * 6 > am::kLdsBytes && lds_for_residency(1, 6) * 7 > am::kLdsBytes, "one workgroup more does not fit");
+constexpr bool residency_is_exact(uint32_t workgroups)
+{
+    const uint32_t granules = (lds_for_residency(1, workgroups) + am::kLdsGranule - 1u) / am::kLdsGranule;
+    return workgroups * granules <= kLdsGranules && (workgroups + 1u) * granules > kLdsGranules;
+}
+static_assert(residency_is_exact(2) && residency_is_exact(3) && residency_is_exact(4) && residency_is_exact(5) && residency_is_exact(6) && residency_is_exact(11),
+              "as many as a rule names fit, and not one more");
 
 // Floats of one array of the EMA vectors and how many arrays there are, per layout.
 inline void d_layout_shape(const am_config &c, uint32_t *rb, uint32_t *arrays, uint64_t *floats)

@@ -236,7 +236,8 @@ am_status launch_step_tau(am_state *st, const am::StepArgs &a)
         return AM_OK;
     }
     const dim3 grid(st->lay.ntiles, tau0 ? 1u : B.nblocks), block(64u * B.rb);
-    const uint32_t lds = am_host::lds_for_residency(am::step_lds_floats(B.rb, B.nblocks, DIL) * (uint32_t)sizeof(float), tau0 ? 0u : am_host::step_workgroups(st->cfg, B));
+    const uint32_t workgroups = tau0 || a.sum_lines ? 0u : am_host::step_workgroups(st->cfg, B, st->has_fwd, a.do_recv != 0u);
+    const uint32_t lds = am_host::lds_for_residency(am::step_lds_floats(B.rb, B.nblocks, DIL) * (uint32_t)sizeof(float), workgroups);
     if (tau0) am::k_step<OPT, GBF, FWD, DIL, true><<<grid, block, lds, st->stream>>>(a);
     else if (a.sum_lines) am::k_step_small<OPT, GBF, FWD, DIL><<<grid, block, lds, st->stream>>>(a);
     else am::k_step<OPT, GBF, FWD, DIL, false><<<grid, block, lds, st->stream>>>(a);
@@ -278,7 +279,8 @@ am_status launch_average_kernel(am_state *st, const am::StepArgs &a)
 {
     const uint32_t nblocks = st->lay.blocks.nblocks;
     const dim3 grid((st->lay.ntiles + 3u) / 4u, TAU0 ? 1u : nblocks), block(256);
-    const uint32_t lds = STAGED ? am_host::lds_for_residency(4u * am::average_wave_bytes<DIL, RB>(nblocks), am_host::average_workgroups(st->cfg, st->lay.blocks, DIL)) : 0u;
+    constexpr uint32_t kStatic = 16u;                        // four waves' shares of the lines before the tile
+    const uint32_t lds = STAGED ? am_host::lds_for_residency(4u * am::average_wave_bytes<DIL, RB>(nblocks), am_host::average_workgroups(st->cfg, st->lay.blocks, DIL), kStatic) : 0u;
     am::k_average<DIL, RB, TAU0, STAGED><<<grid, block, lds, st->stream>>>(a);
     AM_HIP(hipGetLastError());
     return AM_OK;

@@ -202,3 +202,26 @@ def test_a_record_names_sizes_that_every_build_finds(hl):
 def test_averaging_stages_where_that_is_the_faster_form(hl, n, R, kw, staged):
     kw = dict(dict(d_layout=1), **kw)
     assert bool(hl.hl_average_staged(C.byref(_config(n=n, replicas=R, delay=1, **kw)), kw["d_layout"])) == staged
+
+
+@pytest.mark.parametrize("n,R,kw,fwd,receives,workgroups", [
+    # by what the step moves of a replica's part of a tile, more easily with a dense d
+    (16_000_000, 4, dict(d_layout=0), True, True, 5), (16_000_000, 4, dict(d_layout=0), False, True, 5), (16_000_000, 4, dict(d_layout=1), False, True, 6),
+    (16_000_000, 4, dict(d_layout=1, grad_dtype=1), False, True, 0), (16_000_000, 4, dict(d_layout=0, grad_dtype=1), False, True, 5), (16_000_000, 4, dict(d_layout=0), False, False, 0),
+    (16_000_000, 4, dict(optimizer=0), False, True, 5), (16_000_000, 4, dict(optimizer=0, d_layout=1), True, True, 0), (16_000_000, 4, dict(correction=0), True, True, 6), (16_000_000, 4, dict(optimizer=0, beta1=0.0), True, True, 0),
+    (30_000_000, 2, dict(d_layout=0), True, True, 11), (30_000_000, 2, dict(correction=0), True, True, 11), (30_000_000, 2, dict(correction=0), False, True, 0),
+    (30_000_000, 2, dict(d_layout=1), False, True, 0), (30_000_000, 2, dict(d_layout=1, grad_dtype=1), True, True, 0), (30_000_000, 2, dict(d_layout=0, grad_dtype=1), False, True, 11), (3_000_017, 2, dict(optimizer=0, fraction=0.1), False, True, 0),
+    # absent replicas, one replica, eight; a stage that the caches hold
+    (20_000_000, 3, dict(d_layout=0), True, True, 0), (60_000_000, 1, dict(d_layout=0), True, True, 0), (20_000_000, 8, dict(d_layout=0), True, True, 0), (1_300_000, 4, dict(d_layout=0), True, True, 0),
+])
+def test_step_residency_follows_what_a_wave_moves(hl, n, R, kw, fwd, receives, workgroups):
+    assert hl.hl_step_workgroups(C.byref(_config(n=n, replicas=R, delay=1, **kw)), fwd, receives) == workgroups
+
+
+@pytest.mark.parametrize("workgroups", [2, 3, 4, 5, 6, 11])
+@pytest.mark.parametrize("fixed", [0, 16])
+def test_lds_holds_as_many_workgroups_as_a_rule_names(hl, workgroups, fixed):
+    """160 KB of LDS in granules of 1280 bytes: that many fit, one more does not; a larger need is kept, and 0 limits nothing."""
+    granules = -(-(hl.hl_lds_for_residency(100, workgroups, fixed) + fixed) // 1280)
+    assert workgroups * granules <= 128 < (workgroups + 1) * granules
+    assert hl.hl_lds_for_residency(70_000, workgroups, fixed) >= 70_000 and hl.hl_lds_for_residency(100, 0, fixed) == 100
