@@ -181,13 +181,10 @@ __device__ __forceinline__ uint32_t lines_before(const uint8_t *lines, uint32_t 
     for (int off = 1; off < 64; off <<= 1) sum += __shfl_xor(sum, off);
     return sum;
 }
-// The fused step adds up its tiles' places itself for at most this many tiles (2.1M coordinates, and what its waves can add up), and no launch
-// precedes it.  us a step, offsets launched / added up: R = 4 1M per replica 31.0 / 28.9, interleaved 29.0 / 27.9, 2M 53.4 / 52.9; R = 8 2M
-// 97.7 / 98.0, 4M 184.6 / 188.7; with twice the loads 7.1M R = 4 171.7 / 182.4.
+// The fused step adds up its tiles' places itself on the stages that am_host::step_sum_tiles names, and no launch precedes it.
 // The averaging-only kernel (four waves, and little else to read) does so for as many as four waves can add up, 16384
 // tiles (4.2M coordinates): R = 8 2M 31.8 / 29.8, 4.1M 53.5 / 51.4, R = 4 p = 2 % 34.6 / 32.3, R = 1 21.8 / 20.0; 1M R = 4 p = 1 %, whose four serial loads of
 // words became one of bytes, 10.9 / 10.4.
-constexpr uint32_t kSumTilesStep = 8192;
 
 // Single workgroup: exclusive scan of the superblock totals, in place (sb[i] <- sum of sb[<i]),
 // grand total to sb[nsb]; raises flag bit 0 when the total exceeds the ring slot capacity.

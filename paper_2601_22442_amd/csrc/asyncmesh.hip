@@ -649,7 +649,8 @@ am_status step_impl(am_state *st, uint64_t t, const void *const *grads, float lr
             if (b * B.rb + k >= c.replicas) a.rep[8u * b + k] = a.rep[8u * b];
 
     const Round r = plan_round(st, t);
-    if (am_status s = fill_averaging(st, t, lambda_t, r, std::min(am::kSumTiles * B.rb, am::kSumTilesStep), a)) return s;
+    const uint32_t sum_tiles = std::min(am::kSumTiles * B.rb, am_host::step_sum_tiles(c, B, r.recv && r.same_slot));
+    if (am_status s = fill_averaging(st, t, lambda_t, r, sum_tiles, a)) return s;
 
     const bool do_next = (t + 1) % c.avg_interval == 0;      // the next step sends: size its tiles on the way
     a.do_next = do_next;

@@ -55,6 +55,8 @@ uint32_t hl_step_workgroups(const am_config *c, int forward_copy, int receives)
     return am_host::step_workgroups(*c, am_host::block_geometry(c->replicas), forward_copy != 0, receives != 0);
 }
 
+uint32_t hl_step_sum_tiles(const am_config *c, int sync) { return am_host::step_sum_tiles(*c, am_host::block_geometry(c->replicas), sync != 0); }
+
 uint32_t hl_lds_for_residency(uint32_t need, uint32_t workgroups, uint32_t fixed) { return am_host::lds_for_residency(need, workgroups, fixed); }
 
 uint64_t hl_record_sized_step(uint64_t next_lines_step, uint32_t next_buf) { return am_host::record_sized_step(next_lines_step, next_buf); }

@@ -26,6 +26,11 @@ def test_steps_around_the_limit(amlib, tiles, R):
     run_steps(amlib, tiles * T - 100, R, 4, delay=1, fraction=0.02, seed=3, optimizer=O.OPT_SGD, beta1=0.0, check_every=4)
 
 
+@pytest.mark.parametrize("tiles,R,tau", [(6144, 4, 1), (6145, 3, 1), (2048, 20, 1), (2049, 17, 1), (768, 32, 1), (769, 25, 1), (1024, 12, 0), (1025, 9, 0)])
+def test_steps_around_the_limits_by_blocks(amlib, tiles, R, tau):
+    run_steps(amlib, tiles * T - 100, R, 4, delay=tau, fraction=0.05, seed=3, optimizer=O.OPT_SGD, beta1=0.0, check_every=4, d_layout=amlib.D_INTERLEAVED)
+
+
 @pytest.mark.parametrize("tiles", [15, 17, 4097, 16383, 16384, 16385])
 @pytest.mark.parametrize("tau", [0, 1])
 def test_averages_around_the_loads(amlib, tiles, tau):

@@ -225,3 +225,9 @@ def test_lds_holds_as_many_workgroups_as_a_rule_names(hl, workgroups, fixed):
     granules = -(-(hl.hl_lds_for_residency(100, workgroups, fixed) + fixed) // 1280)
     assert workgroups * granules <= 128 < (workgroups + 1) * granules
     assert hl.hl_lds_for_residency(70_000, workgroups, fixed) >= 70_000 and hl.hl_lds_for_residency(100, 0, fixed) == 100
+
+
+def test_steps_add_up_offsets_on_fewer_tiles_with_more_blocks(hl):
+    tiles = {(R, sync): hl.hl_step_sum_tiles(C.byref(_config(replicas=R, delay=0 if sync else 1)), sync) for R in range(1, 33) for sync in (0, 1)}
+    assert all(tiles[R, 0] == (8192 if R <= 2 else 6144 if R <= 4 else 8192 if R <= 16 else 2048 if R <= 24 else 768) for R in range(1, 33))
+    assert all(tiles[R, 1] == (1024 if 9 <= R <= 16 else 8192) for R in range(1, 33))
