@@ -111,11 +111,15 @@ inline Layout make_layout(const am_config &c)
     return L;
 }
 
-// How a subset's index list is cut: a part = one workgroup of four waves with `strips` strips each.  The kernel's registers
-// keep 20 waves a compute unit resident.  Up to eight strips a wave one round of them is the fastest cut (20 / 40 waves a compute unit,
+// How a subset's index list is cut: a part = one workgroup of four waves with `strips` strips each; waves: of a compute unit, of which the
+// kernel's registers keep 20 resident.  Coordinates drawn one by one and written lane by lane: 20 waves, one round, up to eight strips a wave (20 / 40 waves,
 // p = 5 %: 16M 14.2 / 17.1 us, 31.5M, p = 10 % 24.5 / 25.3, 60M 35.3 / 35.6); beyond, two rounds let the second's hashing run beside the
-// first's stores (125.8M 62.7 / 60.5).  A part waits only for earlier ones.  At most 32 strips (a kilobyte of masks in LDS each),
-// from where on the parts grow in number.
+// first's stores (125.8M 62.7 / 60.5).  Whole lines and stratified subsets (the general form of the generator) and strips written row by row have more
+// to hide behind each other: 32 waves, but 20 where at most two strips a wave are left to cut (not the smallest stratified subsets).  us, 20 / 32 waves: whole
+// lines, p = 5 % 12M 17.7 / 20.3, 16M 21.1 / 22.4, 32M 33.5 / 32.8, 48M 45.7 / 42.7, 63M 57.3 / 52.2; stratified, p = 1 % 14M 24.8 / 23.8, 5 % 16M 25.9 / 26.6, 32M 44.9 / 43.0, 63M 85.9 / 76.5, 100M 119 / 109;
+// row by row, whole lines, p = 25 % 12M 19.5 / 17.7, 24M 26.7 / 25.0, p = 100 % 24M 40.1 / 38.5, 48M 89.0 / 83.8, one by one, p = 25 % 32M 37.2 / 36.8, 60M 61.3 / 61.3, p = 100 % 24M
+// 42.0 / 37.9, 60M 105 / 98.2.  A part waits only for earlier ones.  At most 32 strips (a kilobyte of masks in LDS each), from where on the
+// parts grow in number.
 // rows: a strip is written row by row.  Lane by lane / row by row, us: 130M 15 % 106 / 143, 20 % 132 / 144, 25 % 167 / 147,
 // 50 % 313 / 155, 100 % 589 / 219; 17M 20 % 28.6 / 30.4, 25 % 33.6 / 31.0; 4M 20 % 13.9 / 13.8, 100 % 70 / 15.5; up to 2M,
 // where little is written, 1M 30 % 11.2 / 11.8, 50 % 13.0 / 11.9, 100,003 40 % 9.4 / 9.8, 50 % 9.9 / 9.8.
@@ -124,14 +128,17 @@ struct ListShape {
     bool rows;
 };
 
-inline ListShape list_shape(uint64_t n, double fraction, uint32_t compute_units)
+inline ListShape list_shape(const am_config &c, uint32_t compute_units)
 {
     ListShape s;
-    s.nstrips = (uint32_t)((n + am::kStripCoords - 1) / am::kStripCoords);
-    const uint32_t resident = 20u * std::max(compute_units, 1u), waves = s.nstrips > 8u * resident ? 2u * resident : resident;
+    s.nstrips = (uint32_t)((c.n + am::kStripCoords - 1) / am::kStripCoords);
+    s.rows = c.fraction >= (s.nstrips <= 1024u ? 0.45 : 0.22);
+    const uint32_t cus = std::max(compute_units, 1u), resident = 20u * cus;
+    const bool one_by_one = c.subset_kind != AM_SUBSET_STRATIFIED && c.subset_granule != 32;
+    const uint32_t waves = one_by_one && !s.rows ? (s.nstrips > 8u * resident ? 2u * resident : resident)
+                         : !s.rows && s.nstrips <= 2u * resident && (c.subset_granule == 32 || c.fraction >= 0.03) ? resident : 32u * cus;
     s.strips = std::min((s.nstrips + waves - 1u) / waves, 32u);
     s.parts = (s.nstrips + 4u * s.strips - 1u) / (4u * s.strips);
-    s.rows = fraction >= (s.nstrips <= 1024u ? 0.45 : 0.22);
     return s;
 }
 

@@ -205,7 +205,7 @@ am_status check_index_list_args(const am_state *st, const uint64_t *dev_out, uin
 // them, so they need no clearing of their own.
 am_status launch_index_list(am_state *st, uint64_t t, uint32_t *part_count, uint64_t words, uint64_t *dev_out, uint64_t capacity, uint64_t *dev_count)
 {
-    const am_host::ListShape s = am_host::list_shape(st->cfg.n, st->cfg.fraction, st->compute_units);
+    const am_host::ListShape s = am_host::list_shape(st->cfg, st->compute_units);
     if (s.parts > words) return fail(AM_EINVAL, "%u parts of the index list in a scratch of %llu words", s.parts, (unsigned long long)words);
     am::k_list_clear<<<(s.parts + 255u) / 256u, 256, 0, st->stream>>>(part_count, s.parts);
     AM_HIP(hipGetLastError());

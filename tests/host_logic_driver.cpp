@@ -36,10 +36,18 @@ void hl_plan_round(uint64_t K, uint64_t depth, uint64_t tau, uint64_t t, uint64_
 }
 
 // out: nstrips, strips, parts, rows
+void hl_list_shape_of(const am_config *c, uint32_t compute_units, uint32_t *out)
+{
+    const am_host::ListShape s = am_host::list_shape(*c, compute_units);
+    out[0] = s.nstrips; out[1] = s.strips; out[2] = s.parts; out[3] = s.rows;
+}
+
+// the same for coordinates drawn one by one
 void hl_list_shape(uint64_t n, double fraction, uint32_t compute_units, uint32_t *out)
 {
-    const am_host::ListShape s = am_host::list_shape(n, fraction, compute_units);
-    out[0] = s.nstrips; out[1] = s.strips; out[2] = s.parts; out[3] = s.rows;
+    am_config c = {};
+    c.n = n; c.fraction = fraction;
+    hl_list_shape_of(&c, compute_units, out);
 }
 
 void hl_d_shape(const am_config *c, uint32_t *rb, uint32_t *arrays, uint64_t *floats) { am_host::d_layout_shape(*c, rb, arrays, floats); }

@@ -23,3 +23,14 @@ def test_strips_by_the_scalar_form(amlib, n, p, seed, t):
     idx, k = st.subset_indices(t, capacity=min(n, int(n * p * 1.1) + 10_000))
     want = O.subset(seed, t, n, p)
     assert k == want.size and np.array_equal(idx.cpu().numpy().astype(np.uint64), want)
+
+
+@pytest.mark.parametrize("n,p,kw", [(2 * 20 * 256 * 2048 + d, p, kw) for d in (0, 1) for p, kw in
+                                    [(0.01, dict(granule=32)), (0.01, dict(stratified=True)), (0.25, dict())]])
+def test_cuts_of_the_other_draws(amlib, n, p, kw):
+    """Both sides of two strips a wave, from where whole lines and stratified subsets are cut for more waves."""
+    am = amlib
+    cfg = am.make_config(n, 1, fraction=p, seed=5, optimizer=am.OPT_SGD, beta1=0.0, correction=am.CORR_NONE, subset_granule=kw.get("granule", 1), subset_kind=int("stratified" in kw))
+    idx, k = am.init_state(cfg, torch.zeros(n)).subset_indices(2, capacity=min(n, int(n * p * 1.1) + 10_000))
+    want = O.subset(5, 2, n, p, **kw)
+    assert k == want.size and np.array_equal(idx.cpu().numpy().astype(np.uint64), want)

@@ -231,3 +231,17 @@ def test_steps_add_up_offsets_on_fewer_tiles_with_more_blocks(hl):
     tiles = {(R, sync): hl.hl_step_sum_tiles(C.byref(_config(replicas=R, delay=0 if sync else 1)), sync) for R in range(1, 33) for sync in (0, 1)}
     assert all(tiles[R, 0] == (8192 if R <= 2 else 6144 if R <= 4 else 8192 if R <= 16 else 2048 if R <= 24 else 768) for R in range(1, 33))
     assert all(tiles[R, 1] == (1024 if 9 <= R <= 16 else 8192) for R in range(1, 33))
+
+
+@pytest.mark.parametrize("kw", [dict(subset_granule=32), dict(subset_kind=1), dict(subset_kind=1, fraction=0.01), dict(fraction=0.3), dict(fraction=0.3, subset_granule=32), {}])
+def test_list_cut_follows_how_the_subset_is_drawn_and_written(hl, kw):
+    """Waves of a compute unit (strips a wave): 20 for coordinates drawn one by one and written lane by lane (40 beyond eight strips); 32 for the others,
+    where 20 would leave more than two strips a wave, the strips are written row by row or a stratified subset is small.  The parts fit their scratch."""
+    out, cus, short = (C.c_uint32 * 4)(), 256, kw.get("fraction", 0.05) >= 0.03
+    rows, one_by_one = kw.get("fraction", 0.05) >= 0.22, "subset_granule" not in kw and "subset_kind" not in kw
+    for n in (3_000_000, 12_000_000, 20_971_520, 20_971_521, 48_000_000, 83_886_080, 83_886_081, 1 << 27, 1 << 30):
+        hl.hl_list_shape_of(C.byref(_config(n=n, **kw)), cus, out)
+        nstrips, strips, parts = list(out)[:3]
+        waves = cus * ((20 if nstrips <= 8 * 20 * cus else 40) if one_by_one and not rows else 20 if not rows and short and nstrips <= 2 * 20 * cus else 32)
+        assert strips == min(32, -(-nstrips // waves)) and bool(out[3]) == rows
+        assert (parts - 1) * 4 * strips < nstrips <= parts * 4 * strips and parts <= (1 << 27) // 8192 or n > 1 << 27
