@@ -256,19 +256,32 @@ inline uint32_t local_step_workgroups(const am_config &c)
 // Workgroups (of four tiles, a wave each) of the staged averaging-only call that a compute unit may hold at a time; 0: as many as
 // fit.  Where the weights come from memory (more than the 256 MB cache holds) it is fastest with some 114 KB of lines a compute
 // unit on their way; with more the streams get in each other's way, as in the fused step, with fewer latency shows.  So the number
-// follows from the lines that a wave reads.  us a call by workgroups a compute unit, * the one chosen: interleaved, R = 8, 125.8M 5 %
-// 2: 1711, 3: 1574*, 4: 1631, 8: 1675; 1 % 3: 1030, 5: 717, 6: 655, as many as fit 636*; 31.5M 2 % 3: 291, 4: 257*, 8: 271; 10 % 2: 533*, 3: 559, 8: 568; 40 % 2: 936*,
-// 8: 957; R = 4 5 % 4: 231, 5: 228*, 8: 239; R = 12 2: 790, 3: 664*, 8: 727; per replica, 125.8M 5 % 2: 2358*, 3: 2468, 8: 2500; no
-// correction, 31.5M 5 % 3: 318, 4: 310*, 8: 310.  Weights that the cache holds: R = 8, 7M 3: 90.8, 4: 86.1, 8: 83.4.
+// follows from the lines that a wave reads.  But where a tile takes several turns, messages are rounded or the caches still help, latency is the
+// cost: then not fewer than three or four; without a correction a wave has less to wait for (130 KB, none where most coordinates are drawn), and members
+// in whole lines are not limited (interleaved, 80M, p = 40 % R = 8 3: 1.24, R = 4 4: 1.16, R = 12 3: 1.19).
+// us a call by workgroups a compute unit, * the one chosen: interleaved, R = 8, 125.8M 5 % 2: 1711, 3: 1574*, 4: 1631, 8: 1675; 1 % 3: 1030, 5: 717, 6: 655, as many as
+// fit 636*.  Time over as many as fit, 250M weights (80M in brackets): interleaved R = 8 2 % 4: 0.96*, 3: 1.12; 5 % 3: 0.93*, 2: 0.99; 10 % 2: 0.94* (1.13, 3: 1.00*);
+// 40 % 2: 0.97*; 80 % 4: 0.99*, 2: 1.14; 100 % 4: 0.95*, 2: 1.31; R = 5 5 % 4: 0.91*, 5: 0.99; 10 % 3: 0.92*, 4: 0.98 (2: 1.18); R = 12 10 % 3: 0.96*, 20 % 2: 0.96* (3: 0.98*);
+// R = 4 5 % 4: 0.92, 5: 0.96*; 40 % 3: 0.93*; 100 % 4: 0.93*, 2: 1.33; R = 20 20 % 2: 0.89* (160M 0.93, 3: 0.98*).  Per replica R = 8 5 % 2: 0.90* (3: 0.98*), 2 % 3: 0.95*; R = 5 5 % 3: 0.87*;
+// R = 4 5 % 4: 0.93*, 10 % 3: 0.93*, 100 % 4: 0.89*, 2: 1.29; R = 3 5 % 4: 0.92*, 100 % 4: 0.97*, 2: 1.56.  No correction R = 8 5 % 4: 0.92*, R = 12 5: 1.01*, 4: 1.04;
+// R = 4 40 % 5: 0.91*, R = 3 80 % 5: 1.20.  E4M3 interleaved R = 8 10 % 5: 1.00 (2: 1.26), R = 5 20 % 4: 0.99* (2: 1.10), R = 12 5 % 4: 0.94, 3: 1.01 (1.16); R = 20 and 32 5 % 4: 0.93 to 1.07, 3: 1.03 to 1.22.
 inline uint32_t average_workgroups(const am_config &c, const Blocks &b, bool interleaved_d)
 {
-    if (c.n * c.replicas <= 1ull << 26) return 0;
-    const bool by_line = c.subset_granule == 32;
-    auto touched = [&](double coordinates) { return 1.0 - std::pow(1.0 - c.fraction, by_line ? std::ceil(coordinates / am::kLineFloats) : coordinates); };
+    const uint64_t weights = c.n * c.replicas;
+    const bool ema = c.correction != AM_CORR_NONE, e4m3 = c.msg_dtype == AM_MSG_E4M3, wide = b.rb == 8u;
+    if (weights <= 1ull << 26 || c.subset_granule == 32 || (!ema && c.fraction > 0.5) || (e4m3 && b.nblocks > 2u)) return 0;
+    auto touched = [&](double coordinates) { return 1.0 - std::pow(1.0 - c.fraction, coordinates); };
     double kb = touched(2.0 * am::kLineFloats) + c.fraction * b.nblocks;           // of each replica: weights sent or received, ring values
-    if (c.correction != AM_CORR_NONE) kb += touched(interleaved_d ? (double)am::kLineFloats / b.rb : am::kLineFloats);
-    const double workgroups = std::floor(114.0 / 4.0 / (kb * b.rb) + 0.5);
-    return workgroups >= 7.0 ? 0u : std::max(2u, (uint32_t)workgroups);
+    if (ema) kb += touched(interleaved_d ? (double)am::kLineFloats / b.rb : am::kLineFloats);
+    const double replicas = wide ? (double)c.replicas / b.nblocks : b.rb;          // of a wave
+    const bool absent = wide && c.replicas <= 6u;                                  // (slots of the block that ask for nothing)
+    const double on_the_way = !wide ? 114.0 : !ema ? 130.0 : e4m3 ? 150.0 : absent ? 100.0 : 114.0;
+    const double workgroups = std::floor(on_the_way / 4.0 / (kb * replicas) + 0.5);
+    if (workgroups >= (absent ? 6.0 : 7.0)) return 0;
+    uint32_t least = 2;
+    if (c.msg_dtype != AM_MSG_F32 || c.fraction > 0.5 || weights <= 3ull << 25 || (b.nblocks > 2u && weights <= 3ull << 26)) least = 3;
+    if (e4m3 || (b.nblocks == 1u && c.fraction > 0.7) || (c.replicas == 3u && !interleaved_d && c.fraction > 0.3)) least = 4;
+    return std::max(least, (uint32_t)workgroups);
 }
 
 // Dynamic LDS of a workgroup that needs `need` bytes besides `fixed` bytes of static LDS, with which a compute unit holds at most `workgroups` of them (0: no limit):

@@ -65,6 +65,11 @@ uint32_t hl_step_workgroups(const am_config *c, int forward_copy, int receives)
 
 uint32_t hl_step_sum_tiles(const am_config *c, int sync) { return am_host::step_sum_tiles(*c, am_host::block_geometry(c->replicas), sync != 0); }
 
+uint32_t hl_average_workgroups(const am_config *c)
+{
+    return am_host::average_workgroups(*c, am_host::block_geometry(c->replicas), c->d_layout == AM_D_INTERLEAVED && c->correction != AM_CORR_NONE);
+}
+
 uint32_t hl_lds_for_residency(uint32_t need, uint32_t workgroups, uint32_t fixed) { return am_host::lds_for_residency(need, workgroups, fixed); }
 
 uint64_t hl_record_sized_step(uint64_t next_lines_step, uint32_t next_buf) { return am_host::record_sized_step(next_lines_step, next_buf); }

@@ -245,3 +245,19 @@ def test_list_cut_follows_how_the_subset_is_drawn_and_written(hl, kw):
         waves = cus * ((20 if nstrips <= 8 * 20 * cus else 40) if one_by_one and not rows else 20 if not rows and short and nstrips <= 2 * 20 * cus else 32)
         assert strips == min(32, -(-nstrips // waves)) and bool(out[3]) == rows
         assert (parts - 1) * 4 * strips < nstrips <= parts * 4 * strips and parts <= (1 << 27) // 8192 or n > 1 << 27
+
+
+@pytest.mark.parametrize("weights,R,kw,workgroups", [
+    # some 114 KB of lines on their way a compute unit: the measured cases and their neighbours
+    (1_006_632_960, 8, dict(d_layout=1), 3), (1_006_632_960, 8, dict(d_layout=1, fraction=0.01), 0), (250_000_000, 8, dict(d_layout=0), 2), (250_000_000, 8, dict(d_layout=1, fraction=0.1), 2),
+    (250_000_000, 4, dict(d_layout=0), 4), (250_000_000, 4, dict(d_layout=1), 5), (250_000_000, 8, dict(correction=0), 4),
+    # the caches still help; several turns a tile; absent replicas; three blocks
+    (1 << 26, 8, dict(d_layout=0), 0), (80_000_000, 8, dict(d_layout=0), 3), (80_000_000, 8, dict(d_layout=1, fraction=0.1), 3), (250_000_000, 8, dict(d_layout=1, fraction=0.6), 3),
+    (250_000_000, 8, dict(d_layout=1, fraction=1.0), 4), (250_000_000, 4, dict(d_layout=0, fraction=1.0), 4), (250_000_000, 16, dict(d_layout=1, fraction=1.0), 3),
+    (250_000_000, 5, dict(d_layout=1, fraction=0.1), 3), (250_000_000, 5, dict(d_layout=1), 4), (250_000_000, 5, dict(d_layout=1, fraction=0.02), 0), (250_000_000, 5, dict(d_layout=0), 3), (250_000_000, 3, dict(d_layout=0, fraction=0.5), 4), (130_000_000, 20, dict(d_layout=1, fraction=0.2), 3),
+    # rounded messages; no correction where most are drawn; members in whole lines
+    (250_000_000, 8, dict(d_layout=1, fraction=0.2, msg_dtype=1), 3), (250_000_000, 8, dict(d_layout=1, fraction=0.2, msg_dtype=2), 4), (250_000_000, 20, dict(d_layout=1, msg_dtype=2), 0),
+    (250_000_000, 4, dict(correction=0, fraction=0.4), 5), (250_000_000, 4, dict(correction=0, fraction=0.8), 0), (250_000_000, 8, dict(d_layout=1, fraction=0.4, subset_granule=32), 0),
+])
+def test_averaging_residency_follows_the_lines_and_the_turns(hl, weights, R, kw, workgroups):
+    assert hl.hl_average_workgroups(C.byref(_config(n=weights // R + (weights % R > 0), replicas=R, delay=1, **kw))) == workgroups
