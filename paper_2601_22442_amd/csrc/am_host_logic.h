@@ -142,48 +142,46 @@ inline ListShape list_shape(const am_config &c, uint32_t compute_units)
     return s;
 }
 
-// Whether the averaging-only call (with a delay) takes its ring values and interleaved EMA entries through LDS,
-// am::kStageFloats of a block at a time (a turn), or reads them where they are used.  Staging hides the
-// latency of scattered reads, but every turn after a tile's first repeats the arithmetic of the receive with
-// fewer lanes busy.  So it serves tiles that nearly always take one turn, and more turns where the weights
-// come from memory and not from the caches.  Figures: time staged / time direct, on the same arrays, taken before blocks of four and
-// eight replicas let the members' values change hands through LDS: the staged side has become up to a fifth faster since, the direct one has not.
+// Whether the averaging-only call (with a delay) takes its ring values and interleaved EMA entries through LDS, am::kStageFloats of a block at a
+// time (a turn), or reads them where they are used.  Staging hides the latency of scattered reads, but every turn after a tile's first
+// waits once more.  Time staged / time direct on the same arrays, no limit of resident workgroups.
+//
+// Blocks of four and eight replicas, whose members' values change hands through LDS, are faster staged, except where a tile takes several turns
+// and everything the call touches lies in the caches; sizes here in weights including the slots of absent replicas.
+//   interleaved, R = 8, 20 % 0.2M 1.00, 3M 0.97, 8M 1.00, 16M 0.82; 30 % 2M 1.11, 5M 1.08, 6.5M 0.86, 16M 0.77; 50 % 2M 1.28, 5M 1.06, 6.5M 0.73; 100 % 2M 1.44, 3M 1.21, 4M 0.94, 5M 0.79;
+//     R = 12 30 % 3M 1.01, 50 % 3M 1.19, 4M 1.02, 5M 1.00, 100 % 3M 1.20, 4M 0.67; R = 20 50 % 2M 1.06, 3M 1.00; R = 4 40 % 2M 1.01, 50 % 2M 1.11, 3M 1.03, 4M 0.97; 10 to 20 % 8M 1.08 all the same.
+//   per replica, R = 8, 20 % 2M 1.01, 30 % 5M 1.14, 6.5M 0.99, 100 % 5M 1.12, 8M 0.83; R = 5 50 % 6.4M 1.10, 13M 1.04; R = 12 40 % 5M 1.17, 6.5M 1.10, 10M 0.85; R = 32 40 % 3M 1.06, 4M 0.94; R = 4 50 %
+//     4M 1.08, 5M 1.02, 6.5M 0.92; 5 to 20 % 8M 1.10 to 1.18 and R = 8 6 to 10 % 8M 1.10 all the same.
+//   E4M3, interleaved R = 12 50 % 4M 1.15, 5M 1.11, 6.5M 0.98, 100 % 4M 0.91; R = 8 70 % 5M 1.15, 6.5M 0.77.
+//   members in whole lines, interleaved R = 8 8 % 2M 0.99, 10 % 1.05, 30 % 5M 1.27, 6.5M 1.00, 16M 0.54; R = 12 15 % 2M 1.04, 30 % 5M 1.17, 70 % 3M 1.32, 4M 0.98; R = 4 15 % 2M 1.03, 40 % 5M 1.04;
+//     per replica R = 8 8 % 2M 1.02, 20 % 8M 1.13, 10M 0.89, 70 % 6.5M 1.06, 8M 0.95; R = 20 20 % 8M 1.07, 10M 0.80; R = 4 30 % 6.5M 1.06, 50 % 5M 1.13, 70 % 0.99.
+// Blocks of one and two replicas have nothing to hand over: per-replica EMA vectors are dense reads in both forms, and the staged one gains with half a
+// turn at most, or at every fraction where the weights come from memory (11M R = 1 and 2 25 % 0.86 to 0.95, 100 % 0.80 to 0.91); interleaved
+// ones with one turn, where the weights come from memory, and for nearly whole tiles.
 inline bool average_staged(const am_config &c, uint32_t ntiles, const Blocks &b, bool interleaved_d)
 {
     const bool by_line = c.subset_granule == 32, e4m3 = c.msg_dtype == AM_MSG_E4M3;
-    const double drawn = c.fraction * am::kTileCoords, turn = (double)am::kStageFloats / b.rb;     // members of a tile, and those a turn holds
-    // Per-replica EMA vectors are dense reads in both forms.  R = 8: 20M 1 % 0.84, 5 % 0.98, 6.25 % 0.985, 20 % 1.00,
-    // 100 % 1.11; 2M 1 % 0.94, 5 % 0.97, 6.25 % 0.98, 10 % 1.01, 50 % 1.10.  Up to four replicas on stages whose weights
-    // come from memory gain at every fraction: 11M R = 1 to 4 25 % 0.86 to 0.95, 100 % 0.80 to 0.91 (1M, R = 4 25 % 1.07, 100 % 1.15).
-    // Members in whole lines fill a turn of eight replicas each; rounded messages of several blocks, 5 %: R = 12 600k 1.4
-    // to 1.6, 3.6M 1.08 to 1.18, 2 % 1.03 to 1.25 (fp32 3.6M 5 % 0.99, 600k 1.22 but 0.98 of the form before the staging).
-    if (!interleaved_d) {
-        if (by_line && c.msg_dtype != AM_MSG_F32 && b.nblocks > 1u) return false;
-        return drawn <= 0.5 * turn || (b.rb <= 4u && !by_line && c.msg_dtype == AM_MSG_F32 && ntiles > 24576u);
+    if (b.rb >= 4u) {
+        const bool wide = b.rb == 8u, one = wide && b.nblocks == 1u;
+        const double few = by_line ? (one ? 0.09 : b.nblocks > 2u ? 0.2 : wide ? 0.12 : 0.15) : !wide ? 0.45 : b.nblocks <= 2u ? 0.25 : 0.35;
+        if (c.fraction <= few) return true;
+        double small;                                      // millions of weights that the caches hold with what belongs to them
+        if (interleaved_d) {
+            small = by_line || (wide && (one || e4m3)) ? 5.3 : wide ? 3.5 : 3.0;
+            if (c.fraction > (by_line && !one ? 0.55 : 0.8)) small = std::min(small, 3.5);
+        } else {
+            small = by_line ? (wide && b.nblocks <= 3u ? 8.4 : 5.2) : one ? 6.8 : !wide ? 4.2 : b.nblocks <= 2u || e4m3 ? 6.0 : b.nblocks == 3u ? 5.2 : 3.5;
+            if (by_line && c.fraction > 0.5) small = one ? 6.6 : wide && b.nblocks <= 3u ? 5.4 : 4.2;
+            if (c.fraction > 0.8 && b.nblocks >= 3u && !e4m3) small = 3.5;
+        }
+        return (double)c.n * b.rb * b.nblocks > small * 1e6;
     }
+    const double drawn = c.fraction * am::kTileCoords, turn = (double)am::kStageFloats / b.rb;     // members of a tile, and those a turn holds
+    if (!interleaved_d) return drawn <= 0.5 * turn || (!by_line && c.msg_dtype == AM_MSG_F32 && ntiles > 24576u);
     const double members = by_line ? std::max(drawn, (double)am::kLineFloats) : drawn;             // of a tile that receives
-    // Members in whole lines bring whole lines of EMA entries, and E4M3 rounding is most of the arithmetic: with both,
-    // R = 8 5 % 500k 1.48, 8M 1.19; R = 4 20 % 500k 1.47, 8M 1.10, but 100 % 2M 0.77, 8M 0.70.
-    if (by_line && e4m3 && b.rb >= 4u && c.fraction < 0.75) return false;
-    // Eight replicas a block: 8M 5 % R = 8 1.04, R = 5 1.07, 10 % 1.05 and 1.09, 25 % 0.98 and 1.01, 50 % 0.90; 19M 5 % 0.99 and
-    // 1.03; bf16 8M 10 % 1.13, 25 % 1.08, 50 % 0.94.
-    if (by_line && b.rb == 8u && c.fraction < (c.msg_dtype == AM_MSG_F32 ? 0.25 : 0.5)) return false;
-    // One turn at most: R = 8 5 % 262k 0.92, 1M 0.92, 8M 0.82, 20M 0.80; R = 4 16 % 500k 0.90.  Several blocks take a
-    // second turn now and then more lightly than every block's reads in place (12 %, R = 12: 2M 1.0, 8M 0.86),
-    // unless the stage is small (12 %: 500k R = 12 1.18, R = 20 1.40, 900k R = 20 1.14, 2M 0.97) or, with rounded messages, not
-    // large (12 %, bf16 2M R = 12 1.08, 4M 0.89; E4M3 10 %, R = 12 1.3M 1.12, 4M 0.90).
-    const bool tight = b.nblocks == 1u || by_line || ntiles <= 4096u || (c.msg_dtype != AM_MSG_F32 && ntiles <= 8192u);
-    if (members + (tight ? 1.5 * std::sqrt(members * (1.0 - c.fraction)) : 0.0) <= turn) return true;
-    // More turns.  E4M3, R = 12: 8M 14 % 1.06, 30 % 1.17, 100 % 1.08 (2M 1.23, 1.54, 1.26).
-    if (e4m3 && b.nblocks > 1u) return false;
-    // R = 8: 20 % 20M 0.97, 8M 0.89, 4M 1.00, 2M 1.07, 1M 1.20, 262k 1.28; 40 % 20M 0.95, 2M 1.04, 1M 1.23; R = 20 20 %
-    // 2M 0.99, 1.3M 1.08.  Eight replicas a block in E4M3, 20 %: 8M 0.91, 4M 1.14; members in whole lines, 25 %, R = 5: 8M 1.01, 4M 1.11.
-    const bool wide = b.rb == 8u && (by_line || e4m3);
-    const uint64_t weights = c.n * c.replicas;
-    if (ntiles > (wide ? 24576u : 12288u) || weights > (wide ? 1ull << 26 : 1ull << 25)) return true;
-    // Nearly whole tiles, where the EMA entries are the most of what moves: 100 %, R = 8 2M 0.84, 900k 0.93, 500k 1.31; R = 12
-    // 500k 0.81, 262k 1.65; 60 %, R = 8 2M 0.99, 1M 1.11; bf16 messages 50 % 2M 1.06; E4M3 100 % R = 4 2M 0.77, R = 8 1.14.
-    return c.fraction > (c.msg_dtype != AM_MSG_F32 ? 0.75 : 0.5) && (ntiles > 3072u || weights >= 6000000u) && !(e4m3 && b.rb == 8u);
+    if (members + 1.5 * std::sqrt(members * (1.0 - c.fraction)) <= turn) return true;
+    if (ntiles > 12288u || c.n * c.replicas > 1ull << 25) return true;
+    return c.fraction > (c.msg_dtype != AM_MSG_F32 ? 0.75 : 0.5) && (ntiles > 3072u || c.n * c.replicas >= 6000000u);
 }
 
 // Whether a step's arrays come from memory each time (20 to 36 bytes a parameter and replica; half of the 256 MB that the caches hold

@@ -45,3 +45,12 @@ def test_per_replica_turns_of_a_large_stage(amlib, n, R, kw):
 def test_several_blocks_of_a_small_stage(amlib, n, R, p):
     for msg in (amlib.MSG_F32, amlib.MSG_BF16):
         run_average(amlib, n, R, 4, delay=1, fraction=p, msg_dtype=msg, d_layout=amlib.D_INTERLEAVED)
+
+
+@pytest.mark.parametrize("n,R,p,kw", [(662_500, 8, 0.5, {}), (662_501, 8, 0.5, {}), (30_003, 8, 0.25, {}), (218_751, 12, 0.3, {}), (300_000, 12, 0.9, dict(msg_dtype=2)), (30_003, 20, 0.35, {}), (110_000, 32, 0.5, {}),
+                                      (500_000, 4, 0.45, {}), (750_001, 3, 0.5, {}), (700_000, 8, 0.1, dict(subset_granule=32)), (300_000, 12, 0.6, dict(subset_granule=32, msg_dtype=1)), (850_001, 5, 0.5, {}),
+                                      (1_060_000, 8, 0.2, dict(subset_granule=32)), (1_050_001, 4, 0.5, dict(correction=0)), (375_001, 9, 0.3, dict(subset_kind=1))])
+@both_layouts
+def test_forms_around_the_lines(amlib, n, R, p, kw, d_layout):
+    """Several turns of blocks of four and eight on both sides of where the caches hold the stage, whose values change hands through LDS."""
+    run_average(amlib, n, R, 3, delay=1, fraction=p, d_layout=d_layout, **kw)

@@ -174,28 +174,24 @@ def test_a_record_names_sizes_that_every_build_finds(hl):
 
 
 @pytest.mark.parametrize("n,R,kw,staged", [
-    # per-replica EMA vectors: up to half a turn of 256 ring values
-    (20_000_000, 8, dict(fraction=0.0625, d_layout=0), True), (20_000_000, 8, dict(fraction=0.0626, d_layout=0), False),
-    # ... more with up to four replicas of a large stage; none where rounded messages of several blocks come in whole lines
-    (6_300_000, 4, dict(fraction=1.0, d_layout=0), True), (6_200_000, 4, dict(fraction=1.0, d_layout=0), False),
-    (20_000_000, 3, dict(fraction=0.5, d_layout=0, correction=0), True), (20_000_000, 3, dict(fraction=0.5, d_layout=0, msg_dtype=1), False),
-    (600_000, 12, dict(fraction=0.05, d_layout=0, subset_granule=32), True), (600_000, 12, dict(fraction=0.05, d_layout=0, subset_granule=32, msg_dtype=1), False),
-    (600_000, 8, dict(fraction=0.05, d_layout=0, subset_granule=32, msg_dtype=1), True),
-    # interleaved: one turn, or weights that come from memory
-    (100_000, 8, dict(fraction=0.09), True), (100_000, 8, dict(fraction=0.1), False), (2_000_000, 8, dict(fraction=0.2), False),
-    (4_000_000, 8, dict(fraction=0.2), True), (2_000_000, 20, dict(fraction=0.2), True), (500_000, 2, dict(fraction=0.4), True),
-    (500_000, 12, dict(fraction=0.08), True), (500_000, 12, dict(fraction=0.12), False),
-    (2_000_000, 12, dict(fraction=0.12), True), (2_000_000, 12, dict(fraction=0.12, msg_dtype=1), False), (4_000_000, 12, dict(fraction=0.12, msg_dtype=1), True),
-    # nearly whole tiles
-    (1_000_000, 8, dict(fraction=1.0), True), (500_000, 8, dict(fraction=1.0), False), (500_000, 12, dict(fraction=1.0), True), (1_300_000, 8, dict(fraction=0.6), True),
-    (1_300_000, 8, dict(fraction=0.6, msg_dtype=1), False),
-    # E4M3 and members in whole lines
-    (8_000_000, 12, dict(fraction=0.12, msg_dtype=2), True), (8_000_000, 12, dict(fraction=0.2, msg_dtype=2), False),
-    (4_000_000, 8, dict(fraction=0.2, msg_dtype=2), False), (8_000_000, 8, dict(fraction=0.2, msg_dtype=2), True),
-    (4_000_000, 8, dict(fraction=0.05, subset_granule=32), False), (20_000_000, 8, dict(fraction=0.24, subset_granule=32), False),
-    (20_000_000, 8, dict(fraction=0.25, subset_granule=32), True), (20_000_000, 8, dict(fraction=0.25, subset_granule=32, msg_dtype=1), False),
-    (20_000_000, 8, dict(fraction=0.5, subset_granule=32, msg_dtype=1), True),
-    (20_000_000, 8, dict(fraction=0.05, subset_granule=32, msg_dtype=2), False),
+    # blocks of eight: up to a quarter of the coordinates always, more beyond what the caches hold (slots of absent replicas count)
+    (20_000_000, 8, dict(fraction=0.0625, d_layout=0), True), (20_000_000, 8, dict(fraction=0.5, d_layout=0), True), (100_000, 8, dict(fraction=0.25), True), (100_000, 8, dict(fraction=0.26), False),
+    (850_000, 8, dict(fraction=0.5, d_layout=0), False), (850_001, 8, dict(fraction=0.5, d_layout=0), True), (850_001, 5, dict(fraction=0.5, d_layout=0), True),
+    (662_500, 8, dict(fraction=0.5), False), (662_501, 8, dict(fraction=0.5), True), (437_500, 8, dict(fraction=1.0), False), (437_501, 8, dict(fraction=1.0), True),
+    # several blocks; E4M3
+    (218_750, 12, dict(fraction=0.3), False), (218_751, 12, dict(fraction=0.3), True), (300_000, 12, dict(fraction=0.3, msg_dtype=2), False), (300_000, 12, dict(fraction=0.9, msg_dtype=2), True),
+    (375_000, 12, dict(fraction=0.3, d_layout=0), False), (375_001, 12, dict(fraction=0.3, d_layout=0), True), (100_000, 20, dict(fraction=0.35), True), (100_000, 20, dict(fraction=0.36), False),
+    (216_000, 20, dict(fraction=0.5, d_layout=0), False), (217_000, 20, dict(fraction=0.5, d_layout=0), True), (150_000, 20, dict(fraction=1.0, d_layout=0), True), (150_000, 20, dict(fraction=1.0, d_layout=0, msg_dtype=2), False),
+    (110_000, 32, dict(fraction=0.5, d_layout=0), True), (109_000, 32, dict(fraction=0.5, d_layout=0), False),
+    # blocks of four
+    (500_000, 4, dict(fraction=0.45), True), (750_000, 4, dict(fraction=0.5), False), (750_001, 3, dict(fraction=0.5), True), (1_050_000, 4, dict(fraction=0.5, d_layout=0), False), (1_050_001, 4, dict(fraction=0.5, d_layout=0), True),
+    # members in whole lines
+    (500_000, 8, dict(fraction=0.09, subset_granule=32), True), (500_000, 8, dict(fraction=0.1, subset_granule=32), False), (700_000, 8, dict(fraction=0.1, subset_granule=32), True), (300_000, 12, dict(fraction=0.5, subset_granule=32), False),
+    (300_000, 12, dict(fraction=0.6, subset_granule=32), True), (1_050_000, 8, dict(fraction=0.2, subset_granule=32, d_layout=0), False), (1_060_000, 8, dict(fraction=0.2, subset_granule=32, d_layout=0), True),
+    (830_000, 8, dict(fraction=0.6, subset_granule=32, d_layout=0), True), (1_200_000, 4, dict(fraction=0.3, subset_granule=32, d_layout=0), False), (1_200_000, 4, dict(fraction=0.6, subset_granule=32, d_layout=0), True),
+    # blocks of one and two: per replica up to half a turn or a large stage, interleaved one turn, a large stage or nearly whole tiles
+    (500_000, 2, dict(fraction=0.25, d_layout=0), True), (500_000, 2, dict(fraction=0.26, d_layout=0), False), (6_300_000, 2, dict(fraction=1.0, d_layout=0), True), (6_200_000, 2, dict(fraction=1.0, d_layout=0), False),
+    (500_000, 2, dict(fraction=0.4), True), (500_000, 2, dict(fraction=0.5), False), (3_200_000, 2, dict(fraction=0.5), True), (800_000, 2, dict(fraction=0.9), True), (800_000, 1, dict(fraction=1.0), True),
     # the measured cases
     (125_829_120, 8, dict(fraction=0.05), True), (1_048_576, 4, dict(fraction=0.01, d_layout=0), True),
 ])
