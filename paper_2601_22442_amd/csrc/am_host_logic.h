@@ -251,6 +251,13 @@ inline uint32_t local_step_workgroups(const am_config &c)
     return c.optimizer == AM_OPT_SGD ? 5u : 4u;
 }
 
+// Whether the averaging-only kernel finds the replicas' weights in a table, a block's pointers in one line of the kernel's arguments, or in the
+// replicas' records, a line each.  The lines are cold at every launch, which short calls feel; but with a table the requests of a wave's eight
+// replicas leave closer together, which stages at the edge of the caches do not like.  Time table / records, R = 8, 5 %: 0.1M weights 0.72 / 0.82 of the code
+// before both, 4M 0.79 / 0.88; p = 100 %, no delay, interleaved 7.4M 1.11 / 0.96, 10M 1.14 / 0.98, 17.7M 1.04 / 0.95; 50 % without correction 8.2M 1.15 / 0.95; from 30M on the
+// same within 2 %.  Blocks of four: 1M 0.90 / 0.91, and no difference on large stages: the table always.
+inline bool average_weights_table(const am_config &c, const Blocks &b) { return b.rb != 8u || c.n * c.replicas <= 5ull << 20; }
+
 // Workgroups (of four tiles, a wave each) of the staged averaging-only call that a compute unit may hold at a time; 0: as many as
 // fit.  Where the weights come from memory (more than the 256 MB cache holds) it is fastest with some 114 KB of lines a compute
 // unit on their way; with more the streams get in each other's way, as in the fused step, with fewer latency shows.  So the number

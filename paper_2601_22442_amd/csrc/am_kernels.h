@@ -375,11 +375,17 @@ struct StepArgs {
     //   w^ = w - (c_wd w + c_m m')     resp.     w - (c_wd w + c_g g)          (SGD with / without momentum)
     double a_m, b_m, a_v, b_v, c_wd, eps;
     double gamma, inv_replicas;
-    float *w[kMaxReplicas];          // averaging alone: every replica's weights; a block's pointers share one line of the kernel's arguments (in the
-                                     // records they are eight lines, cold at every launch: 500k R = 8 11.4 / 10.4 us a call, 1M R = 4 10.6 / 10.5)
     float *d[kMaxReplicas];          // one array per replica, or (interleaved) one per block: [tiles * 256][rb]
-    ReplicaArgs rep[kMaxReplicas];
+    union {
+        ReplicaArgs rep[kMaxReplicas];
+        float *w[kMaxReplicas];      // averaging alone (am_host::average_weights_table): every replica's weights.  In the records' place: a kernel's
+                                     // arguments are copied at every launch (256 bytes more: SGD 6181 R = 1 6.75 us a step, 6.53 without)
+    };
 };
+
+// Replica i's weights in the averaging-only kernel.
+template <bool TABLE>
+__device__ __forceinline__ float *weights_of(const StepArgs &a, uint32_t i) { return TABLE ? a.w[i] : a.rep[i].w; }
 
 // Precision.  State is fp32 in memory (the method's precision).  The accumulating expressions
 // (moments, weight update, EMA, look-ahead) are evaluated in fp64 from the stored fp32 values
@@ -1318,7 +1324,8 @@ __host__ __device__ constexpr uint32_t average_wave_bytes(uint32_t nblocks)
 // At most 128 registers (the staged form with interleaved EMA entries and items takes 72); in place with
 // interleaved EMA entries, where latency is the cost, at most 80 and 24 tiles: 20 replicas, us a call relative to
 // the form before the staging, 500k p = 0.2 0.85, p = 0.3 0.89, 900k p = 0.2 0.94 (slower than that form at 84 registers).
-template <bool DIL, int RB, bool TAU0, bool STAGED>
+// TABLE: where the weights' pointers are (am_host::average_weights_table).
+template <bool DIL, int RB, bool TAU0, bool STAGED, bool TABLE>
 __global__ void __launch_bounds__(256, (DIL && !TAU0 && !STAGED) ? 6 : 4)
 k_average(const StepArgs a)
 {
@@ -1399,7 +1406,7 @@ k_average(const StepArgs a)
             if (with_w) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) w[k].v[j] = 0.f;
-                if (i < R && need_w) w[k] = load_f32x4(a.w[i] + tbase, loff, nvalid);
+                if (i < R && need_w) w[k] = load_f32x4(weights_of<TABLE>(a, i) + tbase, loff, nvalid);
             }
             if (with_d) {
 #pragma unroll
@@ -1415,7 +1422,7 @@ k_average(const StepArgs a)
         for (int k = 0; k < RB; ++k) {
             const uint32_t i = b * RB + k;
             if (i >= R) continue;
-            store_f32x4(a.w[i] + tbase, loff, nvalid, w[k]);
+            store_f32x4(weights_of<TABLE>(a, i) + tbase, loff, nvalid, w[k]);
             if (!DIL && a.ema) store_f32x4(a.d[i] + tbase, loff, nvalid, dv[k]);
         }
     };

@@ -274,34 +274,34 @@ am_status launch_step_grad(am_state *st, const am::StepArgs &a)
 
 // The averaging-only kernel: one wave per (tile, block of replicas); with tau = 0 (the average is of this
 // call's own values) one wave per tile, which walks the blocks.
-template <bool DIL, int RB, bool TAU0, bool STAGED>
+template <bool DIL, int RB, bool TAU0, bool STAGED, bool TABLE>
 am_status launch_average_kernel(am_state *st, const am::StepArgs &a)
 {
     const uint32_t nblocks = st->lay.blocks.nblocks;
     const dim3 grid((st->lay.ntiles + 3u) / 4u, TAU0 ? 1u : nblocks), block(256);
     constexpr uint32_t kStatic = 16u;                        // four waves' shares of the lines before the tile
     const uint32_t lds = STAGED ? am_host::lds_for_residency(4u * am::average_wave_bytes<DIL, RB>(nblocks), am_host::average_workgroups(st->cfg, st->lay.blocks, DIL), kStatic) : 0u;
-    am::k_average<DIL, RB, TAU0, STAGED><<<grid, block, lds, st->stream>>>(a);
+    am::k_average<DIL, RB, TAU0, STAGED, TABLE><<<grid, block, lds, st->stream>>>(a);
     AM_HIP(hipGetLastError());
     return AM_OK;
 }
 
-template <bool DIL, int RB>
+template <bool DIL, int RB, bool TABLE>
 am_status launch_average_block(am_state *st, const am::StepArgs &a)
 {
-    if (a.do_recv && a.same_slot) return launch_average_kernel<DIL, RB, true, false>(st, a);
-    if (!am_host::average_staged(st->cfg, st->lay.ntiles, st->lay.blocks, DIL)) return launch_average_kernel<DIL, RB, false, false>(st, a);
-    return launch_average_kernel<DIL, RB, false, true>(st, a);
+    if (a.do_recv && a.same_slot) return launch_average_kernel<DIL, RB, true, false, TABLE>(st, a);
+    if (!am_host::average_staged(st->cfg, st->lay.ntiles, st->lay.blocks, DIL)) return launch_average_kernel<DIL, RB, false, false, TABLE>(st, a);
+    return launch_average_kernel<DIL, RB, false, true, TABLE>(st, a);
 }
 
 template <bool DIL>
 am_status launch_average(am_state *st, const am::StepArgs &a)
 {
     switch (st->lay.blocks.rb) {
-    case 8: return launch_average_block<DIL, 8>(st, a);
-    case 4: return launch_average_block<DIL, 4>(st, a);
-    case 2: return launch_average_block<DIL, 2>(st, a);
-    default: return launch_average_block<DIL, 1>(st, a);
+    case 8: return am_host::average_weights_table(st->cfg, st->lay.blocks) ? launch_average_block<DIL, 8, true>(st, a) : launch_average_block<DIL, 8, false>(st, a);
+    case 4: return launch_average_block<DIL, 4, true>(st, a);
+    case 2: return launch_average_block<DIL, 2, true>(st, a);
+    default: return launch_average_block<DIL, 1, true>(st, a);
     }
 }
 
@@ -701,7 +701,8 @@ am_status am_sparse_average(am_state *st, uint64_t t, float lambda_t)
     if (r.send) {
         am::StepArgs a;
         std::memset(&a, 0, sizeof a);
-        for (uint32_t i = 0; i < st->cfg.replicas; ++i) a.w[i] = st->w[i];
+        const bool table = am_host::average_weights_table(st->cfg, st->lay.blocks);
+        for (uint32_t i = 0; i < st->cfg.replicas; ++i) (table ? a.w[i] : a.rep[i].w) = st->w[i];
         if (am_status s = fill_averaging(st, t, lambda_t, r, am::kSumTiles * 4u, a)) return s;
         a.do_next = do_next;
         if (do_next) {

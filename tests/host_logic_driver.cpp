@@ -70,6 +70,8 @@ uint32_t hl_average_workgroups(const am_config *c)
     return am_host::average_workgroups(*c, am_host::block_geometry(c->replicas), c->d_layout == AM_D_INTERLEAVED && c->correction != AM_CORR_NONE);
 }
 
+int hl_average_weights_table(const am_config *c) { return am_host::average_weights_table(*c, am_host::block_geometry(c->replicas)); }
+
 uint32_t hl_lds_for_residency(uint32_t need, uint32_t workgroups, uint32_t fixed) { return am_host::lds_for_residency(need, workgroups, fixed); }
 
 uint64_t hl_record_sized_step(uint64_t next_lines_step, uint32_t next_buf) { return am_host::record_sized_step(next_lines_step, next_buf); }

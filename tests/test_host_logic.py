@@ -257,3 +257,9 @@ def test_list_cut_follows_how_the_subset_is_drawn_and_written(hl, kw):
 ])
 def test_averaging_residency_follows_the_lines_and_the_turns(hl, weights, R, kw, workgroups):
     assert hl.hl_average_workgroups(C.byref(_config(n=weights // R + (weights % R > 0), replicas=R, delay=1, **kw))) == workgroups
+
+
+def test_weights_of_blocks_of_eight_are_named_in_a_table_on_small_stages_only(hl):
+    for R in range(1, 33):
+        for n in ((5 << 20) // R, (5 << 20) // R + 1, 20_000_000):
+            assert bool(hl.hl_average_weights_table(C.byref(_config(n=n, replicas=R)))) == (R <= 4 or n * R <= 5 << 20)
