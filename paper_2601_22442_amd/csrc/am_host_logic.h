@@ -155,6 +155,9 @@ inline ListShape list_shape(const am_config &c, uint32_t compute_units)
 //   E4M3, interleaved R = 12 50 % 4M 1.15, 5M 1.11, 6.5M 0.98, 100 % 4M 0.91; R = 8 70 % 5M 1.15, 6.5M 0.77.
 //   members in whole lines, interleaved R = 8 8 % 2M 0.99, 10 % 1.05, 30 % 5M 1.27, 6.5M 1.00, 16M 0.54; R = 12 15 % 2M 1.04, 30 % 5M 1.17, 70 % 3M 1.32, 4M 0.98; R = 4 15 % 2M 1.03, 40 % 5M 1.04;
 //     per replica R = 8 8 % 2M 1.02, 20 % 8M 1.13, 10M 0.89, 70 % 6.5M 1.06, 8M 0.95; R = 20 20 % 8M 1.07, 10M 0.80; R = 4 30 % 6.5M 1.06, 50 % 5M 1.13, 70 % 0.99.
+//   no correction, R = 8 10 % 8M 0.96, 25 % 3M 1.11, 8M 1.14, 24M 1.02, 40M 0.92, 50 % 8M 1.27, 24M 1.04, 40M 0.99, 100 % 8M 1.11, 11M 1.01, 13M 0.97; R = 5 50 % 24M 1.12; R = 12 25 % 4M 1.01, 50 % 13M 1.02, 24M
+//     0.98, 100 % 5.5M 1.21, 7M 0.67; R = 20 35 % 5.5M 1.14, 8M 0.99, 100 % 3M 1.16, 4M 0.71; R = 4 35 % 4M 1.06, 5.5M 1.01, 50 % 4M 1.15, 5.5M 0.98; whole lines R = 8 10 % 8M 1.14, 11M 0.91, 50 % 16M 1.14,
+//     24M 1.04, 100 % 11M 1.01, 13M 0.98.
 // Blocks of one and two replicas have nothing to hand over: per-replica EMA vectors are dense reads in both forms, and the staged one gains with half a
 // turn at most, or at every fraction where the weights come from memory (11M R = 1 and 2 25 % 0.86 to 0.95, 100 % 0.80 to 0.91); interleaved
 // ones with one turn, where the weights come from memory, and for nearly whole tiles.
@@ -163,17 +166,25 @@ inline bool average_staged(const am_config &c, uint32_t ntiles, const Blocks &b,
     const bool by_line = c.subset_granule == 32, e4m3 = c.msg_dtype == AM_MSG_E4M3;
     if (b.rb >= 4u) {
         const bool wide = b.rb == 8u, one = wide && b.nblocks == 1u;
-        const double few = by_line ? (one ? 0.09 : b.nblocks > 2u ? 0.2 : wide ? 0.12 : 0.15) : !wide ? 0.45 : b.nblocks <= 2u ? 0.25 : 0.35;
-        if (c.fraction <= few) return true;
-        double small;                                      // millions of weights that the caches hold with what belongs to them
-        if (interleaved_d) {
-            small = by_line || (wide && (one || e4m3)) ? 5.3 : wide ? 3.5 : 3.0;
-            if (c.fraction > (by_line && !one ? 0.55 : 0.8)) small = std::min(small, 3.5);
+        double few, small;                                 // staged up to this fraction; beyond, from this many millions of weights (with absent slots) on
+        if (c.correction == AM_CORR_NONE) {                // half of what the caches would have to hold, and less to wait for
+            few = by_line ? (!wide ? 0.12 : b.nblocks <= 2u ? 0.09 : 0.2) : !wide || b.nblocks > 2u ? 0.3 : one ? 0.17 : 0.2;
+            if (one) small = c.fraction > 0.8 ? 11.0 : by_line ? (c.fraction <= 0.2 ? 8.5 : 20.0) : 26.0;
+            else if (wide && b.nblocks == 2u) small = c.fraction > 0.8 ? 5.7 : c.fraction > 0.6 ? (by_line ? 6.0 : 11.0) : by_line && c.fraction <= 0.2 ? 8.5 : 17.0;
+            else if (wide) small = c.fraction > 0.8 ? 3.5 : 5.7;
+            else small = !by_line ? 4.2 : c.fraction <= 0.4 ? 8.5 : c.fraction <= 0.6 ? 5.7 : 4.2;
         } else {
-            small = by_line ? (wide && b.nblocks <= 3u ? 8.4 : 5.2) : one ? 6.8 : !wide ? 4.2 : b.nblocks <= 2u || e4m3 ? 6.0 : b.nblocks == 3u ? 5.2 : 3.5;
-            if (by_line && c.fraction > 0.5) small = one ? 6.6 : wide && b.nblocks <= 3u ? 5.4 : 4.2;
-            if (c.fraction > 0.8 && b.nblocks >= 3u && !e4m3) small = 3.5;
+            few = by_line ? (one ? 0.09 : b.nblocks > 2u ? 0.2 : wide ? 0.12 : 0.15) : !wide ? 0.45 : b.nblocks <= 2u ? 0.25 : 0.35;
+            if (interleaved_d) {
+                small = by_line || (wide && (one || e4m3)) ? 5.3 : wide ? 3.5 : 3.0;
+                if (c.fraction > (by_line && !one ? 0.55 : 0.8)) small = std::min(small, 3.5);
+            } else {
+                small = by_line ? (wide && b.nblocks <= 3u ? 8.4 : 5.2) : one ? 6.8 : !wide ? 4.2 : b.nblocks <= 2u || e4m3 ? 6.0 : b.nblocks == 3u ? 5.2 : 3.5;
+                if (by_line && c.fraction > 0.5) small = one ? 6.6 : wide && b.nblocks <= 3u ? 5.4 : 4.2;
+                if (c.fraction > 0.8 && b.nblocks >= 3u && !e4m3) small = 3.5;
+            }
         }
+        if (c.fraction <= few) return true;
         return (double)c.n * b.rb * b.nblocks > small * 1e6;
     }
     const double drawn = c.fraction * am::kTileCoords, turn = (double)am::kStageFloats / b.rb;     // members of a tile, and those a turn holds

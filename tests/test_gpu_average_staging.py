@@ -49,7 +49,8 @@ def test_several_blocks_of_a_small_stage(amlib, n, R, p):
 
 @pytest.mark.parametrize("n,R,p,kw", [(662_500, 8, 0.5, {}), (662_501, 8, 0.5, {}), (30_003, 8, 0.25, {}), (218_751, 12, 0.3, {}), (300_000, 12, 0.9, dict(msg_dtype=2)), (30_003, 20, 0.35, {}), (110_000, 32, 0.5, {}),
                                       (500_000, 4, 0.45, {}), (750_001, 3, 0.5, {}), (700_000, 8, 0.1, dict(subset_granule=32)), (300_000, 12, 0.6, dict(subset_granule=32, msg_dtype=1)), (850_001, 5, 0.5, {}),
-                                      (1_060_000, 8, 0.2, dict(subset_granule=32)), (1_050_001, 4, 0.5, dict(correction=0)), (375_001, 9, 0.3, dict(subset_kind=1))])
+                                      (1_060_000, 8, 0.2, dict(subset_granule=32)), (1_050_001, 4, 0.5, dict(correction=0)), (375_001, 9, 0.3, dict(subset_kind=1)), (1_375_000, 8, 1.0, dict(correction=0)), (1_375_001, 8, 1.0, dict(correction=0)),
+                                      (230_000, 20, 0.5, dict(correction=0)), (1_063_000, 7, 0.1, dict(correction=0, subset_granule=32))])
 @both_layouts
 def test_forms_around_the_lines(amlib, n, R, p, kw, d_layout):
     """Several turns of blocks of four and eight on both sides of where the caches hold the stage, whose values change hands through LDS."""

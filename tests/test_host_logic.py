@@ -192,12 +192,18 @@ def test_a_record_names_sizes_that_every_build_finds(hl):
     # blocks of one and two: per replica up to half a turn or a large stage, interleaved one turn, a large stage or nearly whole tiles
     (500_000, 2, dict(fraction=0.25, d_layout=0), True), (500_000, 2, dict(fraction=0.26, d_layout=0), False), (6_300_000, 2, dict(fraction=1.0, d_layout=0), True), (6_200_000, 2, dict(fraction=1.0, d_layout=0), False),
     (500_000, 2, dict(fraction=0.4), True), (500_000, 2, dict(fraction=0.5), False), (3_200_000, 2, dict(fraction=0.5), True), (800_000, 2, dict(fraction=0.9), True), (800_000, 1, dict(fraction=1.0), True),
+    # no correction
+    (1_000_000, 8, dict(fraction=0.17, correction=0), True), (3_250_000, 8, dict(fraction=0.18, correction=0), False), (3_250_001, 8, dict(fraction=0.18, correction=0), True), (1_375_000, 8, dict(fraction=1.0, correction=0), False),
+    (1_375_001, 8, dict(fraction=1.0, correction=0), True), (1_000_000, 12, dict(fraction=0.5, correction=0), False), (1_070_000, 12, dict(fraction=0.5, correction=0), True), (700_000, 12, dict(fraction=0.7, correction=0), True),
+    (357_000, 12, dict(fraction=1.0, correction=0), True), (230_000, 20, dict(fraction=0.5, correction=0), False), (240_000, 20, dict(fraction=0.5, correction=0), True), (1_050_001, 4, dict(fraction=0.5, correction=0), True),
+    (1_062_000, 8, dict(fraction=0.1, correction=0, subset_granule=32), False), (1_063_000, 8, dict(fraction=0.1, correction=0, subset_granule=32), True), (2_500_000, 8, dict(fraction=0.5, correction=0, subset_granule=32), False),
+    (2_125_000, 4, dict(fraction=0.4, correction=0, subset_granule=32), False), (1_430_000, 4, dict(fraction=0.5, correction=0, subset_granule=32), True), (500_000, 12, dict(fraction=0.1, correction=0, subset_granule=32), False),
     # the measured cases
     (125_829_120, 8, dict(fraction=0.05), True), (1_048_576, 4, dict(fraction=0.01, d_layout=0), True),
 ])
 def test_averaging_stages_where_that_is_the_faster_form(hl, n, R, kw, staged):
     kw = dict(dict(d_layout=1), **kw)
-    assert bool(hl.hl_average_staged(C.byref(_config(n=n, replicas=R, delay=1, **kw)), kw["d_layout"])) == staged
+    assert bool(hl.hl_average_staged(C.byref(_config(n=n, replicas=R, delay=1, **kw)), kw["d_layout"] and kw.get("correction", 1) != 0)) == staged
 
 
 @pytest.mark.parametrize("n,R,kw,fwd,receives,workgroups", [
