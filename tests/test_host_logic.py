@@ -257,6 +257,11 @@ def test_list_cut_follows_how_the_subset_is_drawn_and_written(hl, kw):
     (1 << 26, 8, dict(d_layout=0), 0), (80_000_000, 8, dict(d_layout=0), 3), (80_000_000, 8, dict(d_layout=1, fraction=0.1), 3), (250_000_000, 8, dict(d_layout=1, fraction=0.6), 3),
     (250_000_000, 8, dict(d_layout=1, fraction=1.0), 4), (250_000_000, 4, dict(d_layout=0, fraction=1.0), 4), (250_000_000, 16, dict(d_layout=1, fraction=1.0), 3),
     (250_000_000, 5, dict(d_layout=1, fraction=0.1), 3), (250_000_000, 5, dict(d_layout=1), 4), (250_000_000, 5, dict(d_layout=1, fraction=0.02), 0), (250_000_000, 5, dict(d_layout=0), 3), (250_000_000, 3, dict(d_layout=0, fraction=0.5), 4), (130_000_000, 20, dict(d_layout=1, fraction=0.2), 3),
+    # tiles of eight replicas that take several turns, without interleaved EMA entries; R = 2 and 3
+    (120_000_000, 8, dict(d_layout=0, fraction=0.1), 2), (120_000_000, 8, dict(d_layout=0, fraction=0.25), 0), (120_000_000, 12, dict(d_layout=0, fraction=0.5), 0), (220_000_000, 12, dict(d_layout=0, fraction=0.5), 3),
+    (220_000_000, 5, dict(d_layout=0, fraction=0.25), 4), (220_000_000, 8, dict(d_layout=0, fraction=1.0), 4), (220_000_000, 8, dict(d_layout=0, fraction=0.25, msg_dtype=1), 0),
+    (220_000_000, 8, dict(correction=0, fraction=0.25), 0), (120_000_000, 5, dict(d_layout=0, fraction=0.25, msg_dtype=2), 0), (120_000_000, 2, dict(d_layout=1, fraction=0.4), 6), (120_000_000, 2, dict(d_layout=1, fraction=1.0), 6),
+    (90_000_000, 3, dict(d_layout=0, fraction=0.2), 4),
     # rounded messages; no correction where most are drawn; members in whole lines
     (250_000_000, 8, dict(d_layout=1, fraction=0.2, msg_dtype=1), 3), (250_000_000, 8, dict(d_layout=1, fraction=0.2, msg_dtype=2), 4), (250_000_000, 20, dict(d_layout=1, msg_dtype=2), 0),
     (250_000_000, 4, dict(correction=0, fraction=0.4), 5), (250_000_000, 4, dict(correction=0, fraction=0.8), 0), (250_000_000, 8, dict(d_layout=1, fraction=0.4, subset_granule=32), 0),
