@@ -248,10 +248,17 @@ inline uint32_t step_sum_tiles(const am_config &c, const Blocks &b, bool sync)
 }
 
 // Whether a step between two averaging rounds (which neither sends nor receives) goes through the kernel of its own.  It pays for blocks of
-// eight waves; the kernel change costs the round's step some microseconds of cold instructions.  us a step on average over rounds, by the
-// fused kernel / by its own: AdamW R = 8 K = 2 15M 575.7 / 571.7, 3M 150.1 / 145.3, 1.5M 81.0 / 78.0, K = 4 500k 25.1 / 24.2, 100,003 8.06 / 8.13; SGD R = 8 1M
-// K = 4 29.4 / 28.9; but AdamW R = 4 K = 4 6M 111.5 / 114.3, SGD R = 4 15M K = 2 203.0 / 205.7, R = 2 15M K = 4 100.2 / 102.7.
-inline bool local_step_alone(const am_config &c, const Blocks &b) { return b.rb == 8u && c.n * c.replicas > 1ull << 20; }
+// eight waves; the kernel change costs the round's step some microseconds of cold instructions, which every second or third step feels on larger
+// stages than every fourth, and full blocks more than those whose absent slots idle.  Time by its own / by the fused kernel on average over rounds, by weights (n R):
+//   K = 2 R = 8 AdamW 1.1M 1.19, 1.6M 1.04, 3M 1.04, 6M 1.03, 10M 0.97, momentum 2.2M to 4M 1.08, 8M 1.02, 10M 0.97, bf16 gradients 1.1M 1.24; R = 12 and 16 2M to 4M 1.07 to 1.10, 10M 0.99;
+//     R = 5 1.1M 1.10, 2.6M and more 0.99, plain SGD 0.90;  K = 3 R = 8 2M to 4M 1.03 to 1.07, 8M 0.99;  K = 4 and 5 0.80 to 1.00 from 1.1M on.
+// us a step: AdamW R = 8 K = 2 15M 575.7 / 571.7 (fused / its own), but R = 4 K = 4 6M 111.5 / 114.3, SGD R = 4 15M K = 2 203.0 / 205.7, R = 2 15M K = 4 100.2 / 102.7.
+inline bool local_step_alone(const am_config &c, const Blocks &b)
+{
+    if (b.rb != 8u) return false;
+    const bool light = c.replicas <= 6u || (c.optimizer == AM_OPT_SGD && c.beta1 == 0.f);
+    return c.n * c.replicas > (c.avg_interval >= 4u ? 1ull << 20 : light ? 5ull << 19 : 6ull << 20);
+}
 
 // The workgroups (four tiles of one replica) of that kernel that a compute unit may hold at a time: some 60 KB of requested operands a compute
 // unit.  us a step by their number: AdamW 30M R = 8 as many as fit 1346, 3: 1285, 4: 1215, 5: 1260, 3M R = 8 135.8, 136.3, 126.8, 131.2; SGD with

@@ -65,6 +65,7 @@ uint32_t hl_step_workgroups(const am_config *c, int forward_copy, int receives)
 
 uint32_t hl_step_sum_tiles(const am_config *c, int sync) { return am_host::step_sum_tiles(*c, am_host::block_geometry(c->replicas), sync != 0); }
 
+int hl_local_step_alone(const am_config *c) { return am_host::local_step_alone(*c, am_host::block_geometry(c->replicas)); }
 uint32_t hl_average_workgroups(const am_config *c)
 {
     return am_host::average_workgroups(*c, am_host::block_geometry(c->replicas), c->d_layout == AM_D_INTERLEAVED && c->correction != AM_CORR_NONE);

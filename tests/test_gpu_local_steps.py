@@ -1,4 +1,5 @@
-"""Steps between two averaging rounds: a kernel of their own for blocks of eight replicas beyond 2^20 parameters x replicas.  Every optimizer, forward copy and gradient type, sizes at the edges of a tile and of
+"""Steps between two averaging rounds: a kernel of their own for blocks of eight replicas beyond 2^20 parameters x replicas with a round every
+fourth step or more seldom, beyond 2.5 or 6 times 2^20 with one every second or third.  Every optimizer, forward copy and gradient type, sizes at the edges of a tile and of
 four, absent replicas and several blocks, idle replicas, gradient factors, and both sides of the line from where the resident
 workgroups are limited."""
 import numpy as np
@@ -17,8 +18,14 @@ PLAIN = dict(optimizer=O.OPT_SGD, beta1=0.0)
 @pytest.mark.parametrize("n,R", [(257, 3), (1025, 8), (131_072, 8), (131_073, 8), (210_175, 5), (90_881, 12), (40_193, 32)])
 @pytest.mark.parametrize("kw", [dict(lookahead=True, gamma=0.9), dict(optimizer=O.OPT_NADAMW, beta1=0.99), SGD, PLAIN,
                                 dict(grad_bf16=True, fwd_bf16=True), dict(SGD, grad_bf16=True, lookahead=True, gamma=0.5)])
-def test_between_rounds(amlib, n, R, kw):
-    run_steps(amlib, n, R, 7, delay=1, avg_interval=3, fraction=0.2, seed=9, check_every=7, **kw)
+@pytest.mark.parametrize("K", [3, 4])
+def test_between_rounds(amlib, n, R, kw, K):
+    run_steps(amlib, n, R, 2 * K + 1, delay=1, avg_interval=K, fraction=0.2, seed=9, check_every=2 * K + 1, **kw)
+
+
+@pytest.mark.parametrize("n,R,K", [((6 << 20) // 8, 8, 2), ((6 << 20) // 8 + 1, 8, 2), ((5 << 19) // 5, 5, 3), ((5 << 19) // 5 + 1, 5, 3)])
+def test_frequent_rounds_on_both_sides_of_the_line(amlib, n, R, K):
+    run_steps(amlib, n, R, 2 * K + 1, delay=1, avg_interval=K, fraction=0.2, seed=9, check_every=2 * K + 1, grad_bf16=True)
 
 
 @pytest.mark.parametrize("n,R", [((5 << 20) // 8, 8), ((5 << 20) // 8 + 1, 8), (900_001, 6)])

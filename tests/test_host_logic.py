@@ -249,6 +249,17 @@ def test_list_cut_follows_how_the_subset_is_drawn_and_written(hl, kw):
         assert (parts - 1) * 4 * strips < nstrips <= parts * 4 * strips and parts <= (1 << 27) // 8192 or n > 1 << 27
 
 
+@pytest.mark.parametrize("weights,R,kw", [
+    (1 << 20, 8, dict(avg_interval=4)), (1 << 20, 5, dict(avg_interval=5)), (6 << 20, 8, dict(avg_interval=2)), (6 << 20, 16, dict(avg_interval=3)), (6 << 20, 8, dict(avg_interval=2, optimizer=0)),
+    (5 << 19, 8, dict(avg_interval=2, optimizer=0, beta1=0.0)), (5 << 19, 5, dict(avg_interval=2)),
+])
+def test_steps_between_rounds_have_a_kernel_of_their_own_where_it_pays(hl, weights, R, kw):
+    """Beyond this many weights, by how often a round comes and by what a wave moves; blocks of four and fewer never."""
+    assert not hl.hl_local_step_alone(C.byref(_config(n=weights // R, replicas=R, delay=1, **kw)))
+    assert hl.hl_local_step_alone(C.byref(_config(n=weights // R + 1, replicas=R, delay=1, **kw)))
+    assert not hl.hl_local_step_alone(C.byref(_config(n=10 * weights, replicas=4, delay=1, **kw)))
+
+
 @pytest.mark.parametrize("weights,R,kw,workgroups", [
     # some 114 KB of lines on their way a compute unit: the measured cases and their neighbours
     (1_006_632_960, 8, dict(d_layout=1), 3), (1_006_632_960, 8, dict(d_layout=1, fraction=0.01), 0), (250_000_000, 8, dict(d_layout=0), 2), (250_000_000, 8, dict(d_layout=1, fraction=0.1), 2),
