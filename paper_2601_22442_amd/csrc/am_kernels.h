@@ -477,14 +477,21 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Whether half `half` (64 bytes) of line `line` of the tile's interleaved EMA entries holds a received coordinate.
-// masks: the lanes' masks of the received subset; sh: log2 of the replicas per block.
-__device__ __forceinline__ bool half_received(const uint8_t *masks, uint32_t line, uint32_t half, uint32_t sh)
+// A touched line of the tile's interleaved EMA entries in the list: its index in the tile, and in bits 8 and 9 whether its 64-byte halves hold a
+// received coordinate.  Called by the line's first lane.  mask: the lane's coordinates that are received; any: the lanes that have one; sh: log2
+// of the replicas per block.
+__device__ __forceinline__ uint32_t touched_line(uint32_t lane, uint32_t mask, uint64_t any, uint32_t sh)
 {
-    if (sh == 3u) return ((masks[line] >> (2u * half)) & 3u) != 0u;                     // two coordinates of one group
-    const uint8_t *p = masks + (2u * line + half) * (4u >> sh);
-    return sh == 2u ? *p != 0u : sh == 1u ? *reinterpret_cast<const uint16_t *>(p) != 0u : *reinterpret_cast<const uint32_t *>(p) != 0u;
+    uint32_t lo = mask & 3u, hi = mask & 12u;              // eight replicas: a line is one group, a half two of its coordinates
+    if (sh != 3u) {
+        const uint32_t lanes = 4u >> sh, group_bits = (1u << lanes) - 1u;
+        lo = (uint32_t)(any >> lane) & group_bits;
+        hi = (uint32_t)(any >> (lane + lanes)) & group_bits;
+    }
+    return lane >> (3u - sh) | (lo ? 0x100u : 0u) | (hi ? 0x200u : 0u);
 }
+__device__ __forceinline__ uint32_t line_index(uint32_t entry) { return entry & 0xFFu; }
+__device__ __forceinline__ bool half_received(uint32_t entry, uint32_t half) { return ((entry >> 8) >> half) & 1u; }
 
 // Where the coordinates of one group (= one lane) sit in the subsets of this step.
 struct GroupSubsets {
@@ -755,15 +762,16 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     // by the wave that hashes the received subset as soon as it knows them.  (Noting the touched lines
     // in memory when a subset is sent and reading them back before hashing was measured slower: the
     // scalar load of the note holds the hashing wave up for longer than the hashing takes.)
-    auto request_d_lines = [&](const uint64_t leaders) {
+    auto request_d_lines = [&](const uint64_t leaders, const uint32_t mask) {
         const uint32_t nlines = (uint32_t)__popcll(leaders);
         if (nlines) {
-            if ((leaders >> lane) & 1ull) L.list[__popcll(leaders & ((1ull << lane) - 1ull))] = lane >> (3u - sh);
+            const uint64_t any = __ballot(mask != 0u);
+            if ((leaders >> lane) & 1ull) L.list[__popcll(leaders & ((1ull << lane) - 1ull))] = touched_line(lane, mask, any, sh);
             wave_lds_sync();
             const float *src = a.d[b0] + (uint64_t)tile * tile_floats + (lane & 7u) * 4u;
             for (uint32_t q0 = 0; q0 < nlines; q0 += 8u) {
                 const uint32_t q = q0 + (lane >> 3);
-                if (q < nlines) lds_dma_16(src + L.list[q] * kLineFloats, L.d + q0 * kLineFloats);
+                if (q < nlines) lds_dma_16(src + line_index(L.list[q]) * kLineFloats, L.d + q0 * kLineFloats);
             }
         }
     };
@@ -786,7 +794,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
         if (job == 0u) {
             s.mask_recv = mask;
             if (kShareRecv) L.masks[64u + lane] = (uint8_t)mask;
-            if (DIL && a.ema && wave == 0u) request_d_lines(lines_of(mask));
+            if (DIL && a.ema && wave == 0u) request_d_lines(lines_of(mask), mask);
         } else if (job == 1u) {
             s.mask_send = mask;
             L.masks[lane] = (uint8_t)mask;
@@ -917,8 +925,9 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     }
 
     // my chunk of the touched lines of d: float offset inside the tile's part of the array
-    const uint32_t d_chunk_off = (DIL && flat < d_lines * 8u) ? L.list[flat >> 3] * kLineFloats + (flat & 7u) * 4u : 0u;
-    const bool d_chunk_changes = DIL && flat < d_lines * 8u && half_received(L.masks + 64u, L.list[flat >> 3], (flat >> 2) & 1u, sh);
+    const uint32_t d_line = (DIL && flat < d_lines * 8u) ? L.list[flat >> 3] : 0u;     // (0: no half received)
+    const uint32_t d_chunk_off = line_index(d_line) * kLineFloats + (flat & 7u) * 4u;
+    const bool d_chunk_changes = DIL && half_received(d_line, (flat >> 2) & 1u);
 
     // ---- my replica of each block of this workgroup (one block, except when tau = 0 and R > 8)
     for (uint32_t bb = 0; bb < (TAU0 ? a.blocks_per_wg : 1u); ++bb) {
@@ -1081,12 +1090,13 @@ __device__ __forceinline__ void step_tile_sync(const StepArgs &a, const uint32_t
         if (DIL && a.ema) {
             const uint64_t leaders = leaders_of(mask);
             const uint32_t nlines = (uint32_t)__popcll(leaders);
-            if ((leaders >> lane) & 1ull) L.list[__popcll(leaders & ((1ull << lane) - 1ull))] = lane >> (3u - sh);    // (the same from every block)
+            const uint64_t any = __ballot(mask != 0u);
+            if ((leaders >> lane) & 1ull) L.list[__popcll(leaders & ((1ull << lane) - 1ull))] = touched_line(lane, mask, any, sh);    // (the same from every block)
             wave_lds_sync();
             const float *src = a.d[b] + (uint64_t)tile * tile_floats + (lane & 7u) * 4u;
             for (uint32_t q0 = 0; q0 < nlines; q0 += 8u) {
                 const uint32_t q = q0 + (lane >> 3);
-                if (q < nlines) lds_dma_16(src + L.list[q] * kLineFloats, L.d + b * tile_floats + q0 * kLineFloats);
+                if (q < nlines) lds_dma_16(src + line_index(L.list[q]) * kLineFloats, L.d + b * tile_floats + q0 * kLineFloats);
             }
         }
         if (!DIL && a.ema) {
@@ -1166,8 +1176,9 @@ __device__ __forceinline__ void step_tile_sync(const StepArgs &a, const uint32_t
         __syncthreads();
         for (uint32_t q = 0; q < a.nblocks; ++q)
             for (uint32_t f = flat; f < d_lines * 8u; f += threads) {
-                if (!half_received(L.masks, L.list[f >> 3], (f >> 2) & 1u, sh)) continue;
-                float *dst = a.d[q] + (uint64_t)tile * tile_floats + L.list[f >> 3] * kLineFloats + (f & 7u) * 4u;
+                const uint32_t line = L.list[f >> 3];
+                if (!half_received(line, (f >> 2) & 1u)) continue;
+                float *dst = a.d[q] + (uint64_t)tile * tile_floats + line_index(line) * kLineFloats + (f & 7u) * 4u;
                 __builtin_nontemporal_store(*reinterpret_cast<const v4f *>(L.d + q * tile_floats + f * 4u), reinterpret_cast<v4f *>(dst));
             }
     }
