@@ -223,8 +223,9 @@ am_status am_lookahead(void *out, uint32_t out_dtype, const float *w, const floa
  * simulated by buffering); a round may then be received twice or never.  Host value, no device work. */
 am_status am_set_delay(am_state *st, uint32_t tau);
 
-/* Diagnostics of the paper's consensus-error figure, enqueued on the stream, results in DEVICE
- * memory (3 doubles): out[0] = sum_i ||w_i - mean_i w_i||^2 (consensus error, appendix notation),
+/* Diagnostics of the paper's consensus-error figure, enqueued on the stream, results in memory
+ * that the device can write (DEVICE or page-locked host memory; read them after the stream has got that
+ * far), 3 doubles: out[0] = sum_i ||w_i - mean_i w_i||^2 (consensus error, appendix notation),
  * out[1] = mean and out[2] = max over the coordinates of the variance over the replicas of the EMA
  * estimates d_i (0 when there is no d).  Deterministic (fixed reduction order). */
 am_status am_diagnostics(am_state *st, double *dev_out3);

@@ -775,9 +775,9 @@ am_status am_diagnostics(am_state *st, double *dev_out3)
     for (uint32_t k = 0; k < st->d_arrays; ++k) a.d[k] = st->d[k];          // per replica, or (interleaved) per block
     a.n = st->cfg.n; a.replicas = st->cfg.replicas;
     const uint64_t want = ((st->cfg.n + 3) / 4 + 255) / 256;               // a thread takes groups of 4 coordinates
-    // Large interleaved stages of eight replicas a block take twice the workgroups, as their EMA row is the slower one (2048 / 4096, us: R = 8 31.5M 313.8 / 304.7, R = 16 8M 172.2
-    // / 169.0; but R = 8 3M 33.3 / 34.3, per replica 31.5M 305.0 / 307.6).
-    const uint64_t most = st->d_rb == 8u && want >= 7500u ? 4096u : 2048u;
+    // Large interleaved stages of one and two blocks of eight replicas take twice the workgroups, as their EMA row is the slower one (2048 / 4096, us: R = 8 31.5M 313.8 / 304.7, R = 16 8M 172.2
+    // / 169.0; but R = 8 3M 33.3 / 34.3, per replica 31.5M 305.0 / 307.6; time 4096 / 2048 R = 20, 24 and 32 8M 1.03 to 1.07).
+    const uint64_t most = st->d_rb == 8u && a.replicas <= 16u && want >= 7500u ? 4096u : 2048u;
     const uint32_t blocks = (uint32_t)(want < most ? want : most);          // 2 x 2 doubles each in the partials area (32 x 1024 doubles)
     const uint32_t rows = st->d_arrays != 0 ? 2u : 1u;
     const dim3 grid(blocks, rows);
