@@ -369,10 +369,10 @@ inline Round plan_round(uint64_t K, uint64_t depth, uint64_t tau, uint64_t t)
 
 // What a checkpoint record says about subsets that are already sized, and what a record is taken to say.
 // A record names sizes only where every build has looked for them, in the words at off_next, which this one does not write: a
-// record says that nothing is sized (unless it was resumed from one that names words not yet used), and the step after the resume
-// hashes its subset once more and finds the same sizes.  Records whose reserved field is not zero (some named
+// record says that nothing is sized, unless it was resumed from one that names words (of step record_step) not yet used at the last step made, and the step
+// after the resume hashes its subset once more and finds the same sizes.  Records whose reserved field is not zero (some named
 // another table in its bit 0) count as not sized, too.
-inline uint64_t record_sized_step(uint64_t next_lines_step, uint32_t next_buf) { return next_buf ? 0 : next_lines_step; }
+inline uint64_t record_sized_step(uint64_t record_step, uint64_t last_t) { return record_step > last_t ? record_step : 0; }
 inline uint64_t resumed_sized_step(const am_snapshot &s) { return s.reserved ? 0 : s.next_lines_step; }
 
 }  // namespace am_host

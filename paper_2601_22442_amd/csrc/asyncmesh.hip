@@ -499,7 +499,7 @@ am_status am_export_state(const am_state *st, am_snapshot *out)
     out->magic = kSnapshotMagic;
     out->config_digest = config_digest(st->cfg);
     out->last_t = st->last_t;
-    out->next_lines_step = am_host::record_sized_step(st->record_step > st->last_t ? st->record_step : 0, 0);
+    out->next_lines_step = am_host::record_sized_step(st->record_step, st->last_t);
     for (uint32_t i = 0; i < AM_MAX_REPLICAS; ++i) { out->opt_steps[i] = st->opt_steps[i]; out->mu_product[i] = st->mu_product[i]; }
     out->delay_now = st->delay_now;
     out->reserved = 0;

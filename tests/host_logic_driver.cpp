@@ -75,7 +75,7 @@ int hl_average_weights_table(const am_config *c) { return am_host::average_weigh
 
 uint32_t hl_lds_for_residency(uint32_t need, uint32_t workgroups, uint32_t fixed) { return am_host::lds_for_residency(need, workgroups, fixed); }
 
-uint64_t hl_record_sized_step(uint64_t next_lines_step, uint32_t next_buf) { return am_host::record_sized_step(next_lines_step, next_buf); }
+uint64_t hl_record_sized_step(uint64_t record_step, uint64_t last_t) { return am_host::record_sized_step(record_step, last_t); }
 
 uint64_t hl_resumed_sized_step(uint64_t next_lines_step, uint32_t reserved)
 {

@@ -164,11 +164,12 @@ def test_list_parts_cover_the_stage_and_fit_their_scratch(hl, compute_units):
 
 
 def test_a_record_names_sizes_that_every_build_finds(hl):
-    """Sizes are named only where they lie in the first table, which is the one every build reads; a record whose
+    """A record passes on the sized step it was resumed with as long as that step is still to come, and names none of its own; a record whose
     reserved field is not zero may mean another table, so nothing in it counts as sized."""
-    for f in (hl.hl_record_sized_step, hl.hl_resumed_sized_step):
-        f.argtypes, f.restype = [C.c_uint64, C.c_uint32], C.c_uint64
-    assert hl.hl_record_sized_step(9, 0) == 9 and hl.hl_record_sized_step(9, 1) == 0 and hl.hl_record_sized_step(0, 0) == 0
+    hl.hl_record_sized_step.argtypes, hl.hl_record_sized_step.restype = [C.c_uint64, C.c_uint64], C.c_uint64
+    hl.hl_resumed_sized_step.argtypes, hl.hl_resumed_sized_step.restype = [C.c_uint64, C.c_uint32], C.c_uint64
+    assert hl.hl_record_sized_step(9, 8) == 9 and hl.hl_record_sized_step(9, 9) == 0 and hl.hl_record_sized_step(9, 1 << 40) == 0
+    assert hl.hl_record_sized_step(1 << 40, 8) == 1 << 40 and hl.hl_record_sized_step(0, 0) == 0
     assert hl.hl_resumed_sized_step(9, 0) == 9
     assert all(hl.hl_resumed_sized_step(9, r) == 0 for r in (1, 2, 3, 1 << 31))
 
