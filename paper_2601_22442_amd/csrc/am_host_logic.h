@@ -240,10 +240,12 @@ inline uint32_t step_workgroups(const am_config &c, const Blocks &b, bool forwar
 // it; sync: no delay.  Every workgroup does it, so with more blocks, or more waves a tile (no delay), it pays on fewer tiles.  Time added up / offsets launched:
 // R = 4 AdamW interleaved 100,003 0.77, 480k 0.85, 1M 0.94, 1.6M 1.00, SGD 1.3M 0.97, 1.6M 1.08; R = 3 1.6M 0.97, 2M 1.08; R = 2 2M 0.94; R = 8 1M 0.96, 2M 0.98; R = 12 1M 0.98,
 // 2M 1.00.  R = 20 250k AdamW 1.02, SGD 0.91, 480k 1.03, 0.94, 1.5M 1.13, p = 100 % 700k 1.10, 1.4M 1.14; R = 24 480k 0.99, 0.96; R = 32 150k 0.98, 0.99, 250k 1.01,
-// 1.04, 740k 1.13.  No delay: R = 8 2M 0.98; R = 9 250k 0.90, 480k 1.00, 1M 1.05; R = 12 250k 0.91, 600k 1.02, 2M 1.07; R = 16 250k 0.93, 1M 1.02, 1.3M 1.07; R = 20 and more 0.96 to 1.00.
+// 1.04, 740k 1.13.  No delay: R = 8 2M 0.98; R = 5 plain SGD 1M 0.99, 1.3M 1.02, 1.6M 1.05, 2M 1.07, AdamW 2M 0.99; SGD and AdamW R = 9 250k 0.90, 400k 0.96, 480k 1.00, 650k 0.97 to 1.00, 1M 1.05; R = 12 250k 0.91, 300k 0.95, 600k 0.96 to 1.02, 2M 1.07; R = 16 250k 0.93, 300k 0.95, 400k to
+// 650k 0.97, 1M 0.97 to 1.02, 1.3M 1.07; R = 13 and 14 300k 1.05, 450k 1.03 and 1.06, 650k 1.03 and 1.05; R = 20 and more 0.96 to 1.00.
 inline uint32_t step_sum_tiles(const am_config &c, const Blocks &b, bool sync)
 {
-    if (sync) return c.replicas > 8u && c.replicas <= 16u ? 1024u : 8192u;
+    if (sync && c.replicas > 8u && c.replicas <= 16u) return c.replicas == 13u || c.replicas == 14u ? 1024u : 2560u;
+    if (sync) return c.replicas >= 5u && c.replicas <= 7u && c.optimizer == AM_OPT_SGD && c.beta1 == 0.f ? 4608u : 8192u;
     return b.nblocks == 4u ? 768u : b.nblocks == 3u ? 2048u : b.rb == 4u ? 6144u : 8192u;
 }
 

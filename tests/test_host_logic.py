@@ -233,7 +233,8 @@ def test_lds_holds_as_many_workgroups_as_a_rule_names(hl, workgroups, fixed):
 def test_steps_add_up_offsets_on_fewer_tiles_with_more_blocks(hl):
     tiles = {(R, sync): hl.hl_step_sum_tiles(C.byref(_config(replicas=R, delay=0 if sync else 1)), sync) for R in range(1, 33) for sync in (0, 1)}
     assert all(tiles[R, 0] == (8192 if R <= 2 else 6144 if R <= 4 else 8192 if R <= 16 else 2048 if R <= 24 else 768) for R in range(1, 33))
-    assert all(tiles[R, 1] == (1024 if 9 <= R <= 16 else 8192) for R in range(1, 33))
+    assert all(tiles[R, 1] == (8192 if R <= 8 or R > 16 else 1024 if R in (13, 14) else 2560) for R in range(1, 33))
+    assert all(hl.hl_step_sum_tiles(C.byref(_config(replicas=R, delay=0, optimizer=0, beta1=0.0)), 1) == (4608 if 5 <= R <= 7 else tiles[R, 1]) for R in range(1, 33))
 
 
 @pytest.mark.parametrize("kw", [dict(subset_granule=32), dict(subset_kind=1), dict(subset_kind=1, fraction=0.01), dict(fraction=0.3), dict(fraction=0.3, subset_granule=32), {}])
