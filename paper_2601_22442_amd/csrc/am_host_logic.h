@@ -272,11 +272,19 @@ inline uint32_t local_step_workgroups(const am_config &c)
 }
 
 // Whether the averaging-only kernel finds the replicas' weights in a table, a block's pointers in one line of the kernel's arguments, or in the
-// replicas' records, a line each.  The lines are cold at every launch, which short calls feel; but with a table the requests of a wave's eight
-// replicas leave closer together, which stages at the edge of the caches do not like.  Time table / records, R = 8, 5 %: 0.1M weights 0.72 / 0.82 of the code
-// before both, 4M 0.79 / 0.88; p = 100 %, no delay, interleaved 7.4M 1.11 / 0.96, 10M 1.14 / 0.98, 17.7M 1.04 / 0.95; 50 % without correction 8.2M 1.15 / 0.95; from 30M on the
-// same within 2 %.  Blocks of four: 1M 0.90 / 0.91, and no difference on large stages: the table always.
-inline bool average_weights_table(const am_config &c, const Blocks &b) { return b.rb != 8u || c.n * c.replicas <= 5ull << 20; }
+// replicas' records, a line each.  The lines are cold at every launch, which calls below 10M weights feel (0.82 to 0.95 of the time with a table), and it makes no difference
+// on large stages; but with a table the requests of a wave's eight replicas leave closer together, which stages at the edge of the caches do not like where they
+// ask for much at a time.  Time table / records, by weights (n R): staged EMA entries, R = 8 5 % 4M 0.92, 7M 1.07, 9.5M 1.06, 13M 0.99, R = 16 5 % 4M 0.91, 7M 1.12, 9.5M 1.14, 13M 0.98;
+// 0.2 % 4M 0.88, 7M 0.97, 9.5M 1.01.  No delay, R = 8 interleaved 100 % 4M 0.99, 7M 1.11, 13M 1.13, 18M 1.10, 26M 1.04, 50 % 7M 1.25, 9.5M 1.04; 25 % 7M 1.01; but R = 16 50 % 4M 0.89, 7M 0.93,
+// 13M 1.02.  No correction R = 8 50 % 7M 1.20, 13M 1.11, 25 % 0.98; R = 12 50 % 7M 0.97, 13M 0.96; R = 16 50 % 1.11, 1.03, 100 % 0.88, 0.96.  Members in whole lines 0.90 to 1.00.  Blocks of four: 1M 0.90 / 0.91
+// of the code before both, the table always.
+inline bool average_weights_table(const am_config &c, const Blocks &b)
+{
+    const uint64_t weights = c.n * c.replicas;
+    if (b.rb != 8u || c.subset_granule == 32 || weights <= 5ull << 20 || weights > 20ull << 20 || c.fraction <= 0.02) return true;
+    if (c.delay == 0 || c.correction == AM_CORR_NONE) return b.nblocks > 1u || c.fraction <= 0.4;
+    return weights > 23ull << 19;
+}
 
 // Workgroups (of four tiles, a wave each) of the staged averaging-only call that a compute unit may hold at a time; 0: as many as
 // fit.  Where the weights come from memory (more than the 256 MB cache holds) it is fastest with some 114 KB of lines a compute

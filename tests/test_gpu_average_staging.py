@@ -57,8 +57,8 @@ def test_forms_around_the_lines(amlib, n, R, p, kw, d_layout):
     run_average(amlib, n, R, 3, delay=1, fraction=p, d_layout=d_layout, **kw)
 
 
-@pytest.mark.parametrize("n,R", [((5 << 20) // 8, 8), ((5 << 20) // 8 + 1, 8), ((5 << 20) // 11, 11), ((5 << 20) // 11 + 1, 11), ((5 << 20) // 4 + 3, 3)])
+@pytest.mark.parametrize("n,R", [((5 << 20) // 8, 8), ((5 << 20) // 8 + 1, 8), ((5 << 20) // 11, 11), ((5 << 20) // 11 + 1, 11), ((5 << 20) // 4 + 3, 3), ((23 << 19) // 8, 8), ((23 << 19) // 8 + 1, 8), ((20 << 20) // 5 + 1, 5)])
 @pytest.mark.parametrize("tau,p", [(0, 0.05), (1, 0.05), (1, 0.9)])
 def test_where_the_weights_are_named(amlib, n, R, tau, p):
-    """Both sides of the line (5 * 2^20 weights of blocks of eight) from where the kernel takes the weights' pointers from the replicas' records."""
+    """Both sides of the lines between which, for blocks of eight, the kernel takes the weights' pointers from the replicas' records."""
     run_average(amlib, n, R, 3, delay=tau, fraction=p, d_layout=amlib.D_INTERLEAVED)

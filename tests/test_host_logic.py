@@ -283,7 +283,13 @@ def test_averaging_residency_follows_the_lines_and_the_turns(hl, weights, R, kw,
     assert hl.hl_average_workgroups(C.byref(_config(n=weights // R + (weights % R > 0), replicas=R, delay=1, **kw))) == workgroups
 
 
-def test_weights_of_blocks_of_eight_are_named_in_a_table_on_small_stages_only(hl):
-    for R in range(1, 33):
-        for n in ((5 << 20) // R, (5 << 20) // R + 1, 20_000_000):
-            assert bool(hl.hl_average_weights_table(C.byref(_config(n=n, replicas=R)))) == (R <= 4 or n * R <= 5 << 20)
+@pytest.mark.parametrize("R,kw,low,high", [
+    # in the records above `low` and up to `high` weights
+    (8, {}, 5 << 20, 23 << 19), (5, dict(fraction=1.0), 5 << 20, 23 << 19), (32, dict(fraction=0.03, d_layout=1), 5 << 20, 23 << 19), (8, dict(fraction=0.02), 0, 0), (8, dict(subset_granule=32), 0, 0), (4, {}, 0, 0),
+    (8, dict(delay=0, fraction=0.5), 5 << 20, 20 << 20), (8, dict(delay=0, fraction=0.4), 0, 0), (12, dict(delay=0, fraction=1.0), 0, 0), (6, dict(correction=0, fraction=0.5), 5 << 20, 20 << 20), (8, dict(correction=0, fraction=0.25), 0, 0),
+])
+def test_weights_of_blocks_of_eight_are_named_in_a_table_but_for_a_few(hl, R, kw, low, high):
+    kw = dict(dict(delay=1), **kw)
+    for weights in (1 << 20, 5 << 20, 23 << 19, 20 << 20):
+        for n in (weights // R, weights // R + 1, 50_000_000):
+            assert bool(hl.hl_average_weights_table(C.byref(_config(n=n, replicas=R, **kw)))) == (not low < n * R <= high)
