@@ -149,14 +149,14 @@ inline ListShape list_shape(const am_config &c, uint32_t compute_units)
 // Blocks of four and eight replicas, whose members' values change hands through LDS, are faster staged, except where a tile takes several turns
 // and everything the call touches lies in the caches; sizes here in weights including the slots of absent replicas.
 //   interleaved, R = 8, 20 % 0.2M 1.00, 3M 0.97, 8M 1.00, 16M 0.82; R = 5 25 % 5M 1.07; 30 % 2M 1.11, 5M 1.08, 6.5M 0.86, 16M 0.77; 50 % 2M 1.28, 5M 1.06, 6.5M 0.73; 100 % 2M 1.44, 3M 1.21, 4M 0.94, 5M 0.79;
-//     R = 12 30 % 3M 1.01, 50 % 3M 1.19, 4M 1.02, 5M 1.00, 100 % 3M 1.20, 4M 0.67; R = 20 50 % 2M 1.06, 3M 1.00; R = 4 40 % 2M 1.01, 50 % 2M 1.11, 3M 1.03, 4M 0.97; 10 to 20 % 8M 1.08 all the same.
+//     R = 12 30 % 3M 1.01, 50 % 3M 1.19, 4M 1.02, 5M 1.00, 100 % 3M 1.20, 4M 0.67; R = 20 50 % 2M 1.06, 3M 1.00; R = 4 40 % 2M 1.01, 50 % 2M 1.11, 3M 1.03, 4M 0.97; 10 % 4M 0.84, 7M 1.05, 9.5M 0.95, 25 % 4M 0.95, 5.5M 1.11, 7M 1.07, 9.5M 0.91.
 //   per replica, R = 8, 20 % 2M 1.01, 30 % 5M 1.14, 6.5M 0.99, 100 % 5M 1.12, 8M 0.83; R = 5 50 % 6.4M 1.10, 13M 1.04; R = 12 40 % 5M 1.17, 6.5M 1.10, 10M 0.85; R = 32 40 % 3M 1.06, 4M 0.94; R = 4 50 %
-//     4M 1.08, 5M 1.02, 6.5M 0.92; 5 to 20 % 8M 1.10 to 1.18 and R = 8 6 to 10 % 8M 1.10 all the same.
+//     4M 1.08, 5M 1.02, 6.5M 0.92; 5 % 4M 0.85, 5.5M 1.08, 7M 1.15, 9.5M 1.00, 25 % 4M 0.99, 5.5M 1.16, 7M 1.14, 9.5M 0.96.
 //   E4M3, interleaved R = 12 50 % 4M 1.15, 5M 1.11, 6.5M 0.98, 100 % 4M 0.91; R = 8 70 % 5M 1.15, 6.5M 0.77.
 //   members in whole lines, interleaved R = 8 8 % 2M 0.99, 10 % 1.05, 30 % 5M 1.27, 6.5M 1.00, 16M 0.54; R = 12 15 % 2M 1.04, 30 % 5M 1.17, R = 16 25 % 6M 1.11, R = 12 70 % 3M 1.32, 4M 0.98; R = 4 15 % 2M 1.03, 40 % 5M 1.04;
 //     per replica R = 8 8 % 2M 1.02, 20 % 8M 1.13, 10M 0.89, 70 % 6.5M 1.06, 8M 0.95; R = 20 20 % 8M 1.07, 10M 0.80; R = 4 30 % 6.5M 1.06, 50 % 5M 1.13, 70 % 0.99.
-//   no correction, R = 8 10 % 8M 0.96, 25 % 3M 1.11, 8M 1.14, 24M 1.02, 40M 0.92, 50 % 8M 1.27, 24M 1.04, 40M 0.99, 100 % 8M 1.11, 11M 1.01, 13M 0.97; R = 5 50 % 24M 1.12; R = 12 25 % 4M 1.01, 50 % 13M 1.02, 24M
-//     0.98, 100 % 5.5M 1.21, 7M 0.67; R = 20 35 % 5.5M 1.14, 8M 0.99, 100 % 3M 1.16, 4M 0.71; R = 4 35 % 4M 1.06, 5.5M 1.01, 50 % 4M 1.15, 5.5M 0.98; whole lines R = 8 10 % 8M 1.14, 11M 0.91, 50 % 16M 1.14,
+//   no correction, R = 8 10 % 8M 0.96, 25 % 3M 1.11, 8M 1.14, 24M 1.02, 40M 0.92, 50 % 8M 1.27, 24M 1.04, 40M 0.99, 100 % 8M 1.11, 11M 1.01, 13M 0.97; R = 5 50 % 24M 1.12, 37M 1.05, 120M 0.95, 100 % 64M 0.96, 128M 1.02, 200M 1.06; R = 12 25 % 4M 1.01, 7M 1.16, 9.5M 0.82, 13M 0.96, 50 % 13M 1.02, 24M
+//     0.98, 100 % 5.5M 1.21, 7M 0.67; R = 20 35 % 5.5M 1.14, 8M 0.99, 100 % 3M 1.16, 4M 0.71; R = 4 25 % 4M 0.99, 7M 1.13, 9.5M 1.04, 18M 0.91, 35 % 4M 1.06, 5.5M 1.01, 50 % 4M 1.15, 5.5M 0.98; whole lines R = 8 10 % 8M 1.14, 11M 0.91, 50 % 16M 1.14,
 //     24M 1.04, R = 5 1.09, 100 % 11M 1.01, 13M 0.98.
 // Blocks of one and two replicas have nothing to hand over: per-replica EMA vectors are dense reads in both forms, and the staged one gains with half a
 // turn at most, or at every fraction where the weights come from memory (11M R = 1 and 2 25 % 0.86 to 0.95, 100 % 0.80 to 0.91); interleaved
@@ -169,8 +169,8 @@ inline bool average_staged(const am_config &c, uint32_t ntiles, const Blocks &b,
         double few, small;                                 // staged up to this fraction; beyond, from this many millions of weights (with absent slots) on
         if (c.correction == AM_CORR_NONE) {                // half of what the caches would have to hold, and less to wait for
             few = by_line ? (!wide ? 0.12 : b.nblocks <= 2u ? 0.09 : 0.2) : !wide || b.nblocks > 2u ? 0.3 : one ? 0.17 : 0.2;
-            if (one) small = c.fraction > 0.8 ? 11.0 : by_line && c.fraction <= 0.2 ? 8.5 : 26.0;
-            else if (wide && b.nblocks == 2u) small = c.fraction > 0.8 ? 5.7 : c.fraction > 0.6 ? (by_line ? 6.0 : 11.0) : by_line && c.fraction <= 0.2 ? 8.5 : 17.0;
+            if (one) small = c.fraction > 0.8 ? 11.0 : by_line && c.fraction <= 0.2 ? 8.5 : !by_line && c.replicas <= 6u && c.fraction <= 0.6 ? 45.0 : 26.0;
+            else if (wide && b.nblocks == 2u) small = c.fraction > 0.8 ? 5.7 : c.fraction > 0.6 ? (by_line ? 6.0 : 11.0) : c.fraction <= (by_line ? 0.2 : 0.4) ? 8.5 : 17.0;
             else if (wide) small = c.fraction > 0.8 ? 3.5 : 5.7;
             else small = !by_line ? 4.2 : c.fraction <= 0.4 ? 8.5 : c.fraction <= 0.6 ? 5.7 : 4.2;
         } else {
@@ -184,8 +184,12 @@ inline bool average_staged(const am_config &c, uint32_t ntiles, const Blocks &b,
                 if (c.fraction > 0.8 && b.nblocks >= 3u && !e4m3) small = 3.5;
             }
         }
-        if (c.fraction <= few) return true;
-        return (double)c.n * b.rb * b.nblocks > small * 1e6;
+        const double slots = (double)c.n * b.rb * b.nblocks / 1e6;
+        // blocks of four with most of a tile's values in one turn: in place where the caches hold what is in place, but not what is staged besides
+        if (!wide && !by_line && c.fraction <= few && c.fraction > (c.correction == AM_CORR_NONE ? 0.15 : interleaved_d ? 0.08 : 0.03))
+            return slots <= 4.7 || slots > (c.correction == AM_CORR_NONE ? 10.0 : 8.5);
+        if (c.correction == AM_CORR_NONE && one && c.replicas <= 6u && c.fraction > 0.85 && slots > 110.0) return false;   // (absent slots' values pass through LDS, too)
+        return c.fraction <= few || slots > small;
     }
     const double drawn = c.fraction * am::kTileCoords, turn = (double)am::kStageFloats / b.rb;     // members of a tile, and those a turn holds
     if (!interleaved_d) return drawn <= 0.5 * turn || (!by_line && c.msg_dtype == AM_MSG_F32 && ntiles > 24576u);

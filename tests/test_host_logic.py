@@ -184,7 +184,10 @@ def test_a_record_names_sizes_that_every_build_finds(hl):
     (375_000, 12, dict(fraction=0.3, d_layout=0), False), (375_001, 12, dict(fraction=0.3, d_layout=0), True), (100_000, 20, dict(fraction=0.35), True), (100_000, 20, dict(fraction=0.36), False),
     (216_000, 20, dict(fraction=0.5, d_layout=0), False), (217_000, 20, dict(fraction=0.5, d_layout=0), True), (150_000, 20, dict(fraction=1.0, d_layout=0), True), (150_000, 20, dict(fraction=1.0, d_layout=0, msg_dtype=2), False),
     (110_000, 32, dict(fraction=0.5, d_layout=0), True), (109_000, 32, dict(fraction=0.5, d_layout=0), False),
-    # blocks of four
+    # blocks of four, also where the caches hold one form and not the other
+    (1_175_000, 4, dict(fraction=0.25, d_layout=0), True), (1_180_000, 4, dict(fraction=0.25, d_layout=0), False), (2_120_000, 3, dict(fraction=0.04, d_layout=0), False), (2_130_000, 3, dict(fraction=0.04, d_layout=0), True),
+    (1_500_000, 4, dict(fraction=0.03, d_layout=0), True), (1_500_000, 4, dict(fraction=0.08), True), (1_500_000, 4, dict(fraction=0.1), False), (1_500_000, 4, dict(fraction=0.1, subset_granule=32), True),
+    (2_400_000, 4, dict(fraction=0.2, correction=0), False), (2_510_000, 4, dict(fraction=0.2, correction=0), True), (2_000_000, 4, dict(fraction=0.15, correction=0), True),
     (500_000, 4, dict(fraction=0.45), True), (750_000, 4, dict(fraction=0.5), False), (750_001, 3, dict(fraction=0.5), True), (1_050_000, 4, dict(fraction=0.5, d_layout=0), False), (1_050_001, 4, dict(fraction=0.5, d_layout=0), True),
     # members in whole lines
     (500_000, 8, dict(fraction=0.09, subset_granule=32), True), (500_000, 8, dict(fraction=0.1, subset_granule=32), False), (700_000, 8, dict(fraction=0.1, subset_granule=32), True), (300_000, 12, dict(fraction=0.5, subset_granule=32), False),
@@ -195,7 +198,7 @@ def test_a_record_names_sizes_that_every_build_finds(hl):
     (500_000, 2, dict(fraction=0.4), True), (500_000, 2, dict(fraction=0.5), False), (3_200_000, 2, dict(fraction=0.5), True), (800_000, 2, dict(fraction=0.9), True), (800_000, 1, dict(fraction=1.0), True),
     # no correction
     (1_000_000, 8, dict(fraction=0.17, correction=0), True), (3_250_000, 8, dict(fraction=0.18, correction=0), False), (3_250_001, 8, dict(fraction=0.18, correction=0), True), (1_375_000, 8, dict(fraction=1.0, correction=0), False),
-    (1_375_001, 8, dict(fraction=1.0, correction=0), True), (1_000_000, 12, dict(fraction=0.5, correction=0), False), (1_070_000, 12, dict(fraction=0.5, correction=0), True), (700_000, 12, dict(fraction=0.7, correction=0), True),
+    (1_375_001, 8, dict(fraction=1.0, correction=0), True), (5_600_000, 5, dict(fraction=0.5, correction=0), False), (5_700_000, 5, dict(fraction=0.5, correction=0), True), (13_700_000, 5, dict(fraction=1.0, correction=0), True), (13_800_000, 5, dict(fraction=1.0, correction=0), False), (1_000_000, 12, dict(fraction=0.5, correction=0), False), (1_070_000, 12, dict(fraction=0.5, correction=0), True), (700_000, 12, dict(fraction=0.7, correction=0), True),
     (357_000, 12, dict(fraction=1.0, correction=0), True), (230_000, 20, dict(fraction=0.5, correction=0), False), (240_000, 20, dict(fraction=0.5, correction=0), True), (1_050_001, 4, dict(fraction=0.5, correction=0), True),
     (1_062_000, 8, dict(fraction=0.1, correction=0, subset_granule=32), False), (1_063_000, 8, dict(fraction=0.1, correction=0, subset_granule=32), True), (3_250_000, 8, dict(fraction=0.5, correction=0, subset_granule=32), False),
     (2_125_000, 4, dict(fraction=0.4, correction=0, subset_granule=32), False), (1_430_000, 4, dict(fraction=0.5, correction=0, subset_granule=32), True), (500_000, 12, dict(fraction=0.1, correction=0, subset_granule=32), False),
