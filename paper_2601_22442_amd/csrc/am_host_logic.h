@@ -294,16 +294,16 @@ inline bool average_weights_table(const am_config &c, const Blocks &b)
 // fit.  Where the weights come from memory (more than the 256 MB cache holds) it is fastest with some 114 KB of lines a compute
 // unit on their way; with more the streams get in each other's way, as in the fused step, with fewer latency shows.  So the number
 // follows from the lines that a wave reads.  But where a tile takes several turns, messages are rounded or the caches still help, latency is the
-// cost: then not fewer than three or four (R = 2 interleaved six); without a correction a wave has less to wait for (130 KB, none where most coordinates are drawn), and members
+// cost: then not fewer than three or four (R = 2 interleaved seven; three with absent replicas); without a correction a wave has less to wait for (130 KB, none where most coordinates are drawn), and members
 // in whole lines are not limited (interleaved, 80M, p = 40 % R = 8 3: 1.24, R = 4 4: 1.16, R = 12 3: 1.19).  Blocks of eight without interleaved EMA entries
 // that take several turns: none either, but for EMA vectors of more than 200M weights.
 // us a call by workgroups a compute unit, * the one chosen: interleaved, R = 8, 125.8M 5 % 2: 1711, 3: 1574*, 4: 1631, 8: 1675; 1 % 3: 1030, 5: 717, 6: 655, as many as
 // fit 636*.  Time over as many as fit, 250M weights (80M in brackets): interleaved R = 8 2 % 4: 0.96*, 3: 1.12; 5 % 3: 0.93*, 2: 0.99; 10 % 2: 0.94* (1.13, 3: 1.00*);
-// 40 % 2: 0.97*; 80 % 4: 0.99*, 2: 1.14; 100 % 4: 0.95*, 2: 1.31; R = 5 5 % 4: 0.91*, 5: 0.99; 10 % 3: 0.92*, 4: 0.98 (2: 1.18); R = 12 10 % 3: 0.96*, 20 % 2: 0.96* (3: 0.98*);
+// 40 % 2: 0.97*; 80 % 4: 0.99*, 2: 1.14; 100 % 4: 0.95*, 2: 1.31; R = 5 5 % 4: 0.91*, 5: 0.99; 10 % 3: 0.92*, 4: 0.98 (2: 1.18); 40 % 3: 0.96*, 2: 1.05; R = 12 10 % 3: 0.96*, 20 % 2: 0.96* (3: 0.98*);
 // R = 4 5 % 4: 0.92, 5: 0.96*; 40 % 3: 0.93*; 100 % 4: 0.93*, 2: 1.33; R = 20 20 % 2: 0.89* (160M 0.93, 3: 0.98*).  Per replica R = 8 5 % 2: 0.90* (3: 0.98*), 2 % 3: 0.95*; R = 5 5 % 3: 0.87*;
 // R = 4 5 % 4: 0.93*, 10 % 3: 0.93*, 100 % 4: 0.89*, 2: 1.29; R = 3 5 % 4: 0.92*, 100 % 4: 0.97*, 2: 1.56.  No correction R = 8 5 % 4: 0.92*, R = 12 5: 1.01*, 4: 1.04;
 // R = 4 40 % 5: 0.91*, R = 3 80 % 5: 1.20.  E4M3 interleaved R = 8 10 % 5: 1.00 (2: 1.26), R = 5 20 % 4: 0.99* (2: 1.10), R = 12 5 % 4: 0.94, 3: 1.01 (1.16); R = 20 and 32 5 % 4: 0.93 to 1.07, 3: 1.03 to 1.22.
-// R = 2 interleaved 40 % 6: 0.96*, 100 % 6: 0.95*, 5: 1.03, R = 3 per replica 20 % 3: 1.05, 4: 0.98*.  Several turns of eight, per replica, 120M, R = 12 25 % 3: 1.03, 50 % 1.04, R = 5 25 % 1.00,
+// R = 2 interleaved, 103M 40 % 6: 0.95*, 5: 0.95, 50 % 7: 1.01*, 6: 1.05, 5: 1.12, 70 % 7: 0.99*, 6: 1.02, 100 % 7: 0.98*, 6: 0.98, 5: 1.04, R = 3 per replica 20 % 3: 1.05, 4: 0.98*.  Several turns of eight, per replica, 120M, R = 12 25 % 3: 1.03, 50 % 1.04, R = 5 25 % 1.00,
 // 50 % 1.18; 220M R = 12 25 % 3: 0.95*, 50 % 0.97*, R = 5 25 % 0.91*, 50 % 4: 0.98*, R = 16 50 % 3: 0.92*, R = 8 100 % 4: 0.98*; no correction, 120M R = 8 25 % 4: 1.03, 3: 1.20, 50 % 1.08, 1.27, R = 12 25 % 1.05, 1.21.
 inline uint32_t average_workgroups(const am_config &c, const Blocks &b, bool interleaved_d)
 {
@@ -323,7 +323,8 @@ inline uint32_t average_workgroups(const am_config &c, const Blocks &b, bool int
     uint32_t least = 2;
     if (c.msg_dtype != AM_MSG_F32 || c.fraction > 0.5 || weights <= 3ull << 25 || (b.nblocks > 2u && weights <= 3ull << 26)) least = 3;
     if (e4m3 || (b.nblocks == 1u && c.fraction > 0.7) || (c.replicas == 3u && !interleaved_d)) least = 4;
-    if (c.replicas == 2u && interleaved_d && c.fraction > 0.7) least = 6;
+    if (absent) least = std::max(least, 3u);
+    if (c.replicas == 2u && interleaved_d && c.fraction > 0.45) least = 7;
     return std::max(least, (uint32_t)workgroups);
 }
 
@@ -341,7 +342,7 @@ constexpr bool residency_is_exact(uint32_t workgroups)
     const uint32_t granules = (lds_for_residency(1, workgroups) + am::kLdsGranule - 1u) / am::kLdsGranule;
     return workgroups * granules <= kLdsGranules && (workgroups + 1u) * granules > kLdsGranules;
 }
-static_assert(residency_is_exact(2) && residency_is_exact(3) && residency_is_exact(4) && residency_is_exact(5) && residency_is_exact(6) && residency_is_exact(11),
+static_assert(residency_is_exact(2) && residency_is_exact(3) && residency_is_exact(4) && residency_is_exact(5) && residency_is_exact(6) && residency_is_exact(7) && residency_is_exact(11),
               "as many as a rule names fit, and not one more");
 
 // Floats of one array of the EMA vectors and how many arrays there are, per layout.

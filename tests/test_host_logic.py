@@ -224,7 +224,7 @@ def test_step_residency_follows_what_a_wave_moves(hl, n, R, kw, fwd, receives, w
     assert hl.hl_step_workgroups(C.byref(_config(n=n, replicas=R, delay=1, **kw)), fwd, receives) == workgroups
 
 
-@pytest.mark.parametrize("workgroups", [2, 3, 4, 5, 6, 11])
+@pytest.mark.parametrize("workgroups", [2, 3, 4, 5, 6, 7, 11])
 @pytest.mark.parametrize("fixed", [0, 16])
 def test_lds_holds_as_many_workgroups_as_a_rule_names(hl, workgroups, fixed):
     """160 KB of LDS in granules of 1280 bytes: that many fit, one more does not; a larger need is kept, and 0 limits nothing."""
@@ -276,8 +276,8 @@ def test_steps_between_rounds_have_a_kernel_of_their_own_where_it_pays(hl, weigh
     # tiles of eight replicas that take several turns, without interleaved EMA entries; R = 2 and 3
     (120_000_000, 8, dict(d_layout=0, fraction=0.1), 2), (120_000_000, 8, dict(d_layout=0, fraction=0.25), 0), (120_000_000, 12, dict(d_layout=0, fraction=0.5), 0), (220_000_000, 12, dict(d_layout=0, fraction=0.5), 3),
     (220_000_000, 5, dict(d_layout=0, fraction=0.25), 4), (220_000_000, 8, dict(d_layout=0, fraction=1.0), 4), (220_000_000, 8, dict(d_layout=0, fraction=0.25, msg_dtype=1), 0),
-    (220_000_000, 8, dict(correction=0, fraction=0.25), 0), (120_000_000, 5, dict(d_layout=0, fraction=0.25, msg_dtype=2), 0), (120_000_000, 2, dict(d_layout=1, fraction=0.4), 6), (120_000_000, 2, dict(d_layout=1, fraction=1.0), 6),
-    (90_000_000, 3, dict(d_layout=0, fraction=0.2), 4),
+    (220_000_000, 8, dict(correction=0, fraction=0.25), 0), (120_000_000, 5, dict(d_layout=0, fraction=0.25, msg_dtype=2), 0), (120_000_000, 2, dict(d_layout=1, fraction=0.4), 6), (120_000_000, 2, dict(d_layout=1, fraction=0.5), 7), (120_000_000, 2, dict(d_layout=1, fraction=1.0), 7),
+    (90_000_000, 3, dict(d_layout=0, fraction=0.2), 4), (126_000_000, 5, dict(d_layout=1, fraction=0.5), 3),
     # rounded messages; no correction where most are drawn; members in whole lines
     (250_000_000, 8, dict(d_layout=1, fraction=0.2, msg_dtype=1), 3), (250_000_000, 8, dict(d_layout=1, fraction=0.2, msg_dtype=2), 4), (250_000_000, 20, dict(d_layout=1, msg_dtype=2), 0),
     (250_000_000, 4, dict(correction=0, fraction=0.4), 5), (250_000_000, 4, dict(correction=0, fraction=0.8), 0), (250_000_000, 8, dict(d_layout=1, fraction=0.4, subset_granule=32), 0),
