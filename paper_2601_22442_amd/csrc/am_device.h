@@ -208,16 +208,16 @@ __device__ __forceinline__ void store_f32x4(float *__restrict__ p, uint64_t mu, 
     }
 }
 
-// A store that goes through to memory (system scope) besides the non-temporal hint, of 16 or 8 bytes at float / element `mu` of
+// A store at the scope of the whole device (past the XCD's own cache, whose lines other XCDs do not see) besides the non-temporal hint, of 16 or 8 bytes at float / element `mu` of
 // p, the same for the whole wave.  The stream mix of the fused step on 125.8M x 8 without its arithmetic: 5.66 ms, 5.82 with the
 // hint alone; but a working set that the caches hold from call to call loses by it (500k x 4 +4 %).
 template <typename T>
 __device__ __forceinline__ void store_through(void *p, uint32_t byte, const T &x)
 {
-    constexpr int kNt = 2, kSystem = 16;
+    constexpr int kNt = 2, kDevice = 16;
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(p, 0, kTileCoords * 4u, 0x00020000);      // one tile's kilobyte: nothing is written past it
-    if constexpr (sizeof(T) == 16) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, x), r, (int)byte, 0, kNt | kSystem);
-    else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, x), r, (int)byte, 0, kNt | kSystem);
+    if constexpr (sizeof(T) == 16) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, x), r, (int)byte, 0, kNt | kDevice);
+    else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, x), r, (int)byte, 0, kNt | kDevice);
 }
 
 // store_f32x4 at float `at` of a tile's part of an array; through: see store_through

@@ -6,7 +6,7 @@
 //                tile's word is its offset inside the superblock, and each superblock has a base
 //   strip      = 64 lanes x 32 consecutive coordinates = 8 tiles: what one wavefront hashes at a time
 //                where only the subset matters (one 32-bit mask per lane, in coordinate order)
-//   line       = 128 bytes = 32 floats, the unit in which memory is written
+//   line       = 128 bytes = 32 floats, the unit in which memory is read (written: half a line)
 //   block      = up to 8 replicas whose sparse values sit side by side in memory
 #pragma once
 #include <stdint.h>

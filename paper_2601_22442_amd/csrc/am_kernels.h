@@ -687,7 +687,7 @@ __device__ __forceinline__ void tile_means(const StepArgs &a, const TileLds &L, 
 // of every per-replica array once, with non-temporal accesses (measured on MI355X: the fastest way
 // through the 4-read / 4-write stream mix of this update).
 //
-// This memory system moves 128-byte lines, and a partial write costs several whole ones.  S^t is
+// This memory system reads 128-byte lines and writes their 64-byte halves; a write of part of a half costs several whole ones.  S^t is
 // the same for every replica, so the sparse structures keep the replicas of a block side by side,
 // [coordinate][replica]: a line holds 32 / rb coordinates of all rb replicas and is written as a whole.
 //  * Ring slot: per block, every tile owns ceil(count rb / 32) whole lines ([block][line][32]); the
@@ -696,9 +696,9 @@ __device__ __forceinline__ void tile_means(const StepArgs &a, const TileLds &L, 
 //    many there are, so the lines sent tau rounds ago are requested without any hashing, straight
 //    into LDS; the waves gather this step's values in LDS and the lines leave with 16 bytes per thread.
 //  * EMA vector d, interleaved layout: [coordinate][replica] per block.  Lines that hold a received
-//    coordinate are copied to LDS (16 bytes per lane), updated there and written back whole.
-//    Per-replica layout: dense per replica; the 8 lanes that share a 128-byte line of d load and
-//    store their groups together whenever any of them holds a received coordinate.
+//    coordinate are copied to LDS (16 bytes per lane) and updated there; of each, the halves that hold one are
+//    written back.  Per-replica layout: dense per replica; the 8 lanes that share a line of d load their
+//    groups together whenever any of them holds a received coordinate, and the 4 that share a half store theirs.
 // Hashing a subset costs ten rounds of two 32 x 32 -> 64 multiplies per lane; the subsets are the
 // same for every wave of the workgroup, so (fused step) one wave hashes the received subset, one
 // the sent one, one the next step's, and the others read the 4-bit masks from LDS after the barrier
@@ -1285,7 +1285,7 @@ __device__ __forceinline__ void average_send_block(float *slot, const F4 (&w)[RB
 
 // Coordinate j of the group receives the old average abar: EMA of the staleness of each replica of the
 // block (own[k] = what replica k itself sent), corrected weight.  dp: the coordinate's RB entries of the
-// interleaved EMA vector (DIL; d_old: the same or their copy in LDS), else the entries are in dv.  HALVES: the
+// interleaved EMA vector (DIL; in memory or their copy in LDS), else the entries are in dv.  HALVES: the
 // replicas' fp64 values are formed four at a time, not eight (76 registers instead of 84).
 template <bool DIL, int RB, bool HALVES>
 __device__ __forceinline__ void average_receive(const StepArgs &a, int j, float abar, const float (&own)[RB], float *dp, F4 (&w)[RB], F4 (&dv)[RB])
