@@ -286,19 +286,31 @@ __device__ __forceinline__ uint16_t f64_to_bf16_bits(double x)
     return f32_to_bf16_bits(f);
 }
 
-__device__ __forceinline__ void store_bf16x4_from_f64(uint16_t *__restrict__ p, uint64_t mu, int nvalid, const double (&x)[4], bool through = false)
+// Four bfloat16 at element mu of p
+__device__ __forceinline__ void store_bf16x4(uint16_t *__restrict__ p, uint64_t mu, const uint16_t (&x)[4], int nvalid, bool through)
 {
     if (nvalid == 4) {
-        v2u t;
-        t.x = (uint32_t)f64_to_bf16_bits(x[0]) | ((uint32_t)f64_to_bf16_bits(x[1]) << 16);
-        t.y = (uint32_t)f64_to_bf16_bits(x[2]) | ((uint32_t)f64_to_bf16_bits(x[3]) << 16);
+        const v2u t = {(uint32_t)x[0] | ((uint32_t)x[1] << 16), (uint32_t)x[2] | ((uint32_t)x[3] << 16)};
         if (through) store_through(p, (uint32_t)mu * 2u, t);
         else __builtin_nontemporal_store(t, reinterpret_cast<v2u *>(p + mu));
     } else {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            if (j < nvalid) p[mu + j] = f64_to_bf16_bits(x[j]);
+            if (j < nvalid) p[mu + j] = x[j];
     }
+}
+
+__device__ __forceinline__ void store_bf16x4_from_f64(uint16_t *__restrict__ p, uint64_t mu, int nvalid, const double (&x)[4], bool through = false)
+{
+    const uint16_t h[4] = {f64_to_bf16_bits(x[0]), f64_to_bf16_bits(x[1]), f64_to_bf16_bits(x[2]), f64_to_bf16_bits(x[3])};
+    store_bf16x4(p, mu, h, nvalid, through);
+}
+
+// fp32 values have one rounding on their way (without look-ahead the forward copy is the rounded weight)
+__device__ __forceinline__ void store_bf16x4_from_f32(uint16_t *__restrict__ p, uint64_t mu, int nvalid, const F4 &x, bool through)
+{
+    const uint16_t h[4] = {f32_to_bf16_bits(x.v[0]), f32_to_bf16_bits(x.v[1]), f32_to_bf16_bits(x.v[2]), f32_to_bf16_bits(x.v[3])};
+    store_bf16x4(p, mu, h, nvalid, through);
 }
 
 }  // namespace am

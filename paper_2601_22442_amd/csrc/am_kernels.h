@@ -551,7 +551,9 @@ __device__ __forceinline__ void store_weights(const StepArgs &a, const ReplicaAr
                                               const F4 &w_hat, const F4 &w_new)
 {
     store_tile_f32x4(r.w + tbase, loff, nvalid, w_new, a.through != 0u);
-    if (FWD != kFwdNone) {
+    if (FWD == kFwdBf16 && !a.lookahead) {
+        store_bf16x4_from_f32(static_cast<uint16_t *>(r.fwd) + tbase, loff, nvalid, w_new, a.through != 0u);
+    } else if (FWD != kFwdNone) {
         // fwd = w + gamma (w^ - w_before): product and sum rounded separately in fp64, then ONE
         // rounding to the stored type
         double f[4];
