@@ -253,6 +253,37 @@ inline uint32_t step_sum_tiles(const am_config &c, const Blocks &b, bool sync)
     return b.nblocks == 4u ? 768u : b.nblocks == 3u ? 2048u : b.rb == 4u ? 6144u : 8192u;
 }
 
+// Whether a step with a delay goes through the kernel of one-wave workgroups instead of the fused kernel's workgroup per tile and block.  Median time by
+// waves / by the fused kernel over random configurations (all optimizers, p = 0.2 to 10 %; 10 % of them are above the figure in brackets, as the placement of the
+// arrays alone moves either by 5 %):
+//   per-replica EMA vectors by replicas, from 30M weights on: 5 0.94, 6 0.96, 7 0.96, 8 0.97, 9 0.77, 12 0.94, 16 0.98, 24 and 32 0.98; by weights: 30M 0.98 (1.01), 60M 0.97 (1.00), 200M 0.95 (0.98);
+//     by fraction: 5 % 0.95, 10 % 0.97, but 20 % 1.02 to 1.06, 50 % 1.3.
+//   no correction: 5 0.96, 6 0.98, 7 0.98, 8 0.98, 9 0.81, 12 0.97, 16 0.98 (2000M in bf16 0.96), 24 0.99 (1.03), 32 0.99 (1.02); 30M and 50M 0.99 (1.03), 60M 0.98 (1.01), 100M and more 0.97 (1.00).
+//   where many of a block's slots are absent, from 13M weights on: 5 per replica 0.95, without 0.98; the others at 15M to 25M 1.00 to 1.02.
+//   interleaved EMA vectors: R = 8 0.5 % 0.99, 2 % 1.00, 5 % 1.01 (1.06), 10 % 1.05.  Blocks of four 0.99 (1.01), of two 1.02 (1.09), single replicas 1.03 (1.14).  Fewer weights: 8M 1.00 (1.05).
+inline bool step_by_waves(const am_config &c, const Blocks &b)
+{
+    if (b.rb != 8u || c.fraction > 0.1) return false;
+    if (c.correction != AM_CORR_NONE ? c.d_layout == AM_D_INTERLEAVED : c.replicas > 16u) return false;
+    const bool idle = c.replicas == 5u || (c.replicas >= 9u && c.replicas <= 11u);         // a third of the fused kernel's waves or more
+    return c.n * c.replicas > (idle ? 3ull << 22 : c.correction != AM_CORR_NONE ? 5ull << 23 : 1ull << 26);
+}
+
+// Replicas that a wave of that kernel takes: two share the hashing and send pairs of values (R = 12 10M 0.96 either way, R = 32 4M 0.98 / 0.965).
+inline uint32_t wave_step_replicas(const am_config &c) { return c.replicas % 2u ? 1u : 2u; }
+
+// Waves of it that a compute unit may hold: 75 KB of requested operands on their way, 84 where a wave takes two replicas (80 without a correction).
+// us a step by their number, one replica a wave: R = 7 20M per replica 14: 875, 16: 873, 18: 884; two: bf16 R = 16 125.8M no correction 8: 10615, 10: 9704, 12: 9581, 16: 9848;
+// AdamW R = 8 31.5M no correction 8: 1391, 10: 1348, 12: 1367, per replica 8: 1610, 10: 1610, 12: 1654.
+inline uint32_t wave_step_workgroups(const am_config &c, uint32_t v, bool receives)
+{
+    const bool ema = c.correction != AM_CORR_NONE;
+    const double moments = c.optimizer != AM_OPT_SGD ? 2.0 : c.beta1 != 0.f ? 1.0 : 0.0;
+    double kb = 1.0 + (c.grad_dtype == AM_BF16 ? 0.5 : 1.0) + moments;
+    if (receives && ema) kb += 1.0 - std::pow(1.0 - c.fraction, (double)am::kLineFloats);
+    return (uint32_t)std::floor((v == 1u ? 75.0 : ema ? 42.0 : 40.0) / kb + 0.5);
+}
+
 // Whether a step between two averaging rounds (which neither sends nor receives) goes through the kernel of its own.  It pays for blocks of
 // eight waves; the kernel change costs the round's step some microseconds of cold instructions, which every second or third step feels on larger
 // stages than every fourth, and full blocks more than those whose absent slots idle.  Time by its own / by the fused kernel on average over rounds, by weights (n R):

@@ -660,14 +660,14 @@ __device__ __forceinline__ void load_block_values(const float *p, float (&x)[RB]
 }
 
 // Mean over the replicas, in replica order and in fp64, of what they sent for the coordinate of
-// rank c of the tile (recv: [block][rank][RB]): the RB values of a block come with one or two wide
+// rank c of the tile (recv: [block][rank][RB], `stride` floats a block): the RB values of a block come with one or two wide
 // LDS reads.  ABSENT: the slots of absent replicas may hold anything; else they hold zeros, which add nothing.
 template <int RB, bool ABSENT>
-__device__ __forceinline__ float replica_mean(const StepArgs &a, const float *recv, uint32_t c)
+__device__ __forceinline__ float replica_mean(const StepArgs &a, const float *recv, uint32_t c, uint32_t stride = kTileCoords * RB)
 {
     double sum = 0.;
     for (uint32_t b = 0; b < a.nblocks; ++b) {
-        const float *p = recv + b * (kTileCoords * RB) + c * RB;
+        const float *p = recv + b * stride + c * RB;
         float x[RB];
         load_block_values<RB>(p, x);
         if (a.msg_dtype != 0u) {
@@ -1056,6 +1056,193 @@ k_step_local(const StepArgs a)
     if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_tile_f32x4(rep.m + tbase, loff, nvalid, m_new, a.through != 0u);
     if (OPT == kOptAdam) store_tile_f32x4(rep.v + tbase, loff, nvalid, v_new, a.through != 0u);
     store_weights<FWD>(a, rep, tbase, loff, nvalid, in, w_hat, w_hat);
+}
+
+// V floats at byte `byte` of a resource; past its end nothing moves.
+template <int V> struct Entry { float v[V]; };
+template <int V>
+__device__ __forceinline__ void store_entry(__amdgpu_buffer_rsrc_t r, uint32_t byte, const Entry<V> &x)
+{
+    if constexpr (V == 2) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, x), r, (int)byte, 0, 0);
+    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), r, (int)byte, 0, 0);
+}
+
+// The step of large stages with a delay and no interleaved EMA vectors (am_host::step_by_waves): a workgroup is ONE wave, which takes V
+// neighbouring replicas of a block through one tile; no barrier, and what the replicas of a tile share meets in the L2.
+// What it buys is order.  The stream mix moves faster the fewer streams are on their way at a time and the finer the grain in which waves come and go
+// (without arithmetic, 125.8M x 8: a workgroup of eight waves a tile 5.7 TB/s with three of them a compute unit and 6.2 with two; one-wave workgroups, 16 a
+// compute unit, 6.1 with a tile's replicas side by side and 6.6 with the replicas of a chunk of 512 tiles one after the other).  So the grid
+// runs over the tiles of a chunk, then its replicas, then the chunks: the waves of one tile are on the same XCD (consecutive workgroups go round the eight) and
+// near enough in time that its ring lines are fetched from memory once and that the parts of the lines it sends merge in the
+// L2 (bytes by the counters as in k_step: 28.4 + 28.3 GB on 125.8M x 16).  The price is in requests: every wave asks for the ring lines, and sends
+// V values of a coordinate at a time, so it pays up to a fraction of 10 %; an interleaved EMA vector, read and written V entries at a
+// time, costs more than the order gives (125.8M x 8 5 %: 5814 / 5846 us), and so do narrower blocks.
+// us a step, k_step / this: per replica, R = 8 31.5M 5 % 1700 / 1586 (9.6 GB: 6.0 TB/s), R = 5 25M 830 / 784, R = 12 10M 818 / 788; no correction R = 8
+// 31.5M 1414 / 1337, bf16 R = 16 125.8M 1 % 9973 / 9518.
+template <int OPT, bool GRAD_BF16, int FWD, int V, bool FULL>
+__device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile, const uint32_t i0, const uint32_t lane, float *lds)
+{
+    const uint32_t sh = a.rb_shift, b = i0 >> sh, slot = i0 & (a.rb - 1u);
+    const uint64_t group = (uint64_t)tile * 64u + lane;
+    const uint64_t mu = group * 4u;
+    const int nvalid = FULL ? 4 : (mu >= a.n ? 0 : (a.n - mu >= 4u ? 4 : (int)(a.n - mu)));
+    const uint64_t tbase = (uint64_t)tile * kTileCoords;
+    const uint32_t loff = lane * 4u;
+    const uint64_t block_floats = (uint64_t)a.cap_lines * kLineFloats;
+    constexpr uint32_t kNone = 0x40000000u;                  // past the end of every resource
+    float *const ring = lds, *const mean = ring + a.nblocks * kStageFloats;
+
+    // ---- dense operands: nothing else is requested before them
+    const ReplicaArgs *const rep = a.rep + 8u * b + slot;
+    GroupIn in[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) load_group<OPT, GRAD_BF16>(rep[v], tbase, loff, nvalid, in[v]);
+    float factor[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) factor[v] = replica_factor(a, i0 + v);
+    __builtin_amdgcn_sched_barrier(0);
+
+    uint32_t word_s = 0, base_s = 0, word_r = 0, base_r = 0;
+    if (a.do_send) { word_s = uniform_load(a.send_meta, tile); base_s = uniform_load(a.send_sb_base, tile / kTilesPerSuperblock); }
+    if (a.do_recv) { word_r = uniform_load(a.recv_meta, tile); base_r = uniform_load(a.recv_sb_base, tile / kTilesPerSuperblock); }
+    // a tile whose lines would pass the slot capacity is left out, at send and at receive alike
+    const uint32_t first_s = base_s + (word_s & 0xFFFFFFu), first_r = base_r + (word_r & 0xFFFFFFu);
+    uint32_t lines_s = word_s >> 24, lines_r = word_r >> 24;
+    if ((uint64_t)first_s + lines_s > a.cap_lines) lines_s = 0;
+    if ((uint64_t)first_r + lines_r > a.cap_lines) lines_r = 0;
+
+    // ---- what every replica sent tau rounds ago goes straight into LDS, a kilobyte of every block (a turn) at a time
+    auto request_ring = [&](const uint32_t c0) {             // from rank c0 on
+        const uint32_t at = (c0 << sh) + loff;
+        if (at < lines_r * kLineFloats) {
+            const float *src = a.ring_recv + (uint64_t)first_r * kLineFloats + at;
+            for (uint32_t q = 0; q < a.nblocks; ++q) lds_dma_16(src + q * block_floats, ring + q * kStageFloats);
+        }
+    };
+    SubsetKey key = a.key;
+    uint32_t mask_recv = 0, rank_recv = 0, count_recv = 0;
+    bool half_recv = false;                                  // the 64 bytes of a per-replica array (4 lanes) holding the group receive something
+    if (lines_r) {
+        request_ring(0u);
+        key.step_lo = a.step_lo[0]; key.step_hi = a.step_hi[0];
+        mask_recv = member_mask(key, group, nvalid);
+        half_recv = ((__ballot(mask_recv != 0u) >> (lane & ~3u)) & 0xFull) != 0ull;
+        if (a.ema && half_recv) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) in[v].d = load_f32x4(a.d[i0 + v] + tbase, loff, nvalid);
+        }
+        rank_recv = wave_prefix_mask4(mask_recv, count_recv);
+    }
+    uint32_t mask_send = 0, rank_send = 0, count_send = 0;
+    if (lines_s) {
+        key.step_lo = a.step_lo[1]; key.step_hi = a.step_hi[1];
+        mask_send = member_mask(key, group, nvalid);
+        rank_send = wave_prefix_mask4(mask_send, count_send);
+    }
+    if (a.do_next && i0 == 0u) {                             // how many lines the tile sends next step
+        key.step_lo = a.step_lo[2]; key.step_hi = a.step_hi[2];
+        uint32_t count;
+        (void)wave_prefix_mask4(member_mask(key, group, nvalid), count);
+        if (lane == 0) a.next_lines[tile] = (uint8_t)((count * a.rb + kLineFloats - 1u) / kLineFloats);
+    }
+    __builtin_amdgcn_sched_barrier(0);                       // (the operands' conversions stay behind the hashing)
+
+    F4 w_hat[V], w_new[V], m_new[V], v_new[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) local_step<OPT>(a, rep[v], factor[v], in[v], w_hat[v], m_new[v], v_new[v]);
+    lds_dma_wait();                                          // (before the first store: the wait counts stores, too)
+    wave_lds_sync();
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_tile_f32x4(rep[v].m + tbase, loff, nvalid, m_new[v], a.through != 0u);
+        if (OPT == kOptAdam) store_tile_f32x4(rep[v].v + tbase, loff, nvalid, v_new[v], a.through != 0u);
+        w_new[v] = w_hat[v];
+    }
+
+    // ---- send: my replicas' values of every coordinate at its rank, zeros in the rest of the tile's last line.  (The slots of absent replicas are
+    //      neither written nor read.)
+    if (lines_s) {
+        const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(a.ring_send + b * block_floats + (uint64_t)first_s * kLineFloats, 0, lines_s * kLineFloats * 4u, 0x00020000);
+        uint32_t c = rank_send;
+        Entry<V> x;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t bit = (mask_send >> j) & 1u;
+#pragma unroll
+            for (int v = 0; v < V; ++v) x.v[v] = w_hat[v].v[j];
+            store_entry<V>(out, bit ? ((c << sh) + slot) * 4u : kNone, x);
+            c += bit;
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) x.v[v] = 0.f;
+        store_entry<V>(out, (((count_send + lane) << sh) + slot) * 4u, x);
+    }
+
+    // ---- receive: the lane of rank c forms the mean (in fp64, in replica order), every lane picks up those of its own coordinates (a lane with
+    //      fewer than four reads entry 0 and drops it, so that the reads are in flight together)
+    if (count_recv) {
+        const uint32_t turn = 64u < (kStageFloats >> sh) ? 64u : kStageFloats >> sh;      // ranks of one
+        for (uint32_t c0 = 0; c0 < count_recv; c0 += turn) { // nearly always one turn
+            if (c0) {
+                wave_lds_sync();
+                request_ring(c0);
+                lds_dma_wait();
+                wave_lds_sync();
+            }
+            if (lane < turn && c0 + lane < count_recv) {
+                if (sh == 3u) mean[lane] = replica_mean<8, true>(a, ring, lane, kStageFloats);
+                else if (sh == 2u) mean[lane] = replica_mean<4, true>(a, ring, lane, kStageFloats);
+                else if (sh == 1u) mean[lane] = replica_mean<2, true>(a, ring, lane, kStageFloats);
+                else mean[lane] = replica_mean<1, true>(a, ring, lane, kStageFloats);
+            }
+            wave_lds_sync();
+            uint32_t c = rank_recv - c0;                     // (wraps below the turn's first: not this turn's)
+            bool mine[4];
+            float abar[4];
+            Entry<V> sent[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t bit = (mask_recv >> j) & 1u;
+                mine[j] = bit && c < turn;
+                const uint32_t at = mine[j] ? c : 0u;
+                abar[j] = mean[at];
+                sent[j] = *reinterpret_cast<const Entry<V> *>(ring + b * kStageFloats + (at << sh) + slot);
+                c += bit;
+            }
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (a.ema) {
+                        const float d_new = (float)fma(a.coef_d, (double)in[v].d.v[j], a.coef_s * ((double)w_hat[v].v[j] - (double)sent[j].v[v]));
+                        if (mine[j]) { in[v].d.v[j] = d_new; w_new[v].v[j] = (float)((double)abar[j] + (double)d_new); }
+                    } else if (mine[j]) {
+                        w_new[v].v[j] = abar[j];
+                    }
+                }
+        }
+        if (a.ema && half_recv) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) store_tile_f32x4(a.d[i0 + v] + tbase, loff, nvalid, in[v].d, a.through != 0u);
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < V; ++v) store_weights<FWD>(a, rep[v], tbase, loff, nvalid, in[v], w_hat[v], w_new[v]);
+}
+
+constexpr uint32_t kWaveChunk = 512;                         // tiles whose replicas follow each other; a multiple of the XCDs (31.5M x 8 per replica, us a step: 64 1659, 128 1626, 256 1636, 512 1593)
+__host__ __device__ inline uint32_t step_wave_lds_floats(uint32_t nblocks) { return nblocks * kStageFloats + 64u; }
+
+// grid = (tiles of a chunk, replicas / V, chunks); blockDim = 64; dynamic LDS = step_wave_lds_floats() floats, or more where fewer are to be resident
+template <int OPT, bool GRAD_BF16, int FWD, int V>
+__global__ void __launch_bounds__(64, 4)
+k_step_wave(const StepArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    const uint32_t tile = blockIdx.z * kWaveChunk + blockIdx.x;
+    if (tile >= a.ntiles) return;
+    if ((uint64_t)(tile + 1u) * kTileCoords <= a.n) step_wave<OPT, GRAD_BF16, FWD, V, true>(a, tile, V * blockIdx.y, threadIdx.x, lds);
+    else step_wave<OPT, GRAD_BF16, FWD, V, false>(a, tile, V * blockIdx.y, threadIdx.x, lds);
 }
 
 // tau = 0 with at most kSyncWaves replicas: the average is of this step's values, so a tile needs all its

@@ -1,0 +1,53 @@
+"""Large stages of blocks of eight replicas through one-wave workgroups (a delay, at most 10 % of the coordinates, no interleaved EMA vectors): from 3 * 2^22
+weights on where many slots of a block are absent, from 5 * 2^23 with and 2^26 without a correction.  One and two replicas a wave, several blocks, absent
+slots, ragged tiles, more received coordinates than a turn holds, every optimizer and type, rounds and steps between them, a slot that is too small, idle replicas."""
+import numpy as np
+import pytest
+import torch
+from test_gpu_parity import TOL_F32, compare, grads_for, make_pair, rel_err, run_steps
+
+from oracle import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+FEW, MANY = 3 << 22, 5 << 23
+PER_REPLICA = dict(d_layout=0)
+LOOK = dict(lookahead=True, gamma=0.9)
+NONE = dict(correction=O.CORR_NONE)
+BF16 = dict(grad_bf16=True, fwd_bf16=True)
+
+
+@pytest.mark.parametrize("n,R,p,kw", [
+    (2_600_001, 5, 0.1, LOOK), (2_700_800, 5, 0.003, dict(NONE, **BF16)), (2_100_483, 9, 0.1, BF16), (2_098_177, 9, 0.05, dict(NONE, optimizer=O.OPT_NADAMW, beta1=0.99)),
+    (2_098_690, 10, 0.1, dict(optimizer=O.OPT_SGD, beta1=0.9)), (2_097_411, 11, 0.02, dict(NONE, optimizer=O.OPT_SGD, beta1=0.0, **LOOK)),
+    (MANY // 8 + 1, 8, 0.1, LOOK), (MANY // 12 + 2, 12, 0.05, dict(optimizer=O.OPT_SGD, beta1=0.0, grad_bf16=True)), (MANY // 32 + 3, 32, 0.1, dict(BF16, **LOOK)),
+    ((1 << 26) // 8 + 7, 8, 0.05, dict(NONE, **LOOK)), ((1 << 26) // 16 + 5, 16, 0.01, dict(NONE, **BF16))])
+def test_parity(amlib, n, R, p, kw):
+    run_steps(amlib, n, R, 4, delay=2, fraction=p, seed=5, check_every=4, **PER_REPLICA, **kw)
+
+
+@pytest.mark.parametrize("kw", [dict(avg_interval=2), dict(subset_granule=32), dict(subset_kind=O.SUBSET_STRATIFIED), dict(correction=O.CORR_EAGER), dict(msg_dtype=O.MSG_E4M3)])
+def test_options(amlib, kw):
+    run_steps(amlib, 2_098_433, 9, 4, delay=1, fraction=0.1, seed=7, check_every=4, **PER_REPLICA, **kw)
+
+
+@pytest.mark.parametrize("n", [FEW // 5, FEW // 5 + 1])
+def test_both_sides_of_the_line(amlib, n):
+    run_steps(amlib, n, 5, 3, delay=1, fraction=0.05, seed=6, check_every=3, **PER_REPLICA)
+
+
+def test_idle_replicas_and_factors(amlib):
+    n, R = 2_600_003, 5
+    st, orc = make_pair(amlib, n, R, delay=1, fraction=0.05, seed=3, **PER_REPLICA)
+    scale = np.array([1.0, 0.5, 0.25, 2.0, 0.125], np.float32)                       # powers of two: the scaled gradients are exact
+    for t in range(1, 4):
+        g, gd = grads_for(n, R, t, 3, False)
+        if t == 2:
+            st.step_masked(t, gd, 1e-3, 0.5, 0b10110)
+            orc.step_masked(t, g, 1e-3, 0.5, 0b10110)
+        else:
+            st.step_masked(t, gd, 1e-3, 0.5, 0b11111, 1.0, torch.from_numpy(scale).cuda())
+            orc.step_masked(t, [x * f for x, f in zip(g, scale)], 1e-3, 0.5, 0b11111)
+    compare(st, orc, "masked")
+    for i in range(R):
+        assert rel_err(st.m[i].cpu().numpy(), orc.m(i)) < TOL_F32
