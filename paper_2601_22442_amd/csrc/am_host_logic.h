@@ -253,35 +253,49 @@ inline uint32_t step_sum_tiles(const am_config &c, const Blocks &b, bool sync)
     return b.nblocks == 4u ? 768u : b.nblocks == 3u ? 2048u : b.rb == 4u ? 6144u : 8192u;
 }
 
-// Whether a step with a delay goes through the kernel of one-wave workgroups instead of the fused kernel's workgroup per tile and block.  Median time by
-// waves / by the fused kernel over random configurations (all optimizers, p = 0.2 to 10 %; 10 % of them are above the figure in brackets, as the placement of the
-// arrays alone moves either by 5 %):
-//   per-replica EMA vectors by replicas, from 30M weights on: 5 0.94, 6 0.96, 7 0.96, 8 0.97, 9 0.77, 12 0.94, 16 0.98, 24 and 32 0.98; by weights: 30M 0.98 (1.01), 60M 0.97 (1.00), 200M 0.95 (0.98);
-//     by fraction: 5 % 0.95, 10 % 0.97, but 20 % 1.02 to 1.06, 50 % 1.3.
-//   no correction: 5 0.96, 6 0.98, 7 0.98, 8 0.98, 9 0.81, 12 0.97, 16 0.98 (2000M in bf16 0.96), 24 0.99 (1.03), 32 0.99 (1.02); 30M and 50M 0.99 (1.03), 60M 0.98 (1.01), 100M and more 0.97 (1.00).
-//   where many of a block's slots are absent, from 13M weights on: 5 per replica 0.95, without 0.98; the others at 15M to 25M 1.00 to 1.02.
-//   interleaved EMA vectors: R = 8 0.5 % 0.99, 2 % 1.00, 5 % 1.01 (1.06), 10 % 1.05.  Blocks of four 0.99 (1.01), of two 1.02 (1.09), single replicas 1.03 (1.14).  Fewer weights: 8M 1.00 (1.05).
+// Whether a step with a delay goes through the kernel of one-wave workgroups instead of the fused kernel's workgroup per tile and block.  Time by
+// waves / by the fused kernel, same arrays, AdamW with look-ahead and 5 % where not said (either moves by 3 to 5 % with the placement of the arrays):
+//   weights (n R)                                40M   60M   90M   130M  200M  250M  300M  1000M
+//   interleaved EMA vectors   R = 8              0.95  0.95  0.97  0.97  0.97        0.96  0.95
+//                             12                 0.90  0.87  0.97  0.97  0.97        0.96
+//                             16                 0.98  0.91  0.95  1.01  0.98        0.99
+//                             6                  0.94  0.92  0.97  0.97  0.97        0.97
+//                             20                 0.96  0.96  0.97  0.96  0.97        0.97
+//                             24                 0.98  0.90  0.94  0.96  1.01        0.99
+//     but                     32                 1.01  0.94  1.00  0.93  1.04        1.03
+//                             7 (a replica a wave) 1.02 0.99 0.99  1.03  1.01        1.01
+//   per replica               8                  0.95  0.93  0.95  0.96        0.92        0.94
+//                             12                 0.89  0.86  0.94  0.94        0.91
+//                             16                 0.97  0.98  0.90  0.96        1.01
+//                             32                 0.97  0.91  0.97  0.88        1.03
+//   no correction             8                  1.01  0.95  0.96  1.00        0.93
+//                             12                 0.92  0.89  0.96  0.97        0.96
+//                             16                 0.99  0.99  0.93  0.98        0.98
+//                             32                 1.01  0.90  1.00  0.87        0.98
+//   where many of a block's slots are absent: R = 5 interleaved 15M 0.97, 25M to 60M 0.93, 300M 0.98; R = 9, 10, 11 80M 0.76 to 0.90 in every layout.
+//   fewer weights: interleaved 15M 0.99 to 1.05, 25M 0.98 to 1.05, per replica 20M and 30M 0.99 to 1.03, no correction 30M 1.04.
+//   by fraction (90M, 250M): interleaved 2 % 0.95, 0.95, but 10 % 1.02, 1.00; per replica and without 10 % 0.94, 0.96, but 15 % 1.09, 20 % 1.08, 30 % 1.23.
+//   types (60M, 250M): interleaved bf16 0.98, 0.98, with look-ahead 0.97, 1.01, AdamW without a forward copy 0.95, 0.99, SGD with momentum 0.95, 0.98; the others 0.94 to 0.99.
 inline bool step_by_waves(const am_config &c, const Blocks &b)
 {
     if (b.rb != 8u || c.fraction > 0.1) return false;
-    if (c.correction != AM_CORR_NONE ? c.d_layout == AM_D_INTERLEAVED : c.replicas > 16u) return false;
     const bool idle = c.replicas == 5u || (c.replicas >= 9u && c.replicas <= 11u);         // a third of the fused kernel's waves or more
+    if (c.correction != AM_CORR_NONE && c.d_layout == AM_D_INTERLEAVED && !idle && (c.replicas % 2u || c.replicas > 24u || c.fraction > 0.06)) return false;
     return c.n * c.replicas > (idle ? 3ull << 22 : c.correction != AM_CORR_NONE ? 5ull << 23 : 1ull << 26);
 }
 
-// Replicas that a wave of that kernel takes: two share the hashing and send pairs of values (R = 12 10M 0.96 either way, R = 32 4M 0.98 / 0.965).
+// Replicas that a wave of that kernel takes: two share the hashing and send pairs of values (R = 12 10M 0.96 either way, R = 32 4M 0.98 / 0.965; four, interleaved 125.8M x 8, 1.005
+// of the fused kernel's time, one 1.01, two 0.98).
 inline uint32_t wave_step_replicas(const am_config &c) { return c.replicas % 2u ? 1u : 2u; }
 
-// Waves of it that a compute unit may hold: 75 KB of requested operands on their way, 84 where a wave takes two replicas (80 without a correction).
-// us a step by their number, one replica a wave: R = 7 20M per replica 14: 875, 16: 873, 18: 884; two: bf16 R = 16 125.8M no correction 8: 10615, 10: 9704, 12: 9581, 16: 9848;
-// AdamW R = 8 31.5M no correction 8: 1391, 10: 1348, 12: 1367, per replica 8: 1610, 10: 1610, 12: 1654.
-inline uint32_t wave_step_workgroups(const am_config &c, uint32_t v, bool receives)
+// Waves of it that a compute unit may hold: the less a wave moves the more of them, and one more where the step is short.  Time over the fused kernel's by their number,
+// two replicas a wave: interleaved 125.8M x 8 (8.3 KB a replica) 8: 0.968, 9: 0.949, 10: 0.953, 11: 0.959; 60M weights 9: 0.961, 10: 0.970, 11: 0.947, 12: 0.949; per replica 31.5M x 8 (9.4 KB) 8: 0.921,
+// 9: 0.927, 10: 0.933, 12: 0.952; 80M weights without a forward copy (7.3 KB) 8: 1.070, 10: 0.990, 12: 0.979, 14: 0.988; bf16 without correction (6.1 KB) 8: 1.083, 10: 0.974, 11: 0.954, 14: 0.966;
+// SGD with momentum (5.3 KB) 8: 1.258, 10: 1.079, 12: 1.013, 14: 0.989; one replica a wave (R = 7) AdamW 14: 1.139, 18: 1.008, 21: 1.006, 25: 1.006.
+inline uint32_t wave_step_workgroups(const am_config &c, const Blocks &b, uint32_t v, bool forward_copy, bool receives)
 {
-    const bool ema = c.correction != AM_CORR_NONE;
-    const double moments = c.optimizer != AM_OPT_SGD ? 2.0 : c.beta1 != 0.f ? 1.0 : 0.0;
-    double kb = 1.0 + (c.grad_dtype == AM_BF16 ? 0.5 : 1.0) + moments;
-    if (receives && ema) kb += 1.0 - std::pow(1.0 - c.fraction, (double)am::kLineFloats);
-    return (uint32_t)std::floor((v == 1u ? 75.0 : ema ? 42.0 : 40.0) / kb + 0.5);
+    const double pairs = (c.n * c.replicas > 1ull << 27 ? 4.0 : 5.0) + 50.0 / step_kilobytes(c, b, forward_copy, receives);
+    return (uint32_t)std::floor(pairs * 2.0 / v + 0.5);
 }
 
 // Whether a step between two averaging rounds (which neither sends nor receives) goes through the kernel of its own.  It pays for blocks of

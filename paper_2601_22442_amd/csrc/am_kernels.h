@@ -1066,20 +1066,34 @@ __device__ __forceinline__ void store_entry(__amdgpu_buffer_rsrc_t r, uint32_t b
     if constexpr (V == 2) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, x), r, (int)byte, 0, 0);
     else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), r, (int)byte, 0, 0);
 }
+template <int V>
+__device__ __forceinline__ Entry<V> load_entry(const float *p)
+{
+    if constexpr (V == 2) return __builtin_bit_cast(Entry<V>, *reinterpret_cast<const v2f *>(p));
+    else return __builtin_bit_cast(Entry<V>, *p);
+}
+template <int V>
+__device__ __forceinline__ void store_entry(float *p, const Entry<V> &x)
+{
+    if constexpr (V == 2) *reinterpret_cast<v2f *>(p) = __builtin_bit_cast(v2f, x);
+    else *p = x.v[0];
+}
 
-// The step of large stages with a delay and no interleaved EMA vectors (am_host::step_by_waves): a workgroup is ONE wave, which takes V
+// The step of large stages with a delay (am_host::step_by_waves): a workgroup is ONE wave, which takes V
 // neighbouring replicas of a block through one tile; no barrier, and what the replicas of a tile share meets in the L2.
 // What it buys is order.  The stream mix moves faster the fewer streams are on their way at a time and the finer the grain in which waves come and go
 // (without arithmetic, 125.8M x 8: a workgroup of eight waves a tile 5.7 TB/s with three of them a compute unit and 6.2 with two; one-wave workgroups, 16 a
 // compute unit, 6.1 with a tile's replicas side by side and 6.6 with the replicas of a chunk of 512 tiles one after the other).  So the grid
 // runs over the tiles of a chunk, then its replicas, then the chunks: the waves of one tile are on the same XCD (consecutive workgroups go round the eight) and
-// near enough in time that its ring lines are fetched from memory once and that the parts of the lines it sends merge in the
+// near enough in time that its ring lines and interleaved EMA entries are fetched from memory once and that the parts of the lines they write merge in the
 // L2 (bytes by the counters as in k_step: 28.4 + 28.3 GB on 125.8M x 16).  The price is in requests: every wave asks for the ring lines, and sends
-// V values of a coordinate at a time, so it pays up to a fraction of 10 %; an interleaved EMA vector, read and written V entries at a
-// time, costs more than the order gives (125.8M x 8 5 %: 5814 / 5846 us), and so do narrower blocks.
-// us a step, k_step / this: per replica, R = 8 31.5M 5 % 1700 / 1586 (9.6 GB: 6.0 TB/s), R = 5 25M 830 / 784, R = 12 10M 818 / 788; no correction R = 8
-// 31.5M 1414 / 1337, bf16 R = 16 125.8M 1 % 9973 / 9518.
-template <int OPT, bool GRAD_BF16, int FWD, int V, bool FULL>
+// V values of a coordinate at a time, so it pays up to a fraction of 10 %.  Interleaved EMA entries cost little where the lane of rank c takes those of the received
+// coordinate c, one load and one store a wave, and the weights change hands through LDS (every lane taking its own four coordinates' entries, eight scattered accesses: 5814 / 5846 us,
+// no gain); narrower blocks have too little to gain.
+// us a step, k_step / this: interleaved, R = 8 125.8M 5 % 5909 / 5633 (33.9 GB: 6.0 TB/s), 31.5M 1474 / 1400; per replica, R = 8 31.5M 1698 / 1581, 125.8M 6665 / 6249, R = 5 25M 830 / 784,
+// R = 12 10M 818 / 788; no correction R = 8 31.5M 1461 / 1361, bf16 R = 16 125.8M 1 % 9973 / 9518.
+// Bound by memory: with a generator of a few instructions in the place of the hashing it takes as long.
+template <int OPT, bool GRAD_BF16, int FWD, bool DIL, int V, bool FULL>
 __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile, const uint32_t i0, const uint32_t lane, float *lds)
 {
     const uint32_t sh = a.rb_shift, b = i0 >> sh, slot = i0 & (a.rb - 1u);
@@ -1091,8 +1105,13 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
     const uint64_t block_floats = (uint64_t)a.cap_lines * kLineFloats;
     constexpr uint32_t kNone = 0x40000000u;                  // past the end of every resource
     float *const ring = lds, *const mean = ring + a.nblocks * kStageFloats;
+    float *const x_lds = mean;                               // (DIL) [V][64] my replicas' weights of the received coordinates of a turn, by rank
+    uint8_t *const list = reinterpret_cast<uint8_t *>(x_lds + V * 64u);     // (DIL) those coordinates
+    const uint32_t turn = 64u < (kStageFloats >> sh) ? 64u : kStageFloats >> sh;      // ranks of a turn
 
-    // ---- dense operands: nothing else is requested before them
+    // ---- dense operands: nothing else is requested before them.  (Until everything is requested the wave goes before the
+    //      older ones of its SIMD, which have arithmetic to do: us a step without / with that, per replica 31.5M x 8 1648 / 1632, interleaved 1447 / 1425.)
+    __builtin_amdgcn_s_setprio(3);
     const ReplicaArgs *const rep = a.rep + 8u * b + slot;
     GroupIn in[V];
 #pragma unroll
@@ -1122,16 +1141,38 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
     SubsetKey key = a.key;
     uint32_t mask_recv = 0, rank_recv = 0, count_recv = 0;
     bool half_recv = false;                                  // the 64 bytes of a per-replica array (4 lanes) holding the group receive something
+    // the rank in the turn from c0 on of the lane's coordinates that are received, one after the other
+    auto each = [&](const uint32_t c0, auto use) {
+        uint32_t c = rank_recv - c0;                         // (wraps below the turn's first: not this turn's)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t bit = (mask_recv >> j) & 1u;
+            if (bit && c < turn) use(j, c);
+            c += bit;
+        }
+    };
+    // interleaved EMA entries: the lane of rank c takes those of its coordinate, one request a wave
+    Entry<V> entry = {};
+    auto request_entries = [&](const uint32_t c0) {
+        each(c0, [&](int j, uint32_t c) { list[c] = (uint8_t)(loff + (uint32_t)j); });
+        wave_lds_sync();
+        if (lane < turn && c0 + lane < count_recv) entry = load_entry<V>(a.d[b] + ((tbase + list[lane]) << sh) + slot);
+    };
+    auto mean_of = [&]() {                                   // of the coordinate of the lane's rank
+        return sh == 3u ? replica_mean<8, true>(a, ring, lane, kStageFloats) : sh == 2u ? replica_mean<4, true>(a, ring, lane, kStageFloats)
+             : sh == 1u ? replica_mean<2, true>(a, ring, lane, kStageFloats) : replica_mean<1, true>(a, ring, lane, kStageFloats);
+    };
     if (lines_r) {
         request_ring(0u);
         key.step_lo = a.step_lo[0]; key.step_hi = a.step_hi[0];
         mask_recv = member_mask(key, group, nvalid);
         half_recv = ((__ballot(mask_recv != 0u) >> (lane & ~3u)) & 0xFull) != 0ull;
-        if (a.ema && half_recv) {
+        if (!DIL && a.ema && half_recv) {
 #pragma unroll
             for (int v = 0; v < V; ++v) in[v].d = load_f32x4(a.d[i0 + v] + tbase, loff, nvalid);
         }
         rank_recv = wave_prefix_mask4(mask_recv, count_recv);
+        if (DIL) request_entries(0u);
     }
     uint32_t mask_send = 0, rank_send = 0, count_send = 0;
     if (lines_s) {
@@ -1146,6 +1187,7 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
         if (lane == 0) a.next_lines[tile] = (uint8_t)((count * a.rb + kLineFloats - 1u) / kLineFloats);
     }
     __builtin_amdgcn_sched_barrier(0);                       // (the operands' conversions stay behind the hashing)
+    __builtin_amdgcn_s_setprio(0);
 
     F4 w_hat[V], w_new[V], m_new[V], v_new[V];
 #pragma unroll
@@ -1178,23 +1220,44 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
         store_entry<V>(out, (((count_send + lane) << sh) + slot) * 4u, x);
     }
 
-    // ---- receive: the lane of rank c forms the mean (in fp64, in replica order), every lane picks up those of its own coordinates (a lane with
-    //      fewer than four reads entry 0 and drops it, so that the reads are in flight together)
-    if (count_recv) {
-        const uint32_t turn = 64u < (kStageFloats >> sh) ? 64u : kStageFloats >> sh;      // ranks of one
-        for (uint32_t c0 = 0; c0 < count_recv; c0 += turn) { // nearly always one turn
-            if (c0) {
-                wave_lds_sync();
-                request_ring(c0);
-                lds_dma_wait();
-                wave_lds_sync();
-            }
+    // ---- receive: the lane of rank c forms the mean (in fp64, in replica order)
+    auto next_turn = [&](const uint32_t c0) {                // nearly always there is none
+        wave_lds_sync();
+        request_ring(c0);
+        if (DIL) request_entries(c0);
+        lds_dma_wait();
+        wave_lds_sync();
+    };
+    if (DIL) {                                               // and the new entries and weights of its coordinate, which change hands through LDS
+        for (uint32_t c0 = 0; c0 < count_recv; c0 += turn) {
+            if (c0) next_turn(c0);
+            each(c0, [&](int j, uint32_t c) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) x_lds[v * 64 + c] = w_hat[v].v[j];
+            });
+            wave_lds_sync();
             if (lane < turn && c0 + lane < count_recv) {
-                if (sh == 3u) mean[lane] = replica_mean<8, true>(a, ring, lane, kStageFloats);
-                else if (sh == 2u) mean[lane] = replica_mean<4, true>(a, ring, lane, kStageFloats);
-                else if (sh == 1u) mean[lane] = replica_mean<2, true>(a, ring, lane, kStageFloats);
-                else mean[lane] = replica_mean<1, true>(a, ring, lane, kStageFloats);
+                const float abar = mean_of();
+                const Entry<V> sent = *reinterpret_cast<const Entry<V> *>(ring + b * kStageFloats + (lane << sh) + slot);
+                Entry<V> d_new;
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    d_new.v[v] = (float)fma(a.coef_d, (double)entry.v[v], a.coef_s * ((double)x_lds[v * 64 + lane] - (double)sent.v[v]));
+                    x_lds[v * 64 + lane] = (float)((double)abar + (double)d_new.v[v]);
+                }
+                store_entry<V>(a.d[b] + ((tbase + list[lane]) << sh) + slot, d_new);
             }
+            wave_lds_sync();
+            each(c0, [&](int j, uint32_t c) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) w_new[v].v[j] = x_lds[v * 64 + c];
+            });
+        }
+    } else if (count_recv) {                                 // every lane picks up those of its own coordinates (a lane with
+                                                             // fewer than four reads entry 0 and drops it, so that the reads are in flight together)
+        for (uint32_t c0 = 0; c0 < count_recv; c0 += turn) {
+            if (c0) next_turn(c0);
+            if (lane < turn && c0 + lane < count_recv) mean[lane] = mean_of();
             wave_lds_sync();
             uint32_t c = rank_recv - c0;                     // (wraps below the turn's first: not this turn's)
             bool mine[4];
@@ -1230,19 +1293,24 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
     for (int v = 0; v < V; ++v) store_weights<FWD>(a, rep[v], tbase, loff, nvalid, in[v], w_hat[v], w_new[v]);
 }
 
-constexpr uint32_t kWaveChunk = 512;                         // tiles whose replicas follow each other; a multiple of the XCDs (31.5M x 8 per replica, us a step: 64 1659, 128 1626, 256 1636, 512 1593)
-__host__ __device__ inline uint32_t step_wave_lds_floats(uint32_t nblocks) { return nblocks * kStageFloats + 64u; }
+// Tiles whose replicas follow each other; a multiple of the XCDs.  us a step by their number, nine waves a compute unit: interleaved 125.8M x 8 64: 5804, 128: 5626, 192: 5750, 256: 5799, 512: 5731,
+// 31.5M 1433, 1409, 1441, 1426, 1436; per replica 125.8M, eight waves, 64: 6332, 128: 6278, 256: 6355, 512: 6457.
+constexpr uint32_t kWaveChunk = 128;
+__host__ __device__ inline uint32_t step_wave_lds_floats(uint32_t nblocks, bool d_interleaved, uint32_t v)
+{
+    return nblocks * kStageFloats + (d_interleaved ? 64u * v + 16u : 64u);
+}
 
 // grid = (tiles of a chunk, replicas / V, chunks); blockDim = 64; dynamic LDS = step_wave_lds_floats() floats, or more where fewer are to be resident
-template <int OPT, bool GRAD_BF16, int FWD, int V>
+template <int OPT, bool GRAD_BF16, int FWD, bool DIL, int V>
 __global__ void __launch_bounds__(64, 4)
 k_step_wave(const StepArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const uint32_t tile = blockIdx.z * kWaveChunk + blockIdx.x;
     if (tile >= a.ntiles) return;
-    if ((uint64_t)(tile + 1u) * kTileCoords <= a.n) step_wave<OPT, GRAD_BF16, FWD, V, true>(a, tile, V * blockIdx.y, threadIdx.x, lds);
-    else step_wave<OPT, GRAD_BF16, FWD, V, false>(a, tile, V * blockIdx.y, threadIdx.x, lds);
+    if ((uint64_t)(tile + 1u) * kTileCoords <= a.n) step_wave<OPT, GRAD_BF16, FWD, DIL, V, true>(a, tile, V * blockIdx.y, threadIdx.x, lds);
+    else step_wave<OPT, GRAD_BF16, FWD, DIL, V, false>(a, tile, V * blockIdx.y, threadIdx.x, lds);
 }
 
 // tau = 0 with at most kSyncWaves replicas: the average is of this step's values, so a tile needs all its

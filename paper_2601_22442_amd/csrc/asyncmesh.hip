@@ -235,16 +235,14 @@ am_status launch_step_tau(am_state *st, const am::StepArgs &a)
         AM_HIP(hipGetLastError());
         return AM_OK;
     }
-    if constexpr (!DIL) {
-        if (!tau0 && !a.sum_lines && am_host::step_by_waves(st->cfg, B)) {
-            const uint32_t v = am_host::wave_step_replicas(st->cfg);
-            const uint32_t lds = am_host::lds_for_residency(am::step_wave_lds_floats(B.nblocks) * (uint32_t)sizeof(float), am_host::wave_step_workgroups(st->cfg, v, a.do_recv != 0u));
-            const dim3 waves(am::kWaveChunk, a.replicas / v, (st->lay.ntiles + am::kWaveChunk - 1u) / am::kWaveChunk);
-            if (v == 2u) am::k_step_wave<OPT, GBF, FWD, 2><<<waves, 64, lds, st->stream>>>(a);
-            else am::k_step_wave<OPT, GBF, FWD, 1><<<waves, 64, lds, st->stream>>>(a);
-            AM_HIP(hipGetLastError());
-            return AM_OK;
-        }
+    if (!tau0 && !a.sum_lines && am_host::step_by_waves(st->cfg, B)) {
+        const uint32_t v = am_host::wave_step_replicas(st->cfg);
+        const uint32_t lds = am_host::lds_for_residency(am::step_wave_lds_floats(B.nblocks, DIL, v) * (uint32_t)sizeof(float), am_host::wave_step_workgroups(st->cfg, B, v, st->has_fwd, a.do_recv != 0u));
+        const dim3 waves(am::kWaveChunk, a.replicas / v, (st->lay.ntiles + am::kWaveChunk - 1u) / am::kWaveChunk);
+        if (v == 2u) am::k_step_wave<OPT, GBF, FWD, DIL, 2><<<waves, 64, lds, st->stream>>>(a);
+        else am::k_step_wave<OPT, GBF, FWD, DIL, 1><<<waves, 64, lds, st->stream>>>(a);
+        AM_HIP(hipGetLastError());
+        return AM_OK;
     }
     const dim3 grid(st->lay.ntiles, tau0 ? 1u : B.nblocks), block(64u * B.rb);
     const uint32_t workgroups = tau0 || a.sum_lines ? 0u : am_host::step_workgroups(st->cfg, B, st->has_fwd, a.do_recv != 0u);

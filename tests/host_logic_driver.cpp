@@ -65,6 +65,13 @@ uint32_t hl_step_workgroups(const am_config *c, int forward_copy, int receives)
 
 uint32_t hl_step_sum_tiles(const am_config *c, int sync) { return am_host::step_sum_tiles(*c, am_host::block_geometry(c->replicas), sync != 0); }
 
+// waves of a compute unit in the step by one-wave workgroups; 0: the fused kernel's workgroups
+uint32_t hl_step_by_waves(const am_config *c, int forward_copy)
+{
+    const am_host::Blocks b = am_host::block_geometry(c->replicas);
+    return am_host::step_by_waves(*c, b) ? am_host::wave_step_workgroups(*c, b, am_host::wave_step_replicas(*c), forward_copy != 0, true) : 0u;
+}
+
 int hl_local_step_alone(const am_config *c) { return am_host::local_step_alone(*c, am_host::block_geometry(c->replicas)); }
 uint32_t hl_average_workgroups(const am_config *c)
 {

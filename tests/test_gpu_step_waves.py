@@ -1,5 +1,5 @@
-"""Large stages of blocks of eight replicas through one-wave workgroups (a delay, at most 10 % of the coordinates, no interleaved EMA vectors): from 3 * 2^22
-weights on where many slots of a block are absent, from 5 * 2^23 with and 2^26 without a correction.  One and two replicas a wave, several blocks, absent
+"""Large stages of blocks of eight replicas through one-wave workgroups (a delay, at most 10 % of the coordinates; interleaved EMA vectors 6 % and an even number of at most 24
+replicas, where not many slots are absent): from 3 * 2^22 weights on where many slots of a block are absent, from 5 * 2^23 with and 2^26 without a correction.  One and two replicas a wave, several blocks, absent
 slots, ragged tiles, more received coordinates than a turn holds, every optimizer and type, rounds and steps between them, a slot that is too small, idle replicas."""
 import numpy as np
 import pytest
@@ -11,7 +11,7 @@ from oracle import oracle as O
 pytestmark = pytest.mark.gpu
 
 FEW, MANY = 3 << 22, 5 << 23
-PER_REPLICA = dict(d_layout=0)
+PER_REPLICA, INTERLEAVED = dict(d_layout=0), dict(d_layout=1)
 LOOK = dict(lookahead=True, gamma=0.9)
 NONE = dict(correction=O.CORR_NONE)
 BF16 = dict(grad_bf16=True, fwd_bf16=True)
@@ -24,6 +24,19 @@ BF16 = dict(grad_bf16=True, fwd_bf16=True)
     ((1 << 26) // 8 + 7, 8, 0.05, dict(NONE, **LOOK)), ((1 << 26) // 16 + 5, 16, 0.01, dict(NONE, **BF16))])
 def test_parity(amlib, n, R, p, kw):
     run_steps(amlib, n, R, 4, delay=2, fraction=p, seed=5, check_every=4, **PER_REPLICA, **kw)
+
+
+@pytest.mark.parametrize("n,R,p,kw", [
+    (2_600_001, 5, 0.1, LOOK), (2_100_483, 9, 0.1, BF16), (2_098_690, 10, 0.1, dict(optimizer=O.OPT_SGD, beta1=0.9)), (2_097_411, 11, 0.02, dict(optimizer=O.OPT_SGD, beta1=0.0, **LOOK)),
+    (MANY // 8 + 1, 8, 0.06, LOOK), (MANY // 12 + 2, 12, 0.05, dict(optimizer=O.OPT_NADAMW, beta1=0.99, grad_bf16=True)), (MANY // 24 + 3, 24, 0.06, dict(BF16, **LOOK)),
+    (MANY // 8 + 254, 8, 0.003, dict(correction=O.CORR_EAGER))])
+def test_interleaved(amlib, n, R, p, kw):
+    run_steps(amlib, n, R, 4, delay=2, fraction=p, seed=5, check_every=4, **INTERLEAVED, **kw)
+
+
+@pytest.mark.parametrize("kw", [dict(avg_interval=2), dict(subset_granule=32), dict(subset_kind=O.SUBSET_STRATIFIED), dict(msg_dtype=O.MSG_E4M3)])
+def test_options_interleaved(amlib, kw):
+    run_steps(amlib, 2_098_433, 9, 4, delay=1, fraction=0.1, seed=7, check_every=4, **INTERLEAVED, **kw)
 
 
 @pytest.mark.parametrize("kw", [dict(avg_interval=2), dict(subset_granule=32), dict(subset_kind=O.SUBSET_STRATIFIED), dict(correction=O.CORR_EAGER), dict(msg_dtype=O.MSG_E4M3)])

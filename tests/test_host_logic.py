@@ -224,6 +224,19 @@ def test_step_residency_follows_what_a_wave_moves(hl, n, R, kw, fwd, receives, w
     assert hl.hl_step_workgroups(C.byref(_config(n=n, replicas=R, delay=1, **kw)), fwd, receives) == workgroups
 
 
+@pytest.mark.parametrize("n,R,kw,fwd,waves", [
+    # interleaved EMA vectors: even numbers of replicas up to 24 and small fractions, or many absent slots
+    (125_829_120, 8, dict(d_layout=1), True, 10), (5_242_880, 8, dict(d_layout=1), True, 0), (5_242_881, 8, dict(d_layout=1), True, 11), (31_457_281, 8, dict(d_layout=1, fraction=0.07), True, 0),
+    (31_457_281, 7, dict(d_layout=1), True, 0), (10_000_000, 32, dict(d_layout=1), True, 0), (10_000_000, 24, dict(d_layout=1), True, 10), (2_600_000, 5, dict(d_layout=1, fraction=0.1), True, 21),
+    # per replica and without a correction
+    (31_457_281, 8, dict(d_layout=0, fraction=0.1), True, 9), (31_457_281, 7, dict(d_layout=0), False, 20), (31_457_281, 8, dict(d_layout=0, fraction=0.11), True, 0), (8_388_608, 8, dict(correction=0), True, 0),
+    (8_388_609, 8, dict(correction=0), True, 11), (125_829_120, 16, dict(correction=0, grad_dtype=1, fwd_dtype=1, fraction=0.01), True, 11), (31_457_281, 4, dict(d_layout=0), True, 0),
+])
+def test_large_steps_go_by_waves(hl, n, R, kw, fwd, waves):
+    hl.hl_step_by_waves.restype = C.c_uint32
+    assert hl.hl_step_by_waves(C.byref(_config(n=n, replicas=R, delay=1, **kw)), fwd) == waves
+
+
 @pytest.mark.parametrize("workgroups", [2, 3, 4, 5, 6, 7, 11])
 @pytest.mark.parametrize("fixed", [0, 16])
 def test_lds_holds_as_many_workgroups_as_a_rule_names(hl, workgroups, fixed):
