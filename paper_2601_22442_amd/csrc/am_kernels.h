@@ -758,7 +758,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     // replica, whose values its wave loads and never uses -- with a condition the compiler parks
     // the conversions of the loaded values, and with them a wait for memory, right behind the loads)
     load_group<OPT, GRAD_BF16>(rep, tbase, i < R ? loff : 0u, nvalid, in);      // (an absent replica's wave: one group for all lanes)
-    const float factor = replica_factor(a, i < R ? i : 0u);
+    const float factor = SUM ? 1.0f : replica_factor(a, i < R ? i : 0u);       // (small stages: where it is used, so that the hashing starts at once)
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- subsets: bit j of a lane's mask = coordinate 4 group + j is received / sent now.
@@ -912,7 +912,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     // 10107 / 9924, R = 8, 31.5M 1195 / 1162; per-replica d, 31.5M, R = 2 369 / 363; absent replicas: R = 12, 10M, bf16 772 /
     // 751 (per replica), 713 / 692 (interleaved), R = 6 386 / 364; no change beyond noise on the headline step.
     F4 w_hat, m_new, v_new;
-    if (!TAU0 && i < R) local_step<OPT>(a, rep, factor, in, w_hat, m_new, v_new);
+    if (!TAU0 && i < R) local_step<OPT>(a, rep, SUM ? replica_factor(a, i) : factor, in, w_hat, m_new, v_new);
     lds_dma_wait();
     __syncthreads();
     if (!TAU0 && i < R) {                                  // the moments are final: out they go at once
