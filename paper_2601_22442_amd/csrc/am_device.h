@@ -171,6 +171,8 @@ __device__ __forceinline__ void lds_dma_16(const float *src, float *lds_wave_bas
                                      (__attribute__((address_space(3))) void *)lds_wave_base, 16, 0, 0);
 }
 __device__ __forceinline__ void lds_dma_wait() { __builtin_amdgcn_s_waitcnt(0x0F70); }     // vmcnt(0)
+// Until the wave's LDS accesses are complete: a direct load that overwrites what they read comes through the memory system, not behind them.
+__device__ __forceinline__ void lds_access_wait() { __builtin_amdgcn_s_waitcnt(0xC07F); }  // lgkmcnt(0)
 
 // ---------------------------------------------------------------------------------------------
 // 128-bit accesses with a scalar tail (only the last group of an array can be partial)

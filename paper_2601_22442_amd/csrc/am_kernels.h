@@ -1223,6 +1223,7 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
     // ---- receive: the lane of rank c forms the mean (in fp64, in replica order)
     auto next_turn = [&](const uint32_t c0) {                // nearly always there is none
         wave_lds_sync();
+        lds_access_wait();                                   // what the last turn read from the ring's stretch has been read
         request_ring(c0);
         if (DIL) request_entries(c0);
         lds_dma_wait();

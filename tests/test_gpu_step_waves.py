@@ -44,6 +44,13 @@ def test_options(amlib, kw):
     run_steps(amlib, 2_098_433, 9, 4, delay=1, fraction=0.1, seed=7, check_every=4, **PER_REPLICA, **kw)
 
 
+@pytest.mark.parametrize("R,layout,kw", [(9, PER_REPLICA, {}), (10, PER_REPLICA, {}), (9, INTERLEAVED, {}), (10, INTERLEAVED, {}), (9, PER_REPLICA, NONE), (10, PER_REPLICA, NONE)])
+def test_several_turns(amlib, R, layout, kw):
+    """Whole lines of 32 coordinates are drawn, as many as a turn holds: a tile with two or more takes as many turns, each of which
+    overwrites in LDS what the one before has read."""
+    run_steps(amlib, 2_100_001, R, 4, delay=1, fraction=0.1, subset_granule=32, seed=11, check_every=2, **layout, **kw)
+
+
 @pytest.mark.parametrize("n", [FEW // 5, FEW // 5 + 1])
 def test_both_sides_of_the_line(amlib, n):
     run_steps(amlib, n, 5, 3, delay=1, fraction=0.05, seed=6, check_every=3, **PER_REPLICA)
