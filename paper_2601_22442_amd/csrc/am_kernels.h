@@ -429,7 +429,7 @@ __device__ __forceinline__ void write_send_word(const StepArgs &a, uint32_t tile
     if (tile + 1u == a.ntiles) a.send_sb_out[tile / kTilesPerSuperblock + 1u] = first + lines;
 }
 
-// Replica i's own gradient factor, a scalar load that is requested beside the operands.  (A vector load where the factor is used waits
+// Replica i's own gradient factor, a scalar load that large stages request beside the operands.  (A vector load where the factor is used waits
 // for everything that is on its way before it.)
 __device__ __forceinline__ float replica_factor(const StepArgs &a, uint32_t i)
 {
@@ -437,9 +437,12 @@ __device__ __forceinline__ float replica_factor(const StepArgs &a, uint32_t i)
     return a.replica_scale ? ((const_f32_ptr)(uintptr_t)a.replica_scale)[i] : 1.0f;
 }
 
-// Local optimizer step on one group, from loaded operands; factor: replica_factor().
+// Local optimizer step on one group of replica i, from loaded operands.  early: its replica_factor(), where the caller has requested it beside the
+// operands; nullptr: read where it is used, in kernels that have no registers for it: held from the operands on, it takes two to four vector registers, without factors, too.
+// Time so / read late: k_step_sync (65 / 61 registers: two workgroups of 16 waves no longer fit a compute unit) R = 13 3M 1.10, R = 15 300k 1.17, R = 16 no correction 3M 1.17; the
+// walking form (40 bytes of scratch a lane / none) R = 20 1.5M 1.10, R = 32 1.09.  Small stages: with factors 1M R = 4 0.98, without 1.002 (2M R = 4, 31.5M R = 8, k_step: 0.99 and 0.99 with factors).
 template <int OPT>
-__device__ __forceinline__ void local_step(const StepArgs &a, const ReplicaArgs &r, float factor, const GroupIn &in,
+__device__ __forceinline__ void local_step(const StepArgs &a, const ReplicaArgs &r, uint32_t i, const float *early, const GroupIn &in,
                                            F4 &w_hat, F4 &m_new, F4 &v_new)
 {
     // A replica that is idle in this tick keeps its weights and moments; its gradient was not loaded.
@@ -453,7 +456,7 @@ __device__ __forceinline__ void local_step(const StepArgs &a, const ReplicaArgs 
 #pragma unroll
     for (int j = 0; j < 4; ++j) g[j] = (double)in.g.v[j];      // grad_scale is folded into b_m, b_v, c_g
     if (a.replica_scale) {
-        const double rs = (double)factor;
+        const double rs = (double)(early ? *early : a.replica_scale[i]);
 #pragma unroll
         for (int j = 0; j < 4; ++j) g[j] *= rs;
     }
@@ -627,7 +630,7 @@ __device__ __forceinline__ void step_replica(const StepArgs &a, const ReplicaArg
 {
     const uint32_t rb = a.rb;
     if (TAU0) {
-        local_step<OPT>(a, r, replica_factor(a, i), in, w_hat, m_new, v_new);
+        local_step<OPT>(a, r, i, nullptr, in, w_hat, m_new, v_new);
         // the moments are final: out they go, before the averaging needs registers
         if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_tile_f32x4(r.m + tbase, loff, nvalid, m_new, a.through != 0u);
         if (OPT == kOptAdam) store_tile_f32x4(r.v + tbase, loff, nvalid, v_new, a.through != 0u);
@@ -758,7 +761,8 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     // replica, whose values its wave loads and never uses -- with a condition the compiler parks
     // the conversions of the loaded values, and with them a wait for memory, right behind the loads)
     load_group<OPT, GRAD_BF16>(rep, tbase, i < R ? loff : 0u, nvalid, in);      // (an absent replica's wave: one group for all lanes)
-    const float factor = SUM ? 1.0f : replica_factor(a, i < R ? i : 0u);       // (small stages: where it is used, so that the hashing starts at once)
+    constexpr bool kEarlyFactor = !TAU0 && !SUM;
+    const float factor = kEarlyFactor ? replica_factor(a, i < R ? i : 0u) : 1.0f;
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- subsets: bit j of a lane's mask = coordinate 4 group + j is received / sent now.
@@ -897,7 +901,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
                     load_group<OPT, GRAD_BF16>(a.rep[8u * b + wave], tbase, loff, nvalid, pre);
                     load_group_sparse<DIL>(a, ib, tbase, loff, nvalid, s, pre);
                 }
-                local_step<OPT>(a, a.rep[8u * b + wave], replica_factor(a, ib), pre, w_hat, m_new, v_new);
+                local_step<OPT>(a, a.rep[8u * b + wave], ib, nullptr, pre, w_hat, m_new, v_new);
                 uint32_t c = s.rank_recv;
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
@@ -912,7 +916,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     // 10107 / 9924, R = 8, 31.5M 1195 / 1162; per-replica d, 31.5M, R = 2 369 / 363; absent replicas: R = 12, 10M, bf16 772 /
     // 751 (per replica), 713 / 692 (interleaved), R = 6 386 / 364; no change beyond noise on the headline step.
     F4 w_hat, m_new, v_new;
-    if (!TAU0 && i < R) local_step<OPT>(a, rep, SUM ? replica_factor(a, i) : factor, in, w_hat, m_new, v_new);
+    if (!TAU0 && i < R) local_step<OPT>(a, rep, i, kEarlyFactor ? &factor : nullptr, in, w_hat, m_new, v_new);
     lds_dma_wait();
     __syncthreads();
     if (!TAU0 && i < R) {                                  // the moments are final: out they go at once
@@ -1052,7 +1056,7 @@ k_step_local(const StepArgs a)
         if (lane == 0) a.next_lines[tile] = (uint8_t)((count * a.rb + kLineFloats - 1u) / kLineFloats);
     }
     F4 w_hat, m_new, v_new;
-    local_step<OPT>(a, rep, factor, in, w_hat, m_new, v_new);
+    local_step<OPT>(a, rep, i, &factor, in, w_hat, m_new, v_new);
     if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_tile_f32x4(rep.m + tbase, loff, nvalid, m_new, a.through != 0u);
     if (OPT == kOptAdam) store_tile_f32x4(rep.v + tbase, loff, nvalid, v_new, a.through != 0u);
     store_weights<FWD>(a, rep, tbase, loff, nvalid, in, w_hat, w_hat);
@@ -1191,7 +1195,7 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
 
     F4 w_hat[V], w_new[V], m_new[V], v_new[V];
 #pragma unroll
-    for (int v = 0; v < V; ++v) local_step<OPT>(a, rep[v], factor[v], in[v], w_hat[v], m_new[v], v_new[v]);
+    for (int v = 0; v < V; ++v) local_step<OPT>(a, rep[v], i0 + v, &factor[v], in[v], w_hat[v], m_new[v], v_new[v]);
     lds_dma_wait();                                          // (before the first store: the wait counts stores, too)
     wave_lds_sync();
 #pragma unroll
@@ -1338,7 +1342,6 @@ __device__ __forceinline__ void step_tile_sync(const StepArgs &a, const uint32_t
     const ReplicaArgs rep = a.rep[8u * b + slot];
     GroupIn in;
     load_group<OPT, GRAD_BF16>(rep, tbase, loff, nvalid, in);
-    const float factor = replica_factor(a, wave);
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- the subset: hashed by the first wave of every block (which requests its block's lines of an
@@ -1397,7 +1400,7 @@ __device__ __forceinline__ void step_tile_sync(const StepArgs &a, const uint32_t
             *reinterpret_cast<v4f *>(L.recv + q * tile_floats + f * 4u) = v4f{0.f, 0.f, 0.f, 0.f};
 
     F4 w_hat, m_new, v_new;
-    local_step<OPT>(a, rep, factor, in, w_hat, m_new, v_new);
+    local_step<OPT>(a, rep, wave, nullptr, in, w_hat, m_new, v_new);
     lds_dma_wait();
     __syncthreads();
     if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_tile_f32x4(rep.m + tbase, loff, nvalid, m_new, a.through != 0u);

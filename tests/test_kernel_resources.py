@@ -1,0 +1,50 @@
+"""Registers of kernels whose time depends on how many of their waves are resident, as the compiler reports them (no GPU needed)."""
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2601_22442_amd.build import HIPCC_FLAGS, PKG
+
+FLAGS = [f for f in HIPCC_FLAGS if f not in ("-shared", "-Wall", "-Wextra")]
+ADAM = 2
+# template arguments: optimizer, bf16 gradients, forward copy (none, fp32, bf16), interleaved EMA vectors, walking
+SYNC = [("k_step_sync", (ADAM, bf16, fwd, dil)) for bf16, fwd in ((False, 1), (True, 2), (False, 0)) for dil in (False, True)]
+WALKING = [("k_step", (ADAM, bf16, fwd, dil, True)) for bf16, fwd in ((False, 1), (False, 0)) for dil in (False, True)]
+
+
+def _cxx(kernel):
+    name, args = kernel
+    return f"am::{name}<{', '.join(str(x).lower() for x in args)}>"
+
+
+def _mangled(kernel):
+    name, args = kernel
+    return f"_ZN2am{len(name)}{name}I" + "".join(f"L{'b' if isinstance(x, bool) else 'i'}{int(x)}E" for x in args) + "E"
+
+
+@pytest.fixture(scope="module")
+def resources(tmp_path_factory):
+    if shutil.which("hipcc") is None:
+        pytest.skip("no hipcc")
+    kernels = SYNC + WALKING
+    src = tmp_path_factory.mktemp("kernels") / "kernels.hip"
+    src.write_text(f'#include "{PKG}/csrc/am_kernels.h"\n' + "".join(f"template __global__ void {_cxx(k)}(const am::StepArgs);\n" for k in kernels))
+    out = subprocess.run(["hipcc", *FLAGS, "-c", "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-o", "/dev/null", str(src)],
+                         capture_output=True, text=True, check=True).stderr
+    found = {}
+    for part in out.split("Function Name: ")[1:]:
+        found[part.split()[0]] = {k: int(v) for k, v in re.findall(r"remark: .*? (VGPRs|VGPRs Spill|ScratchSize)(?: \[\S+\])?: (\d+)", part)}
+    return {k: next(v for name, v in found.items() if name.startswith(_mangled(k))) for k in kernels}
+
+
+@pytest.mark.parametrize("kernel", SYNC, ids=_cxx)
+def test_two_workgroups_of_sixteen_waves_fit(resources, kernel):
+    """32 waves on the four SIMDs of a compute unit: eight each, 64 registers of 512."""
+    assert resources[kernel]["VGPRs"] <= 64 and resources[kernel]["ScratchSize"] == 0
+
+
+@pytest.mark.parametrize("kernel", WALKING, ids=_cxx)
+def test_the_walking_step_needs_no_scratch(resources, kernel):
+    assert resources[kernel]["VGPRs Spill"] == 0 and resources[kernel]["ScratchSize"] == 0
