@@ -4,8 +4,9 @@ slots, ragged tiles, more received coordinates than a turn holds, every optimize
 import numpy as np
 import pytest
 import torch
-from test_gpu_parity import TOL_F32, compare, grads_for, make_pair, rel_err, run_steps
+from test_gpu_parity import EMPTY_P, TOL_F32, compare, grads_for, make_pair, rel_err, run_steps
 
+import synth_inputs as si
 from oracle import oracle as O
 
 pytestmark = pytest.mark.gpu
@@ -71,3 +72,46 @@ def test_idle_replicas_and_factors(amlib):
     compare(st, orc, "masked")
     for i in range(R):
         assert rel_err(st.m[i].cpu().numpy(), orc.m(i)) < TOL_F32
+
+
+@pytest.mark.parametrize("layout,kw", [(PER_REPLICA, LOOK), (INTERLEAVED, LOOK), (PER_REPLICA, dict(NONE, optimizer=O.OPT_SGD, beta1=0.9))])
+def test_idle_replicas_and_factors_of_a_pair(amlib, layout, kw):
+    """Two replicas a wave: factors that differ inside a pair, one idle replica of a pair, the other one of the next."""
+    n, R = 2_100_003, 10
+    st, orc = make_pair(amlib, n, R, delay=1, fraction=0.05, seed=3, **layout, **kw)
+    scale = np.array([1.0, 0.5, 0.25, 2.0, 0.125, 4.0, 0.5, 1.0, 2.0, 0.25], np.float32)      # powers of two: the scaled gradients are exact
+    for t in range(1, 5):
+        g, gd = grads_for(n, R, t, 3, False)
+        mask = 0b10_0110_1101 if t % 2 == 0 else 0b11_1111_1111
+        st.step_masked(t, gd, 1e-3, 0.5, mask, 1.0, torch.from_numpy(scale).cuda())
+        orc.step_masked(t, [x * f for x, f in zip(g, scale)], 1e-3, 0.5, mask)
+    compare(st, orc, "masked pairs")
+
+
+@pytest.mark.parametrize("R,layout", [(10, PER_REPLICA), (10, INTERLEAVED), (9, PER_REPLICA), (9, INTERLEAVED)])
+def test_a_slot_that_is_too_small(amlib, R, layout):
+    """The tiles past the slot's capacity evolve as if never averaged, those before it follow the method, and the flag is raised."""
+    n, p, seed, steps, cap, rb = 2_100_003, 0.1, 19, 4, 40_000, 8
+    kw = dict(delay=1, seed=seed, **LOOK)
+    w0 = si.stage_weights(n, seed)
+    st = amlib.init_state(amlib.make_config(n, R, fraction=p, ring_cap_lines=cap, **layout, **kw), torch.from_numpy(w0).cuda())
+    full, never = O.Oracle(n, R, fraction=p, **kw), O.Oracle(n, R, fraction=EMPTY_P, **kw)
+    full.set_w(w0); never.set_w(w0)
+    first_dropped = []
+    for t in range(1, steps + 1):
+        g, gd = grads_for(n, R, t, seed, False)
+        st.step(t, gd, 1e-3, 0.5); full.step(t, g, 1e-3, 0.5); never.step(t, g, 1e-3, 0.5)
+        counts = np.bincount((O.subset(seed, t, n, p) // 256).astype(np.int64), minlength=-(-n // 256))
+        lines = -(-counts * rb // 32)
+        start = np.cumsum(lines) - lines
+        assert (start + lines > cap).any()
+        first_dropped.append(int(np.argmax(start + lines > cap)))
+    lo, hi = min(first_dropped) * 256, (max(first_dropped) + 1) * 256
+    assert 0 < lo <= hi < n - 100_000
+    for i in range(R):
+        for name in ("w", "m", "v", "d", "fwd"):
+            got = getattr(st, name)[i].cpu().numpy()
+            assert rel_err(got[:lo], getattr(full, name)(i)[:lo]) < TOL_F32, (name, i, "kept tiles")
+            assert rel_err(got[hi:], getattr(never, name)(i)[hi:]) < TOL_F32, (name, i, "dropped tiles")
+    assert not np.any(st.d[0].cpu().numpy()[hi:]) and np.any(st.d[0].cpu().numpy()[:lo])
+    assert st.read_flags() & 1
