@@ -431,10 +431,10 @@ __device__ __forceinline__ void write_send_word(const StepArgs &a, uint32_t tile
 
 // Replica i's own gradient factor, a scalar load that large stages request beside the operands.  (A vector load where the factor is used waits
 // for everything that is on its way before it.)
-__device__ __forceinline__ float replica_factor(const StepArgs &a, uint32_t i)
+__device__ __forceinline__ float replica_factor(const StepArgs &a, const ReplicaArgs &r, uint32_t i)
 {
-    typedef const float __attribute__((address_space(4))) *const_f32_ptr;
-    return a.replica_scale ? ((const_f32_ptr)(uintptr_t)a.replica_scale)[i] : 1.0f;
+    const float *const p = a.replica_scale ? a.replica_scale + i : r.w;
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)uniform_load(reinterpret_cast<const uint32_t *>(p), 0)));
 }
 
 // Local optimizer step on one group of replica i, from loaded operands.  early: its replica_factor(), where the caller has requested it beside the
@@ -548,13 +548,14 @@ __device__ __forceinline__ void load_group_sparse(const StepArgs &a, uint32_t i,
     if (!DIL && a.ema && s.half_recv) in.d = load_f32x4(a.d[i] + tbase, loff, nvalid);
 }
 
-// The new weights of one group and their forward copy.
-template <int FWD>
+// The new weights of one group and their forward copy.  SHORT: a bf16 copy without look-ahead is one conversion of the stored weight (the same bits); not in the
+// walking form, which has no registers for a second way through (us a step with it / without: R = 20 1.5M 231 / 222, R = 32 408 / 389).
+template <int FWD, bool SHORT = true>
 __device__ __forceinline__ void store_weights(const StepArgs &a, const ReplicaArgs &r, uint64_t tbase, uint32_t loff, int nvalid, const GroupIn &in,
                                               const F4 &w_hat, const F4 &w_new)
 {
     store_tile_f32x4(r.w + tbase, loff, nvalid, w_new, a.through != 0u);
-    if (FWD == kFwdBf16 && !a.lookahead) {
+    if (SHORT && FWD == kFwdBf16 && !a.lookahead) {
         store_bf16x4_from_f32(static_cast<uint16_t *>(r.fwd) + tbase, loff, nvalid, w_new, a.through != 0u);
     } else if (FWD != kFwdNone) {
         // fwd = w + gamma (w^ - w_before): product and sum rounded separately in fp64, then ONE
@@ -576,9 +577,9 @@ __device__ __forceinline__ void store_weights(const StepArgs &a, const ReplicaAr
 }
 
 // Replica i (slot `slot` of its block) of one group, from its stepped weights to stored results: the
-// receive, the new weights and the forward copy.
+// receive, the new weights and the forward copy.  WALKS: the workgroup walks the blocks of its tile.
 // recv_block: what the replicas of i's block sent tau rounds ago, [rank][rb] (TAU0: unused, the sent value is w^ itself).
-template <int FWD, bool DIL, bool TAU0>
+template <int FWD, bool DIL, bool TAU0, bool WALKS>
 __device__ __forceinline__ void finish_replica(const StepArgs &a, const ReplicaArgs &r, uint32_t i, uint32_t slot, uint64_t tbase, uint32_t loff, int nvalid,
                                                const GroupSubsets &s, const bool tile_receives, const float (&abar)[4], GroupIn &in,
                                                const F4 &w_hat, const float *recv_block, const TileLds &L)
@@ -619,7 +620,7 @@ __device__ __forceinline__ void finish_replica(const StepArgs &a, const ReplicaA
     }
     if (!DIL && a.ema && s.half_recv) store_tile_f32x4(a.d[i] + tbase, loff, nvalid, in.d, a.through != 0u);
 
-    store_weights<FWD>(a, r, tbase, loff, nvalid, in, w_hat, w_new);
+    store_weights<FWD, !WALKS>(a, r, tbase, loff, nvalid, in, w_hat, w_new);
 }
 
 // The same from loaded operands: local step (unless the caller has done it while it waited), send, receive.
@@ -642,7 +643,7 @@ __device__ __forceinline__ void step_replica(const StepArgs &a, const ReplicaArg
         for (int j = 0; j < 4; ++j)
             if ((s.mask_send >> j) & 1u) L.send[(c++) * rb + slot] = w_hat.v[j];
     }
-    finish_replica<FWD, DIL, TAU0>(a, r, i, slot, tbase, loff, nvalid, s, tile_receives, abar, in, w_hat, recv_block, L);
+    finish_replica<FWD, DIL, TAU0, TAU0>(a, r, i, slot, tbase, loff, nvalid, s, tile_receives, abar, in, w_hat, recv_block, L);
 }
 
 template <int RB>
@@ -762,7 +763,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     // the conversions of the loaded values, and with them a wait for memory, right behind the loads)
     load_group<OPT, GRAD_BF16>(rep, tbase, i < R ? loff : 0u, nvalid, in);      // (an absent replica's wave: one group for all lanes)
     constexpr bool kEarlyFactor = !TAU0 && !SUM;
-    const float factor = kEarlyFactor ? replica_factor(a, i < R ? i : 0u) : 1.0f;
+    const float factor = kEarlyFactor ? replica_factor(a, rep, i < R ? i : 0u) : 1.0f;
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- subsets: bit j of a lane's mask = coordinate 4 group + j is received / sent now.
@@ -1046,7 +1047,7 @@ k_step_local(const StepArgs a)
     const ReplicaArgs rep = a.rep[8u * (i >> a.rb_shift) + (i & (a.rb - 1u))];
     GroupIn in;
     load_group<OPT, GRAD_BF16>(rep, tbase, loff, nvalid, in);
-    const float factor = replica_factor(a, i);
+    const float factor = replica_factor(a, rep, i);
     __builtin_amdgcn_sched_barrier(0);
     if (a.do_next && i == 0u) {                              // how many lines the tile sends next step
         SubsetKey key = a.key;
@@ -1122,7 +1123,7 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
     for (int v = 0; v < V; ++v) load_group<OPT, GRAD_BF16>(rep[v], tbase, loff, nvalid, in[v]);
     float factor[V];
 #pragma unroll
-    for (int v = 0; v < V; ++v) factor[v] = replica_factor(a, i0 + v);
+    for (int v = 0; v < V; ++v) factor[v] = replica_factor(a, rep[v], i0 + v);
     __builtin_amdgcn_sched_barrier(0);
 
     uint32_t word_s = 0, base_s = 0, word_r = 0, base_r = 0;
@@ -1443,7 +1444,7 @@ __device__ __forceinline__ void step_tile_sync(const StepArgs &a, const uint32_t
     }
     TileLds mine = L;
     if (DIL) mine.d = L.d + b * tile_floats;
-    finish_replica<FWD, DIL, true>(a, rep, wave, slot, tbase, loff, nvalid, s, count != 0u, abar, in, w_hat, nullptr, mine);
+    finish_replica<FWD, DIL, true, false>(a, rep, wave, slot, tbase, loff, nvalid, s, count != 0u, abar, in, w_hat, nullptr, mine);
     if (DIL && a.ema && d_lines) {
         __syncthreads();
         for (uint32_t q = 0; q < a.nblocks; ++q)

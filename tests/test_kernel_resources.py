@@ -11,7 +11,7 @@ FLAGS = [f for f in HIPCC_FLAGS if f not in ("-shared", "-Wall", "-Wextra")]
 ADAM = 2
 # template arguments: optimizer, bf16 gradients, forward copy (none, fp32, bf16), interleaved EMA vectors, walking
 SYNC = [("k_step_sync", (ADAM, bf16, fwd, dil)) for bf16, fwd in ((False, 1), (True, 2), (False, 0)) for dil in (False, True)]
-WALKING = [("k_step", (ADAM, bf16, fwd, dil, True)) for bf16, fwd in ((False, 1), (False, 0)) for dil in (False, True)]
+WALKING = [("k_step", (ADAM, bf16, fwd, dil, True)) for bf16, fwd in ((False, 1), (True, 2), (False, 0)) for dil in (False, True)]
 
 
 def _cxx(kernel):
