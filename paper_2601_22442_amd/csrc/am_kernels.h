@@ -429,20 +429,13 @@ __device__ __forceinline__ void write_send_word(const StepArgs &a, uint32_t tile
     if (tile + 1u == a.ntiles) a.send_sb_out[tile / kTilesPerSuperblock + 1u] = first + lines;
 }
 
-// Replica i's own gradient factor, a scalar load that large stages request beside the operands.  (A vector load where the factor is used waits
-// for everything that is on its way before it.)
-__device__ __forceinline__ float replica_factor(const StepArgs &a, const ReplicaArgs &r, uint32_t i)
-{
-    const float *const p = a.replica_scale ? a.replica_scale + i : r.w;
-    return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)uniform_load(reinterpret_cast<const uint32_t *>(p), 0)));
-}
-
-// Local optimizer step on one group of replica i, from loaded operands.  early: its replica_factor(), where the caller has requested it beside the
-// operands; nullptr: read where it is used, in kernels that have no registers for it: held from the operands on, it takes two to four vector registers, without factors, too.
-// Time so / read late: k_step_sync (65 / 61 registers: two workgroups of 16 waves no longer fit a compute unit) R = 13 3M 1.10, R = 15 300k 1.17, R = 16 no correction 3M 1.17; the
-// walking form (40 bytes of scratch a lane / none) R = 20 1.5M 1.10, R = 32 1.09.  Small stages: with factors 1M R = 4 0.98, without 1.002 (2M R = 4, 31.5M R = 8, k_step: 0.99 and 0.99 with factors).
-template <int OPT>
-__device__ __forceinline__ void local_step(const StepArgs &a, const ReplicaArgs &r, uint32_t i, const float *early, const GroupIn &in,
+// Local optimizer step on one group of replica i, from loaded operands.  SCALAR: the replica's gradient factor is a scalar load; a vector load waits for everything
+// that is on its way before it, but the kernels of small stages and those without delay have no scalar registers to spare (the former spill some already).  Either way it is read where it is
+// used: requested beside the operands it takes registers in every step, without factors, too.  us a step, vector load / requested early / scalar load here: 3M AdamW, with factors R = 2 43.8 / 42.1 / 41.9,
+// R = 8 150.8 / 148.7 / 148.4, without R = 1 24.5 / 25.0 / 24.5, R = 2 41.6 / 42.1 / 41.6; SGD with momentum R = 1 18.4 / 19.0 / 18.4, R = 6 4M with 94.9 / 90.2 / 89.6.  No delay, early: k_step_sync (65
+// registers for 61: two workgroups of 16 waves no longer fit a compute unit) R = 13 3M 1.10 of the time, R = 15 300k 1.17, R = 16 no correction 3M 1.17; the walking form (40 bytes of scratch a lane for none) R = 20 1.5M 1.10, R = 32 1.09.
+template <int OPT, bool SCALAR>
+__device__ __forceinline__ void local_step(const StepArgs &a, const ReplicaArgs &r, uint32_t i, const GroupIn &in,
                                            F4 &w_hat, F4 &m_new, F4 &v_new)
 {
     // A replica that is idle in this tick keeps its weights and moments; its gradient was not loaded.
@@ -456,7 +449,7 @@ __device__ __forceinline__ void local_step(const StepArgs &a, const ReplicaArgs 
 #pragma unroll
     for (int j = 0; j < 4; ++j) g[j] = (double)in.g.v[j];      // grad_scale is folded into b_m, b_v, c_g
     if (a.replica_scale) {
-        const double rs = (double)(early ? *early : a.replica_scale[i]);
+        const double rs = (double)(SCALAR ? __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)uniform_load(reinterpret_cast<const uint32_t *>(a.replica_scale), i))) : a.replica_scale[i]);
 #pragma unroll
         for (int j = 0; j < 4; ++j) g[j] *= rs;
     }
@@ -631,7 +624,7 @@ __device__ __forceinline__ void step_replica(const StepArgs &a, const ReplicaArg
 {
     const uint32_t rb = a.rb;
     if (TAU0) {
-        local_step<OPT>(a, r, i, nullptr, in, w_hat, m_new, v_new);
+        local_step<OPT, false>(a, r, i, in, w_hat, m_new, v_new);
         // the moments are final: out they go, before the averaging needs registers
         if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_tile_f32x4(r.m + tbase, loff, nvalid, m_new, a.through != 0u);
         if (OPT == kOptAdam) store_tile_f32x4(r.v + tbase, loff, nvalid, v_new, a.through != 0u);
@@ -762,8 +755,6 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     // replica, whose values its wave loads and never uses -- with a condition the compiler parks
     // the conversions of the loaded values, and with them a wait for memory, right behind the loads)
     load_group<OPT, GRAD_BF16>(rep, tbase, i < R ? loff : 0u, nvalid, in);      // (an absent replica's wave: one group for all lanes)
-    constexpr bool kEarlyFactor = !TAU0 && !SUM;
-    const float factor = kEarlyFactor ? replica_factor(a, rep, i < R ? i : 0u) : 1.0f;
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- subsets: bit j of a lane's mask = coordinate 4 group + j is received / sent now.
@@ -902,7 +893,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
                     load_group<OPT, GRAD_BF16>(a.rep[8u * b + wave], tbase, loff, nvalid, pre);
                     load_group_sparse<DIL>(a, ib, tbase, loff, nvalid, s, pre);
                 }
-                local_step<OPT>(a, a.rep[8u * b + wave], ib, nullptr, pre, w_hat, m_new, v_new);
+                local_step<OPT, false>(a, a.rep[8u * b + wave], ib, pre, w_hat, m_new, v_new);
                 uint32_t c = s.rank_recv;
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
@@ -917,7 +908,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &a, const uint32_t tile
     // 10107 / 9924, R = 8, 31.5M 1195 / 1162; per-replica d, 31.5M, R = 2 369 / 363; absent replicas: R = 12, 10M, bf16 772 /
     // 751 (per replica), 713 / 692 (interleaved), R = 6 386 / 364; no change beyond noise on the headline step.
     F4 w_hat, m_new, v_new;
-    if (!TAU0 && i < R) local_step<OPT>(a, rep, i, kEarlyFactor ? &factor : nullptr, in, w_hat, m_new, v_new);
+    if (!TAU0 && i < R) local_step<OPT, !SUM>(a, rep, i, in, w_hat, m_new, v_new);
     lds_dma_wait();
     __syncthreads();
     if (!TAU0 && i < R) {                                  // the moments are final: out they go at once
@@ -1047,7 +1038,6 @@ k_step_local(const StepArgs a)
     const ReplicaArgs rep = a.rep[8u * (i >> a.rb_shift) + (i & (a.rb - 1u))];
     GroupIn in;
     load_group<OPT, GRAD_BF16>(rep, tbase, loff, nvalid, in);
-    const float factor = replica_factor(a, rep, i);
     __builtin_amdgcn_sched_barrier(0);
     if (a.do_next && i == 0u) {                              // how many lines the tile sends next step
         SubsetKey key = a.key;
@@ -1057,7 +1047,7 @@ k_step_local(const StepArgs a)
         if (lane == 0) a.next_lines[tile] = (uint8_t)((count * a.rb + kLineFloats - 1u) / kLineFloats);
     }
     F4 w_hat, m_new, v_new;
-    local_step<OPT>(a, rep, i, &factor, in, w_hat, m_new, v_new);
+    local_step<OPT, true>(a, rep, i, in, w_hat, m_new, v_new);
     if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_tile_f32x4(rep.m + tbase, loff, nvalid, m_new, a.through != 0u);
     if (OPT == kOptAdam) store_tile_f32x4(rep.v + tbase, loff, nvalid, v_new, a.through != 0u);
     store_weights<FWD>(a, rep, tbase, loff, nvalid, in, w_hat, w_hat);
@@ -1121,9 +1111,6 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
     GroupIn in[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) load_group<OPT, GRAD_BF16>(rep[v], tbase, loff, nvalid, in[v]);
-    float factor[V];
-#pragma unroll
-    for (int v = 0; v < V; ++v) factor[v] = replica_factor(a, rep[v], i0 + v);
     __builtin_amdgcn_sched_barrier(0);
 
     uint32_t word_s = 0, base_s = 0, word_r = 0, base_r = 0;
@@ -1196,7 +1183,7 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
 
     F4 w_hat[V], w_new[V], m_new[V], v_new[V];
 #pragma unroll
-    for (int v = 0; v < V; ++v) local_step<OPT>(a, rep[v], i0 + v, &factor[v], in[v], w_hat[v], m_new[v], v_new[v]);
+    for (int v = 0; v < V; ++v) local_step<OPT, true>(a, rep[v], i0 + v, in[v], w_hat[v], m_new[v], v_new[v]);
     lds_dma_wait();                                          // (before the first store: the wait counts stores, too)
     wave_lds_sync();
 #pragma unroll
@@ -1401,7 +1388,7 @@ __device__ __forceinline__ void step_tile_sync(const StepArgs &a, const uint32_t
             *reinterpret_cast<v4f *>(L.recv + q * tile_floats + f * 4u) = v4f{0.f, 0.f, 0.f, 0.f};
 
     F4 w_hat, m_new, v_new;
-    local_step<OPT>(a, rep, wave, nullptr, in, w_hat, m_new, v_new);
+    local_step<OPT, false>(a, rep, wave, in, w_hat, m_new, v_new);
     lds_dma_wait();
     __syncthreads();
     if (OPT == kOptSgdMomentum || OPT == kOptAdam) store_tile_f32x4(rep.m + tbase, loff, nvalid, m_new, a.through != 0u);
