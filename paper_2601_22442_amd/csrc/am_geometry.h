@@ -22,5 +22,8 @@ constexpr uint32_t kStageFloats = 256;      // ring values of a block (and EMA e
 constexpr uint32_t kLdsBytes = 160 * 1024, kLdsGranule = 1280;      // of a compute unit
 constexpr uint32_t kMaxReplicas = 32;
 constexpr uint32_t kMaxBlockReplicas = 8;
+// Tiles whose replicas follow each other in the step by one-wave workgroups; a multiple of the XCDs.  us a step by their number, nine waves a compute unit: interleaved 125.8M x 8 64: 5804, 128: 5626, 192: 5750, 256: 5799, 512: 5731,
+// 31.5M 1433, 1409, 1441, 1426, 1436; per replica 125.8M, eight waves, 64: 6332, 128: 6278, 256: 6355, 512: 6457.
+constexpr uint32_t kWaveChunk = 128;
 
 }  // namespace am

@@ -288,6 +288,15 @@ inline bool step_by_waves(const am_config &c, const Blocks &b)
 // of the fused kernel's time, one 1.01, two 0.98).
 inline uint32_t wave_step_replicas(const am_config &c) { return c.replicas % 2u ? 1u : 2u; }
 
+// Its grid: the tiles of a chunk and the tile's waves in x, the chunks in y, and past 32768 chunks (2^30 coordinates) in z, too: neither of those may pass 65535, and
+// a stage has up to 131,040 chunks.
+struct Grid { uint32_t x, y, z; };
+inline Grid wave_step_grid(uint32_t ntiles, uint32_t waves_of_a_tile)
+{
+    const uint32_t chunks = (ntiles + am::kWaveChunk - 1u) / am::kWaveChunk, y = std::min(chunks, 32768u);
+    return {am::kWaveChunk * waves_of_a_tile, y, (chunks + y - 1u) / y};
+}
+
 // Waves of it that a compute unit may hold: the less a wave moves the more of them, and one more where the step is short.  Time over the fused kernel's by their number,
 // two replicas a wave: interleaved 125.8M x 8 (8.3 KB a replica) 8: 0.968, 9: 0.949, 10: 0.953, 11: 0.959; 60M weights 9: 0.961, 10: 0.970, 11: 0.947, 12: 0.949; per replica 31.5M x 8 (9.4 KB) 8: 0.921,
 // 9: 0.927, 10: 0.933, 12: 0.952; 80M weights without a forward copy (7.3 KB) 8: 1.070, 10: 0.990, 12: 0.979, 14: 0.988; bf16 without correction (6.1 KB) 8: 1.083, 10: 0.974, 11: 0.954, 14: 0.966;

@@ -1286,24 +1286,22 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
     for (int v = 0; v < V; ++v) store_weights<FWD>(a, rep[v], tbase, loff, nvalid, in[v], w_hat[v], w_new[v]);
 }
 
-// Tiles whose replicas follow each other; a multiple of the XCDs.  us a step by their number, nine waves a compute unit: interleaved 125.8M x 8 64: 5804, 128: 5626, 192: 5750, 256: 5799, 512: 5731,
-// 31.5M 1433, 1409, 1441, 1426, 1436; per replica 125.8M, eight waves, 64: 6332, 128: 6278, 256: 6355, 512: 6457.
-constexpr uint32_t kWaveChunk = 128;
+// Floats of dynamic LDS that it needs.
 __host__ __device__ inline uint32_t step_wave_lds_floats(uint32_t nblocks, bool d_interleaved, uint32_t v)
 {
     return nblocks * kStageFloats + (d_interleaved ? 64u * v + 16u : 64u);
 }
 
-// grid = (tiles of a chunk, replicas / V, chunks); blockDim = 64; dynamic LDS = step_wave_lds_floats() floats, or more where fewer are to be resident
+// grid = am_host::wave_step_grid(); blockDim = 64; dynamic LDS = step_wave_lds_floats() floats, or more where fewer are to be resident
 template <int OPT, bool GRAD_BF16, int FWD, bool DIL, int V>
 __global__ void __launch_bounds__(64, 4)
 k_step_wave(const StepArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    const uint32_t tile = blockIdx.z * kWaveChunk + blockIdx.x;
+    const uint32_t tile = (blockIdx.z * gridDim.y + blockIdx.y) * kWaveChunk + blockIdx.x % kWaveChunk, i0 = V * (blockIdx.x / kWaveChunk);
     if (tile >= a.ntiles) return;
-    if ((uint64_t)(tile + 1u) * kTileCoords <= a.n) step_wave<OPT, GRAD_BF16, FWD, DIL, V, true>(a, tile, V * blockIdx.y, threadIdx.x, lds);
-    else step_wave<OPT, GRAD_BF16, FWD, DIL, V, false>(a, tile, V * blockIdx.y, threadIdx.x, lds);
+    if ((uint64_t)(tile + 1u) * kTileCoords <= a.n) step_wave<OPT, GRAD_BF16, FWD, DIL, V, true>(a, tile, i0, threadIdx.x, lds);
+    else step_wave<OPT, GRAD_BF16, FWD, DIL, V, false>(a, tile, i0, threadIdx.x, lds);
 }
 
 // tau = 0 with at most kSyncWaves replicas: the average is of this step's values, so a tile needs all its

@@ -238,7 +238,8 @@ am_status launch_step_tau(am_state *st, const am::StepArgs &a)
     if (!tau0 && !a.sum_lines && am_host::step_by_waves(st->cfg, B)) {
         const uint32_t v = am_host::wave_step_replicas(st->cfg);
         const uint32_t lds = am_host::lds_for_residency(am::step_wave_lds_floats(B.nblocks, DIL, v) * (uint32_t)sizeof(float), am_host::wave_step_workgroups(st->cfg, B, v, st->has_fwd, a.do_recv != 0u));
-        const dim3 waves(am::kWaveChunk, a.replicas / v, (st->lay.ntiles + am::kWaveChunk - 1u) / am::kWaveChunk);
+        const am_host::Grid g = am_host::wave_step_grid(st->lay.ntiles, a.replicas / v);
+        const dim3 waves(g.x, g.y, g.z);
         if (v == 2u) am::k_step_wave<OPT, GBF, FWD, DIL, 2><<<waves, 64, lds, st->stream>>>(a);
         else am::k_step_wave<OPT, GBF, FWD, DIL, 1><<<waves, 64, lds, st->stream>>>(a);
         AM_HIP(hipGetLastError());

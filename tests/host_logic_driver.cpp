@@ -72,6 +72,13 @@ uint32_t hl_step_by_waves(const am_config *c, int forward_copy)
     return am_host::step_by_waves(*c, b) ? am_host::wave_step_workgroups(*c, b, am_host::wave_step_replicas(*c), forward_copy != 0, true) : 0u;
 }
 
+// its grid, x, y and z
+void hl_wave_step_grid(uint32_t ntiles, uint32_t waves_of_a_tile, uint32_t *out)
+{
+    const am_host::Grid g = am_host::wave_step_grid(ntiles, waves_of_a_tile);
+    out[0] = g.x; out[1] = g.y; out[2] = g.z;
+}
+
 int hl_local_step_alone(const am_config *c) { return am_host::local_step_alone(*c, am_host::block_geometry(c->replicas)); }
 uint32_t hl_average_workgroups(const am_config *c)
 {

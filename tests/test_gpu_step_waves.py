@@ -4,7 +4,7 @@ slots, ragged tiles, more received coordinates than a turn holds, every optimize
 import numpy as np
 import pytest
 import torch
-from test_gpu_parity import EMPTY_P, TOL_F32, compare, grads_for, make_pair, rel_err, run_steps
+from test_gpu_parity import EMPTY_P, TOL_F32, _free_hbm, _full_size_case, compare, grads_for, make_pair, rel_err, run_steps
 
 import synth_inputs as si
 from oracle import oracle as O
@@ -115,3 +115,11 @@ def test_a_slot_that_is_too_small(amlib, R, layout):
             assert rel_err(got[hi:], getattr(never, name)(i)[hi:]) < TOL_F32, (name, i, "dropped tiles")
     assert not np.any(st.d[0].cpu().numpy()[hi:]) and np.any(st.d[0].cpu().numpy()[:lo])
     assert st.read_flags() & 1
+
+
+def test_more_chunks_than_one_dimension_of_a_grid_holds(amlib):
+    """128 tiles a chunk, 65535 chunks and one tile: windows at both ends and about 2^30, where the grid's next layer begins."""
+    n = 65_535 * 128 * 256 + 1
+    if _free_hbm() < 160e9:
+        pytest.skip("not enough free HBM")
+    _full_size_case(amlib, n, 5, 1, 0.002, 3, [(0, 30_000), ((1 << 30) - 15_000, 30_000), (n - 30_001, 30_001)], lookahead=False, optimizer=O.OPT_SGD, beta1=0.0, **PER_REPLICA)

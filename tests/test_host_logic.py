@@ -237,6 +237,16 @@ def test_large_steps_go_by_waves(hl, n, R, kw, fwd, waves):
     assert hl.hl_step_by_waves(C.byref(_config(n=n, replicas=R, delay=1, **kw)), fwd) == waves
 
 
+@pytest.mark.parametrize("n", [2_097_153, 32_768 * 128 * 256, 32_768 * 128 * 256 + 1, 65_535 * 128 * 256 + 1, (1 << 31) + 1, (1 << 32) - (1 << 20) - 1])
+@pytest.mark.parametrize("waves", [4, 5, 16, 31])
+def test_the_grid_of_a_step_by_waves_covers_every_stage(hl, n, waves):
+    """128 tiles a chunk: a grid may have 65535 workgroups in y and in z, and 2^32 work-items in x."""
+    ntiles, g = (n + 255) // 256, (C.c_uint32 * 3)()
+    hl.hl_wave_step_grid(ntiles, waves, g)
+    assert g[0] == 128 * waves and g[1] <= 65_535 and g[2] <= 65_535
+    assert g[1] * g[2] * 128 >= ntiles and g[1] * (g[2] - 1) * 128 < ntiles          # no tile is left out, no layer of the grid is idle
+
+
 @pytest.mark.parametrize("workgroups", [2, 3, 4, 5, 6, 7, 11])
 @pytest.mark.parametrize("fixed", [0, 16])
 def test_lds_holds_as_many_workgroups_as_a_rule_names(hl, workgroups, fixed):
