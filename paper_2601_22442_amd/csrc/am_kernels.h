@@ -1074,7 +1074,10 @@ __device__ __forceinline__ void store_entry(float *p, const Entry<V> &x)
     else *p = x.v[0];
 }
 
-// The step of large stages with a delay (am_host::step_by_waves): a workgroup is ONE wave, which takes V
+constexpr uint32_t kWaveBlockShift = 3;                      // log2 of a block's replicas, in the kernel below
+constexpr uint32_t kWaveTurn = kStageFloats >> kWaveBlockShift;         // received coordinates of a turn
+
+// The step of large stages of blocks of eight replicas with a delay, in rounds that send (am_host::step_by_waves; steps between rounds go through k_step_local): a workgroup is ONE wave, which takes V
 // neighbouring replicas of a block through one tile; no barrier, and what the replicas of a tile share meets in the L2.
 // What it buys is order.  The stream mix moves faster the fewer streams are on their way at a time and the finer the grain in which waves come and go
 // (without arithmetic, 125.8M x 8: a workgroup of eight waves a tile 5.7 TB/s with three of them a compute unit and 6.2 with two; one-wave workgroups, 16 a
@@ -1091,7 +1094,8 @@ __device__ __forceinline__ void store_entry(float *p, const Entry<V> &x)
 template <int OPT, bool GRAD_BF16, int FWD, bool DIL, int V, bool FULL>
 __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile, const uint32_t i0, const uint32_t lane, float *lds)
 {
-    const uint32_t sh = a.rb_shift, b = i0 >> sh, slot = i0 & (a.rb - 1u);
+    constexpr uint32_t sh = kWaveBlockShift, turn = kWaveTurn;
+    const uint32_t b = i0 >> sh, slot = i0 & ((1u << sh) - 1u);
     const uint64_t group = (uint64_t)tile * 64u + lane;
     const uint64_t mu = group * 4u;
     const int nvalid = FULL ? 4 : (mu >= a.n ? 0 : (a.n - mu >= 4u ? 4 : (int)(a.n - mu)));
@@ -1100,9 +1104,8 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
     const uint64_t block_floats = (uint64_t)a.cap_lines * kLineFloats;
     constexpr uint32_t kNone = 0x40000000u;                  // past the end of every resource
     float *const ring = lds, *const mean = ring + a.nblocks * kStageFloats;
-    float *const x_lds = mean;                               // (DIL) [V][64] my replicas' weights of the received coordinates of a turn, by rank
-    uint8_t *const list = reinterpret_cast<uint8_t *>(x_lds + V * 64u);     // (DIL) those coordinates
-    const uint32_t turn = 64u < (kStageFloats >> sh) ? 64u : kStageFloats >> sh;      // ranks of a turn
+    float *const x_lds = mean;                               // (DIL) [V][turn] my replicas' weights of the received coordinates of a turn, by rank
+    uint8_t *const list = reinterpret_cast<uint8_t *>(x_lds + V * turn);     // (DIL) those coordinates
 
     // ---- dense operands: nothing else is requested before them.  (Until everything is requested the wave goes before the
     //      older ones of its SIMD, which have arithmetic to do: us a step without / with that, per replica 31.5M x 8 1648 / 1632, interleaved 1447 / 1425.)
@@ -1113,8 +1116,8 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
     for (int v = 0; v < V; ++v) load_group<OPT, GRAD_BF16>(rep[v], tbase, loff, nvalid, in[v]);
     __builtin_amdgcn_sched_barrier(0);
 
-    uint32_t word_s = 0, base_s = 0, word_r = 0, base_r = 0;
-    if (a.do_send) { word_s = uniform_load(a.send_meta, tile); base_s = uniform_load(a.send_sb_base, tile / kTilesPerSuperblock); }
+    const uint32_t word_s = uniform_load(a.send_meta, tile), base_s = uniform_load(a.send_sb_base, tile / kTilesPerSuperblock);
+    uint32_t word_r = 0, base_r = 0;
     if (a.do_recv) { word_r = uniform_load(a.recv_meta, tile); base_r = uniform_load(a.recv_sb_base, tile / kTilesPerSuperblock); }
     // a tile whose lines would pass the slot capacity is left out, at send and at receive alike
     const uint32_t first_s = base_s + (word_s & 0xFFFFFFu), first_r = base_r + (word_r & 0xFFFFFFu);
@@ -1151,8 +1154,7 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
         if (lane < turn && c0 + lane < count_recv) entry = load_entry<V>(a.d[b] + ((tbase + list[lane]) << sh) + slot);
     };
     auto mean_of = [&]() {                                   // of the coordinate of the lane's rank
-        return sh == 3u ? replica_mean<8, true>(a, ring, lane, kStageFloats) : sh == 2u ? replica_mean<4, true>(a, ring, lane, kStageFloats)
-             : sh == 1u ? replica_mean<2, true>(a, ring, lane, kStageFloats) : replica_mean<1, true>(a, ring, lane, kStageFloats);
+        return replica_mean<1 << sh, true>(a, ring, lane, kStageFloats);
     };
     if (lines_r) {
         request_ring(0u);
@@ -1176,7 +1178,7 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
         key.step_lo = a.step_lo[2]; key.step_hi = a.step_hi[2];
         uint32_t count;
         (void)wave_prefix_mask4(member_mask(key, group, nvalid), count);
-        if (lane == 0) a.next_lines[tile] = (uint8_t)((count * a.rb + kLineFloats - 1u) / kLineFloats);
+        if (lane == 0) a.next_lines[tile] = (uint8_t)(((count << sh) + kLineFloats - 1u) / kLineFloats);
     }
     __builtin_amdgcn_sched_barrier(0);                       // (the operands' conversions stay behind the hashing)
     __builtin_amdgcn_s_setprio(0);
@@ -1226,7 +1228,7 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
             if (c0) next_turn(c0);
             each(c0, [&](int j, uint32_t c) {
 #pragma unroll
-                for (int v = 0; v < V; ++v) x_lds[v * 64 + c] = w_hat[v].v[j];
+                for (int v = 0; v < V; ++v) x_lds[v * turn + c] = w_hat[v].v[j];
             });
             wave_lds_sync();
             if (lane < turn && c0 + lane < count_recv) {
@@ -1235,15 +1237,15 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
                 Entry<V> d_new;
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
-                    d_new.v[v] = (float)fma(a.coef_d, (double)entry.v[v], a.coef_s * ((double)x_lds[v * 64 + lane] - (double)sent.v[v]));
-                    x_lds[v * 64 + lane] = (float)((double)abar + (double)d_new.v[v]);
+                    d_new.v[v] = (float)fma(a.coef_d, (double)entry.v[v], a.coef_s * ((double)x_lds[v * turn + lane] - (double)sent.v[v]));
+                    x_lds[v * turn + lane] = (float)((double)abar + (double)d_new.v[v]);
                 }
                 store_entry<V>(a.d[b] + ((tbase + list[lane]) << sh) + slot, d_new);
             }
             wave_lds_sync();
             each(c0, [&](int j, uint32_t c) {
 #pragma unroll
-                for (int v = 0; v < V; ++v) w_new[v].v[j] = x_lds[v * 64 + c];
+                for (int v = 0; v < V; ++v) w_new[v].v[j] = x_lds[v * turn + c];
             });
         }
     } else if (count_recv) {                                 // every lane picks up those of its own coordinates (a lane with
@@ -1289,7 +1291,7 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
 // Floats of dynamic LDS that it needs.
 __host__ __device__ inline uint32_t step_wave_lds_floats(uint32_t nblocks, bool d_interleaved, uint32_t v)
 {
-    return nblocks * kStageFloats + (d_interleaved ? 64u * v + 16u : 64u);
+    return nblocks * kStageFloats + (d_interleaved ? kWaveTurn * v + kWaveTurn / 4u : kWaveTurn);
 }
 
 // grid = am_host::wave_step_grid(); blockDim = 64; dynamic LDS = step_wave_lds_floats() floats, or more where fewer are to be resident

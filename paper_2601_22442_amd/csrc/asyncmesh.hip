@@ -235,7 +235,7 @@ am_status launch_step_tau(am_state *st, const am::StepArgs &a)
         AM_HIP(hipGetLastError());
         return AM_OK;
     }
-    if (!tau0 && !a.sum_lines && am_host::step_by_waves(st->cfg, B)) {
+    if (a.do_send && !tau0 && !a.sum_lines && am_host::step_by_waves(st->cfg, B)) {
         const uint32_t v = am_host::wave_step_replicas(st->cfg);
         const uint32_t lds = am_host::lds_for_residency(am::step_wave_lds_floats(B.nblocks, DIL, v) * (uint32_t)sizeof(float), am_host::wave_step_workgroups(st->cfg, B, v, st->has_fwd, a.do_recv != 0u));
         const am_host::Grid g = am_host::wave_step_grid(st->lay.ntiles, a.replicas / v);
