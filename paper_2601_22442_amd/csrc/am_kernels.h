@@ -1196,7 +1196,7 @@ __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile
     }
 
     // ---- send: my replicas' values of every coordinate at its rank, zeros in the rest of the tile's last line.  (The slots of absent replicas are
-    //      neither written nor read.)
+    //      not written: they stay zero, as am_init_state leaves them, and other kernels of the same stage add them up.)
     if (lines_s) {
         const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(a.ring_send + b * block_floats + (uint64_t)first_s * kLineFloats, 0, lines_s * kLineFloats * 4u, 0x00020000);
         uint32_t c = rank_send;

@@ -123,3 +123,18 @@ def test_more_chunks_than_one_dimension_of_a_grid_holds(amlib):
     if _free_hbm() < 160e9:
         pytest.skip("not enough free HBM")
     _full_size_case(amlib, n, 5, 1, 0.002, 3, [(0, 30_000), ((1 << 30) - 15_000, 30_000), (n - 30_001, 30_001)], lookahead=False, optimizer=O.OPT_SGD, beta1=0.0, **PER_REPLICA)
+
+
+@pytest.mark.parametrize("n,R,layout", [(1_500_003, 9, PER_REPLICA), (1_500_003, 9, INTERLEAVED), (1_300_001, 10, INTERLEAVED), (1_200_002, 11, PER_REPLICA)])
+def test_first_step_and_the_one_after_a_resume_of_a_smaller_stage(amlib, n, R, layout):
+    """Up to 8192 tiles these two, whose subsets are not sized yet, go by waves and all others through the kernel that adds up the sizes itself: what
+    one leaves in the ring, the slots of absent replicas with it, the other reads."""
+    st, orc = make_pair(amlib, n, R, delay=2, fraction=0.05, seed=13, **layout, **LOOK)
+    for t in range(1, 10):
+        if t == 6:
+            arrays = [[x.clone() for x in getattr(st, k)] for k in ("w", "m", "v", "d_storage", "fwd")]
+            st = amlib.Stage.resume(st.cfg, st.export_state(), *arrays, st.workspace.clone())
+        g, gd = grads_for(n, R, t, 13, False)
+        st.step(t, gd, 1e-3, 0.5); orc.step(t, g, 1e-3, 0.5)
+        if t in (1, 4, 6, 9):
+            compare(st, orc, f"step {t}")
