@@ -297,10 +297,13 @@ inline Grid wave_step_grid(uint32_t ntiles, uint32_t waves_of_a_tile)
     return {am::kWaveChunk * waves_of_a_tile, y, (chunks + y - 1u) / y};
 }
 
-// Waves of it that a compute unit may hold: the less a wave moves the more of them, and one more where the step is short.  Time over the fused kernel's by their number,
-// two replicas a wave: interleaved 125.8M x 8 (8.3 KB a replica) 8: 0.968, 9: 0.949, 10: 0.953, 11: 0.959; 60M weights 9: 0.961, 10: 0.970, 11: 0.947, 12: 0.949; per replica 31.5M x 8 (9.4 KB) 8: 0.921,
-// 9: 0.927, 10: 0.933, 12: 0.952; 80M weights without a forward copy (7.3 KB) 8: 1.070, 10: 0.990, 12: 0.979, 14: 0.988; bf16 without correction (6.1 KB) 8: 1.083, 10: 0.974, 11: 0.954, 14: 0.966;
-// SGD with momentum (5.3 KB) 8: 1.258, 10: 1.079, 12: 1.013, 14: 0.989; one replica a wave (R = 7) AdamW 14: 1.139, 18: 1.008, 21: 1.006, 25: 1.006.
+// Waves of it that a compute unit may hold at most: the less a wave moves the more of them, and one more where the step is short.  (LDS comes in shares, by which 8 to 12, 14, 16, 18, 21, 25 and 32 can
+// be held to: a bound of 13 holds 12, of 15 14, of 17 16, of 19 and 20 18, of 22 to 24 21.)  Time over the fused kernel's by the number resident, median of three placements of the arrays,
+// * what the bound holds; two replicas a wave: AdamW interleaved 250M weights (8.4 KB a replica) 8: 0.969, 9: 0.964, 10: 0.967*, 11: 0.974, 14: 0.992, 60M 9: 0.966, 10: 0.964, 11: 0.967*, 14: 0.980; per
+// replica (9.5 KB) 250M 8: 0.929, 9: 0.933*, 10: 0.942, 14: 0.977, 60M 8: 0.925, 10: 0.936*; interleaved without a forward copy (7.4 KB) 250M 8: 1.000, 10: 0.974, 11: 0.980*; bf16 without correction (7.0 KB) 250M
+// 8: 0.973, 10: 0.940, 11: 0.943*, 14: 0.956; SGD with momentum, interleaved (5.4 KB) 60M 8: 1.135, 10: 1.024, 12: 0.991, 14: 0.981*, 250M 10: 0.996, 11: 0.989, 12: 0.994*, 14: 1.008; plain SGD, interleaved
+// (3.4 KB) 250M 8: 1.412, 12: 1.037, 16: 0.887, 18: 0.884*, 21: 0.889, without correction (3.1 KB) 16: 0.939, 18: 0.905, 21: 0.875*.  One replica a wave: AdamW R = 7 250M 8: 1.178, 12: 0.939, 14: 0.935, 18: 0.955*, 21: 0.964,
+// R = 5 interleaved 60M 12: 1.013, 16: 0.969, 21: 0.981*.
 inline uint32_t wave_step_workgroups(const am_config &c, const Blocks &b, uint32_t v, bool forward_copy, bool receives)
 {
     const double pairs = (c.n * c.replicas > 1ull << 27 ? 4.0 : 5.0) + 50.0 / step_kilobytes(c, b, forward_copy, receives);
@@ -383,7 +386,7 @@ inline uint32_t average_workgroups(const am_config &c, const Blocks &b, bool int
 }
 
 // Dynamic LDS of a workgroup that needs `need` bytes besides `fixed` bytes of static LDS, with which a compute unit holds at most `workgroups` of them (0: no limit):
-// the smallest allocation of which one more does not fit.
+// the smallest allocation of which one more does not fit.  (1 to 12, 14, 16, 18, 21, 25 and 32 fit exactly.)
 constexpr uint32_t kLdsGranules = am::kLdsBytes / am::kLdsGranule;
 constexpr uint32_t lds_for_residency(uint32_t need, uint32_t workgroups, uint32_t fixed = 0)
 {
@@ -396,8 +399,24 @@ constexpr bool residency_is_exact(uint32_t workgroups)
     const uint32_t granules = (lds_for_residency(1, workgroups) + am::kLdsGranule - 1u) / am::kLdsGranule;
     return workgroups * granules <= kLdsGranules && (workgroups + 1u) * granules > kLdsGranules;
 }
-static_assert(residency_is_exact(2) && residency_is_exact(3) && residency_is_exact(4) && residency_is_exact(5) && residency_is_exact(6) && residency_is_exact(7) && residency_is_exact(11),
-              "as many as a rule names fit, and not one more");
+// How many it holds: the largest number that is exact and not above `workgroups`.
+constexpr uint32_t workgroups_held(uint32_t workgroups)
+{
+    while (workgroups > 1u && !residency_is_exact(workgroups)) --workgroups;
+    return workgroups;
+}
+constexpr bool residency_holds(uint32_t workgroups)
+{
+    return kLdsGranules / ((lds_for_residency(1, workgroups) + am::kLdsGranule - 1u) / am::kLdsGranule) == workgroups_held(workgroups);
+}
+constexpr bool every_residency_holds()
+{
+    for (uint32_t w = 1; w <= 32u; ++w)
+        if (!residency_holds(w)) return false;
+    return true;
+}
+static_assert(every_residency_holds() && workgroups_held(7) == 7u && workgroups_held(11) == 11u && workgroups_held(13) == 12u && workgroups_held(20) == 18u,
+              "as many as a rule names fit, or the next number below that shares of the LDS allow, and not one more");
 
 // Floats of one array of the EMA vectors and how many arrays there are, per layout.
 inline void d_layout_shape(const am_config &c, uint32_t *rb, uint32_t *arrays, uint64_t *floats)

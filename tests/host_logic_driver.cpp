@@ -72,6 +72,9 @@ uint32_t hl_step_by_waves(const am_config *c, int forward_copy)
     return am_host::step_by_waves(*c, b) ? am_host::wave_step_workgroups(*c, b, am_host::wave_step_replicas(*c), forward_copy != 0, true) : 0u;
 }
 
+// how many of them the launch's LDS lets be resident
+uint32_t hl_workgroups_held(uint32_t workgroups) { return am_host::workgroups_held(workgroups); }
+
 // its grid, x, y and z
 void hl_wave_step_grid(uint32_t ntiles, uint32_t waves_of_a_tile, uint32_t *out)
 {

@@ -247,6 +247,14 @@ def test_the_grid_of_a_step_by_waves_covers_every_stage(hl, n, waves):
     assert g[1] * g[2] * 128 >= ntiles and g[1] * (g[2] - 1) * 128 < ntiles          # no tile is left out, no layer of the grid is idle
 
 
+@pytest.mark.parametrize("bound", range(1, 33))
+def test_every_number_that_a_rule_can_name_is_held_to(hl, bound):
+    """160 KB in granules of 1280 bytes: a compute unit holds as many as named, or the next smaller number that equal shares allow."""
+    attainable = {128 // g for g in range(1, 129)}
+    share = -(-hl.hl_lds_for_residency(1, bound, 0) // 1280)
+    assert 128 // share == hl.hl_workgroups_held(bound) == max(k for k in attainable if k <= bound)
+
+
 @pytest.mark.parametrize("workgroups", [2, 3, 4, 5, 6, 7, 11])
 @pytest.mark.parametrize("fixed", [0, 16])
 def test_lds_holds_as_many_workgroups_as_a_rule_names(hl, workgroups, fixed):
