@@ -254,34 +254,53 @@ inline uint32_t step_sum_tiles(const am_config &c, const Blocks &b, bool sync)
 }
 
 // Whether a step with a delay goes through the kernel of one-wave workgroups instead of the fused kernel's workgroup per tile and block.  Time by
-// waves / by the fused kernel, same arrays, AdamW with look-ahead and 5 % where not said (either moves by 3 to 5 % with the placement of the arrays):
-//   weights (n R)                                40M   60M   90M   130M  200M  250M  300M  1000M
-//   interleaved EMA vectors   R = 8              0.95  0.95  0.97  0.97  0.97        0.96  0.95
-//                             12                 0.90  0.87  0.97  0.97  0.97        0.96
-//                             16                 0.98  0.91  0.95  1.01  0.98        0.99
-//                             6                  0.94  0.92  0.97  0.97  0.97        0.97
-//                             20                 0.96  0.96  0.97  0.96  0.97        0.97
-//                             24                 0.98  0.90  0.94  0.96  1.01        0.99
-//     but                     32                 1.01  0.94  1.00  0.93  1.04        1.03
-//                             7 (a replica a wave) 1.02 0.99 0.99  1.03  1.01        1.01
-//   per replica               8                  0.95  0.93  0.95  0.96        0.92        0.94
-//                             12                 0.89  0.86  0.94  0.94        0.91
-//                             16                 0.97  0.98  0.90  0.96        1.01
-//                             32                 0.97  0.91  0.97  0.88        1.03
-//   no correction             8                  1.01  0.95  0.96  1.00        0.93
-//                             12                 0.92  0.89  0.96  0.97        0.96
-//                             16                 0.99  0.99  0.93  0.98        0.98
-//                             32                 1.01  0.90  1.00  0.87        0.98
-//   where many of a block's slots are absent: R = 5 interleaved 15M 0.97, 25M to 60M 0.93, 300M 0.98; R = 9, 10, 11 80M 0.76 to 0.90 in every layout.
-//   fewer weights: interleaved 15M 0.99 to 1.05, 25M 0.98 to 1.05, per replica 20M and 30M 0.99 to 1.03, no correction 30M 1.04.
-//   by fraction (90M, 250M): interleaved 2 % 0.95, 0.95, but 10 % 1.02, 1.00; per replica and without 10 % 0.94, 0.96, but 15 % 1.09, 20 % 1.08, 30 % 1.23.
-//   types (60M, 250M): interleaved bf16 0.98, 0.98, with look-ahead 0.97, 1.01, AdamW without a forward copy 0.95, 0.99, SGD with momentum 0.95, 0.98; the others 0.94 to 0.99.
+// waves / by the fused kernel, same arrays, median of three to eight placements of the arrays on one to three boxes, AdamW with look-ahead and 5 % where not said (a single placement is off the median by up to 5 %):
+//   weights (n R)                                45M   60M   90M   130M  200M  300M  400M  500M  1000M
+//   interleaved EMA vectors   R = 6              0.97  0.98  0.97  1.00  0.98        0.98
+//                             8                  0.97  0.97  0.97  0.97  0.96  0.97  0.96  0.96  0.96
+//                             12                 0.97  0.95  0.97  0.97  0.98  0.97  0.96  0.97  0.98
+//                             14                 0.97  0.97  0.99  0.99  0.98        0.97
+//                             18                 0.92  0.91  0.90  0.91  0.91        0.91
+//     few absent slots        16                 1.02  0.95  0.98  0.99  0.99  1.00  0.98  0.99  1.02
+//                             20                 1.01  0.98  0.95  0.97  0.97        0.98
+//                             22                 1.02  1.01  0.95  0.98  0.99        0.99
+//                             24                 0.97  0.99  0.97  0.99  0.99  0.99  0.99  0.99  1.00
+//     SGD with momentum, R = 8 0.98, but 16 1.00; 6 % 8 0.98, 12 0.96 to 0.97, but 20 0.98 to 0.99, 22 1.00 to 1.01, 24 0.99 to 1.02; 10 % 1.00 to 1.04; 1 and 2 % 8 and 12 0.94 to 0.97, 16 0.94 to 0.96, 20 0.95 to 0.97.
+//     R = 32 0.93 to 1.04, R = 7 0.99 to 1.03 (one placement).
+//   per replica               7                  0.94  0.94  0.94  0.96  0.94  0.94
+//                             8                  0.95  0.95  0.96  0.98  0.97  0.97
+//                             13, 15             0.96  0.94  0.97  0.96  0.95  0.95
+//                             12, 16             0.93  0.93  0.94  0.95  0.94  0.94
+//                             23                 0.96  0.99  0.94  0.96  0.98  0.95
+//                             32                 0.96  0.93  0.96  0.92  0.95  0.95
+//                             31                 0.99              0.95        0.99
+//   no correction (70M first) 7, 8                     0.95        0.95  0.95  0.95        0.95
+//                             15                       0.96        0.98  0.95  0.97        0.98
+//                             16, 32                   0.95        0.94  0.95  0.95        0.97
+//                             13, 23                   0.97        0.98        0.97
+//                             31                       0.98        1.00        1.03
+//     17, 19, 25 0.87 to 0.95; 10 % (60M, 250M) per replica 7, 8, 16 0.92 to 0.98, 31 1.03, no correction 0.95 to 0.99, 31 1.06; one placement: 15 % 1.09, 20 % 1.08, 30 % 1.23.
+//   three tenths or more of the fused kernel's waves absent: R = 9 0.78 to 0.84 (10 % 0.79 to 0.93), 10 0.82 to 0.87 (0.85 to 0.93), 11 per replica 0.90 (0.90 to 0.94), interleaved 0.94 to 0.97, 6 % 0.96, 7 % 0.99, 8 % 1.01, 10 % 1.06;
+//     5 per replica 0.92 to 0.96 (0.95 to 0.99), interleaved 15M 0.97, 45M 0.98, 130M 1.00, 300M 0.99, 2 % 0.95, 6 % 1.00, 8 % 1.03, 10 % 1.06 (13M to 18M 1.06, too).
+//   types and kinds, R = 8 and 12 (60M, 250M): bf16 0.90 to 0.98, without a forward copy 0.89 to 0.98, SGD with momentum 0.88 to 0.99, plain 0.72 to 0.91, members in whole lines 0.95 to 0.99, stratified 0.93 to 0.98, messages in bf16
+//     0.91 to 0.98, E4M3 0.90 to 0.97.
+//   fewer weights (one placement): interleaved 15M 0.99 to 1.05, 25M 0.98 to 1.05, per replica 20M and 30M 0.99 to 1.03, no correction 30M 1.04.
 inline bool step_by_waves(const am_config &c, const Blocks &b)
 {
     if (b.rb != 8u || c.fraction > 0.1) return false;
-    const bool idle = c.replicas == 5u || (c.replicas >= 9u && c.replicas <= 11u);         // a third of the fused kernel's waves or more
-    if (c.correction != AM_CORR_NONE && c.d_layout == AM_D_INTERLEAVED && !idle && (c.replicas % 2u || c.replicas > 24u || c.fraction > 0.06)) return false;
-    return c.n * c.replicas > (idle ? 3ull << 22 : c.correction != AM_CORR_NONE ? 5ull << 23 : 1ull << 26);
+    const uint64_t weights = c.n * c.replicas;
+    const uint32_t slots = 8u * b.nblocks, absent = slots - c.replicas;
+    const bool idle = 10u * absent >= 3u * slots, odd = c.replicas % 2u != 0u;             // (R = 5, 9, 10 and 11)
+    if (odd && c.replicas > 25u) return false;
+    if (c.correction == AM_CORR_NONE || c.d_layout != AM_D_INTERLEAVED)
+        return weights > (idle ? 3ull << 22 : c.correction != AM_CORR_NONE ? 5ull << 23 : 1ull << 26);
+    if (c.replicas == 5u && weights > 1ull << 24) return c.fraction <= (weights > 1ull << 26 ? 0.03 : 0.05);
+    if (c.replicas == 11u && c.fraction > 0.06) return false;
+    if (idle) return weights > 3ull << 22;
+    if (odd || c.replicas > 24u || c.fraction > 0.06) return false;
+    if (c.replicas >= 16u && 5u * absent < slots)
+        return weights > (c.replicas == 16u ? 3ull << 24 : 1ull << 26) && weights <= 1ull << 29 && c.fraction <= 0.05 && !(c.optimizer == AM_OPT_SGD && c.beta1 != 0.f);
+    return weights > 5ull << 23;
 }
 
 // Replicas that a wave of that kernel takes: two share the hashing and send pairs of values (R = 12 10M 0.96 either way, R = 32 4M 0.98 / 0.965; four, interleaved 125.8M x 8, 1.005

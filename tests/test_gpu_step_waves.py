@@ -35,6 +35,11 @@ def test_interleaved(amlib, n, R, p, kw):
     run_steps(amlib, n, R, 4, delay=2, fraction=p, seed=5, check_every=4, **INTERLEAVED, **kw)
 
 
+@pytest.mark.parametrize("n,R,p,kw", [((1 << 26) // 24 + 3, 24, 0.05, dict(BF16, **LOOK)), (MANY // 18 + 5, 18, 0.06, {})])
+def test_interleaved_three_blocks(amlib, n, R, p, kw):
+    run_steps(amlib, n, R, 4, delay=2, fraction=p, seed=5, check_every=4, **INTERLEAVED, **kw)
+
+
 @pytest.mark.parametrize("kw", [dict(avg_interval=2), dict(subset_granule=32), dict(subset_kind=O.SUBSET_STRATIFIED), dict(msg_dtype=O.MSG_E4M3)])
 def test_options_interleaved(amlib, kw):
     run_steps(amlib, 2_098_433, 9, 4, delay=1, fraction=0.1, seed=7, check_every=4, **INTERLEAVED, **kw)

@@ -237,6 +237,23 @@ def test_large_steps_go_by_waves(hl, n, R, kw, fwd, waves):
     assert hl.hl_step_by_waves(C.byref(_config(n=n, replicas=R, delay=1, **kw)), fwd) == waves
 
 
+@pytest.mark.parametrize("n,R,kw,waves", [
+    # interleaved EMA vectors, few absent slots: neither the shortest nor the longest steps, small fractions, no momentum alone
+    (50_331_648 // 16, 16, {}, False), (50_331_648 // 16 + 1, 16, {}, True), (1 << 25, 16, {}, True), ((1 << 25) + 1, 16, {}, False), (10_000_000, 16, dict(fraction=0.06), False),
+    (10_000_000, 16, dict(optimizer=0), False), (10_000_000, 16, dict(optimizer=0, beta1=0.0), True), (60_000_000 // 22, 22, {}, False), (90_000_000 // 22, 22, {}, True), (45_000_000 // 18, 18, dict(fraction=0.06), True),
+    (125_829_120, 8, {}, True), (31_457_281, 8, dict(optimizer=0, fraction=0.06), True), (10_000_000, 14, {}, True),
+    # many: five and eleven replicas, one a wave, up to smaller fractions than nine and ten
+    (9_000_003, 5, dict(fraction=0.05), True), (9_000_003, 5, dict(fraction=0.06), False), (26_000_003, 5, dict(fraction=0.03), True), (26_000_003, 5, dict(fraction=0.05), False), (2_600_000, 5, {}, True),
+    (4_090_912, 11, dict(fraction=0.06), True), (4_090_912, 11, dict(fraction=0.07), False), (6_666_669, 9, dict(fraction=0.1), True), (6_666_669, 10, dict(fraction=0.1), True),
+    # every other layout: odd numbers, too, but the largest
+    (10_000_000, 25, dict(d_layout=0), True), (10_000_000, 31, dict(d_layout=0), False), (10_000_000, 27, dict(correction=0), False), (10_000_000, 32, dict(d_layout=0, fraction=0.1), True),
+    (26_000_003, 5, dict(d_layout=0, fraction=0.1), True), (4_090_912, 11, dict(correction=0, fraction=0.1), True),
+])
+def test_large_steps_go_by_waves_where_that_is_faster(hl, n, R, kw, waves):
+    hl.hl_step_by_waves.restype = C.c_uint32
+    assert bool(hl.hl_step_by_waves(C.byref(_config(n=n, replicas=R, delay=1, **dict(dict(d_layout=1), **kw))), True)) == waves
+
+
 @pytest.mark.parametrize("n", [2_097_153, 32_768 * 128 * 256, 32_768 * 128 * 256 + 1, 65_535 * 128 * 256 + 1, (1 << 31) + 1, (1 << 32) - (1 << 20) - 1])
 @pytest.mark.parametrize("waves", [4, 5, 16, 31])
 def test_the_grid_of_a_step_by_waves_covers_every_stage(hl, n, waves):
