@@ -295,7 +295,7 @@ def main():
                    "subset_granule": args.subset_granule, "subset_kind": args.subset_kind, "bf16": w["bf16"], "algorithmic_bytes_per_param": bpp},
         "step_GBps": bytes_per_launch / (ms_per_step * 1e-3) / 1e9,
         "step_frac_of_hbm_peak": bytes_per_launch / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBPS,
-        "roofline": {"kernel": "k_average (+ offsets pass)" if args.averaging_only else "k_step (k_step_wave on large stages)", "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS,
+        "roofline": {"kernel": "k_average (+ offsets pass)" if args.averaging_only else "the step's kernel (k_step, k_step_small, k_step_sync or k_step_wave, by the stage)", "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBPS, "traffic": None,
                      "kernel_ms": kernel_ms_mean, "kernel_ms_median": statistics.median(launch_ms),
                      "kernel_ms_min": min(launch_ms), "kernel_ms_max": max(launch_ms), "launches": len(launch_ms),
