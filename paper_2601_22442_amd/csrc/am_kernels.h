@@ -1084,12 +1084,13 @@ constexpr uint32_t kWaveTurn = kStageFloats >> kWaveBlockShift;         // recei
 // compute unit, 6.1 with a tile's replicas side by side and 6.6 with the replicas of a chunk of 512 tiles one after the other).  So the grid
 // runs over the tiles of a chunk, then its replicas, then the chunks: the waves of one tile are on the same XCD (consecutive workgroups go round the eight) and
 // near enough in time that its ring lines and interleaved EMA entries are fetched from memory once and that the parts of the lines they write merge in the
-// L2 (bytes by the counters as in k_step: 28.4 + 28.3 GB on 125.8M x 16).  The price is in requests: every wave asks for the ring lines, and sends
-// V values of a coordinate at a time, so it pays up to a fraction of 10 %.  Interleaved EMA entries cost little where the lane of rank c takes those of the received
+// L2 (GB read + written a launch by the counters, k_step / this: interleaved 125.8M x 8 17.14 + 16.73 / 17.15 + 16.54, per replica 19.64 + 18.59 either way; this alone:
+// bf16 without correction 125.8M x 16 28.38 + 28.32).  The price is in requests: every wave asks for the ring lines, and sends V values of a coordinate at a time, so it pays up to a fraction of 10 %.  Interleaved EMA entries cost little where the lane of rank c takes those of the received
 // coordinate c, one load and one store a wave, and the weights change hands through LDS (every lane taking its own four coordinates' entries, eight scattered accesses: 5814 / 5846 us,
 // no gain); narrower blocks have too little to gain.
-// us a step, k_step / this: interleaved, R = 8 125.8M 5 % 5909 / 5633 (33.9 GB: 6.0 TB/s), 31.5M 1474 / 1400; per replica, R = 8 31.5M 1698 / 1581, 125.8M 6665 / 6249, R = 5 25M 830 / 784,
-// R = 12 10M 818 / 788; no correction R = 8 31.5M 1461 / 1361, bf16 R = 16 125.8M 1 % 9973 / 9518.
+// us a step, k_step / this, median of ten processes that allocate their arrays once, on two boxes (one process differs from the next by less than 2 % in either): interleaved, R = 8 125.8M 5 % 5897 / 5746
+// (33.69 GB: 5.86 TB/s), 31.5M 1460 / 1415, R = 12 30M 2195 / 2103; per replica, R = 8 with factors 31.5M 1688 / 1576, 125.8M 6850 / 6400; bf16 without correction R = 16 125.8M 1 % 9914 / 9480.  On arrays that a
+// process frees and allocates again many times both get faster, k_step the more: 125.8M x 8 interleaved 5456 / 5525, per replica 6165 / 6165.
 // Bound by memory: with a generator of a few instructions in the place of the hashing it takes as long.
 template <int OPT, bool GRAD_BF16, int FWD, bool DIL, int V, bool FULL>
 __device__ __forceinline__ void step_wave(const StepArgs &a, const uint32_t tile, const uint32_t i0, const uint32_t lane, float *lds)
