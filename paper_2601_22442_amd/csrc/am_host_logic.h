@@ -254,7 +254,7 @@ inline uint32_t step_sum_tiles(const am_config &c, const Blocks &b, bool sync)
 }
 
 // Whether a step with a delay goes through the kernel of one-wave workgroups instead of the fused kernel's workgroup per tile and block.  Time by
-// waves / by the fused kernel, same arrays, median of three to eight placements of the arrays on one to three boxes, AdamW with look-ahead and 5 % where not said (a single placement is off the median by up to 5 %; most of these arrays were freed
+// waves / by the fused kernel, same arrays, median of three to eight placements of the arrays on one to three cards, AdamW with look-ahead and 5 % where not said (a single placement is off the median by up to 5 %; most of these arrays were freed
 // and allocated again in one process: where a process allocates them once, R = 8 gains 2.5 % interleaved, 6.5 % per replica, 4.5 % in bf16 without correction, R = 12 4 %):
 //   weights (n R)                                45M   60M   90M   130M  200M  300M  400M  500M  1000M
 //   interleaved EMA vectors   R = 6              0.97  0.98  0.97  1.00  0.98        0.98

@@ -1088,7 +1088,7 @@ constexpr uint32_t kWaveTurn = kStageFloats >> kWaveBlockShift;         // recei
 // bf16 without correction 125.8M x 16 28.38 + 28.32).  The price is in requests: every wave asks for the ring lines, and sends V values of a coordinate at a time, so it pays up to a fraction of 10 %.  Interleaved EMA entries cost little where the lane of rank c takes those of the received
 // coordinate c, one load and one store a wave, and the weights change hands through LDS (every lane taking its own four coordinates' entries, eight scattered accesses: 5814 / 5846 us,
 // no gain); narrower blocks have too little to gain.
-// us a step, k_step / this, median of ten processes that allocate their arrays once, on two boxes (one process differs from the next by less than 2 % in either): interleaved, R = 8 125.8M 5 % 5897 / 5746
+// us a step, k_step / this, median of ten processes that allocate their arrays once, on two cards (one process differs from the next by less than 2 % in either): interleaved, R = 8 125.8M 5 % 5897 / 5746
 // (33.69 GB: 5.86 TB/s), 31.5M 1460 / 1415, R = 12 30M 2195 / 2103; per replica, R = 8 with factors 31.5M 1688 / 1576, 125.8M 6850 / 6400; bf16 without correction R = 16 125.8M 1 % 9914 / 9480.  On arrays that a
 // process frees and allocates again many times both get faster, k_step the more: 125.8M x 8 interleaved 5456 / 5525, per replica 6165 / 6165.
 // Bound by memory: with a generator of a few instructions in the place of the hashing it takes as long.
